@@ -1,8 +1,9 @@
-"""ctypes binding of libabq.so — the same names as include/abq.h, argument marshalling only.
+"""Binding of libabq.so — the same names as include/abq.h, argument marshalling only.
 
 torch is used for device memory (tensors own every buffer) and for the current stream; every
-step of the path runs in the library's HIP kernels.  A missing library is an error: there is
-no fallback of any kind.
+step of the path runs in the library's HIP kernels.  The online calls (activations and matmuls) are
+functions of the extension module abq_native (csrc/python/), which costs a call about a microsecond; everything a program
+calls at load time goes through ctypes here.  A missing library is an error: there is no fallback of any kind.
 """
 import ctypes
 import os
@@ -11,6 +12,7 @@ import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libabq.so")
+NATIVE_PATH = os.path.join(HERE, "abq_native.so")
 
 ABQ_OK = 0
 ABQ_ERR_NULL, ABQ_ERR_BITS, ABQ_ERR_SHAPE, ABQ_ERR_ALIGN = -1, -2, -3, -4
@@ -64,8 +66,9 @@ _lib = None
 class AbqError(RuntimeError):
     def __init__(self, status, where):
         self.status = status
-        msg = _lib.abq_status_string(status).decode() if _lib is not None else "?"
-        extra = f" (hipError {_lib.abq_last_hip_error()})" if status == ABQ_ERR_HIP and _lib is not None else ""
+        lib = load()
+        msg = lib.abq_status_string(status).decode()
+        extra = f" (hipError {lib.abq_last_hip_error()})" if status == ABQ_ERR_HIP else ""
         super().__init__(f"{where}: {msg} [{status}]{extra}")
 
 
@@ -166,54 +169,6 @@ def abq_unpack_weights(p, N, K, layout, packed, which):
     return out
 
 
-def abq_quant_pack_act(q, x_fp16, layout=ABQ_LAYOUT_AUTO, out=None):
-    """x_fp16 float16 [M,K] (device) -> packed activation blob."""
-    lib = load()
-    M, K = x_fp16.shape
-    _dev(x_fp16, torch.float16)
-    nbytes = lib.abq_packed_act_bytes(q, M, K, layout)
-    if out is None:
-        out = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=x_fp16.device)
-    _check(lib.abq_quant_pack_act(q, M, K, _ptr(x_fp16), layout, _ptr(out), out.numel(), _stream()), "abq_quant_pack_act")
-    return out
-
-
-def abq_pack_act_codes(q, a_codes, a_scale, a_zero, layout=ABQ_LAYOUT_AUTO, out=None):
-    lib = load()
-    M, K = a_codes.shape
-    _dev(a_codes, torch.uint8), _dev(a_scale, torch.float32, (M,)), _dev(a_zero, torch.int32, (M,))
-    nbytes = lib.abq_packed_act_bytes(q, M, K, layout)
-    if out is None:
-        out = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=a_codes.device)
-    _check(lib.abq_pack_act_codes(q, M, K, _ptr(a_codes), _ptr(a_scale), _ptr(a_zero), layout, _ptr(out), out.numel(),
-                                  _stream()), "abq_pack_act_codes")
-    return out
-
-
-def abq_f4_pack_codes(bits, codes, scale, zero, out=None):
-    """codes uint8 [rows,K] (weights: rows = N; activations: rows = M) -> blob of the 4-bit floating-point MFMA path."""
-    lib = load()
-    rows, K = codes.shape
-    _dev(codes, torch.uint8), _dev(scale, torch.float32, (rows,)), _dev(zero, torch.int32, (rows,))
-    nbytes = lib.abq_f4_packed_bytes(bits, rows, K)
-    if out is None:
-        out = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=codes.device)
-    _check(lib.abq_f4_pack_codes(bits, rows, K, _ptr(codes), _ptr(scale), _ptr(zero), _ptr(out), out.numel(), _stream()),
-           "abq_f4_pack_codes")
-    return out
-
-
-def abq_f4_gemm(p, q, M, N, K, packed_act, packed_w, y=None, acc=None, want_acc=False):
-    """-> (y float16 [M,N], acc int32 [M,N] or None)."""
-    dev = packed_w.device
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=dev)
-    if acc is None and want_acc:
-        acc = torch.empty((M, N), dtype=torch.int32, device=dev)
-    _check(load().abq_f4_gemm(p, q, M, N, K, _ptr(packed_act), _ptr(packed_w), _ptr(y), _ptr(acc), _stream()), "abq_f4_gemm")
-    return y, acc
-
-
 def abq_unpack_act(q, M, K, layout, packed, which):
     """-> (codes uint8 [M,K], scale float32 [M], zero int32 [M], sum int32 [M])."""
     lib = load()
@@ -227,66 +182,8 @@ def abq_unpack_act(q, M, K, layout, packed, which):
     return codes, scale, zero, asum
 
 
-def abq_gemm(p, q, M, N, K, packed_act, a_layout, packed_w, w_layout, y=None, acc=None, want_acc=False, workspace=None):
-    """-> (y float16 [M,N], acc int32 [M,N] or None).  Buffers are allocated when not given."""
-    lib = load()
-    dev = packed_w.device
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=dev)
-    if acc is None and want_acc:
-        acc = torch.empty((M, N), dtype=torch.int32, device=dev)
-    need = lib.abq_gemm_workspace_bytes(p, q, M, N, K)
-    if need and workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
-    _check(lib.abq_gemm(p, q, M, N, K, _ptr(packed_act), a_layout, _ptr(packed_w), w_layout, _ptr(y), _ptr(acc),
-                        _ptr(workspace), 0 if workspace is None else workspace.numel(), _stream()), "abq_gemm")
-    return y, acc
-
-
 def abq_gemm_act_codes_workspace_bytes(p, q, M, N, K, w_layout):
     return load().abq_gemm_act_codes_workspace_bytes(p, q, M, N, K, w_layout)
-
-
-def abq_gemm_act_codes(p, q, M, N, K, a_codes, a_scale, a_zero, packed_w, w_layout, y=None, acc=None, want_acc=False,
-                       workspace=None):
-    """Activation packing fused into the matmul -> (y float16 [M,N], acc int32 [M,N] or None)."""
-    lib = load()
-    dev = packed_w.device
-    if y is None:
-        y = torch.empty((M, N), dtype=torch.float16, device=dev)
-    if acc is None and want_acc:
-        acc = torch.empty((M, N), dtype=torch.int32, device=dev)
-    need = lib.abq_gemm_act_codes_workspace_bytes(p, q, M, N, K, w_layout)
-    if need and workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
-    _check(lib.abq_gemm_act_codes(p, q, M, N, K, _ptr(a_codes), _ptr(a_scale), _ptr(a_zero), _ptr(packed_w), w_layout,
-                                  _ptr(y), _ptr(acc), _ptr(workspace), 0 if workspace is None else workspace.numel(),
-                                  _stream()), "abq_gemm_act_codes")
-    return y, acc
-
-
-def abq_gemm_act_codes_requant(p, q, M, N, K, a_codes, a_scale, a_zero, packed_w, w_layout, q_out, out_scale, out_zero,
-                               want_y=True, workspace=None):
-    """-> (codes uint8 [M,N] of the next layer under (out_scale, out_zero), y float16 [M,N] or None)."""
-    lib = load()
-    dev = packed_w.device
-    _dev(out_scale, torch.float32, (M,)), _dev(out_zero, torch.int32, (M,))
-    codes = torch.empty((M, N), dtype=torch.uint8, device=dev)
-    y = torch.empty((M, N), dtype=torch.float16, device=dev) if want_y else None
-    need = lib.abq_gemm_act_codes_workspace_bytes(p, q, M, N, K, w_layout)
-    if need and workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
-    _check(lib.abq_gemm_act_codes_requant(p, q, M, N, K, _ptr(a_codes), _ptr(a_scale), _ptr(a_zero), _ptr(packed_w), w_layout, q_out,
-                                          _ptr(out_scale), _ptr(out_zero), _ptr(codes), _ptr(y), _ptr(workspace),
-                                          0 if workspace is None else workspace.numel(), _stream()), "abq_gemm_act_codes_requant")
-    return codes, y
-
-
-def abq_gemm_act_codes_static(p, q, M, N, K, a_codes, a_scale, a_zero, packed_w, w_layout, y, acc=None):
-    """abq_gemm_act_codes without a workspace and without any allocation: the caller passes every buffer."""
-    _check(load().abq_gemm_act_codes_static(p, q, M, N, K, _ptr(a_codes), _ptr(a_scale), _ptr(a_zero), _ptr(packed_w), w_layout,
-                                            _ptr(y), _ptr(acc), _stream()), "abq_gemm_act_codes_static")
-    return y, acc
 
 
 class AbqProblem(_c.Structure):
@@ -315,18 +212,6 @@ def make_problems(problems):
 def abq_gemm_grouped_workspace_bytes(p, q, M, problems, a_layout, w_layout):
     arr = problems if isinstance(problems, _c.Array) else make_problems(problems)
     return load().abq_gemm_grouped_workspace_bytes(p, q, M, len(arr), _c.addressof(arr), a_layout, w_layout)
-
-
-def abq_gemm_grouped(p, q, M, problems, a_layout, w_layout, workspace=None):
-    """One call for a list of independent problems that share p, q, M (see make_problems); outputs are written to
-    the y / acc tensors of each problem."""
-    lib = load()
-    arr = problems if isinstance(problems, _c.Array) else make_problems(problems)
-    need = lib.abq_gemm_grouped_workspace_bytes(p, q, M, len(arr), _c.addressof(arr), a_layout, w_layout)
-    if need and workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device="cuda")
-    _check(lib.abq_gemm_grouped(p, q, M, len(arr), _c.addressof(arr), a_layout, w_layout, _ptr(workspace),
-                                0 if workspace is None else workspace.numel(), _stream()), "abq_gemm_grouped")
 
 
 class AbqPlan(_c.Structure):
@@ -359,41 +244,20 @@ def abq_plan_clear():
     load().abq_plan_clear()
 
 
-def abq_rmsnorm_quant_act(q, x_fp16, gamma_fp16, eps, want_y=False):
-    """-> (codes uint8 [M,K], a_scale float32 [M], a_zero int32 [M], y float16 [M,K] or None)."""
-    M, K = x_fp16.shape
-    dev = x_fp16.device
-    codes = torch.empty((M, K), dtype=torch.uint8, device=dev)
-    scale = torch.empty(M, dtype=torch.float32, device=dev)
-    zero = torch.empty(M, dtype=torch.int32, device=dev)
-    y = torch.empty((M, K), dtype=torch.float16, device=dev) if want_y else None
-    _check(load().abq_rmsnorm_quant_act(q, M, K, _ptr(x_fp16), _ptr(gamma_fp16), float(eps), _ptr(codes), _ptr(scale),
-                                        _ptr(zero), _ptr(y), _stream()), "abq_rmsnorm_quant_act")
-    return codes, scale, zero, y
+# The online calls, from abq_native; their docstrings say what they take and return.
+_NATIVE = ("abq_quant_pack_act", "abq_pack_act_codes", "abq_f4_pack_codes", "abq_rmsnorm_quant_act", "abq_add_rmsnorm_quant_act",
+           "abq_silu_mul_quant_act", "abq_gemm", "abq_gemm_act_codes", "abq_gemm_act_codes_requant", "abq_gemm_act_codes_static",
+           "abq_gemm_grouped", "abq_f4_gemm")
 
 
-def abq_add_rmsnorm_quant_act(q, x_fp16, residual_fp16, gamma_fp16, eps, want_y=False, sum_out=None):
-    """-> (codes, a_scale, a_zero, h = x + residual as float16 [M,K], y float16 [M,K] or None)."""
-    M, K = x_fp16.shape
-    dev = x_fp16.device
-    codes = torch.empty((M, K), dtype=torch.uint8, device=dev)
-    scale = torch.empty(M, dtype=torch.float32, device=dev)
-    zero = torch.empty(M, dtype=torch.int32, device=dev)
-    h = torch.empty((M, K), dtype=torch.float16, device=dev) if sum_out is None else sum_out
-    y = torch.empty((M, K), dtype=torch.float16, device=dev) if want_y else None
-    _check(load().abq_add_rmsnorm_quant_act(q, M, K, _ptr(x_fp16), _ptr(residual_fp16), _ptr(gamma_fp16), float(eps), _ptr(codes),
-                                            _ptr(scale), _ptr(zero), _ptr(h), _ptr(y), _stream()), "abq_add_rmsnorm_quant_act")
-    return codes, scale, zero, h, y
-
-
-def abq_silu_mul_quant_act(q, gate_fp16, up_fp16, want_h=False):
-    """-> (codes uint8 [M,K], a_scale float32 [M], a_zero int32 [M], h float16 [M,K] or None)."""
-    M, K = gate_fp16.shape
-    dev = gate_fp16.device
-    codes = torch.empty((M, K), dtype=torch.uint8, device=dev)
-    scale = torch.empty(M, dtype=torch.float32, device=dev)
-    zero = torch.empty(M, dtype=torch.int32, device=dev)
-    h = torch.empty((M, K), dtype=torch.float16, device=dev) if want_h else None
-    _check(load().abq_silu_mul_quant_act(q, M, K, _ptr(gate_fp16), _ptr(up_fp16), _ptr(codes), _ptr(scale), _ptr(zero),
-                                         _ptr(h), _stream()), "abq_silu_mul_quant_act")
-    return codes, scale, zero, h
+def __getattr__(name):
+    """Loads abq_native at the first use of one of its functions, and puts all of them into this module."""
+    if name not in _NATIVE:
+        raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
+    load()
+    if not os.path.exists(NATIVE_PATH):
+        raise RuntimeError(f"{NATIVE_PATH} is missing: build it with `python -m paper_2408_08554_amd.build` (there is no fallback path)")
+    from . import abq_native
+    abq_native.init(AbqError, make_problems)
+    globals().update({n: getattr(abq_native, n) for n in _NATIVE})
+    return globals()[name]

@@ -1,4 +1,5 @@
-"""Compile the HIP sources under csrc/ for gfx950 into paper_2408_08554_amd/libabq.so.
+"""Compile the HIP sources under csrc/ for gfx950 into paper_2408_08554_amd/libabq.so, and csrc/python/ (host code) into
+the extension module abq_native beside it.
 
 Run here on the CPU container (hipcc cross-compiles); the built library travels with the
 tree.  `python -m paper_2408_08554_amd.build` rebuilds everything
@@ -8,11 +9,13 @@ import concurrent.futures
 import glob
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libabq.so")
+NATIVE = os.path.join(HERE, "abq_native.so")           # the online entry points as a Python extension module
 PROBE_LIB = os.path.join(HERE, "libabq_probe.so")   # measurement aids of the benchmark, not part of libabq.so
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -56,6 +59,24 @@ def _check_no_scratch(src: str, remarks: str, kernel: str) -> None:
         raise RuntimeError(f"{src}: no resource-usage remark for {kernel}; the scratch check did not run")
 
 
+def _build_native(newest_header: float = 0.0) -> None:
+    """abq_native (csrc/python/): host code against the installed torch's headers and libraries, and libabq.so beside it."""
+    import torch
+    src = os.path.join(CSRC, "python", "abq_native.cpp")
+    if newest_header and os.path.exists(NATIVE) and os.path.getmtime(NATIVE) >= max(newest_header, os.path.getmtime(src)):
+        return
+    root = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-Wno-missing-field-initializers",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", sysconfig.get_paths()["include"], "-isystem", os.path.join(root, "include"),
+           "-isystem", os.path.join(root, "include", "torch", "csrc", "api", "include"), "-isystem", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"),
+           src, "-o", NATIVE, "-L" + HERE, "-labq", "-L" + os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+           "-Wl,-rpath,$ORIGIN"]
+    done = subprocess.run(cmd, stderr=subprocess.PIPE, text=True)
+    if done.returncode:
+        raise RuntimeError(f"g++ failed on {src}:\n{done.stderr}")
+
+
 def build(verbose: bool = False, incremental: bool = False) -> str:
     """Compiles every source (always, unless `incremental`: then only what is older than its source or a header)."""
     os.makedirs(OBJ, exist_ok=True)
@@ -75,6 +96,7 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
                 print("compiled", os.path.basename(s), flush=True)
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *sorted(objs), "-o", LIB], check=True)
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", *sorted(probe_objs), "-o", PROBE_LIB], check=True)
+    _build_native(newest)
     return LIB
 
 
