@@ -404,6 +404,9 @@ static bool choose_direct(const GemmArgs& g, const ActLayout& A, const WeightLay
     lookup_plan(g.p, g.q, g.M, g.N, g.K, &ov);
     const int env = tuning_env("ABQ_DIRECT_R");
     const int forced = ov.direct_r != 0 ? ov.direct_r : env;
+    // Unpacked rows of a K that is no multiple of 16: only this kernel reads them (the others stage whole 16-byte vectors), and
+    // where it is not the fastest it loses less than the pack launch in front of them costs (2.5 us).
+    if (g.a_raw && g.K % 16 != 0) return direct_plan(g.p, g.M, A.Kp / kSuperK, 0, pl);
     if (forced < 0) return false;
     if (forced == 0 && !direct_by_rule(g.p, g.M, A.Kp / kSuperK, W)) return false;
     return direct_plan(g.p, g.M, A.Kp / kSuperK, forced, pl);
@@ -547,14 +550,27 @@ int abq_gemm(int p, int q, int M, int N, int K, const void* packed_act, int a_la
     return gemm_impl(p, q, M, N, K, packed_act, a_layout, packed_w, w_layout, y_fp16, acc_i32, workspace, workspace_bytes, stream, kNoRequant);
 }
 
-// The fused call runs as one kernel when abq_gemm on the same problem would pick the streaming kernel
-// and the rows of A can be read as whole 16-byte vectors.
+// The fused call needs no workspace when abq_gemm on the same problem would pick a decode kernel and the rows of A can
+// be read as whole 16-byte vectors; it is one kernel then.
 static bool fused_act_direct(const WeightLayout& W, int force, int p, int q, int M, int N, int K)
 {
     if (!W.has_fields || force == ABQ_USE_PLANES) return false;
     if (W.g128) return M <= kSkinnyMaxM && K % 16 == 0;
     if (!choose_fields(true, W.has_planes, force, p, q, M, N)) return false;
     return streaming_shape(M, N) && K % 16 == 0;
+}
+// Rows that are no whole number of 16-byte vectors are one kernel too where the direct kernel takes them (it reads rows of
+// any length from 16 on); the workspace that the query names stays unused then.
+static bool fused_act_ragged(const WeightLayout& W, int force, int p, int q, int M, int N, int K)
+{
+    if (!W.has_fields || force == ABQ_USE_PLANES || K % 16 == 0 || K < 16 || M > kSkinnyMaxM) return false;
+    const int nsuper = (K + kSuperK - 1) / kSuperK;
+    DirectPlan pl;
+    if (W.g128) return M == 1 && p <= 4 && direct_plan_g128(p, nsuper, &pl);
+    PlanOverride ov;
+    lookup_plan(p, q, M, N, K, &ov);
+    if (ov.direct_r < 0) return false;   // (another decode kernel is asked for: it takes packed rows)
+    return choose_fields(true, W.has_planes, force, p, q, M, N) && direct_plan(p, M, nsuper, 0, &pl);
 }
 
 size_t abq_gemm_act_codes_workspace_bytes(int p, int q, int M, int N, int K, int w_layout)
@@ -585,18 +601,20 @@ static int gemm_act_codes_impl(int p, int q, int M, int N, int K, const uint8_t*
         return ABQ_ERR_ALIGN;
     if (W.g128 && (acc_i32 || rq.codes)) return ABQ_ERR_LAYOUT;
     hipStream_t s = (hipStream_t)stream;
-    if (fused_act_direct(W, force, p, q, M, N, K)) {
+    const bool no_workspace = fused_act_direct(W, force, p, q, M, N, K);
+    const int act_layout = W.g128 ? ABQ_LAYOUT_FIELDS : base_layout;
+    const size_t act_bytes = abq_packed_act_bytes(q, M, K, act_layout);
+    if (!no_workspace) {
+        if (!workspace) return ABQ_ERR_NULL;
+        if (workspace_bytes < act_bytes + abq_gemm_workspace_bytes(p, q, M, N, K)) return ABQ_ERR_SIZE;
+    }
+    if (no_workspace || fused_act_ragged(W, force, p, q, M, N, K)) {
         ActLayout A;
         if (!make_act_layout(q, M, K, ABQ_LAYOUT_FIELDS, &A)) return ABQ_ERR_LAYOUT;
         GemmArgs g{p, q, M, N, K, nullptr, a_codes, a_scale, a_zero, (const uint8_t*)packed_w, y_fp16, acc_i32, nullptr, 0, rq};
         return hip_status(launch_decode(g, A, W, s));
     }
     // Otherwise the two steps run back to back, the packed activations living in the caller's workspace.
-    const int act_layout = W.g128 ? ABQ_LAYOUT_FIELDS : base_layout;
-    const size_t act_bytes = abq_packed_act_bytes(q, M, K, act_layout);
-    const size_t need = act_bytes + abq_gemm_workspace_bytes(p, q, M, N, K);
-    if (!workspace) return ABQ_ERR_NULL;
-    if (workspace_bytes < need) return ABQ_ERR_SIZE;
     if (int e = abq_pack_act_codes(q, M, K, a_codes, a_scale, a_zero, act_layout, workspace, act_bytes, stream)) return e;
     return gemm_impl(p, q, M, N, K, workspace, act_layout, packed_w, w_layout, y_fp16, acc_i32,
                      (uint8_t*)workspace + act_bytes, workspace_bytes - act_bytes, stream, rq);
@@ -645,10 +663,43 @@ int abq_gemm_act_codes_static(int p, int q, int M, int N, int K, const uint8_t* 
     return abq_gemm_act_codes(p, q, M, N, K, a_codes, a_scale, a_zero, packed_w, w_layout, y_fp16, acc_i32, ws, need, stream);
 }
 
-// Validation and layouts of a group; fills the per-problem arrays (sized by the caller) and says whether one
-// launch can serve it.
+// How a group is launched: member by member through the single calls, as direct launches, through the streaming kernel's
+// grouped launch, or (per-group blobs) the members the direct kernel takes in one launch and the others streamed.
+enum class GroupRoute { kSingle, kDirect, kStream, kSplit };
+
+// Direct for up to eight rows of A below p = 8 (measured on the LLaMA-7B block: W4A8 M = 1 19.6 vs 22.0 us, W2A8 13.9 vs
+// 17.9, W4A8 M = 8 26.0 vs 25.1; at p = 8 its two launches, one per length of K, cost more than they gain: 34.8 vs 33.3 us), and
+// wherever the streaming launch does not fit (K below 2048 or no multiple of 16): a block of K = 1120, M = 2 then is two launches
+// instead of seven.
+// `streams`: the streaming launch fits; only then does a group of unpacked codes need no workspace.
+static GroupRoute group_route(int p, int q, int M, int count, bool raw, int force, const GemmArgs* args, const ActLayout* A,
+                              const WeightLayout* W, bool* streams, int* waves, size_t* lds)
+{
+    *streams = false;
+    // grouped only where every problem would go to the int8-MFMA family's decode kernels anyway
+    if (force == ABQ_USE_PLANES || M > kSkinnyMaxM) return GroupRoute::kSingle;
+    bool g128 = false;
+    for (int i = 0; i < count; ++i) {
+        g128 = g128 || W[i].g128;
+        if (!W[i].g128 && !choose_fields(W[i].has_fields && (raw || A[i].has_fields), W[i].has_planes && !raw && A[i].has_planes, force, p, q, M, args[i].N))
+            return GroupRoute::kSingle;
+    }
+    *streams = gemm_grouped_fits(M, count, args, A, W, waves, lds);
+    const bool may_direct = tuning_env("ABQ_DIRECT_R") >= 0;
+    const bool direct = may_direct && gemm_direct_grouped_fits(p, M, count, args, A, W);
+    if (direct && M <= 8 && p < 8) return GroupRoute::kDirect;
+    int d128 = 0;
+    if (g128 && may_direct)
+        for (int i = 0; i < count; ++i) d128 += gemm_direct_g128_fits(p, M, args[i], A[i], W[i]) ? 1 : 0;
+    if (d128 == count) return GroupRoute::kDirect;
+    if (*streams) return d128 > 0 ? GroupRoute::kSplit : GroupRoute::kStream;
+    return direct ? GroupRoute::kDirect : GroupRoute::kSingle;
+}
+
+// Validation and layouts of a group; fills the per-problem arrays (sized by the caller) and says how it is launched.
 static int prepare_group(int p, int q, int M, int count, const abq_problem* pr, int a_layout, int w_layout,
-                         GemmArgs* args, ActLayout* A, WeightLayout* W, bool* raw, bool* fits, int* waves, size_t* lds)
+                         GemmArgs* args, ActLayout* A, WeightLayout* W, bool* raw, GroupRoute* route, bool* streams, int* waves,
+                         size_t* lds)
 {
     if (!pr) return ABQ_ERR_NULL;
     if (count < 1 || count > 4096) return ABQ_ERR_SHAPE;
@@ -671,11 +722,7 @@ static int prepare_group(int p, int q, int M, int count, const abq_problem* pr, 
         args[i] = GemmArgs{p, q, M, c.N, c.K, (const uint8_t*)c.packed_act, c.a_codes, c.a_scale, c.a_zero,
                            (const uint8_t*)c.packed_w, c.y_fp16, c.acc_i32, nullptr, 0};
     }
-    // one launch only where every problem would go to the streaming kernel of the int8-MFMA family anyway
-    *fits = force != ABQ_USE_PLANES && M <= kSkinnyMaxM;
-    for (int i = 0; i < count && *fits; ++i)
-        *fits = W[i].g128 || choose_fields(W[i].has_fields && (*raw || A[i].has_fields), W[i].has_planes && !*raw && A[i].has_planes, force, p, q, M, pr[i].N);
-    if (*fits) *fits = gemm_grouped_fits(M, count, args, A, W, waves, lds);
+    *route = group_route(p, q, M, count, *raw, force, args, A, W, streams, waves, lds);
     return ABQ_OK;
 }
 
@@ -686,12 +733,13 @@ size_t abq_gemm_grouped_workspace_bytes(int p, int q, int M, int count, const ab
     std::vector<GemmArgs> args(count);
     std::vector<ActLayout> A(count);
     std::vector<WeightLayout> W(count);
-    bool raw = false, fits = false;
+    bool raw = false, streams = false;
+    GroupRoute route = GroupRoute::kSingle;
     int waves = 0;
     size_t lds = 0;
-    if (prepare_group(p, q, M, count, host_problems, a_layout, w_layout, args.data(), A.data(), W.data(), &raw, &fits, &waves, &lds) != ABQ_OK)
+    if (prepare_group(p, q, M, count, host_problems, a_layout, w_layout, args.data(), A.data(), W.data(), &raw, &route, &streams, &waves, &lds) != ABQ_OK)
         return 0;
-    if (fits || !raw) return 0;
+    if (streams || !raw) return 0;
     size_t need = 0;
     for (int i = 0; i < count; ++i) {
         const size_t n = abq_gemm_act_codes_workspace_bytes(p, q, M, host_problems[i].N, host_problems[i].K, w_layout);
@@ -708,18 +756,25 @@ int abq_gemm_grouped(int p, int q, int M, int count, const abq_problem* host_pro
     std::vector<GemmArgs> args(count);
     std::vector<ActLayout> A(count);
     std::vector<WeightLayout> W(count);
-    bool raw = false, fits = false;
+    bool raw = false, streams = false;
+    GroupRoute route = GroupRoute::kSingle;
     int waves = 0;
     size_t lds = 0;
-    if (int e = prepare_group(p, q, M, count, host_problems, a_layout, w_layout, args.data(), A.data(), W.data(), &raw, &fits, &waves, &lds))
+    if (int e = prepare_group(p, q, M, count, host_problems, a_layout, w_layout, args.data(), A.data(), W.data(), &raw, &route, &streams, &waves, &lds))
         return e;
     if (misaligned(workspace)) return ABQ_ERR_ALIGN;
-    // grouped: the direct kernel for up to eight rows of A below p = 8 (measured on the LLaMA-7B block: W4A8 M = 1 19.6 vs
-    // 22.0 us, W2A8 13.9 vs 17.9, W4A8 M = 8 26.0 vs 25.1; at p = 8 its two launches, one per length of K, cost more than
-    // they gain: 34.8 vs 33.3 us)
-    if (fits && M <= 8 && p < 8 && tuning_env("ABQ_DIRECT_R") >= 0 && gemm_direct_grouped_fits(p, M, count, args.data(), A.data(), W.data()))
+    if (raw && !streams) {   // every problem's workspace need is checked before the first launch
+        size_t need = 0;
+        for (int i = 0; i < count; ++i) {
+            const size_t n = abq_gemm_act_codes_workspace_bytes(p, q, M, host_problems[i].N, host_problems[i].K, w_layout);
+            if (n > need) need = n;
+        }
+        if (need > 0 && !workspace) return ABQ_ERR_NULL;
+        if (workspace_bytes < need) return ABQ_ERR_SIZE;
+    }
+    if (route == GroupRoute::kDirect)
         return hip_status(launch_gemm_direct_grouped(p, q, M, count, args.data(), A.data(), W.data(), (hipStream_t)stream));
-    if (fits && W[0].g128 && tuning_env("ABQ_DIRECT_R") >= 0) {
+    if (route == GroupRoute::kSplit) {
         // per-group blobs: the members the direct kernel's g128 variant takes (K <= 8192) go there in one launch, the others
         // to the streaming kernel's grouped launch (LLaMA-7B block W4A8 g128 M = 1: 28.2 us as one streaming launch)
         std::vector<GemmArgs> a1, a2;
@@ -731,26 +786,14 @@ int abq_gemm_grouped(int p, int q, int M, int count, const abq_problem* host_pro
             (d ? A1 : A2).push_back(A[i]);
             (d ? W1 : W2).push_back(W[i]);
         }
-        if (!a1.empty()) {
-            if (int e = hip_status(launch_gemm_direct_grouped(p, q, M, (int)a1.size(), a1.data(), A1.data(), W1.data(), (hipStream_t)stream))) return e;
-            if (a2.empty()) return ABQ_OK;
-            if (a2.size() == 1) return hip_status(launch_gemm_skinny(a2[0], A2[0], W2[0], (hipStream_t)stream));   // (a set of one: the single launch's plan)
-            int waves2 = 0;
-            size_t lds2 = 0;
-            if (!gemm_grouped_fits(M, (int)a2.size(), a2.data(), A2.data(), W2.data(), &waves2, &lds2)) return ABQ_ERR_SHAPE;   // (a subset of a set that fits)
-            return hip_status(launch_gemm_grouped(p, M, (int)a2.size(), a2.data(), A2.data(), W2.data(), waves2, lds2, (hipStream_t)stream));
-        }
+        if (int e = hip_status(launch_gemm_direct_grouped(p, q, M, (int)a1.size(), a1.data(), A1.data(), W1.data(), (hipStream_t)stream))) return e;
+        if (a2.size() == 1) return hip_status(launch_gemm_skinny(a2[0], A2[0], W2[0], (hipStream_t)stream));   // (a set of one: the single launch's plan)
+        int waves2 = 0;
+        size_t lds2 = 0;
+        if (!gemm_grouped_fits(M, (int)a2.size(), a2.data(), A2.data(), W2.data(), &waves2, &lds2)) return ABQ_ERR_SHAPE;   // (a subset of a set that fits)
+        return hip_status(launch_gemm_grouped(p, M, (int)a2.size(), a2.data(), A2.data(), W2.data(), waves2, lds2, (hipStream_t)stream));
     }
-    if (fits) return hip_status(launch_gemm_grouped(p, M, count, args.data(), A.data(), W.data(), waves, lds, (hipStream_t)stream));
-    if (raw) {   // every problem's workspace need is checked before the first launch
-        size_t need = 0;
-        for (int i = 0; i < count; ++i) {
-            const size_t n = abq_gemm_act_codes_workspace_bytes(p, q, M, host_problems[i].N, host_problems[i].K, w_layout);
-            if (n > need) need = n;
-        }
-        if (need > 0 && !workspace) return ABQ_ERR_NULL;
-        if (workspace_bytes < need) return ABQ_ERR_SIZE;
-    }
+    if (route == GroupRoute::kStream) return hip_status(launch_gemm_grouped(p, M, count, args.data(), A.data(), W.data(), waves, lds, (hipStream_t)stream));
     for (int i = 0; i < count; ++i) {
         const abq_problem& c = host_problems[i];
         const int e = raw ? abq_gemm_act_codes(p, q, M, c.N, c.K, c.a_codes, c.a_scale, c.a_zero, c.packed_w, w_layout, c.y_fp16,

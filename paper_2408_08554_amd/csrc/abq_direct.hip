@@ -79,7 +79,7 @@ bool gemm_direct_grouped_fits(int p, int M, int count, const GemmArgs* probs, co
     for (int i = 0; i < count; ++i) {
         DirectPlan pl;
         if (!W[i].has_fields || W[i].g128) return false;
-        if (probs[i].a_raw ? (probs[i].K % 16 != 0) : !A[i].has_fields) return false;
+        if (probs[i].a_raw ? probs[i].K < 16 : !A[i].has_fields) return false;
         if ((probs[i].a_raw != nullptr) != (probs[0].a_raw != nullptr)) return false;
         if (!direct_plan(p, M, A[i].Kp / kSuperK, 0, &pl)) return false;
     }
@@ -101,7 +101,7 @@ bool gemm_direct_g128_fits(int p, int M, const GemmArgs& g, const ActLayout& A, 
 {
     DirectPlan pl;
     if (!W.g128 || !W.has_fields || M != 1 || p > 4 || g.acc || g.rq.codes) return false;
-    if (g.a_raw ? (g.K % 16 != 0) : !A.has_fields) return false;
+    if (g.a_raw ? g.K < 16 : !A.has_fields) return false;
     return direct_plan_g128(p, A.Kp / kSuperK, &pl);
 }
 

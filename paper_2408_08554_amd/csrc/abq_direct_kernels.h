@@ -38,7 +38,7 @@ struct DirectProblem {
     const u4v* fields[3];      // per plane group
     const int8_t* a_codes;     // [M][Kp] packed activations (code less oa), or null with a_raw
     const RowParams* aparams;
-    const uint8_t* a_raw;      // [M][K] unpacked codes with a_scale / a_zero (activation pack fused in), K a multiple of 16
+    const uint8_t* a_raw;      // [M][K] unpacked codes with a_scale / a_zero (activation pack fused in), K >= 16
     const float* a_scale;
     const int32_t* a_zero;
     const RowParams* wparams;
@@ -57,6 +57,21 @@ struct DirectParams {
     uint32_t a_mask;                        // (2^q - 1) in every byte (unpacked codes are masked to q bits)
     DirectProblem d[kDirectMaxGroup];
 };
+
+typedef int v4i_byte __attribute__((ext_vector_type(4), aligned(1)));
+
+// The last `left` (1..15) bytes of a row at the bottom of a 16-byte value, zeros above; `end16`: the row's last 16 bytes.
+__device__ __forceinline__ v4i row_tail16(const v4i& end16, int left)
+{
+    const unsigned drop = 16u - (unsigned)left;                     // bytes in front of the tail
+    uint32_t w[5] = {(uint32_t)end16.x, (uint32_t)end16.y, (uint32_t)end16.z, (uint32_t)end16.w, 0u};
+    if (drop & 8u) { w[0] = w[2]; w[1] = w[3]; w[2] = 0u; w[3] = 0u; }
+    if (drop & 4u) { w[0] = w[1]; w[1] = w[2]; w[2] = w[3]; w[3] = 0u; }
+    v4i t;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t[j] = (int)__builtin_amdgcn_alignbyte(w[j + 1], w[j], drop & 3u);
+    return t;
+}
 
 constexpr int dmax(int a, int b) { return a > b ? a : b; }
 constexpr int dmin(int a, int b) { return a < b ? a : b; }
@@ -285,7 +300,9 @@ __global__ __launch_bounds__(1024) void direct_kernel(DirectParams gp)
         const int k = (sc0 * 8 + sl) * 64 + G * 16;
         v4i v{0, 0, 0, 0};
         if constexpr (RAW) {   // (masked and offset further down, behind the last load of this prologue: nothing waits in between)
-            if (m_l < M && sl < 8 * nsc && k < pr.K) v = *reinterpret_cast<const v4i*>(pr.a_raw + (size_t)m_l * pr.K + k);
+            // (rows of codes may start anywhere: global memory takes 16-byte loads at any address.  The last K % 16 codes of a
+            // row are the end of the load that stops at K, put in place below)
+            if (m_l < M && sl < 8 * nsc && k < pr.K) v = *reinterpret_cast<const v4i_byte*>(pr.a_raw + (size_t)m_l * pr.K + min(k, pr.K - 16));
         } else {
             if (m_l < M && sl < 8 * nsc) v = *reinterpret_cast<const v4i*>(pr.a_codes + (size_t)m_l * Kp + k);
         }
@@ -326,6 +343,14 @@ __global__ __launch_bounds__(1024) void direct_kernel(DirectParams gp)
             aq[q] = live ? v4i{(int)(((uint32_t)c.x & gp.a_mask) ^ flip), (int)(((uint32_t)c.y & gp.a_mask) ^ flip),
                                (int)(((uint32_t)c.z & gp.a_mask) ^ flip), (int)(((uint32_t)c.w & gp.a_mask) ^ flip)}
                          : v4i{0, 0, 0, 0};
+        }
+        if (pr.K & 15) {   // (uniform) the lanes that hold the last K % 16 codes of a row
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                const int sl = i_l < SL ? q * SL + i_l : 8 * R;
+                const int left = pr.K - ((sc0 * 8 + sl) * 64 + G * 16);
+                if (m_l < M && sl < 8 * nsc && left > 0 && left < 16) aq[q] = row_tail16(aq[q], left);
+            }
         }
     }
 

@@ -15,7 +15,7 @@
 // SiLU * up (KIND 1): h = half_rne((g / (1 + e)) * up) with e = exp(-g) as a fixed sequence of binary32
 // operations (no math library, no fused multiply-add): t = clamp(-g * log2(e), -126, 126), n = rint(t),
 // f = t - n, 2^f by a degree-6 Horner polynomial with coefficients ln(2)^k / k!, e = ldexp(2^f, n).
-#include "abq_internal.h"
+#include "abq_rows.h"
 #include "../../include/abq.h"
 
 namespace abq {
@@ -121,9 +121,10 @@ __device__ __forceinline__ uint16_t produce_half(uint16_t ab, uint16_t bb, float
     else return silu_mul_half(ab, bb);
 }
 
-// Fast path: K a multiple of 8 and at most 8 * BLOCK * VPT.  A thread keeps its VPT 16-byte vectors of x and
-// of gamma in registers across the three passes (sum of squares, range, codes): the row is read once.
-template <int KIND, int VPT, int BLOCK>
+// Rows of up to 32768 elements: a thread keeps its VPT vectors of x and of gamma in registers across the three passes
+// (sum of squares, range, codes), so the row is read once.  RAGGED: rows that are no whole number of vectors or start
+// off a 16-byte boundary.  Vectors past the row are zeros, which neither sum nor range sees.
+template <int KIND, int VPT, int BLOCK, bool RAGGED>
 __global__ __launch_bounds__(BLOCK) void producer_quant_rows_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ gamma,
                                                                  float eps, int q, int K, uint8_t* __restrict__ codes,
                                                                  float* __restrict__ scale, int32_t* __restrict__ zero,
@@ -134,29 +135,27 @@ __global__ __launch_bounds__(BLOCK) void producer_quant_rows_kernel(const uint16
     __shared__ uint64_t s_lo64[W], s_hi64[W];
     __shared__ float s_r, s_min[W], s_max[W];
     const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nvec = K >> 3, qmax = (1 << q) - 1;
-    const uint4* xrow = reinterpret_cast<const uint4*>(x + (size_t)m * K);
-    const uint4* grow = reinterpret_cast<const uint4*>(KIND == 0 ? gamma : gamma + (size_t)m * K);
+    const int nvec = (K + 7) >> 3, qmax = (1 << q) - 1;
+    const uint16_t* xrow = x + (size_t)m * K;
+    const uint16_t* grow = KIND == 0 ? gamma : gamma + (size_t)m * K;
     uint32_t xv[VPT][4], gv[VPT][4];
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
-        const int v = tid + i * BLOCK;
-        const uint4 a = xrow[v < nvec ? v : nvec - 1], b = grow[v < nvec ? v : nvec - 1];   // clamped: no conditional load
-        const bool in = v < nvec;
-        xv[i][0] = in ? a.x : 0u; xv[i][1] = in ? a.y : 0u; xv[i][2] = in ? a.z : 0u; xv[i][3] = in ? a.w : 0u;
-        gv[i][0] = b.x; gv[i][1] = b.y; gv[i][2] = b.z; gv[i][3] = b.w;
+        load_half8<RAGGED>(xrow, tid + i * BLOCK, K, xv[i]);
+        load_half8<RAGGED>(grow, tid + i * BLOCK, K, gv[i]);
     }
     if constexpr (KIND == 0) {
         if (residual) {   // x + residual first; the sum is the row that is normalized and the next residual
-            const uint4* rrow = reinterpret_cast<const uint4*>(residual + (size_t)m * K);
 #pragma unroll
-            for (int i = 0; i < VPT; ++i) {
+            for (int i = 0; i < VPT; ++i) {   // (a thread writes only the elements it has read: residual and sum_out may be one buffer)
                 const int v = tid + i * BLOCK;
-                const uint4 c = rrow[v < nvec ? v : nvec - 1];
-                xv[i][0] = add_half2(xv[i][0], c.x); xv[i][1] = add_half2(xv[i][1], c.y);
-                xv[i][2] = add_half2(xv[i][2], c.z); xv[i][3] = add_half2(xv[i][3], c.w);
-                if (v < nvec) reinterpret_cast<uint4*>(sum_out + (size_t)m * K)[v] = uint4{xv[i][0], xv[i][1], xv[i][2], xv[i][3]};
-                else { xv[i][0] = 0u; xv[i][1] = 0u; xv[i][2] = 0u; xv[i][3] = 0u; }
+                if (v < nvec) {
+                    uint32_t c[4];
+                    load_half8<RAGGED>(residual + (size_t)m * K, v, K, c);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) xv[i][j] = add_half2(xv[i][j], c[j]);
+                    store_half8<RAGGED>(sum_out + (size_t)m * K, v, K, xv[i]);
+                }
             }
         }
     }
@@ -178,6 +177,7 @@ __global__ __launch_bounds__(BLOCK) void producer_quant_rows_kernel(const uint16
         __syncthreads();
         if (tid == 0) {
             uint64_t tl = 0, th = 0;
+#pragma unroll
             for (int w = 0; w < W; ++w) add128(tl, th, s_lo64[w], s_hi64[w]);
             s_r = inv_rms(tl, th, K, eps);
         }
@@ -189,6 +189,8 @@ __global__ __launch_bounds__(BLOCK) void producer_quant_rows_kernel(const uint16
     float vmin = 0.0f, vmax = 0.0f;
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
+        const int v = tid + i * BLOCK;
+        if (VPT > 1 && v >= nvec) continue;   // (whole waves past the row skip the work)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const uint16_t y0 = produce_half<KIND>((uint16_t)(xv[i][j] & 0xFFFFu), (uint16_t)(gv[i][j] & 0xFFFFu), r);
@@ -198,9 +200,7 @@ __global__ __launch_bounds__(BLOCK) void producer_quant_rows_kernel(const uint16
             vmin = fminf(vmin, fminf(f0, f1));
             vmax = fmaxf(vmax, fmaxf(f0, f1));
         }
-        const int v = tid + i * BLOCK;
-        if (y_out && v < nvec)
-            reinterpret_cast<uint4*>(y_out + (size_t)m * K)[v] = uint4{xv[i][0], xv[i][1], xv[i][2], xv[i][3]};
+        if (y_out) store_half8<RAGGED>(y_out + (size_t)m * K, v, K, xv[i]);
     }
     for (int off = 32; off > 0; off >>= 1) {
         vmin = fminf(vmin, __shfl_xor(vmin, off, 64));
@@ -210,33 +210,19 @@ __global__ __launch_bounds__(BLOCK) void producer_quant_rows_kernel(const uint16
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < W; ++w) { vmin = fminf(vmin, s_min[w]); vmax = fmaxf(vmax, s_max[w]); }
-    float delta = 1.0f;
-    int z = 0;
-    if (vmax != vmin) {
-        delta = __fdiv_rn(__fsub_rn(vmax, vmin), (float)qmax);
-        const float zf = rintf(__fdiv_rn(-vmin, delta));
-        z = zf < 0.0f ? 0 : (zf > (float)qmax ? qmax : (int)zf);
-    }
-    if (tid == 0) { scale[m] = delta; zero[m] = z; }
+    const TokenQuantizer tq(vmin, vmax, qmax);
+    if (tid == 0) { scale[m] = tq.delta; zero[m] = tq.z; }
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
-        uint32_t out[2] = {0u, 0u};
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-#pragma unroll
-            for (int hsel = 0; hsel < 2; ++hsel) {
-                const float f = half_to_f32((uint16_t)(hsel ? xv[i][j] >> 16 : xv[i][j] & 0xFFFFu));
-                int c = (int)rintf(__fdiv_rn(f, delta)) + z;
-                c = c < 0 ? 0 : (c > qmax ? qmax : c);
-                const int e = 2 * j + hsel;
-                out[e >> 2] |= (uint32_t)c << (8 * (e & 3));
-            }
-        }
         const int v = tid + i * BLOCK;
-        if (v < nvec) reinterpret_cast<uint2*>(codes + (size_t)m * K)[v] = uint2{out[0], out[1]};
+        if (v >= nvec) continue;
+        uint32_t out[2];
+        tq.codes8(xv[i], out);
+        store_bytes8<RAGGED>(codes + (size_t)m * K, v, K, out);
     }
 }
 
+// Any row length (beyond 32768 elements): element by element, the row read once per pass.
 template <int KIND, int BLOCK>
 __global__ __launch_bounds__(BLOCK) void producer_quant_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ gamma,
                                                               float eps, int q, int K, uint8_t* __restrict__ codes,
@@ -300,22 +286,9 @@ __global__ __launch_bounds__(BLOCK) void producer_quant_kernel(const uint16_t* _
     __syncthreads();
 #pragma unroll
     for (int w = 0; w < W; ++w) { vmin = fminf(vmin, s_min[w]); vmax = fmaxf(vmax, s_max[w]); }
-    float delta = 1.0f;
-    int z = 0;
-    if (vmax != vmin) {
-        delta = __fdiv_rn(__fsub_rn(vmax, vmin), (float)qmax);
-        const float zf = rintf(__fdiv_rn(-vmin, delta));
-        z = zf < 0.0f ? 0 : (zf > (float)qmax ? qmax : (int)zf);
-    }
-    if (tid == 0) { scale[m] = delta; zero[m] = z; }
-
-    // codes
-    for (int k = tid; k < K; k += BLOCK) {
-        const float f = half_to_f32(normalized(k));
-        int c = (int)rintf(__fdiv_rn(f, delta)) + z;
-        c = c < 0 ? 0 : (c > qmax ? qmax : c);
-        codes[(size_t)m * K + k] = (uint8_t)c;
-    }
+    const TokenQuantizer tq(vmin, vmax, qmax);
+    if (tid == 0) { scale[m] = tq.delta; zero[m] = tq.z; }
+    for (int k = tid; k < K; k += BLOCK) codes[(size_t)m * K + k] = (uint8_t)tq.codes2<0>((uint32_t)normalized(k), 0u);
 }
 
 // KIND 0: b = gamma [K], eps used;  KIND 1: b = up [M,K], eps ignored.
@@ -324,13 +297,13 @@ static hipError_t launch_producer_quant(int q, int M, int K, const uint16_t* a, 
                                         float* scale, int32_t* zero, uint16_t* y_out, hipStream_t s,
                                         const uint16_t* residual = nullptr, uint16_t* sum_out = nullptr)
 {
-    // rows of whole, 16-byte aligned vectors that fit a workgroup's registers take the fast path
-    const bool vec_ok = K % 8 == 0 && K <= 16384 && ((uintptr_t)y_out & 15u) == 0;
-    if (vec_ok && K <= 2048) producer_quant_rows_kernel<KIND, 1, 256><<<M, 256, 0, s>>>(a, b, eps, q, K, codes, scale, zero, y_out, residual, sum_out);
-    else if (vec_ok && K <= 4096) producer_quant_rows_kernel<KIND, 1, 512><<<M, 512, 0, s>>>(a, b, eps, q, K, codes, scale, zero, y_out, residual, sum_out);
-    else if (vec_ok && K <= 8192) producer_quant_rows_kernel<KIND, 2, 512><<<M, 512, 0, s>>>(a, b, eps, q, K, codes, scale, zero, y_out, residual, sum_out);
-    else if (vec_ok) producer_quant_rows_kernel<KIND, 4, 512><<<M, 512, 0, s>>>(a, b, eps, q, K, codes, scale, zero, y_out, residual, sum_out);
-    else producer_quant_kernel<KIND, 256><<<M, 256, 0, s>>>(a, b, eps, q, K, codes, scale, zero, y_out, residual, sum_out);
+    const bool ragged = K % 8 != 0;   // (the tensors are 16-byte aligned; then every row of codes is 8-byte, every row of halves 16-byte aligned)
+    const bool done = for_row_shape((K + 7) / 8, M, [&](auto block, auto vpt) {
+        constexpr int B = decltype(block)::value, V = decltype(vpt)::value;
+        if (ragged) producer_quant_rows_kernel<KIND, V, B, true><<<M, B, 0, s>>>(a, b, eps, q, K, codes, scale, zero, y_out, residual, sum_out);
+        else producer_quant_rows_kernel<KIND, V, B, false><<<M, B, 0, s>>>(a, b, eps, q, K, codes, scale, zero, y_out, residual, sum_out);
+    });
+    if (!done) producer_quant_kernel<KIND, 256><<<M, 256, 0, s>>>(a, b, eps, q, K, codes, scale, zero, y_out, residual, sum_out);
     return hipGetLastError();
 }
 

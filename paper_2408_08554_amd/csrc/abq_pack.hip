@@ -1,6 +1,6 @@
 // Packing kernels: weight BitPacking (offline), activation BitPacking / ReQuant (online),
 // and the decode hooks the tests use.  Sec. 3.4 step 1 and Fig. 3b of the paper.
-#include "abq_internal.h"
+#include "abq_rows.h"
 #include "../../include/abq.h"
 
 #include <hip/hip_fp16.h>
@@ -259,121 +259,157 @@ __global__ __launch_bounds__(BLOCK) void act_rows_kernel(const void* __restrict_
     }
 }
 
-// ---- fast path of the same step: int8 rows only (no planes), rows 16-byte aligned -----------------
-// One workgroup per token; a thread handles 16 consecutive k per step with 128-bit loads and
-// stores.  The first two steps of a thread stay in registers between the min/max pass and the
-// quantizing pass (rows up to 32*BLOCK elements are read once).
-__device__ __forceinline__ void half8_to_float(const uint4& v, float* f)
+// ---- the same step for field-packed rows only (no planes), any K --------------------------------------
+__device__ __forceinline__ void write_act_header(const ActLayout& L, int tid, uint8_t* blob)
 {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        f[2 * i] = half_bits_to_float((uint16_t)(w[i] & 0xFFFFu));
-        f[2 * i + 1] = half_bits_to_float((uint16_t)(w[i] >> 16));
-    }
+    if (tid >= kHeaderBytes / 4) return;
+    uint32_t v = 0;
+    if (tid == 0) v = kMagicA; else if (tid == 1) v = 1; else if (tid == 2) v = (uint32_t)L.q;
+    else if (tid == 3) v = (uint32_t)L.M; else if (tid == 4) v = (uint32_t)L.K; else if (tid == 5) v = (uint32_t)L.layout;
+    ((uint32_t*)blob)[tid] = v;
 }
 
-template <bool SRC_HALF, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void act_rows_fast_kernel(const void* __restrict__ src, const float* __restrict__ a_scale,
-                                                              const int32_t* __restrict__ a_zero, ActLayout L,
-                                                              uint8_t* __restrict__ blob)
+template <int W>
+__device__ __forceinline__ int32_t block_sum(int32_t v, int32_t* s, int lane, int wave)   // (the total in thread 0)
 {
-    __shared__ float s_lo[BLOCK / 64], s_hi[BLOCK / 64];
-    __shared__ int32_t s_sum[BLOCK / 64];
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    if constexpr (W > 1) {
+        if (lane == 0) s[wave] = v;
+        __syncthreads();
+        v = 0;
+#pragma unroll
+        for (int w = 0; w < W; ++w) v += s[w];
+    }
+    return v;
+}
+
+// Quantizer: a thread keeps its VPT vectors of eight halves between the range and the codes, so the row is read once; it
+// writes eight bytes per vector, zeros from K to Kp.  Bound by its bytes (2 M K read, M Kp written) once the division is
+// five operations: 2048 x 5120 14.1 -> 11.5 us, and rows off a 16-byte boundary no longer go element by element.
+template <int VPT, int BLOCK, bool RAGGED>
+__global__ __launch_bounds__(BLOCK) void act_quant_rows_kernel(const uint16_t* __restrict__ x, ActLayout L, uint8_t* __restrict__ blob)
+{
+    constexpr int W = BLOCK / 64;
+    __shared__ float s_lo[W], s_hi[W];
+    __shared__ int32_t s_sum[W];
     const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int q = L.q, K = L.K, qmax = (1 << q) - 1;
-    const int nvalid = K / 16, nblk = L.Kp / 16;       // 16-element blocks with data / in the padded row
-    if (m == 0 && tid < kHeaderBytes / 4) {
-        uint32_t v = 0;
-        if (tid == 0) v = kMagicA; else if (tid == 1) v = 1; else if (tid == 2) v = (uint32_t)q;
-        else if (tid == 3) v = (uint32_t)L.M; else if (tid == 4) v = (uint32_t)K; else if (tid == 5) v = (uint32_t)L.layout;
-        ((uint32_t*)blob)[tid] = v;
-    }
-    // SRC_HALF: 16 halves = two uint4; codes: one uint4
-    constexpr int VPB = SRC_HALF ? 2 : 1;
-    const uint4* row = (const uint4*)src + (size_t)m * nvalid * VPB;
-    uint4 keep[2][VPB];
+    const int K = L.K, qmax = (1 << L.q) - 1;
+    if (m == 0) write_act_header(L, tid, blob);
+    const uint16_t* row = x + (size_t)m * K;
+    uint32_t xv[VPT][4];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int e = tid + i * BLOCK;
+    for (int i = 0; i < VPT; ++i) load_half8<RAGGED>(row, tid + i * BLOCK, K, xv[i]);
+    float lo = 0.0f, hi = 0.0f;
 #pragma unroll
-        for (int v = 0; v < VPB; ++v) keep[i][v] = e < nvalid ? row[(size_t)e * VPB + v] : make_uint4(0, 0, 0, 0);
-    }
-    float delta = 1.0f;
-    int z = 0;
-    if (SRC_HALF) {
-        float lo = 0.0f, hi = 0.0f;
-        for (int e = tid; e < nvalid; e += BLOCK) {
-            float f[16];
-            if (e < 2 * BLOCK) {
-                half8_to_float(keep[e >= BLOCK ? 1 : 0][0], f);
-                half8_to_float(keep[e >= BLOCK ? 1 : 0][VPB - 1], f + 8);
-            } else {
-                half8_to_float(row[(size_t)e * VPB], f);
-                half8_to_float(row[(size_t)e * VPB + VPB - 1], f + 8);
-            }
+    for (int i = 0; i < VPT; ++i)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) { lo = fminf(lo, f[i]); hi = fmaxf(hi, f[i]); }
+        for (int j = 0; j < 4; ++j) {
+            const float f0 = half_bits_to_float((uint16_t)(xv[i][j] & 0xFFFFu)), f1 = half_bits_to_float((uint16_t)(xv[i][j] >> 16));
+            lo = fminf(lo, fminf(f0, f1));
+            hi = fmaxf(hi, fmaxf(f0, f1));
         }
-        for (int off = 32; off > 0; off >>= 1) {
-            lo = fminf(lo, __shfl_xor(lo, off, 64));
-            hi = fmaxf(hi, __shfl_xor(hi, off, 64));
-        }
+    for (int off = 32; off > 0; off >>= 1) {
+        lo = fminf(lo, __shfl_xor(lo, off, 64));
+        hi = fmaxf(hi, __shfl_xor(hi, off, 64));
+    }
+    if constexpr (W > 1) {
         if (lane == 0) { s_lo[wave] = lo; s_hi[wave] = hi; }
         __syncthreads();
 #pragma unroll
-        for (int w = 0; w < BLOCK / 64; ++w) { lo = fminf(lo, s_lo[w]); hi = fmaxf(hi, s_hi[w]); }
-        if (hi != lo) {
-            delta = __fdiv_rn(__fsub_rn(hi, lo), (float)qmax);
-            const float zf = rintf(__fdiv_rn(-lo, delta));
-            z = zf < 0.0f ? 0 : (zf > (float)qmax ? qmax : (int)zf);
-        }
+        for (int w = 0; w < W; ++w) { lo = fminf(lo, s_lo[w]); hi = fmaxf(hi, s_hi[w]); }
     }
-    const uint32_t oa4 = (q == 8) ? 0x80808080u : 0u;           // a - 128 as a byte == a ^ 0x80
-    const uint32_t mask4 = (uint32_t)qmax * 0x01010101u;
-    int8_t* out = (int8_t*)(blob + L.off_codes) + (size_t)m * L.Kp;
+    const TokenQuantizer tq(lo, hi, qmax);
+    const uint32_t oa4 = (L.q == 8) ? 0x80808080u : 0u;           // a - 128 as a byte == a ^ 0x80
+    uint8_t* out = blob + L.off_codes + (size_t)m * L.Kp;
     uint32_t sum = 0;
-    for (int e = tid; e < nblk; e += BLOCK) {
-        uint32_t dw[4] = {0, 0, 0, 0};
-        if (e < nvalid) {
-            if (SRC_HALF) {
-                float f[16];
-                if (e < 2 * BLOCK) {
-                    half8_to_float(keep[e >= BLOCK ? 1 : 0][0], f);
-                    half8_to_float(keep[e >= BLOCK ? 1 : 0][VPB - 1], f + 8);
-                } else {
-                    half8_to_float(row[(size_t)e * VPB], f);
-                    half8_to_float(row[(size_t)e * VPB + VPB - 1], f + 8);
-                }
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    int c = (int)rintf(__fdiv_rn(f[i], delta)) + z;
-                    c = c < 0 ? 0 : (c > qmax ? qmax : c);
-                    dw[i >> 2] |= (uint32_t)c << (8 * (i & 3));
-                }
+    for (int i = 0; i < VPT; ++i) {
+        const int v = tid + i * BLOCK, left = K - 8 * v;           // elements of the row from this vector on
+        if (8 * v >= L.Kp) continue;
+        uint32_t dw[2] = {0u, 0u};
+        if (left > 0) {
+            tq.codes8(xv[i], dw);
+            if (RAGGED && left < 8) {                              // the padding holds zeros, not the zero-point
+                const uint64_t mask = ~(~0ull << (8 * left));
+                dw[0] &= (uint32_t)mask;
+                dw[1] &= (uint32_t)(mask >> 32);
+                sum = __builtin_amdgcn_udot4(dw[1], 0x01010101u, __builtin_amdgcn_udot4(dw[0], 0x01010101u, sum, false), false);
+                dw[0] ^= oa4 & (uint32_t)mask;
+                dw[1] ^= oa4 & (uint32_t)(mask >> 32);
             } else {
-                const uint4 v = e < 2 * BLOCK ? keep[e >= BLOCK ? 1 : 0][0] : row[e];
-                dw[0] = v.x & mask4; dw[1] = v.y & mask4; dw[2] = v.z & mask4; dw[3] = v.w & mask4;
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                sum = __builtin_amdgcn_udot4(dw[i], 0x01010101u, sum, false);   // sum of the four codes
-                dw[i] ^= oa4;
+                sum = __builtin_amdgcn_udot4(dw[1], 0x01010101u, __builtin_amdgcn_udot4(dw[0], 0x01010101u, sum, false), false);
+                dw[0] ^= oa4;
+                dw[1] ^= oa4;
             }
         }
-        *reinterpret_cast<uint4*>(out + (size_t)e * 16) = make_uint4(dw[0], dw[1], dw[2], dw[3]);
+        *reinterpret_cast<uint2*>(out + 8 * (size_t)v) = uint2{dw[0], dw[1]};
     }
-    int32_t isum = (int32_t)sum;
-    for (int off = 32; off > 0; off >>= 1) isum += __shfl_xor(isum, off, 64);
-    if (lane == 0) s_sum[wave] = isum;
-    __syncthreads();
-    if (tid == 0) {
-        int32_t t = 0;
+    const int32_t t = block_sum<W>((int32_t)sum, s_sum, lane, wave);
+    if (tid == 0) ((RowParams*)(blob + L.off_params))[m] = RowParams{t, tq.delta, tq.z, 0};
+}
+
+// Given codes: sixteen bytes per thread and step, VPT loads in flight.  RAGGED: K no multiple of 16, so that rows start
+// anywhere and the last vector is gathered byte by byte.
+template <int VPT, int BLOCK, bool RAGGED>
+__global__ __launch_bounds__(BLOCK) void act_code_rows_kernel(const uint8_t* __restrict__ codes, const float* __restrict__ a_scale,
+                                                              const int32_t* __restrict__ a_zero, ActLayout L,
+                                                              uint8_t* __restrict__ blob)
+{
+    constexpr int W = BLOCK / 64;
+    __shared__ int32_t s_sum[W];
+    const int m = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int K = L.K, nfull = K >> 4, nblk = L.Kp >> 4;
+    if (m == 0) write_act_header(L, tid, blob);
+    const uint8_t* row = codes + (size_t)m * K;
+    uint8_t* out = blob + L.off_codes + (size_t)m * L.Kp;
+    const float sc = a_scale[m];
+    const int32_t zp = a_zero[m];
+    const uint32_t oa4 = (L.q == 8) ? 0x80808080u : 0u;           // a - 128 as a byte == a ^ 0x80
+    const uint32_t mask4 = (uint32_t)((1 << L.q) - 1) * 0x01010101u;
+    uint32_t sum = 0;
+    for (int e0 = tid; e0 - tid < nblk; e0 += VPT * BLOCK) {
+        uint32_t dw[VPT][4];
 #pragma unroll
-        for (int w = 0; w < BLOCK / 64; ++w) t += s_sum[w];
-        RowParams* params = (RowParams*)(blob + L.off_params);
-        params[m] = SRC_HALF ? RowParams{t, delta, z, 0} : RowParams{t, a_scale[m], a_zero[m], 0};
+        for (int i = 0; i < VPT; ++i) {
+            const int e = e0 + i * BLOCK, ec = e < nfull ? e : nfull - 1;
+            if (!RAGGED || nfull > 0) {
+                if constexpr (RAGGED) {
+                    const u32x4_byte a = *reinterpret_cast<const u32x4_byte*>(row + 16 * ec);
+                    dw[i][0] = a.x; dw[i][1] = a.y; dw[i][2] = a.z; dw[i][3] = a.w;
+                } else {
+                    const uint4 a = *reinterpret_cast<const uint4*>(row + 16 * ec);
+                    dw[i][0] = a.x; dw[i][1] = a.y; dw[i][2] = a.z; dw[i][3] = a.w;
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < VPT; ++i) {
+            const int e = e0 + i * BLOCK;
+            if (e >= nblk) continue;
+            uint32_t o4[4] = {oa4, oa4, oa4, oa4};
+            if (e >= nfull) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) { dw[i][j] = 0u; o4[j] = 0u; }
+                if (RAGGED && e == nfull) {
+#pragma unroll
+                    for (int b = 0; b < 15; ++b)
+                        if (16 * e + b < K) {
+                            dw[i][b >> 2] |= (uint32_t)row[16 * e + b] << (8 * (b & 3));
+                            o4[b >> 2] |= oa4 & (0xFFu << (8 * (b & 3)));
+                        }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                dw[i][j] &= mask4;
+                sum = __builtin_amdgcn_udot4(dw[i][j], 0x01010101u, sum, false);   // sum of the four codes
+                dw[i][j] ^= o4[j];
+            }
+            *reinterpret_cast<uint4*>(out + 16 * (size_t)e) = uint4{dw[i][0], dw[i][1], dw[i][2], dw[i][3]};
+        }
     }
+    const int32_t t = block_sum<W>((int32_t)sum, s_sum, lane, wave);
+    if (tid == 0) ((RowParams*)(blob + L.off_params))[m] = RowParams{t, sc, zp, 0};
 }
 
 __global__ void unpack_act_bytes_kernel(const int8_t* __restrict__ in, int q, int M, int K, int Kp,
@@ -448,19 +484,32 @@ hipError_t launch_unpack_weights(const WeightLayout& L, const uint8_t* blob, int
 hipError_t launch_pack_act_codes(const ActLayout& L, const uint8_t* codes, const float* a_scale, const int32_t* a_zero,
                                  uint8_t* blob, hipStream_t s)
 {
-    if (!L.has_planes && L.K % 16 == 0)
-        act_rows_fast_kernel<false, 256><<<L.M, 256, 0, s>>>(codes, a_scale, a_zero, L, blob);
-    else
+    if (L.has_planes) {
         act_rows_kernel<false, 256><<<L.M, 256, 0, s>>>(codes, a_scale, a_zero, L, blob);
+    } else {
+        const int nblk = L.Kp / 16;
+        auto go = [&](auto block, auto vpt) {
+            constexpr int B = decltype(block)::value, V = decltype(vpt)::value;
+            if (L.K % 16) act_code_rows_kernel<V, B, true><<<L.M, B, 0, s>>>(codes, a_scale, a_zero, L, blob);
+            else act_code_rows_kernel<V, B, false><<<L.M, B, 0, s>>>(codes, a_scale, a_zero, L, blob);
+        };
+        if (nblk <= 128) go(std::integral_constant<int, 128>{}, std::integral_constant<int, 1>{});
+        else if (nblk <= 256) go(std::integral_constant<int, 256>{}, std::integral_constant<int, 1>{});
+        else if (nblk <= 512) go(std::integral_constant<int, 256>{}, std::integral_constant<int, 2>{});
+        else if (nblk <= 768) go(std::integral_constant<int, 256>{}, std::integral_constant<int, 3>{});
+        else go(std::integral_constant<int, 512>{}, std::integral_constant<int, 2>{});
+    }
     return hipGetLastError();
 }
 
 hipError_t launch_quant_pack_act(const ActLayout& L, const uint16_t* x, uint8_t* blob, hipStream_t s)
 {
-    if (!L.has_planes && L.K % 16 == 0)
-        act_rows_fast_kernel<true, 256><<<L.M, 256, 0, s>>>(x, nullptr, nullptr, L, blob);
-    else
-        act_rows_kernel<true, 256><<<L.M, 256, 0, s>>>(x, nullptr, nullptr, L, blob);
+    const bool done = !L.has_planes && for_row_shape(L.Kp / 8, L.M, [&](auto block, auto vpt) {
+        constexpr int B = decltype(block)::value, V = decltype(vpt)::value;
+        if (L.K % 8) act_quant_rows_kernel<V, B, true><<<L.M, B, 0, s>>>(x, L, blob);
+        else act_quant_rows_kernel<V, B, false><<<L.M, B, 0, s>>>(x, L, blob);
+    });
+    if (!done) act_rows_kernel<true, 256><<<L.M, 256, 0, s>>>(x, nullptr, nullptr, L, blob);   // planes, or a row of more than 32768
     return hipGetLastError();
 }
 

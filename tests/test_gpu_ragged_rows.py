@@ -1,0 +1,79 @@
+"""Rows of activations of any length on the device: the row kernels' workgroup choices and tails, and the decode kernel
+that reads unpacked rows starting at any byte, against the oracle (codes, sums, padding and accumulators bit for bit)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2408_08554_amd import synth
+from helpers import check_against_oracle, check_g128, gpu_gemm_fused, to_dev
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+FIELDS = 2
+# one K per workgroup choice, off and on a vector, one element past and short of it
+LENGTHS = [1, 7, 9, 17, 504, 513, 1023, 2049, 4091, 4104, 8199, 12289, 16385, 32761, 33000]
+
+
+@pytest.mark.parametrize("K", LENGTHS)
+@pytest.mark.parametrize("M,q", [(3, 8), (300, 5)])
+def test_row_packers_any_length(abq, M, q, K):
+    if M > 3 and K > 13000:
+        M = 260
+    print("rows", M, q, K, flush=True)
+    x = synth.act_fp16(5000 + K, M, K)
+    x[1] = 0
+    c = synth.make_case(2, q, M, 16, K, seed=5100 + K)
+    ref_codes, ref_scale, ref_zero = oracle.quant_act(x, q)
+    Kp, oa = (K + 511) // 512 * 512, 128 if q == 8 else 0
+    off = 256 + (M * 16 + 255) // 256 * 256
+    for packed, codes, scale, zero in ((abq.abq_quant_pack_act(q, to_dev(torch, x)), ref_codes, ref_scale, ref_zero),
+                                       (abq.abq_pack_act_codes(q, to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero)),
+                                        c.A, c.a_scale, c.a_zero)):
+        _, sc, zp, sm = abq.abq_unpack_act(q, M, K, FIELDS, packed, FIELDS)
+        rows = packed.cpu().numpy()[off:off + M * Kp].view(np.int8).reshape(M, Kp)
+        assert np.array_equal(rows[:, :K].astype(np.int64) + oa, codes.astype(np.int64))
+        assert not rows[:, K:].any()                                          # padding is zero bytes
+        assert np.array_equal(sc.cpu().numpy(), scale) and np.array_equal(zp.cpu().numpy(), zero)
+        assert np.array_equal(sm.cpu().numpy().astype(np.int64), codes.astype(np.int64).sum(axis=1))
+
+
+@pytest.mark.parametrize("M", [1, 2, 5, 16])
+@pytest.mark.parametrize("p,q,N,K", [(4, 8, 40, 17), (3, 5, 33, 31), (8, 8, 20, 1000), (1, 3, 50, 4091), (7, 7, 16, 2062), (2, 8, 31, 13001)])
+def test_fused_decode_of_rows_of_any_length(abq, M, p, q, N, K):
+    c = synth.make_case(p, q, M, N, K, seed=5200 + M + K, name=f"W{p}A{q} {M}x{N}x{K}")
+    print(c.name, flush=True)
+    y, acc = gpu_gemm_fused(torch, abq, c, FIELDS)
+    check_against_oracle(c, y, acc)
+
+
+@pytest.mark.parametrize("p,M", [(4, 2), (8, 3), (3, 12)])
+def test_grouped_short_and_ragged_rows_equal_single_calls(abq, p, M):
+    q, cases, problems = 8, [], []
+    for i, (N, K) in enumerate([(64, 1120), (40, 1120), (30, 3001), (64, 700)]):
+        c = synth.make_case(p, q, M, N, K, seed=5300 + i, name=f"grouped W{p}A{q} {M}x{N}x{K}")
+        cases.append(c)
+        problems.append({"N": N, "K": K, "packed_w": abq.abq_pack_weights(p, to_dev(torch, c.W), to_dev(torch, c.w_scale), to_dev(torch, c.w_zero)),
+                         "a_codes": to_dev(torch, c.A), "a_scale": to_dev(torch, c.a_scale), "a_zero": to_dev(torch, c.a_zero),
+                         "y": torch.empty((M, N), dtype=torch.float16, device="cuda")})
+    print("grouped", p, M, flush=True)
+    arr = abq.make_problems(problems)
+    need = abq.abq_gemm_grouped_workspace_bytes(p, q, M, arr, FIELDS, FIELDS)
+    abq.abq_gemm_grouped(p, q, M, arr, FIELDS, FIELDS, workspace=torch.empty(need, dtype=torch.uint8, device="cuda") if need else None)
+    torch.cuda.synchronize()
+    for c, d in zip(cases, problems):
+        y1, _ = gpu_gemm_fused(torch, abq, c, FIELDS)
+        assert np.array_equal(d["y"].cpu().numpy().view(np.uint16), y1.view(np.uint16)), c.name
+
+
+@pytest.mark.parametrize("p,K", [(4, 1000), (3, 4091), (2, 9001)])
+def test_g128_one_row_of_any_length(abq, p, K):
+    N, q = 40, 8
+    c = synth.make_case(p, q, 1, N, K, seed=5400 + K, name=f"g128 W{p}A{q} 1x{N}x{K}")
+    sh, zg = synth.group_quant_params(c)
+    pw = abq.abq_pack_weights_g128(p, to_dev(torch, c.W), to_dev(torch, sh.view(np.float16)), to_dev(torch, zg))
+    print(c.name, flush=True)
+    y, _ = abq.abq_gemm_act_codes(p, q, 1, N, K, to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero), pw, abq.ABQ_LAYOUT_FIELDS_G128)
+    torch.cuda.synchronize()
+    check_g128(c, sh, zg, y.cpu().numpy())
