@@ -89,6 +89,15 @@ __device__ __forceinline__ v4i merged_operand(const u4v* w)
     return r;
 }
 
+// a * b + c, low 32 bits, factors of 24 bits (written as the instruction: the compiler otherwise splits it into a multiply and
+// half of a three-operand add)
+__device__ __forceinline__ int32_t mad24(int32_t a, int32_t b, int32_t c)
+{
+    int32_t d;
+    asm("v_mad_i32_i24 %0, %1, %2, %3" : "=v"(d) : "v"(a), "v"(b), "v"(c));
+    return d;
+}
+
 // A tile in LDS: [128 rows][16 vectors of 16 B], vector v of row `row` stored at position v ^ (row & 15),
 // so that the 16 rows an operand read touches (same v) land in 16 different 16-byte bank groups.
 // Lane (r = lane%16, G = lane/16) reads, for m-tile mt and slice sl, vector 4*sl + G of row 16*mt + r.
@@ -100,6 +109,8 @@ __device__ __forceinline__ void read_a_operands(const uint8_t* a_buf, int r, int
     for (int mt = 0; mt < MT; ++mt) aop[mt] = *reinterpret_cast<const v4i*>(p + mt * 16 * kARow);
 }
 
+// The weights are the instruction's first operand, so that a lane's four accumulator registers are four adjacent channels of
+// one row of Y: the epilogue packs them into one 8-byte LDS write.
 template <int P, int NTW, int MT, int SL>
 __device__ __forceinline__ void slice_mfma(const u4v (*w)[phase_regs(P)], const v4i* aop, v4i (*acc)[NTW])
 {
@@ -107,7 +118,7 @@ __device__ __forceinline__ void slice_mfma(const u4v (*w)[phase_regs(P)], const 
     for (int nt = 0; nt < NTW; ++nt) {
         const v4i bop = merged_operand<P, SL>(w[nt]);
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(aop[mt], bop, acc[mt][nt], 0, 0, 0);
+        for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(bop, aop[mt], acc[mt][nt], 0, 0, 0);
     }
 }
 
@@ -296,57 +307,64 @@ __global__ __launch_bounds__(256, (WD == 4 ? 2 : (NTW <= 2 ? (MT == 4 ? 3 : 2) :
         }
     }
 
-    // Fused epilogue.  Lane l, register reg of accumulator tile (mt, nt) is row 16*mt + 4*(l/16) + reg,
-    // column 16*nt + l%16.  The fp16 values are transposed through LDS (the A buffers are free now; waves
-    // 0,1 use the first, waves 2,3 the second) so that each lane then stores 16 contiguous bytes of a row
-    // of Y instead of 2: full 32..128-byte row segments per wave instead of scattered halves.
+    // Fused epilogue.  Lane (G = l/16, r = l%16), register reg of accumulator tile (mt, nt) is row 16*mt + r, channel
+    // 16*nt + 4*G + reg.  The fp16 values pass through LDS (the A buffers are free now; waves 0,1 use the first, waves 2,3 the
+    // second; a wave reads back only what it wrote) so that each lane then stores 16 contiguous bytes of a row of Y.
     __syncthreads();   // every wave is done reading A
     constexpr int kWCols = NTW * kTileN;                       // columns of Y this wave owns
-    uint16_t* stage = reinterpret_cast<uint16_t*>((wave < 2 ? lds_a0 : lds_a1) + (wave & 1) * (kBM * kWCols * 2));
+    uint8_t* const stage = (wave < 2 ? lds_a0 : lds_a1) + (wave & 1) * (kBM * kWCols * 2);
     // Eq. 3's affine dequant in the integers, with everything that depends on the row or on the column alone taken out of
     // the element loop:  raw = S + ow sumA + oa sumW - K oa ow  (the sum over the codes themselves; S is over the stored,
     // offset operands) and centered = raw - wz sumA - az (sumW - K wz), all modulo 2^32 as in epilogue_value.  That
-    // leaves two multiplies per element.  32-bit integer multiplies run at a quarter of the vector rate and made this
-    // epilogue a third of a prefill launch; where every factor fits 24 bits (sums of codes below 2^23: the host checks
-    // K (2^p - 1) and K (2^q - 1)) the 24-bit multiply-add gives the same low 32 bits at the full rate.
-    RowParams pw[NTW];
-    int32_t col_raw[NTW], col_cw[NTW], col_nwz[NTW];
-#pragma unroll
-    for (int nt = 0; nt < NTW; ++nt) {
-        pw[nt] = par_w[wave * kWCols + nt * 16 + r];
-        col_raw[nt] = (int32_t)((uint32_t)prm.oa * (uint32_t)pw[nt].sum - (uint32_t)prm.K * (uint32_t)prm.oa * (uint32_t)prm.ow);
-        col_cw[nt] = (int32_t)((uint32_t)pw[nt].sum - (uint32_t)prm.K * (uint32_t)pw[nt].zero);
-        col_nwz[nt] = -pw[nt].zero;
-    }
+    // leaves two multiplies per element.  32-bit integer multiplies run at a quarter of the vector rate; where every
+    // factor fits 24 bits (sums of codes below 2^23: the host checks K (2^p - 1) and K (2^q - 1)) the 24-bit multiply-add
+    // gives the same low 32 bits at the full rate.
+    // What bounds this part is vector issue and LDS writes, hence one 8-byte LDS write per four elements, spread over the
+    // banks, and fused multiply-adds.  (One 2-byte write per element with its four row groups on the same banks, separate
+    // multiplies and adds: W4A4 M=2048 5120->13824 with its quantizer 135.1 us, now 132.7; W6A6 M=128 4096->11008 17.3, now 16.7.)
+    auto swz = [](int row) { return NTW == 4 ? (row >> 1) & 7 : (NTW == 2 ? (row >> 2) & 3 : 0); };   // 16-byte piece of a row -> bank spread
     auto dequant_tile = [&](auto narrow, auto plain) {
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
+        for (int nt = 0; nt < NTW; ++nt) {
+            RowParams pw[4];
+            int32_t col_raw[4], col_cw[4], col_wz[4];
 #pragma unroll
             for (int reg = 0; reg < 4; ++reg) {
-                const int ml = mt * 16 + 4 * G + reg;
-                const int m = m0 + ml;
-                const RowParams pa = par_a[ml];
-                const int32_t row_raw = (int32_t)((uint32_t)prm.ow * (uint32_t)pa.sum), naz = -pa.zero;
+                pw[reg] = par_w[wave * kWCols + nt * 16 + 4 * G + reg];
+                col_raw[reg] = (int32_t)((uint32_t)prm.oa * (uint32_t)pw[reg].sum - (uint32_t)prm.K * (uint32_t)prm.oa * (uint32_t)prm.ow);
+                col_cw[reg] = (int32_t)((uint32_t)pw[reg].sum - (uint32_t)prm.K * (uint32_t)pw[reg].zero);
+                col_wz[reg] = (int32_t)((uint32_t)prm.ow - (uint32_t)pw[reg].zero);
+            }
+            uint8_t* const dst = stage + r * (kWCols * 2) + (((2 * nt + (G >> 1)) ^ swz(r)) << 4) + (G & 1) * 8;
 #pragma unroll
-                for (int nt = 0; nt < NTW; ++nt) {
-                    const int32_t raw = (int32_t)((uint32_t)acc[mt][nt][reg] + (uint32_t)row_raw + (uint32_t)col_raw[nt]);
+            for (int mt = 0; mt < MT; ++mt) {
+                const RowParams pa = par_a[mt * 16 + r];
+                const int m = m0 + mt * 16 + r;
+                const int32_t naz = (int32_t)(0u - (uint32_t)pa.zero);
+                uint32_t hv[4];
+#pragma unroll
+                for (int reg = 0; reg < 4; ++reg) {
+                    const int32_t s = (int32_t)((uint32_t)acc[mt][nt][reg] + (uint32_t)col_raw[reg]);   // (raw less ow sumA)
                     int32_t centered;
                     if constexpr (decltype(narrow)::value)
-                        centered = __mul24(naz, col_cw[nt]) + (__mul24(col_nwz[nt], pa.sum) + raw);
+                        centered = mad24(naz, col_cw[reg], mad24(col_wz[reg], pa.sum, s));
                     else
-                        centered = (int32_t)((uint32_t)raw + (uint32_t)col_nwz[nt] * (uint32_t)pa.sum + (uint32_t)naz * (uint32_t)col_cw[nt]);
-                    const float v = ((float)centered * pa.scale) * pw[nt].scale;
-                    uint32_t hv;
-                    asm("v_cvt_f16_f32 %0, %1" : "=v"(hv) : "v"(v));   // (the instruction itself: see epilogue_value)
-                    const uint16_t h = (uint16_t)hv;
-                    stage[ml * kWCols + nt * 16 + r] = h;
+                        centered = (int32_t)((uint32_t)s + (uint32_t)col_wz[reg] * (uint32_t)pa.sum + (uint32_t)naz * (uint32_t)col_cw[reg]);
+                    const float v = ((float)centered * pa.scale) * pw[reg].scale;
+                    asm("v_cvt_f16_f32 %0, %1" : "=v"(hv[reg]) : "v"(v));   // (the instruction itself: see epilogue_value)
                     if constexpr (!decltype(plain)::value) {
-                        const int n = n0 + wave * kWCols + nt * 16 + r;
-                        if (prm.acc && m < prm.M && n < prm.N) prm.acc[(size_t)m * prm.N + n] = raw;
-                        if (prm.rq.codes && m < prm.M && n < prm.N)
-                            prm.rq.codes[(size_t)m * prm.N + n] = requant_code(h, prm.rq.scale[m], prm.rq.zero[m], prm.rq.qmax);
+                        const int n = n0 + wave * kWCols + nt * 16 + 4 * G + reg;
+                        if (m < prm.M && n < prm.N) {
+                            if (prm.acc) prm.acc[(size_t)m * prm.N + n] = (int32_t)((uint32_t)s + (uint32_t)prm.ow * (uint32_t)pa.sum);
+                            if (prm.rq.codes)
+                                prm.rq.codes[(size_t)m * prm.N + n] = requant_code((uint16_t)hv[reg], prm.rq.scale[m], prm.rq.zero[m], prm.rq.qmax);
+                        }
                     }
                 }
+                uint2 h4;
+                h4.x = __builtin_amdgcn_perm(hv[1], hv[0], 0x05040100u);   // the low halves of both
+                h4.y = __builtin_amdgcn_perm(hv[3], hv[2], 0x05040100u);
+                *reinterpret_cast<uint2*>(dst + mt * 16 * kWCols * 2) = h4;
             }
         }
     };
@@ -366,7 +384,7 @@ __global__ __launch_bounds__(256, (WD == 4 ? 2 : (NTW <= 2 ? (MT == 4 ? 3 : 2) :
         const int ml = idx / kPieces, piece = idx % kPieces;
         const int m = m0 + ml, n = n0 + wave * kWCols + piece * 8;
         if (prm.y && m < prm.M && n < prm.N) {
-            const uint4 v = *reinterpret_cast<const uint4*>(stage + ml * kWCols + piece * 8);
+            const uint4 v = *reinterpret_cast<const uint4*>(stage + ml * kWCols * 2 + ((piece ^ swz(ml & 15)) << 4));
             uint16_t* dst = prm.y + (size_t)m * prm.N + n;
             if (vec_ok && n + 8 <= prm.N) {
                 *reinterpret_cast<uint4*>(dst) = v;
