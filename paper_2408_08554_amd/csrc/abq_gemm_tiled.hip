@@ -409,8 +409,8 @@ __global__ __launch_bounds__(256, (WD == 4 ? 2 : (NTW <= 2 ? (MT == 4 ? 3 : 2) :
 // gives sum_k a' of every row in every column, an MFMA of ones against the B operand gives sum_k w' of every column
 // in every row — both already in the accumulator layout.  k past K holds a' = 0 and w' = z (the packer pads the last
 // group of a g128 blob with its zero-point), so padded k add nothing; groups wholly past K carry scale 0.
-// Then two 24-bit integer multiply-adds, one conversion and one fused multiply-add per element and group: M*N*K/128
-// of each, which is what bounds this kernel (the vector ALU, not the matrix pipe).
+// What bounds this kernel is the vector ALU: M*N*K/128 times the operations per element and group.  step_g128 (p = 7, 8) takes five
+// (two 24-bit multiplies, a three-operand add, a conversion, a fused multiply-add), step_g128_centred (p <= 6) three.
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 template <int P, int NTW, int MT, int PH>
@@ -466,8 +466,104 @@ __device__ __forceinline__ void step_g128(const u4v (*w)[phase_regs(P)], const u
     }
 }
 
+// The same step for p <= 6, where w' - z + 64 is a byte of 0..127 for every code and zero-point: the zero-point goes into the
+// operand (one add per dword of four bytes, no carries between them), and the 64 comes off again through the accumulators' start
+// value -64 sum_k a', an MFMA's result that serves all columns.  What remains per element and group is one multiply-add for the
+// token's zero-point, one conversion, one fused multiply-add, and with two tiles per wave these run under the next unit's MFMAs
+// (left alone, the scheduler puts all MFMAs of a unit first and the matrix pipe then idles through the flush).  The sums are the
+// same integers in the same order.  p = 7, 8 have no room for z in the byte.  With its quantizer, W4A8 M=1024 5120->13824 167 us
+// -> 153 by the centred operand -> 140 by the overlap; M=1024 11008->4096 p = 1..6 100-108 -> 81-96, M=32 4096^2 16-20 -> 13-14.
+template <int P, int NTW, int MT, int PH>
+__device__ __forceinline__ void step_g128_centred(const u4v (*w)[phase_regs(P)], const u4v* gq, const uint8_t* a_buf, int r, int G,
+                                                  const v4i* nzc, v4f (*facc)[NTW])
+{
+    const int one4 = 0x01010101, m64 = (int)0xC0C0C0C0u;
+    const v4i ones{one4, one4, one4, one4}, minus64{m64, m64, m64, m64}, zero4{0, 0, 0, 0}, wbase{-128 * 64, -128 * 64, -128 * 64, -128 * 64};
+    v4i a0[MT], a1[MT], start[MT], b[2][2], c[2][MT], wsum[2];
+    auto read_group = [&](auto JC) {
+        constexpr int SL = 2 * decltype(JC)::value;
+        read_a_operands<MT>(a_buf, r, G, SL, a0);
+        read_a_operands<MT>(a_buf, r, G, SL + 1, a1);
+    };
+    // unit U = group 2*PH + U/NTW of the super-chunk against tile U%NTW: its operands, its products, its flush into the tile sums
+    auto expand = [&](auto UC) {
+        constexpr int U = decltype(UC)::value, J = U / NTW, nt = U % NTW, SL = 4 * PH + 2 * J, gj = 2 * PH + J, s = U & 1;
+        const int z = ((int)(gq[nt].z << (24 - 8 * gj))) >> 24;
+        const uint32_t off = __builtin_amdgcn_perm(0u, (uint32_t)(64 - z), 0u);   // its low byte in all four
+        b[s][0] = merged_operand<P, SL>(w[nt]);
+        b[s][1] = merged_operand<P, SL + 1>(w[nt]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            b[s][0][i] = (int)((uint32_t)b[s][0][i] + off);
+            b[s][1][i] = (int)((uint32_t)b[s][1][i] + off);
+        }
+    };
+    auto multiply = [&](auto UC) {
+        constexpr int U = decltype(UC)::value, s = U & 1;
+        if constexpr (U % NTW == 0) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) start[mt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[mt], minus64, zero4, 0, 0, 0);
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) start[mt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[mt], minus64, start[mt], 0, 0, 0);
+        }
+        wsum[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones, b[s][0], wbase, 0, 0, 0);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) c[s][mt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[mt], b[s][0], start[mt], 0, 0, 0);
+        wsum[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones, b[s][1], wsum[s], 0, 0, 0);   // (every row: the column's sum of w' - z)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) c[s][mt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[mt], b[s][1], c[s][mt], 0, 0, 0);
+    };
+    auto flush = [&](auto UC) {
+        constexpr int U = decltype(UC)::value, nt = U % NTW, gj = 2 * PH + U / NTW, s = U & 1;
+        const uint32_t sbits = (gj < 2 ? gq[nt].x : gq[nt].y) >> (16 * (gj & 1));
+        const float sc = __half2float(__ushort_as_half((unsigned short)(sbits & 0xFFFFu)));
+        const int wz = wsum[s].x;
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int reg = 0; reg < 4; ++reg) {
+                const int t = __mul24(nzc[mt][reg], wz) + c[s][mt][reg];
+                facc[mt][nt][reg] = fmaf((float)t, sc, facc[mt][nt][reg]);
+            }
+    };
+    // A unit's flush runs under the products of the next one: one MFMA (16 cycles of the matrix pipe), then a few vector instructions.
+    // (The next operands are expanded one unit ahead, or the MFMAs would wait for them in a row of their own.)
+    auto overlap = [&](auto UC) {                      // products of unit U, flush of U - 1, operands of U + 1
+        constexpr int U = decltype(UC)::value;
+        constexpr int mfmas = (U % NTW == 0 ? 2 * MT : 0) + 2 * MT + 2;
+        multiply(UC);
+        flush(std::integral_constant<int, U - 1>{});
+        if constexpr (U + 1 < 2 * NTW) expand(std::integral_constant<int, U + 1>{});
+#pragma unroll
+        for (int i = 0; i < mfmas; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, U % NTW == 0 ? 4 : 7, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    read_group(std::integral_constant<int, 0>{});
+    expand(std::integral_constant<int, 0>{});
+    multiply(std::integral_constant<int, 0>{});
+    if constexpr (NTW == 1) {                          // (three workgroups per CU overlap each other; two units in flight would spill)
+        flush(std::integral_constant<int, 0>{});
+        __builtin_amdgcn_sched_barrier(0);
+        read_group(std::integral_constant<int, 1>{});
+        expand(std::integral_constant<int, 1>{});
+        multiply(std::integral_constant<int, 1>{});
+    } else {
+        expand(std::integral_constant<int, 1>{});
+        __builtin_amdgcn_sched_barrier(0);
+        overlap(std::integral_constant<int, 1>{});
+        read_group(std::integral_constant<int, 1>{});
+        overlap(std::integral_constant<int, 2>{});
+        overlap(std::integral_constant<int, 3>{});
+    }
+    flush(std::integral_constant<int, 2 * NTW - 1>{});
+}
+
+// (Registers: one tile per wave fits three workgroups per CU at p = 1, 2, 4; the merges of p = 3, 5..7 would spill.)
 template <int P, int NTW>
-__global__ __launch_bounds__(256, 2) void tiled_g128_kernel(TiledParams prm)
+__global__ __launch_bounds__(256, NTW == 1 && P <= 4 && P != 3 ? 3 : 2) void tiled_g128_kernel(TiledParams prm)
 {
     constexpr int MT = 4;
     constexpr int kBM = MT * 16, kBN = 4 * NTW * kTileN;
@@ -522,12 +618,16 @@ __global__ __launch_bounds__(256, 2) void tiled_g128_kernel(TiledParams prm)
     a_prefetch(0, lds_a0);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (a wave's direct loads land before it enters a barrier, here and below: see tiled_kernel)
     __syncthreads();
-    // zero-points of this lane's accumulator rows, less oa
+    // zero-points of this lane's accumulator rows, less oa; negated where the token's correction is all that is left
+    constexpr bool kCentred = P <= 6;
     v4i zc[MT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int reg = 0; reg < 4; ++reg) zc[mt][reg] = par_a[mt * 16 + 4 * G + reg].zero - prm.oa;
+        for (int reg = 0; reg < 4; ++reg) {
+            const int zr = par_a[mt * 16 + 4 * G + reg].zero - prm.oa;
+            zc[mt][reg] = kCentred ? -zr : zr;
+        }
 
     const int nsteps = prm.nsuper * 2;
     for (int sc = 0; sc < prm.nsuper; ++sc) {
@@ -536,14 +636,16 @@ __global__ __launch_bounds__(256, 2) void tiled_g128_kernel(TiledParams prm)
             load_tiles<P, NTW>(prm, tile0, sc, 1, lane, wb);
             load_records(scn, gq_next);
             a_prefetch(2 * sc + 1, lds_a1);
-            step_g128<P, NTW, MT, 0>(wa, gq, lds_a0, r, G, zc, facc);
+            if constexpr (kCentred) step_g128_centred<P, NTW, MT, 0>(wa, gq, lds_a0, r, G, zc, facc);
+            else step_g128<P, NTW, MT, 0>(wa, gq, lds_a0, r, G, zc, facc);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
         }
         {
             load_tiles<P, NTW>(prm, tile0, scn, 0, lane, wa);
             a_prefetch(min(2 * sc + 2, nsteps - 1), lds_a0);
-            step_g128<P, NTW, MT, 1>(wb, gq, lds_a1, r, G, zc, facc);
+            if constexpr (kCentred) step_g128_centred<P, NTW, MT, 1>(wb, gq, lds_a1, r, G, zc, facc);
+            else step_g128<P, NTW, MT, 1>(wb, gq, lds_a1, r, G, zc, facc);
             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
         }

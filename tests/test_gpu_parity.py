@@ -968,6 +968,24 @@ def test_g128_prefill_exact_when_the_float_sum_is_exact(abq):
     assert np.array_equal(y.view(np.uint16), y16ref)
 
 
+@pytest.mark.parametrize("M,N", [(33, 100), (300, 9850)], ids=["one_tile_per_wave", "two_tiles_per_wave"])
+@pytest.mark.parametrize("p", [1, 3, 5, 6, 7])
+def test_g128_prefill_extremes(abq, p, M, N):
+    """Zero-points at both ends of their range against codes at both ends, for tokens and groups (the operand byte w' - z + 64
+    then takes its extremes), a last group of 20 values that also leaves two groups of the last step empty, and the two tile widths."""
+    q, K = 8, 128 * 9 + 20
+    c = synth.make_case(p, q, M, N, K, seed=9850 + p, name=f"g128 prefill ends W{p}A{q} {M}x{N}x{K}")
+    say(c.name)
+    sh, zg = synth.group_quant_params(c)
+    top = (1 << p) - 1
+    zg[:, 0::2], zg[:, 1::2] = 0, top
+    c.W[0::3], c.W[1::3] = top, 0
+    c.A[0::4], c.A[1::4] = 255, 0
+    c.a_zero[0::2], c.a_zero[1::2] = 0, 255
+    c.a_scale[:] = np.float32(2e-4)      # (outputs of saturated rows stay inside binary16)
+    check_g128(c, sh, zg, run_g128(abq, c, sh, zg, False))
+
+
 # ---- ReQuant fused into the matmul epilogue (the consumer side of Fig. 3b) --------------------------------------
 @pytest.mark.parametrize("p,q,q_out,M,N,K,layout", [(4, 8, 8, 1, 300, 4096, FIELDS),      # direct decode kernel
                                                     (2, 8, 4, 7, 70, 1552, FIELDS),       # direct, ragged
