@@ -319,6 +319,12 @@ __global__ __launch_bounds__(BLOCK) void act_quant_rows_kernel(const uint16_t* _
         for (int w = 0; w < W; ++w) { lo = fminf(lo, s_lo[w]); hi = fmaxf(hi, s_hi[w]); }
     }
     const TokenQuantizer tq(lo, hi, qmax);
+    if constexpr (VPT >= 8) {   // the halves are converted again for the codes: kept as floats they would not fit the registers
+#pragma unroll
+        for (int i = 0; i < VPT; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) asm("" : "+v"(xv[i][j]));
+    }
     const uint32_t oa4 = (L.q == 8) ? 0x80808080u : 0u;           // a - 128 as a byte == a ^ 0x80
     uint8_t* out = blob + L.off_codes + (size_t)m * L.Kp;
     uint32_t sum = 0;
@@ -504,12 +510,24 @@ hipError_t launch_pack_act_codes(const ActLayout& L, const uint8_t* codes, const
 
 hipError_t launch_quant_pack_act(const ActLayout& L, const uint16_t* x, uint8_t* blob, hipStream_t s)
 {
-    const bool done = !L.has_planes && for_row_shape(L.Kp / 8, L.M, [&](auto block, auto vpt) {
+    if (L.has_planes) {
+        act_rows_kernel<true, 256><<<L.M, 256, 0, s>>>(x, nullptr, nullptr, L, blob);
+        return hipGetLastError();
+    }
+    auto go = [&](auto block, auto vpt) {
         constexpr int B = decltype(block)::value, V = decltype(vpt)::value;
         if (L.K % 8) act_quant_rows_kernel<V, B, true><<<L.M, B, 0, s>>>(x, L, blob);
         else act_quant_rows_kernel<V, B, false><<<L.M, B, 0, s>>>(x, L, blob);
-    });
-    if (!done) act_rows_kernel<true, 256><<<L.M, 256, 0, s>>>(x, nullptr, nullptr, L, blob);   // planes, or a row of more than 32768
+    };
+    const int nvec = L.Kp / 8;
+    static_assert(ABQ_MAX_K <= 8 * 1024 * 16, "the longest row fits the last shape");
+    // Beyond for_row_shape's 32768 elements: this kernel keeps one vector per step, not two, so that 16 of them fit a workgroup of
+    // 1024 threads.  (Such a row element by element, as blobs with planes are packed: K = 53248 M = 1 77 us, here 8.9; M = 512 160,
+    // here 27; K = 131072 M = 512 374, here 55.)
+    if (!for_row_shape(nvec, L.M, go)) {
+        if (nvec <= 8192) go(std::integral_constant<int, 1024>{}, std::integral_constant<int, 8>{});
+        else go(std::integral_constant<int, 1024>{}, std::integral_constant<int, 16>{});
+    }
     return hipGetLastError();
 }
 

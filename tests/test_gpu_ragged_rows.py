@@ -77,3 +77,45 @@ def test_g128_one_row_of_any_length(abq, p, K):
     y, _ = abq.abq_gemm_act_codes(p, q, 1, N, K, to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero), pw, abq.ABQ_LAYOUT_FIELDS_G128)
     torch.cuda.synchronize()
     check_g128(c, sh, zg, y.cpu().numpy())
+
+
+def _graph_us(fn, count=8):
+    """Device time of one call, from replays of a graph of `count` calls (the fastest of five)."""
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        fn()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        for _ in range(count):
+            fn()
+    best = float("inf")
+    for _ in range(6):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record(), g.replay(), b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / count)
+    return best
+
+
+@pytest.mark.parametrize("K", [32768 + 16, 53248, 65536 + 9, 131072 - 5, 131072])
+def test_quantizer_of_the_longest_rows(abq, K):
+    """Rows of more than 32768 halves: codes, sums and padding, and the time of such a row against that of the longest row below."""
+    M, q = 3, 8
+    print("long rows", K, flush=True)
+    x = synth.act_fp16(5500 + K, M, K)
+    codes, scale, zero = oracle.quant_act(x, q)
+    xd = to_dev(torch, x)
+    packed = abq.abq_quant_pack_act(q, xd)
+    _, sc, zp, sm = abq.abq_unpack_act(q, M, K, FIELDS, packed, FIELDS)
+    Kp, off = (K + 511) // 512 * 512, 256 + (M * 16 + 255) // 256 * 256
+    rows = packed.cpu().numpy()[off:off + M * Kp].view(np.int8).reshape(M, Kp)
+    assert np.array_equal(rows[:, :K].astype(np.int64) + 128, codes.astype(np.int64)) and not rows[:, K:].any()
+    assert np.array_equal(sc.cpu().numpy(), scale) and np.array_equal(zp.cpu().numpy(), zero)
+    assert np.array_equal(sm.cpu().numpy().astype(np.int64), codes.astype(np.int64).sum(axis=1))
+    # one workgroup per row either way, so the time goes with the row at most (a fixed part keeps it below); element by element, a
+    # row just above 32768 took ten times the one just below
+    ref = torch.from_numpy(x[:, :32768].copy()).cuda()
+    out = torch.empty_like(packed)
+    longest, below = _graph_us(lambda: abq.abq_quant_pack_act(q, xd, out=out)), _graph_us(lambda: abq.abq_quant_pack_act(q, ref, out=out))
+    assert longest < 2.0 * below * K / 32768, f"{longest:.1f} us against {below:.1f} us for 32768"
