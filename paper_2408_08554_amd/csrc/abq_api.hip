@@ -404,8 +404,7 @@ static bool choose_direct(const GemmArgs& g, const ActLayout& A, const WeightLay
     lookup_plan(g.p, g.q, g.M, g.N, g.K, &ov);
     const int env = tuning_env("ABQ_DIRECT_R");
     const int forced = ov.direct_r != 0 ? ov.direct_r : env;
-    // Unpacked rows of a K that is no multiple of 16: only this kernel reads them (the others stage whole 16-byte vectors), and
-    // where it is not the fastest it loses less than the pack launch in front of them costs (2.5 us).
+    // (unpacked rows of a K that is no multiple of 16: only this kernel reads them, and fused_act_ragged has decided that it does)
     if (g.a_raw && g.K % 16 != 0) return direct_plan(g.p, g.M, A.Kp / kSuperK, 0, pl);
     if (forced < 0) return false;
     if (forced == 0 && !direct_by_rule(g.p, g.M, A.Kp / kSuperK, W)) return false;
@@ -559,8 +558,26 @@ static bool fused_act_direct(const WeightLayout& W, int force, int p, int q, int
     if (!choose_fields(true, W.has_planes, force, p, q, M, N)) return false;
     return streaming_shape(M, N) && K % 16 == 0;
 }
-// Rows that are no whole number of 16-byte vectors are one kernel too where the direct kernel takes them (it reads rows of
-// any length from 16 on); the workspace that the query names stays unused then.
+// Unpacked rows of a K that is no multiple of 16: the direct kernel reads them as they are, the others take packed rows.  Every
+// 16-channel tile reads all of A, and a 16-byte load off a dword boundary costs several times one that is on it, so the direct
+// kernel's loss goes with the bytes of A that a CU reads, against the 2.5-4 us of the pack launch in front of the others.
+// Measured (one kernel / pack + matmul, us; 9576 sizes of K = 770..13822, 512..13824 channels, M = 1..16, six widths):
+//   M = 1, and up to M = 4 where the rows start on dword boundaries (K a multiple of 4): one kernel (W2A8 13824 ch, K = 5118:
+//     6.0 / 8.7), except the longest streams of the wide widths (W8A8, K = 13816: 36.4 / 33.3; 8192 ch: 20.7 / 21.8);
+//   more rows on dword boundaries: up to 144 KiB of A per CU (W2A8: 4096 ch, K = 4092, M = 16 5.2 / 7.7; 13824 ch, K = 5124,
+//     M = 16 18.5 / 12.0);
+//   other rows: up to 48 KiB (W2A8: 4096 ch, K = 4090, M = 8 5.7 / 6.6; 13824 ch, K = 5118, M = 4 11.8 / 9.9, M = 16 37 / 12).
+// The choice is 0.5 % from the better one of each size on average, at most 35 % (one kernel always: 10 % and 4.7 times).
+static bool ragged_by_rule(int p, int M, int K, const WeightLayout& W)
+{
+    const bool dwords = K % 4 == 0;
+    const int nsuper = (K + kSuperK - 1) / kSuperK;
+    if (M == 1 || (dwords && M <= 4))
+        return !(p >= 5 && nsuper > 24 && (size_t)p * W.NT * kTileN * (size_t)nsuper * kSuperK / 8 > ((size_t)96 << 20));
+    const long tiles_per_cu = (W.NT + num_cus() - 1) / num_cus();
+    return (long)M * K * tiles_per_cu <= (dwords ? 144L << 10 : 48L << 10);
+}
+// Such a call is one kernel then; the workspace that the query names stays unused.
 static bool fused_act_ragged(const WeightLayout& W, int force, int p, int q, int M, int N, int K)
 {
     if (!W.has_fields || force == ABQ_USE_PLANES || K % 16 == 0 || K < 16 || M > kSkinnyMaxM) return false;
@@ -570,7 +587,7 @@ static bool fused_act_ragged(const WeightLayout& W, int force, int p, int q, int
     PlanOverride ov;
     lookup_plan(p, q, M, N, K, &ov);
     if (ov.direct_r < 0) return false;   // (another decode kernel is asked for: it takes packed rows)
-    return choose_fields(true, W.has_planes, force, p, q, M, N) && direct_plan(p, M, nsuper, 0, &pl);
+    return choose_fields(true, W.has_planes, force, p, q, M, N) && ragged_by_rule(p, M, K, W) && direct_plan(p, M, nsuper, 0, &pl);
 }
 
 size_t abq_gemm_act_codes_workspace_bytes(int p, int q, int M, int N, int K, int w_layout)

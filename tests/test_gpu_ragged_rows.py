@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 from paper_2408_08554_amd import synth
-from helpers import check_against_oracle, check_g128, gpu_gemm_fused, to_dev
+from helpers import check_against_oracle, check_g128, check_sampled, gpu_gemm, gpu_gemm_fused, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -119,3 +119,23 @@ def test_quantizer_of_the_longest_rows(abq, K):
     out = torch.empty_like(packed)
     longest, below = _graph_us(lambda: abq.abq_quant_pack_act(q, xd, out=out)), _graph_us(lambda: abq.abq_quant_pack_act(q, ref, out=out))
     assert longest < 2.0 * below * K / 32768, f"{longest:.1f} us against {below:.1f} us for 32768"
+
+
+@pytest.mark.parametrize("p,M,N,K,one_kernel", [
+    (2, 1, 13824, 5118, True), (5, 1, 13824, 5118, True),                                # one row
+    (1, 4, 13824, 5124, True), (1, 8, 13824, 5124, False),                               # up to four rows on dword boundaries
+    (4, 16, 4096, 9212, True), (4, 16, 4096, 9220, False),                               # else 144 KiB of A per compute unit
+    (4, 12, 4096, 4090, True), (4, 13, 4096, 4090, False), (8, 16, 1024, 3070, True), (8, 16, 1024, 3074, False),   # 48 KiB
+    (2, 2, 13824, 5118, True), (2, 3, 13824, 5118, False), (2, 16, 13824, 5118, False)])
+def test_kernel_of_ragged_rows(abq, p, M, N, K, one_kernel):
+    """Rows that are no whole number of 16-byte vectors go to the direct kernel as they are only while it reads few bytes of them;
+    the others are packed first and run on the kernel of packed rows.  Both give the oracle's result."""
+    c = synth.make_case(p, 8, M, N, K, seed=5600 + M + K, name=f"W{p}A8 {M}x{N}x{K}")
+    print(c.name, flush=True)
+    lib = abq.load()
+    y1, _ = gpu_gemm(torch, abq, c, FIELDS, FIELDS, want_acc=False)
+    packed_kernel = lib.abq_last_decode_kernel()
+    y, acc = gpu_gemm_fused(torch, abq, c, FIELDS)
+    assert lib.abq_last_decode_kernel() == (1 if one_kernel else packed_kernel)
+    check_sampled(c, y, acc)
+    assert np.array_equal(y.view(np.uint16), y1.view(np.uint16))
