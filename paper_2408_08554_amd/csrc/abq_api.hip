@@ -405,7 +405,7 @@ static bool choose_direct(const GemmArgs& g, const ActLayout& A, const WeightLay
     const int env = tuning_env("ABQ_DIRECT_R");
     const int forced = ov.direct_r != 0 ? ov.direct_r : env;
     // (unpacked rows of a K that is no multiple of 16: only this kernel reads them, and fused_act_ragged has decided that it does)
-    if (g.a_raw && g.K % 16 != 0) return direct_plan(g.p, g.M, A.Kp / kSuperK, 0, pl);
+    if (g.a_raw && g.K % 16 != 0) return direct_plan(g.p, g.M, A.Kp / kSuperK, forced > 0 ? forced : 0, pl);
     if (forced < 0) return false;
     if (forced == 0 && !direct_by_rule(g.p, g.M, A.Kp / kSuperK, W)) return false;
     return direct_plan(g.p, g.M, A.Kp / kSuperK, forced, pl);
@@ -586,8 +586,9 @@ static bool fused_act_ragged(const WeightLayout& W, int force, int p, int q, int
     if (W.g128) return M == 1 && p <= 4 && direct_plan_g128(p, nsuper, &pl);
     PlanOverride ov;
     lookup_plan(p, q, M, N, K, &ov);
-    if (ov.direct_r < 0) return false;   // (another decode kernel is asked for: it takes packed rows)
-    return choose_fields(true, W.has_planes, force, p, q, M, N) && ragged_by_rule(p, M, K, W) && direct_plan(p, M, nsuper, 0, &pl);
+    const int forced = ov.direct_r != 0 ? ov.direct_r : tuning_env("ABQ_DIRECT_R");
+    if (forced < 0) return false;   // (another decode kernel is asked for: it takes packed rows)
+    return choose_fields(true, W.has_planes, force, p, q, M, N) && (forced > 0 || ragged_by_rule(p, M, K, W)) && direct_plan(p, M, nsuper, forced, &pl);
 }
 
 size_t abq_gemm_act_codes_workspace_bytes(int p, int q, int M, int N, int K, int w_layout)

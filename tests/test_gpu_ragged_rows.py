@@ -139,3 +139,33 @@ def test_kernel_of_ragged_rows(abq, p, M, N, K, one_kernel):
     assert lib.abq_last_decode_kernel() == (1 if one_kernel else packed_kernel)
     check_sampled(c, y, acc)
     assert np.array_equal(y.view(np.uint16), y1.view(np.uint16))
+
+
+def _kernels(fn):
+    """Names of the kernels that a call launches."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        fn()
+        torch.cuda.synchronize()
+    return [e.name for e in prof.events() if "abq::" in e.name]
+
+
+@pytest.mark.parametrize("K", [4090, 4096])
+def test_plan_entry_holds_for_unpacked_rows_of_any_length(abq, K):
+    """A table entry's super-chunks per wave (the kernel's third parameter) and its choice of another kernel, off and on a vector."""
+    p, q, M, N = 4, 8, 1, 64
+    c = synth.make_case(p, q, M, N, K, seed=5700 + K)
+    print("plan", K, flush=True)
+    pw = abq.abq_pack_weights(p, to_dev(torch, c.W), to_dev(torch, c.w_scale), to_dev(torch, c.w_zero))
+    a = (to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero))
+    try:
+        for r in (1, 2, 4, -1):
+            abq.abq_plan_set(p, q, M, N, K, direct_r=r)
+            names = _kernels(lambda: abq.abq_gemm_act_codes(p, q, M, N, K, *a, pw, FIELDS))
+            if r > 0:
+                assert len(names) == 1 and f"direct_kernel<{p}, 1, {r}, true" in names[0], (r, names)
+            else:
+                assert "skinny_kernel" in names[-1], (r, names)
+    finally:
+        abq.abq_plan_clear()
