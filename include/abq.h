@@ -323,15 +323,16 @@ void abq_plan_clear(void);
  * them).  `count` independent problems that share p, q, M and the layouts, each with its own N, K,
  * weights, activations and outputs, are served by ONE kernel launch per eight problems when every
  * problem is decode-shaped: M <= 16, K >= 2048 (K a multiple of 16 for unpacked codes), up to 16 rows of
- * A fitting LDS ((M * (K + 528) below ~120 KB), field-packed weights.  Otherwise the problems run one
- * after the other exactly as abq_gemm / abq_gemm_act_codes would run them.  Results are bit-identical
- * to the single calls either way.
+ * A fitting LDS ((M * (K + 528) below ~120 KB), field-packed weights.  Other groups with M <= 16 run as one
+ * launch per length of K and eight problems too where that is faster (few bytes of A, no plan-table entry
+ * for a member); otherwise the problems run one after the other exactly as abq_gemm / abq_gemm_act_codes
+ * would run them.  Results are bit-identical to the single calls either way.
  *   host_problems: HOST array of `count` descriptors holding DEVICE pointers.  Each gives its activations
  *                  either packed (packed_act, a_codes = NULL) or as unpacked codes (a_codes, a_scale, a_zero,
  *                  packed_act = NULL); all problems of a call use the same form.  The array is read before the
  *                  call returns.
- *   workspace:     at least abq_gemm_grouped_workspace_bytes(...) bytes (0 whenever one launch serves the group
- *                  or the activations are packed).
+ *   workspace:     at least abq_gemm_grouped_workspace_bytes(...) bytes: 0 for packed activations and for groups of the
+ *                  decode shape above, else the largest single call's need (required whichever way the group runs).
  * Errors as abq_gemm; ABQ_ERR_SHAPE also for count < 1, ABQ_ERR_LAYOUT for mixed activation forms. */
 typedef struct abq_problem {
     int N, K;

@@ -685,10 +685,29 @@ int abq_gemm_act_codes_static(int p, int q, int M, int N, int K, const uint8_t* 
 // grouped launch, or (per-group blobs) the members the direct kernel takes in one launch and the others streamed.
 enum class GroupRoute { kSingle, kDirect, kStream, kSplit };
 
-// Direct for up to eight rows of A below p = 8 (measured on the LLaMA-7B block: W4A8 M = 1 19.6 vs 22.0 us, W2A8 13.9 vs
-// 17.9, W4A8 M = 8 26.0 vs 25.1; at p = 8 its two launches, one per length of K, cost more than they gain: 34.8 vs 33.3 us), and
-// wherever the streaming launch does not fit (K below 2048 or no multiple of 16): a block of K = 1120, M = 2 then is two launches
-// instead of seven.
+// Where the streaming launch fits: direct for up to eight rows of A below p = 8 (measured on the LLaMA-7B block: W4A8 M = 1 19.6 vs
+// 22.0 us, W2A8 13.9 vs 17.9, W4A8 M = 8 26.0 vs 25.1; at p = 8 its two launches, one per length of K, cost more than they gain:
+// 34.8 vs 33.3 us).
+// Where it does not (K below 2048, unpacked rows of a K that is no multiple of 16, more rows than fit LDS): direct while it reads
+// few bytes of A, as ragged_by_rule has it for single calls, with more room because a group saves the single calls' launches.
+// Measured (direct / one after the other, us a block of seven layers, replayed; hidden x intermediate size):
+//   1120 x 3008: W4A8 M = 2 7.5 / 21.0, W8A8 M = 16 11.6 / 27.7; 4096 x 11008, M = 16: W1A8 30.7 / 40.5, W4A8 35.8 / 47.0;
+//   5120 x 13824, M = 16 (1210 KiB a CU): W1A8 58.6 / 55.2, W2A8 60.4 / 60.1, W4A8 65.1 / 72.5; 5124 x 13828: 68 / 73, 71 / 78, 74 / 86;
+//   rows off dword boundaries: 4090 x 11006: M = 8 (386 KiB) 40.1 / 48.7, M = 16 (771 KiB) 68.8 / 62.8 at W2A8; 3201 x 8641, M = 16
+//   (474 KiB) 63.6 / 57.6; 5118 x 13822: M = 8 (605 KiB) 81 / 72, M = 16 160 / 81.
+static bool group_direct_by_rule(int p, int M, int count, const GemmArgs* args, const WeightLayout* W)
+{
+    double bytes = 0;   // of A that a compute unit reads
+    bool dwords = true;
+    for (int i = 0; i < count; ++i) {
+        PlanOverride ov;
+        lookup_plan(p, args[i].q, M, args[i].N, args[i].K, &ov);
+        if (ov.direct_r != 0 || ov.skinny_waves != 0 || ov.skinny_kgroups != 0) return false;   // (the single call follows the entry)
+        dwords = dwords && !(args[i].a_raw && args[i].K % 4 != 0);
+        bytes += (double)M * args[i].K * W[i].NT / num_cus();
+    }
+    return bytes <= (dwords ? (p == 1 ? 1024 : 1280) : 400) * 1024.0;
+}
 // `streams`: the streaming launch fits; only then does a group of unpacked codes need no workspace.
 static GroupRoute group_route(int p, int q, int M, int count, bool raw, int force, const GemmArgs* args, const ActLayout* A,
                               const WeightLayout* W, bool* streams, int* waves, size_t* lds)
@@ -705,13 +724,13 @@ static GroupRoute group_route(int p, int q, int M, int count, bool raw, int forc
     *streams = gemm_grouped_fits(M, count, args, A, W, waves, lds);
     const bool may_direct = tuning_env("ABQ_DIRECT_R") >= 0;
     const bool direct = may_direct && gemm_direct_grouped_fits(p, M, count, args, A, W);
-    if (direct && M <= 8 && p < 8) return GroupRoute::kDirect;
+    if (direct && *streams && M <= 8 && p < 8) return GroupRoute::kDirect;
     int d128 = 0;
     if (g128 && may_direct)
         for (int i = 0; i < count; ++i) d128 += gemm_direct_g128_fits(p, M, args[i], A[i], W[i]) ? 1 : 0;
     if (d128 == count) return GroupRoute::kDirect;
     if (*streams) return d128 > 0 ? GroupRoute::kSplit : GroupRoute::kStream;
-    return direct ? GroupRoute::kDirect : GroupRoute::kSingle;
+    return direct && group_direct_by_rule(p, M, count, args, W) ? GroupRoute::kDirect : GroupRoute::kSingle;
 }
 
 // Validation and layouts of a group; fills the per-problem arrays (sized by the caller) and says how it is launched.

@@ -169,3 +169,40 @@ def test_plan_entry_holds_for_unpacked_rows_of_any_length(abq, K):
                 assert "skinny_kernel" in names[-1], (r, names)
     finally:
         abq.abq_plan_clear()
+
+
+@pytest.mark.parametrize("p,M,K,count,packed,direct", [
+    (2, 16, 5118, 4, False, True), (2, 16, 5118, 6, False, False),        # off dword boundaries: 400 KiB of A per compute unit
+    (2, 16, 5124, 15, False, True), (2, 16, 5124, 17, False, False),      # on them: 1280 KiB
+    (1, 16, 5124, 12, False, True), (1, 16, 5124, 14, False, False),      # W1: 1024 KiB
+    (8, 3, 1120, 4, False, True), (8, 3, 1120, 4, True, True)])           # short rows of the widest weights
+def test_route_of_groups_the_streaming_launch_does_not_fit(abq, p, M, K, count, packed, direct):
+    """Direct launches while the group reads few bytes of A and no member has a plan entry, else one call after the other; the same
+    results either way.  (4096 channels: one tile per compute unit.)"""
+    q, N = 8, 4096
+    c = synth.make_case(p, q, M, N, K, seed=5800 + K + M, name=f"grouped W{p}A{q} {count} x {M}x{N}x{K}")
+    print(c.name, packed, flush=True)
+    pw = abq.abq_pack_weights(p, to_dev(torch, c.W), to_dev(torch, c.w_scale), to_dev(torch, c.w_zero))
+    a = (to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero))
+    acts = {"packed_act": abq.abq_pack_act_codes(q, *a)} if packed else dict(zip(("a_codes", "a_scale", "a_zero"), a))
+    problems = [{"N": N, "K": K, "packed_w": pw, **acts, "y": torch.zeros((M, N), dtype=torch.float16, device="cuda")} for _ in range(count)]
+    arr = abq.make_problems(problems)
+    need = abq.abq_gemm_grouped_workspace_bytes(p, q, M, arr, FIELDS, FIELDS)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda") if need else None
+    run = lambda: abq.abq_gemm_grouped(p, q, M, arr, FIELDS, FIELDS, workspace=ws)
+    grouped = lambda names: all("direct_kernel" in n and ", true, false>" in n for n in names) and len(names) == (count + 7) // 8   # (GROUPED)
+    names = _kernels(run)
+    assert grouped(names) == direct, names
+    y1, _ = gpu_gemm_fused(torch, abq, c, FIELDS, want_acc=False)
+    for d in problems:
+        assert np.array_equal(d["y"].cpu().numpy().view(np.uint16), y1.view(np.uint16))
+        d["y"].zero_()
+    if direct:
+        try:
+            abq.abq_plan_set(p, q, M, N, K, direct_r=-1)
+            names = _kernels(run)
+        finally:
+            abq.abq_plan_clear()
+        assert not grouped(names) and sum("skinny_kernel" in n for n in names) == count, names
+        for d in problems:
+            assert np.array_equal(d["y"].cpu().numpy().view(np.uint16), y1.view(np.uint16))
