@@ -288,7 +288,7 @@ __global__ __launch_bounds__(BLOCK) void producer_quant_kernel(const uint16_t* _
     for (int w = 0; w < W; ++w) { vmin = fminf(vmin, s_min[w]); vmax = fmaxf(vmax, s_max[w]); }
     const TokenQuantizer tq(vmin, vmax, qmax);
     if (tid == 0) { scale[m] = tq.delta; zero[m] = tq.z; }
-    for (int k = tid; k < K; k += BLOCK) codes[(size_t)m * K + k] = (uint8_t)tq.codes2<0>((uint32_t)normalized(k), 0u);
+    for (int k = tid; k < K; k += BLOCK) codes[(size_t)m * K + k] = (uint8_t)tq.code(half_to_f32(normalized(k)));
 }
 
 // KIND 0: b = gamma [K], eps used;  KIND 1: b = up [M,K], eps ignored.

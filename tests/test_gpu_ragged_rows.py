@@ -206,3 +206,31 @@ def test_route_of_groups_the_streaming_launch_does_not_fit(abq, p, M, K, count, 
         assert not grouped(names) and sum("skinny_kernel" in n for n in names) == count, names
         for d in problems:
             assert np.array_equal(d["y"].cpu().numpy().view(np.uint16), y1.view(np.uint16))
+
+
+@pytest.mark.parametrize("M", [4, 260])
+@pytest.mark.parametrize("K", [7, 513, 4096, 4091, 12289, 16392, 33000, 53248])
+def test_halves_that_are_no_numbers(abq, M, K):
+    """A NaN moves no row's range and gets the code of zero, an infinity makes the step infinite and every code zero: the same from
+    the row kernels, the kernel of blobs with planes and the producers."""
+    q, rng = 8, np.random.default_rng(5900 + K)
+    if M > 4 and K > 13000:
+        pytest.skip("the long rows' kernels do not depend on M")
+    print("NaN", M, K, flush=True)
+    x = synth.act_fp16(5900 + K, M, K)
+    x[0, rng.random(K) < 0.3] = np.nan
+    x[1], x[2, K - 1], x[3, 0] = np.nan, np.nan, -np.nan
+    codes, scale, zero = oracle.quant_act(np.where(np.isnan(x), np.float16(0), x), q)
+    for layout in (FIELDS, 3):
+        got = [t.cpu().numpy() for t in abq.abq_unpack_act(q, M, K, layout, abq.abq_quant_pack_act(q, to_dev(torch, x), layout), FIELDS)]
+        assert np.array_equal(got[0], codes) and np.array_equal(got[1], scale) and np.array_equal(got[2], zero), layout
+        assert np.array_equal(got[3].astype(np.int64), codes.astype(np.int64).sum(axis=1))
+    up = synth.act_fp16(5901 + K, M, K)
+    c, sc, zp, h = (t.cpu().numpy() for t in abq.abq_silu_mul_quant_act(q, to_dev(torch, x), to_dev(torch, up), want_h=True))
+    assert np.array_equal(np.isnan(h), np.isnan(x))
+    codes, scale, zero = oracle.quant_act(np.where(np.isnan(h), np.float16(0), h), q)
+    assert np.array_equal(c, codes) and np.array_equal(sc, scale) and np.array_equal(zp, zero)
+    x = synth.act_fp16(5902 + K, M, K)
+    x[0, 3], x[1, K - 1], x[2, 1], x[2, 2] = np.inf, -np.inf, np.inf, -np.inf
+    a, b = ([t.cpu().numpy() for t in abq.abq_unpack_act(q, M, K, layout, abq.abq_quant_pack_act(q, to_dev(torch, x), layout), FIELDS)] for layout in (FIELDS, 3))
+    assert all(np.array_equal(s, t) for s, t in zip(a, b)) and np.isinf(a[1][:3]).all() and not a[0][:3].any()
