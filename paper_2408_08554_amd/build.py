@@ -40,9 +40,12 @@ def _compile(src: str, newest_header: float = 0.0) -> str:
     return obj
 
 
-# Kernels that load registers with hand-written load instructions and wait for them by hand: the compiler does not know
-# that such a register fills later, so it must not spill it in between.  The build fails if one of them uses scratch memory.
-NO_SCRATCH = {"abq_f4.hip": "f4_gemm_kernel"}
+# Kernels that may not use scratch memory; the build fails if one does.  f4_gemm_kernel loads registers with hand-written load
+# instructions and waits for them by hand: the compiler does not know that such a register fills later, so it must not spill it
+# in between.  tiled_kernel's K loop counts on its loads staying in flight: a reload from scratch inside it waits for all of them.
+NO_SCRATCH = {"abq_f4.hip": "f4_gemm_kernel", "abq_gemm_tiled.hip": "tiled_kernel"}
+# (64 x 256 tiles at p = 7, three plane groups of four tiles per wave: two registers over the 256 of two workgroups per CU)
+SCRATCH_ALLOWED = ("tiled_kernelILi7ELi4ELi4ELi2E",)
 
 
 def _check_no_scratch(src: str, remarks: str, kernel: str) -> None:
@@ -50,11 +53,11 @@ def _check_no_scratch(src: str, remarks: str, kernel: str) -> None:
     for line in remarks.splitlines():
         if "Function Name:" in line:
             name = line.split("Function Name:")[1].strip()
-        elif "ScratchSize [bytes/lane]:" in line and name and kernel in name:
+        elif "ScratchSize [bytes/lane]:" in line and name and kernel in name and not any(k in name for k in SCRATCH_ALLOWED):
             seen += 1
             if int(line.split(":")[-1].split()[0]) != 0:
                 os.remove(os.path.join(OBJ, os.path.relpath(src, CSRC).replace(os.sep, "_") + ".o"))
-                raise RuntimeError(f"{src}: kernel {name} uses scratch memory; its hand-written loads would be spilled before they land")
+                raise RuntimeError(f"{src}: kernel {name} uses scratch memory (see NO_SCRATCH)")
     if not seen:
         raise RuntimeError(f"{src}: no resource-usage remark for {kernel}; the scratch check did not run")
 

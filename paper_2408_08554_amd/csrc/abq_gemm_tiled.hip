@@ -228,6 +228,10 @@ __global__ __launch_bounds__(256, (WD == 4 ? 2 : (NTW <= 2 ? (MT == 4 ? 3 : 2) :
     const int8_t* a_tile = prm.a_codes + (size_t)m0 * prm.Kp;   // uniform
     auto a_prefetch = [&](int step, uint8_t* buf) {
         const int8_t* base = a_tile + (size_t)step * kStepK;     // uniform
+        // Scalar base + 32-bit lane offset; left alone, the step is folded into a second set of 64-bit lane offsets, 8 to 16
+        // registers: p = 7 on 64 x 128 tiles spilled inside the K loop (512 x 11008 x 4096 40.2 us, now 38.4), and p = 1 on 64 x 256
+        // fits three workgroups per CU now (2048 x 13824 x 5120 107.5, now 101.3).  One tile per wave has the registers (1 % slower so).
+        if constexpr (NTW >= 2) asm("" : "+s"(base));
 #pragma unroll
         for (int u = 0; u < MT; ++u)
             __builtin_amdgcn_global_load_lds((const void*)(base + a_goff[u]),

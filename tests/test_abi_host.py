@@ -450,3 +450,12 @@ def test_build_refuses_scratch_memory_in_kernels_with_hand_written_loads(tmp_pat
     with pytest.raises(RuntimeError, match="did not run"):
         bld._check_no_scratch(src, "", "f4_gemm_kernel")
     assert "abq_f4.hip" in bld.NO_SCRATCH
+    # the prefill kernel's K loop waits for every load in flight at a reload: refused too, but for its one listed shape
+    assert bld.NO_SCRATCH["abq_gemm_tiled.hip"] == "tiled_kernel" and len(bld.SCRATCH_ALLOWED) == 1
+    tiled = lambda shape: ("x: remark: Function Name: _ZN3abq12tiled_kernelILi7ELi%dELi4ELi2EEEvNS_11TiledParamsE [-R]\n"
+                           "x: remark:     ScratchSize [bytes/lane]: %d [-R]\n") % shape
+    src = os.path.join(bld.CSRC, "abq_gemm_tiled.hip")
+    (tmp_path / "abq_gemm_tiled.hip.o").write_bytes(b"x")
+    bld._check_no_scratch(src, tiled((2, 0)) + tiled((4, 12)), "tiled_kernel")
+    with pytest.raises(RuntimeError, match="scratch"):
+        bld._check_no_scratch(src, tiled((2, 16)), "tiled_kernel")
