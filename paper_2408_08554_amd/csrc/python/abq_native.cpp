@@ -6,7 +6,7 @@
 // Python version: torch.empty 1.7 us, torch.cuda.current_stream 2.8, the size query through ctypes 0.4, the call through
 // ctypes with 15 converted arguments 3.3 with its launch.  Here arguments arrive by vectorcall and are matched by position
 // (or by interned keyword), the stream is read from c10 directly, and the tensors come from ATen without the argument
-// parser of torch.empty.  The GIL is released around the library call, as ctypes does.
+// parser of torch.empty.  The GIL is released around allocations and the library call, as torch and ctypes do.
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 
@@ -129,20 +129,65 @@ bool rows_cols(const at::Tensor* t, int* M, int* K)
     return true;
 }
 
-at::Tensor empty(at::IntArrayRef shape, at::ScalarType type, const at::Tensor& like)
-{
-    return at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
-}
+// The GIL given up for a scope, taken back however the scope is left.
+struct NoGil {
+    PyThreadState* const state = PyEval_SaveThread();
+    NoGil() = default;
+    NoGil(const NoGil&) = delete;
+    ~NoGil() { PyEval_RestoreThread(state); }
+};
+
+// Memory the call makes itself: a buffer the caller may have given (its address then), or a new one where it is wanted.  Made without
+// the GIL, in the same scope as the library call: an allocation may wait for the device, and torch.empty gives the GIL up too.
+struct Buffer {
+    at::Tensor made;
+    void* ptr = nullptr;
+    bool wanted = false;
+
+    bool arg(PyObject* given, bool want)
+    {
+        wanted = want && is_none(given);
+        return pointer(given, &ptr);
+    }
+    void* make(at::IntArrayRef shape, at::ScalarType type, at::Device device)
+    {
+        if (wanted) {
+            made = at::empty(shape, at::TensorOptions().dtype(type).device(device));
+            ptr = made.data_ptr();
+        }
+        return ptr;
+    }
+    uint16_t* half(int rows, int cols, at::Device device) { return (uint16_t*)make({rows, cols}, at::kHalf, device); }
+    int32_t* i32(int rows, int cols, at::Device device) { return (int32_t*)make({rows, cols}, at::kInt, device); }
+};
+// A workspace: the caller's, or a new one where none was given and some is needed.
+struct Workspace : Buffer {
+    size_t bytes = 0;
+
+    bool arg(PyObject* given, size_t need)
+    {
+        wanted = is_none(given) && need;
+        bytes = need;
+        if (is_none(given)) return true;
+        const at::Tensor* t = tensor(given);
+        if (!t) return false;
+        ptr = t->data_ptr();
+        bytes = (size_t)t->numel();
+        return true;
+    }
+    void* make(at::Device device) { return Buffer::make({(int64_t)bytes}, at::kByte, device); }
+};
 void* stream() { return (void*)c10::hip::getCurrentHIPStream().stream(); }
 
 // ---- results -------------------------------------------------------------------------------------
 // new reference: the caller's own object where one was given, else the tensor made here (None if neither)
-PyObject* result(PyObject* given, at::Tensor& made)
+PyObject* result(PyObject* given, Buffer& b)
 {
     if (!is_none(given)) { Py_INCREF(given); return given; }
-    if (!made.defined()) Py_RETURN_NONE;
-    return THPVariable_Wrap(std::move(made));
+    if (!b.made.defined()) Py_RETURN_NONE;
+    return THPVariable_Wrap(std::move(b.made));
 }
+PyObject* result(Buffer& b) { return result(nullptr, b); }
 PyObject* pack(std::initializer_list<PyObject*> items)
 {
     PyObject* t = PyTuple_New((Py_ssize_t)items.size());
@@ -165,43 +210,14 @@ PyObject* fail(int status, const char* where)
     return nullptr;
 }
 
-// One library call without the GIL; false (with the exception set) on an error status.
+// The allocations and the library call, without the GIL; false (with the exception set) on an error status.
 template <class F>
 bool call(const char* where, F&& f)
 {
-    int status;
-    Py_BEGIN_ALLOW_THREADS
-    status = f();
-    Py_END_ALLOW_THREADS
+    const int status = [&] { NoGil no_gil; return f(); }();
     if (status == ABQ_OK) return true;
     fail(status, where);
     return false;
-}
-
-// Output argument: the caller's tensor, or a new one where none was given (and `wanted`).
-bool output(PyObject* given, bool wanted, at::IntArrayRef shape, at::ScalarType type, const at::Tensor& like, at::Tensor* made, void** ptr)
-{
-    if (!is_none(given) || !wanted) return pointer(given, ptr);
-    *made = empty(shape, type, like);
-    *ptr = made->data_ptr();
-    return true;
-}
-// Workspace of `need` bytes: the caller's, or a new one where none was given and some is needed.
-bool workspace_arg(PyObject* given, size_t need, const at::Tensor& like, at::Tensor* made, void** ptr, size_t* bytes)
-{
-    *ptr = nullptr;
-    *bytes = 0;
-    if (!is_none(given)) {
-        const at::Tensor* t = tensor(given);
-        if (!t) return false;
-        *ptr = t->data_ptr();
-        *bytes = (size_t)t->numel();
-    } else if (need) {
-        *made = empty({(int64_t)need}, at::kByte, like);
-        *ptr = made->data_ptr();
-        *bytes = need;
-    }
-    return true;
 }
 
 // ---- activations ---------------------------------------------------------------------------------
@@ -213,15 +229,16 @@ PyObject* quant_pack_act(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyO
     int q, layout = ABQ_LAYOUT_AUTO, M, K;
     if (!sig_quant_pack.parse(args, nargs, kw, a) || !to_int(a[0], &q) || (a[2] && !to_int(a[2], &layout))) return nullptr;
     const at::Tensor* x = tensor(a[1]);
-    void *xp, *op;
+    void* xp;
     if (!x || !rows_cols(x, &M, &K) || !checked(a[1], at::kHalf, x->sizes(), &xp)) return nullptr;
-    at::Tensor made;
-    const size_t need = std::max<size_t>(abq_packed_act_bytes(q, M, K, layout), 16);
-    if (!output(a[3], true, {(int64_t)need}, at::kByte, *x, &made, &op)) return nullptr;
-    const size_t have = is_none(a[3]) ? need : (size_t)tensor(a[3])->numel();
-    void* s = stream();
-    if (!call("abq_quant_pack_act", [&] { return abq_quant_pack_act(q, M, K, (const uint16_t*)xp, layout, op, have, s); })) return nullptr;
-    return result(a[3], made);
+    Workspace out;
+    if (!out.arg(a[3], std::max<size_t>(abq_packed_act_bytes(q, M, K, layout), 16))) return nullptr;
+    if (!call("abq_quant_pack_act", [&] {
+            void* o = out.make(x->device());
+            return abq_quant_pack_act(q, M, K, (const uint16_t*)xp, layout, o, out.bytes, stream());
+        }))
+        return nullptr;
+    return result(a[3], out);
     END_HANDLE_TH_ERRORS
 }
 
@@ -233,18 +250,18 @@ PyObject* pack_act_codes(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyO
     int q, layout = ABQ_LAYOUT_AUTO, M, K;
     if (!sig_pack_codes.parse(args, nargs, kw, a) || !to_int(a[0], &q) || (a[4] && !to_int(a[4], &layout))) return nullptr;
     const at::Tensor* c = tensor(a[1]);
-    void *cp, *sp, *zp, *op;
+    void *cp, *sp, *zp;
     if (!c || !rows_cols(c, &M, &K) || !checked(a[1], at::kByte, c->sizes(), &cp) || !checked(a[2], at::kFloat, {M}, &sp) ||
         !checked(a[3], at::kInt, {M}, &zp))
         return nullptr;
-    at::Tensor made;
-    const size_t need = std::max<size_t>(abq_packed_act_bytes(q, M, K, layout), 16);
-    if (!output(a[5], true, {(int64_t)need}, at::kByte, *c, &made, &op)) return nullptr;
-    const size_t have = is_none(a[5]) ? need : (size_t)tensor(a[5])->numel();
-    void* s = stream();
-    if (!call("abq_pack_act_codes", [&] { return abq_pack_act_codes(q, M, K, (const uint8_t*)cp, (const float*)sp, (const int32_t*)zp, layout, op, have, s); }))
+    Workspace out;
+    if (!out.arg(a[5], std::max<size_t>(abq_packed_act_bytes(q, M, K, layout), 16))) return nullptr;
+    if (!call("abq_pack_act_codes", [&] {
+            void* o = out.make(c->device());
+            return abq_pack_act_codes(q, M, K, (const uint8_t*)cp, (const float*)sp, (const int32_t*)zp, layout, o, out.bytes, stream());
+        }))
         return nullptr;
-    return result(a[5], made);
+    return result(a[5], out);
     END_HANDLE_TH_ERRORS
 }
 
@@ -256,26 +273,31 @@ PyObject* f4_pack_codes(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyOb
     int bits, R, K;
     if (!sig_f4_pack.parse(args, nargs, kw, a) || !to_int(a[0], &bits)) return nullptr;
     const at::Tensor* c = tensor(a[1]);
-    void *cp, *sp, *zp, *op;
+    void *cp, *sp, *zp;
     if (!c || !rows_cols(c, &R, &K) || !checked(a[1], at::kByte, c->sizes(), &cp) || !checked(a[2], at::kFloat, {R}, &sp) ||
         !checked(a[3], at::kInt, {R}, &zp))
         return nullptr;
-    at::Tensor made;
-    const size_t need = std::max<size_t>(abq_f4_packed_bytes(bits, R, K), 16);
-    if (!output(a[4], true, {(int64_t)need}, at::kByte, *c, &made, &op)) return nullptr;
-    const size_t have = is_none(a[4]) ? need : (size_t)tensor(a[4])->numel();
-    void* s = stream();
-    if (!call("abq_f4_pack_codes", [&] { return abq_f4_pack_codes(bits, R, K, (const uint8_t*)cp, (const float*)sp, (const int32_t*)zp, op, have, s); }))
+    Workspace out;
+    if (!out.arg(a[4], std::max<size_t>(abq_f4_packed_bytes(bits, R, K), 16))) return nullptr;
+    if (!call("abq_f4_pack_codes", [&] {
+            void* o = out.make(c->device());
+            return abq_f4_pack_codes(bits, R, K, (const uint8_t*)cp, (const float*)sp, (const int32_t*)zp, o, out.bytes, stream());
+        }))
         return nullptr;
-    return result(a[4], made);
+    return result(a[4], out);
     END_HANDLE_TH_ERRORS
 }
 
 // RMSNorm (with or without the residual add) and SiLU * up with the quantizer fused in
 struct QuantOutputs {
     at::Tensor codes, scale, zero;
-    QuantOutputs(int M, int K, const at::Tensor& like)
-        : codes(empty({M, K}, at::kByte, like)), scale(empty({M}, at::kFloat, like)), zero(empty({M}, at::kInt, like)) {}
+    void make(int M, int K, at::Device device)   // (without the GIL)
+    {
+        const auto options = at::TensorOptions().device(device);
+        codes = at::empty({M, K}, options.dtype(at::kByte));
+        scale = at::empty({M}, options.dtype(at::kFloat));
+        zero = at::empty({M}, options.dtype(at::kInt));
+    }
     uint8_t* c() { return (uint8_t*)codes.data_ptr(); }
     float* s() { return (float*)scale.data_ptr(); }
     int32_t* z() { return (int32_t*)zero.data_ptr(); }
@@ -289,22 +311,23 @@ PyObject* rmsnorm_quant_act(PyObject*, PyObject* const* args, Py_ssize_t nargs, 
     int q, M, K;
     if (!sig_rmsnorm.parse(args, nargs, kw, a) || !to_int(a[0], &q)) return nullptr;
     const at::Tensor* x = tensor(a[1]);
-    void *gp, *yp = nullptr;
+    void* gp;
     if (!x || !rows_cols(x, &M, &K) || !pointer(a[2], &gp)) return nullptr;
     const double eps = PyFloat_AsDouble(a[3]);
     if (eps == -1.0 && PyErr_Occurred()) return nullptr;
     const int want = a[4] ? PyObject_IsTrue(a[4]) : 0;
     if (want < 0) return nullptr;
-    QuantOutputs o(M, K, *x);
-    at::Tensor y;
-    if (!output(nullptr, want, {M, K}, at::kHalf, *x, &y, &yp)) return nullptr;
+    QuantOutputs o;
+    Buffer y;
+    y.arg(nullptr, want);
     const void* xp = x->data_ptr();
-    void* s = stream();
     if (!call("abq_rmsnorm_quant_act", [&] {
-            return abq_rmsnorm_quant_act(q, M, K, (const uint16_t*)xp, (const uint16_t*)gp, (float)eps, o.c(), o.s(), o.z(), (uint16_t*)yp, s);
+            o.make(M, K, x->device());
+            uint16_t* yp = y.half(M, K, x->device());
+            return abq_rmsnorm_quant_act(q, M, K, (const uint16_t*)xp, (const uint16_t*)gp, (float)eps, o.c(), o.s(), o.z(), yp, stream());
         }))
         return nullptr;
-    return pack({THPVariable_Wrap(std::move(o.codes)), THPVariable_Wrap(std::move(o.scale)), THPVariable_Wrap(std::move(o.zero)), result(nullptr, y)});
+    return pack({THPVariable_Wrap(std::move(o.codes)), THPVariable_Wrap(std::move(o.scale)), THPVariable_Wrap(std::move(o.zero)), result(y)});
     END_HANDLE_TH_ERRORS
 }
 
@@ -316,23 +339,24 @@ PyObject* add_rmsnorm_quant_act(PyObject*, PyObject* const* args, Py_ssize_t nar
     int q, M, K;
     if (!sig_add_rmsnorm.parse(args, nargs, kw, a) || !to_int(a[0], &q)) return nullptr;
     const at::Tensor* x = tensor(a[1]);
-    void *rp, *gp, *hp, *yp = nullptr;
+    void *rp, *gp;
     if (!x || !rows_cols(x, &M, &K) || !pointer(a[2], &rp) || !pointer(a[3], &gp)) return nullptr;
     const double eps = PyFloat_AsDouble(a[4]);
     if (eps == -1.0 && PyErr_Occurred()) return nullptr;
     const int want = a[5] ? PyObject_IsTrue(a[5]) : 0;
     if (want < 0) return nullptr;
-    QuantOutputs o(M, K, *x);
-    at::Tensor h, y;
-    if (!output(a[6], true, {M, K}, at::kHalf, *x, &h, &hp) || !output(nullptr, want, {M, K}, at::kHalf, *x, &y, &yp)) return nullptr;
+    QuantOutputs o;
+    Buffer h, y;
+    if (!h.arg(a[6], true) || !y.arg(nullptr, want)) return nullptr;
     const void* xp = x->data_ptr();
-    void* s = stream();
     if (!call("abq_add_rmsnorm_quant_act", [&] {
+            o.make(M, K, x->device());
+            uint16_t *hp = h.half(M, K, x->device()), *yp = y.half(M, K, x->device());
             return abq_add_rmsnorm_quant_act(q, M, K, (const uint16_t*)xp, (const uint16_t*)rp, (const uint16_t*)gp, (float)eps, o.c(), o.s(), o.z(),
-                                             (uint16_t*)hp, (uint16_t*)yp, s);
+                                             hp, yp, stream());
         }))
         return nullptr;
-    return pack({THPVariable_Wrap(std::move(o.codes)), THPVariable_Wrap(std::move(o.scale)), THPVariable_Wrap(std::move(o.zero)), result(a[6], h), result(nullptr, y)});
+    return pack({THPVariable_Wrap(std::move(o.codes)), THPVariable_Wrap(std::move(o.scale)), THPVariable_Wrap(std::move(o.zero)), result(a[6], h), result(y)});
     END_HANDLE_TH_ERRORS
 }
 
@@ -344,20 +368,21 @@ PyObject* silu_mul_quant_act(PyObject*, PyObject* const* args, Py_ssize_t nargs,
     int q, M, K;
     if (!sig_silu.parse(args, nargs, kw, a) || !to_int(a[0], &q)) return nullptr;
     const at::Tensor* g = tensor(a[1]);
-    void *up, *hp = nullptr;
+    void* up;
     if (!g || !rows_cols(g, &M, &K) || !pointer(a[2], &up)) return nullptr;
     const int want = a[3] ? PyObject_IsTrue(a[3]) : 0;
     if (want < 0) return nullptr;
-    QuantOutputs o(M, K, *g);
-    at::Tensor h;
-    if (!output(nullptr, want, {M, K}, at::kHalf, *g, &h, &hp)) return nullptr;
+    QuantOutputs o;
+    Buffer h;
+    h.arg(nullptr, want);
     const void* gp = g->data_ptr();
-    void* s = stream();
     if (!call("abq_silu_mul_quant_act", [&] {
-            return abq_silu_mul_quant_act(q, M, K, (const uint16_t*)gp, (const uint16_t*)up, o.c(), o.s(), o.z(), (uint16_t*)hp, s);
+            o.make(M, K, g->device());
+            uint16_t* hp = h.half(M, K, g->device());
+            return abq_silu_mul_quant_act(q, M, K, (const uint16_t*)gp, (const uint16_t*)up, o.c(), o.s(), o.z(), hp, stream());
         }))
         return nullptr;
-    return pack({THPVariable_Wrap(std::move(o.codes)), THPVariable_Wrap(std::move(o.scale)), THPVariable_Wrap(std::move(o.zero)), result(nullptr, h)});
+    return pack({THPVariable_Wrap(std::move(o.codes)), THPVariable_Wrap(std::move(o.scale)), THPVariable_Wrap(std::move(o.zero)), result(h)});
     END_HANDLE_TH_ERRORS
 }
 
@@ -372,15 +397,18 @@ PyObject* gemm(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyObject* kw)
     const at::Tensor* w = tensor(a[7]);
     const int want = a[11] ? PyObject_IsTrue(a[11]) : 0;
     if (!w || want < 0) return nullptr;
-    at::Tensor y, acc, ws;
-    void *ap, *yp, *cp, *wsp;
-    size_t wsb;
-    if (!pointer(a[5], &ap) || !output(a[9], true, {d[2], d[3]}, at::kHalf, *w, &y, &yp) || !output(a[10], want, {d[2], d[3]}, at::kInt, *w, &acc, &cp) ||
-        !workspace_arg(a[12], abq_gemm_workspace_bytes(d[0], d[1], d[2], d[3], d[4]), *w, &ws, &wsp, &wsb))
-        return nullptr;
+    Buffer y, acc;
+    Workspace ws;
+    void* ap;
+    if (!pointer(a[5], &ap) || !y.arg(a[9], true) || !acc.arg(a[10], want) || !ws.arg(a[12], abq_gemm_workspace_bytes(d[0], d[1], d[2], d[3], d[4]))) return nullptr;
     const void* wp = w->data_ptr();
-    void* s = stream();
-    if (!call("abq_gemm", [&] { return abq_gemm(d[0], d[1], d[2], d[3], d[4], ap, a_layout, wp, w_layout, (uint16_t*)yp, (int32_t*)cp, wsp, wsb, s); })) return nullptr;
+    if (!call("abq_gemm", [&] {
+            uint16_t* yp = y.half(d[2], d[3], w->device());
+            int32_t* cp = acc.i32(d[2], d[3], w->device());
+            void* wsp = ws.make(w->device());
+            return abq_gemm(d[0], d[1], d[2], d[3], d[4], ap, a_layout, wp, w_layout, yp, cp, wsp, ws.bytes, stream());
+        }))
+        return nullptr;
     return pack({result(a[9], y), result(a[10], acc)});
     END_HANDLE_TH_ERRORS
 }
@@ -395,18 +423,19 @@ PyObject* gemm_act_codes(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyO
     const at::Tensor* w = tensor(a[8]);
     const int want = a[12] ? PyObject_IsTrue(a[12]) : 0;
     if (!w || want < 0) return nullptr;
-    at::Tensor y, acc, ws;
-    void *ap, *sp, *zp, *yp, *cp, *wsp;
-    size_t wsb;
-    if (!pointer(a[5], &ap) || !pointer(a[6], &sp) || !pointer(a[7], &zp) || !output(a[10], true, {d[2], d[3]}, at::kHalf, *w, &y, &yp) ||
-        !output(a[11], want, {d[2], d[3]}, at::kInt, *w, &acc, &cp) ||
-        !workspace_arg(a[13], abq_gemm_act_codes_workspace_bytes(d[0], d[1], d[2], d[3], d[4], w_layout), *w, &ws, &wsp, &wsb))
+    Buffer y, acc;
+    Workspace ws;
+    void *ap, *sp, *zp;
+    if (!pointer(a[5], &ap) || !pointer(a[6], &sp) || !pointer(a[7], &zp) || !y.arg(a[10], true) || !acc.arg(a[11], want) ||
+        !ws.arg(a[13], abq_gemm_act_codes_workspace_bytes(d[0], d[1], d[2], d[3], d[4], w_layout)))
         return nullptr;
     const void* wp = w->data_ptr();
-    void* s = stream();
     if (!call("abq_gemm_act_codes", [&] {
-            return abq_gemm_act_codes(d[0], d[1], d[2], d[3], d[4], (const uint8_t*)ap, (const float*)sp, (const int32_t*)zp, wp, w_layout, (uint16_t*)yp,
-                                      (int32_t*)cp, wsp, wsb, s);
+            uint16_t* yp = y.half(d[2], d[3], w->device());
+            int32_t* cp = acc.i32(d[2], d[3], w->device());
+            void* wsp = ws.make(w->device());
+            return abq_gemm_act_codes(d[0], d[1], d[2], d[3], d[4], (const uint8_t*)ap, (const float*)sp, (const int32_t*)zp, wp, w_layout, yp, cp, wsp,
+                                      ws.bytes, stream());
         }))
         return nullptr;
     return pack({result(a[10], y), result(a[11], acc)});
@@ -423,22 +452,23 @@ PyObject* gemm_act_codes_requant(PyObject*, PyObject* const* args, Py_ssize_t na
     const at::Tensor* w = tensor(a[8]);
     const int want = a[13] ? PyObject_IsTrue(a[13]) : 1;
     if (!w || want < 0) return nullptr;
-    void *ap, *sp, *zp, *osp, *ozp, *kp, *yp, *wsp;
-    size_t wsb;
+    void *ap, *sp, *zp, *osp, *ozp;
     if (!checked(a[11], at::kFloat, {d[2]}, &osp) || !checked(a[12], at::kInt, {d[2]}, &ozp)) return nullptr;
-    at::Tensor codes, y, ws;
-    if (!pointer(a[5], &ap) || !pointer(a[6], &sp) || !pointer(a[7], &zp) || !output(nullptr, true, {d[2], d[3]}, at::kByte, *w, &codes, &kp) ||
-        !output(nullptr, want, {d[2], d[3]}, at::kHalf, *w, &y, &yp) ||
-        !workspace_arg(a[14], abq_gemm_act_codes_workspace_bytes(d[0], d[1], d[2], d[3], d[4], w_layout), *w, &ws, &wsp, &wsb))
+    Buffer codes, y;
+    Workspace ws;
+    if (!pointer(a[5], &ap) || !pointer(a[6], &sp) || !pointer(a[7], &zp) || !codes.arg(nullptr, true) || !y.arg(nullptr, want) ||
+        !ws.arg(a[14], abq_gemm_act_codes_workspace_bytes(d[0], d[1], d[2], d[3], d[4], w_layout)))
         return nullptr;
     const void* wp = w->data_ptr();
-    void* s = stream();
     if (!call("abq_gemm_act_codes_requant", [&] {
+            void* kp = codes.make({d[2], d[3]}, at::kByte, w->device());
+            uint16_t* yp = y.half(d[2], d[3], w->device());
+            void* wsp = ws.make(w->device());
             return abq_gemm_act_codes_requant(d[0], d[1], d[2], d[3], d[4], (const uint8_t*)ap, (const float*)sp, (const int32_t*)zp, wp, w_layout, q_out,
-                                              (const float*)osp, (const int32_t*)ozp, (uint8_t*)kp, (uint16_t*)yp, wsp, wsb, s);
+                                              (const float*)osp, (const int32_t*)ozp, (uint8_t*)kp, yp, wsp, ws.bytes, stream());
         }))
         return nullptr;
-    return pack({result(nullptr, codes), result(nullptr, y)});
+    return pack({result(codes), result(y)});
     END_HANDLE_TH_ERRORS
 }
 
@@ -451,13 +481,12 @@ PyObject* gemm_act_codes_static(PyObject*, PyObject* const* args, Py_ssize_t nar
     if (!sig_static.parse(args, nargs, kw, a) || !to_ints(a, 5, d) || !to_int(a[9], &w_layout)) return nullptr;
     void *ap, *sp, *zp, *wp, *yp, *cp;
     if (!pointer(a[5], &ap) || !pointer(a[6], &sp) || !pointer(a[7], &zp) || !pointer(a[8], &wp) || !pointer(a[10], &yp) || !pointer(a[11], &cp)) return nullptr;
-    void* s = stream();
     if (!call("abq_gemm_act_codes_static", [&] {
             return abq_gemm_act_codes_static(d[0], d[1], d[2], d[3], d[4], (const uint8_t*)ap, (const float*)sp, (const int32_t*)zp, wp, w_layout,
-                                             (uint16_t*)yp, (int32_t*)cp, s);
+                                             (uint16_t*)yp, (int32_t*)cp, stream());
         }))
         return nullptr;
-    at::Tensor none;
+    Buffer none;
     return pack({result(a[10], none), result(a[11], none)});
     END_HANDLE_TH_ERRORS
 }
@@ -472,12 +501,16 @@ PyObject* f4_gemm(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyObject* 
     const at::Tensor* w = tensor(a[6]);
     const int want = a[9] ? PyObject_IsTrue(a[9]) : 0;
     if (!w || want < 0) return nullptr;
-    at::Tensor y, acc;
-    void *ap, *yp, *cp;
-    if (!pointer(a[5], &ap) || !output(a[7], true, {d[2], d[3]}, at::kHalf, *w, &y, &yp) || !output(a[8], want, {d[2], d[3]}, at::kInt, *w, &acc, &cp)) return nullptr;
+    Buffer y, acc;
+    void* ap;
+    if (!pointer(a[5], &ap) || !y.arg(a[7], true) || !acc.arg(a[8], want)) return nullptr;
     const void* wp = w->data_ptr();
-    void* s = stream();
-    if (!call("abq_f4_gemm", [&] { return abq_f4_gemm(d[0], d[1], d[2], d[3], d[4], ap, wp, (uint16_t*)yp, (int32_t*)cp, s); })) return nullptr;
+    if (!call("abq_f4_gemm", [&] {
+            uint16_t* yp = y.half(d[2], d[3], w->device());
+            int32_t* cp = acc.i32(d[2], d[3], w->device());
+            return abq_f4_gemm(d[0], d[1], d[2], d[3], d[4], ap, wp, yp, cp, stream());
+        }))
+        return nullptr;
     return pack({result(a[7], y), result(a[8], acc)});
     END_HANDLE_TH_ERRORS
 }
@@ -507,21 +540,13 @@ PyObject* gemm_grouped(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyObj
     }
     const int count = (int)(view.len / (Py_ssize_t)sizeof(abq_problem));
     const abq_problem* pr = (const abq_problem*)view.buf;
-    void* wsp = nullptr;
-    size_t wsb = 0;
-    at::Tensor ws;
-    if (!is_none(a[6])) {
-        const at::Tensor* t = tensor(a[6]);
-        if (!t) return nullptr;
-        wsp = t->data_ptr();
-        wsb = (size_t)t->numel();
-    } else if (const size_t need = abq_gemm_grouped_workspace_bytes(d[0], d[1], d[2], count, pr, a_layout, w_layout)) {
-        ws = at::empty({(int64_t)need}, at::TensorOptions().dtype(at::kByte).device(at::kCUDA));
-        wsp = ws.data_ptr();
-        wsb = need;
-    }
-    void* s = stream();
-    if (!call("abq_gemm_grouped", [&] { return abq_gemm_grouped(d[0], d[1], d[2], count, pr, a_layout, w_layout, wsp, wsb, s); })) return nullptr;
+    Workspace ws;
+    if (!ws.arg(a[6], is_none(a[6]) ? abq_gemm_grouped_workspace_bytes(d[0], d[1], d[2], count, pr, a_layout, w_layout) : 0)) return nullptr;
+    if (!call("abq_gemm_grouped", [&] {
+            void* wsp = ws.make(at::kCUDA);
+            return abq_gemm_grouped(d[0], d[1], d[2], count, pr, a_layout, w_layout, wsp, ws.bytes, stream());
+        }))
+        return nullptr;
     Py_RETURN_NONE;
     END_HANDLE_TH_ERRORS
 }
