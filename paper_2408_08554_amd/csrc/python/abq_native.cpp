@@ -71,12 +71,18 @@ struct Signature {
     }
 };
 
+// a 64-bit value as an int; nothing is cut off
+bool fits_int(int64_t v, int* out)
+{
+    *out = (int)v;
+    if (*out == v) return true;
+    PyErr_Format(PyExc_OverflowError, "%lld does not fit a 32-bit integer", (long long)v);
+    return false;
+}
 bool to_int(PyObject* o, int* out)
 {
     const long v = PyLong_AsLong(o);
-    if (v == -1 && PyErr_Occurred()) return false;
-    *out = (int)v;
-    return true;
+    return !(v == -1 && PyErr_Occurred()) && fits_int(v, out);
 }
 // `count` leading arguments as integers
 bool to_ints(PyObject* const* a, int count, int* out)
@@ -124,9 +130,7 @@ bool rows_cols(const at::Tensor* t, int* M, int* K)
         PyErr_SetString(PyExc_ValueError, "expected a tensor of two dimensions");
         return false;
     }
-    *M = (int)t->size(0);
-    *K = (int)t->size(1);
-    return true;
+    return fits_int(t->size(0), M) && fits_int(t->size(1), K);
 }
 
 // The GIL given up for a scope, taken back however the scope is left.

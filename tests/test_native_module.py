@@ -1,5 +1,5 @@
-"""The extension module of the online calls, as far as it goes without a device: arguments, errors, threads.  (Host tensors take a
-call up to the current stream, which only a device has.)"""
+"""The extension module of the online calls, as far as it goes without a device: arguments, errors, threads.  Every call here is one
+that is refused: by the module, for want of a stream where there is no device, or by the library (K = 0), which launches nothing."""
 import threading
 import time
 
@@ -50,6 +50,48 @@ def test_allocations_leave_other_threads_running():
 def test_a_failed_allocation_is_an_exception():
     for _ in range(3):
         with pytest.raises(RuntimeError):
-            B.abq_gemm(4, 8, 1 << 30, 1 << 30, 512, host(16), FIELDS, host(16), FIELDS)
+            B.abq_gemm(4, 8, 1 << 30, 1 << 30, 0, host(16), FIELDS, host(16), FIELDS)
         with pytest.raises(RuntimeError):
-            B.abq_gemm_act_codes(4, 8, 1, -1, 512, host(1, 512), host(1), host(1), host(16), FIELDS)
+            B.abq_gemm_act_codes(4, 8, 1, -1, 0, host(1, 512), host(1), host(1), host(16), FIELDS)
+
+
+BEYOND = [1 << 31, -(1 << 31) - 1, (1 << 32) + 8, 1 << 70]
+
+
+@pytest.mark.parametrize("value", BEYOND)
+def test_integers_beyond_32_bits_are_refused(value):
+    """Each integer argument in turn; the outputs would otherwise be made, and the problem run, at the size that is left."""
+    t, f = host(16), FIELDS
+    act = (host(1, 512), host(1), host(1), host(16))
+    calls = [lambda *d: B.abq_gemm(*d[:5], t, d[5], t, d[6], host(1)), lambda *d: B.abq_gemm_act_codes(*d[:5], *act, d[5], host(1)),
+             lambda *d: B.abq_gemm_act_codes_static(*d[:5], *act, d[5], host(1)), lambda *d: B.abq_f4_gemm(*d[:5], t, t, host(1)),
+             lambda *d: B.abq_gemm_act_codes_requant(*d[:5], *act, d[5], d[6], host(1), host(1)),
+             lambda *d: B.abq_gemm_grouped(*d[:3], [], d[3], d[4]), lambda *d: B.abq_quant_pack_act(d[0], host(1, 16), d[1]),
+             lambda *d: B.abq_pack_act_codes(d[0], host(1, 16), host(1), host(1), d[1]), lambda *d: B.abq_f4_pack_codes(d[0], host(1, 16), host(1), host(1)),
+             lambda *d: B.abq_rmsnorm_quant_act(d[0], host(1, 16), host(16), 1e-5), lambda *d: B.abq_silu_mul_quant_act(d[0], host(1, 16), host(1, 16)),
+             lambda *d: B.abq_add_rmsnorm_quant_act(d[0], host(1, 16), host(1, 16), host(16), 1e-5)]
+    for call, count in zip(calls, (7, 6, 6, 5, 7, 5, 2, 2, 1, 1, 1, 1)):
+        for at in range(count):
+            args = [2, 2, 1, 64, 0, f, f]
+            args[at] = value
+            with pytest.raises(OverflowError):
+                call(*args)
+
+
+def test_rows_beyond_32_bits_are_refused():
+    wide = host(1).expand(1, (1 << 32) + 16)
+    with pytest.raises(OverflowError):
+        B.abq_silu_mul_quant_act(8, wide, wide)
+    with pytest.raises(OverflowError):
+        B.abq_rmsnorm_quant_act(8, wide.T, wide, 1e-5)
+
+
+def test_integers_of_other_types():
+    """What the interpreter takes for an integer, as ctypes does; a float or a text is none."""
+    np = pytest.importorskip("numpy")
+    for one in (True, np.int64(1), torch.tensor(1)):
+        with pytest.raises(RuntimeError):
+            B.abq_gemm(4, 8, one, 64, 0, host(16), FIELDS, host(16), FIELDS)
+    for other in (1.0, "1", None):
+        with pytest.raises(TypeError):
+            B.abq_gemm(4, 8, other, 64, 0, host(16), FIELDS, host(16), FIELDS)
