@@ -258,6 +258,6 @@ def __getattr__(name):
     if not os.path.exists(NATIVE_PATH):
         raise RuntimeError(f"{NATIVE_PATH} is missing: build it with `python -m paper_2408_08554_amd.build` (there is no fallback path)")
     from . import abq_native
-    abq_native.init(AbqError, make_problems)
+    abq_native.init(AbqError, make_problems, _c.Array)
     globals().update({n: getattr(abq_native, n) for n in _NATIVE})
     return globals()[name]

@@ -12,6 +12,7 @@
 
 #include <ATen/ops/empty.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Device.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
@@ -21,6 +22,7 @@ namespace {
 
 PyObject* g_error = nullptr;           // binding.AbqError(status, where)
 PyObject* g_make_problems = nullptr;   // binding.make_problems(list of dicts) -> ctypes array
+PyObject* g_array = nullptr;           // ctypes.Array
 
 // ---- arguments -----------------------------------------------------------------------------------
 // Parameter names of one function; the first `required` have no default (an argument not given stays null).
@@ -101,15 +103,45 @@ const at::Tensor* tensor(PyObject* o)
     }
     return &THPVariable_Unpack(o);
 }
-// address of a tensor's data; None (or an argument not given) is the null pointer
+// address of an operand's data: a tensor, or an object with a data_ptr() of its own (a storage); None (or an argument not
+// given) is the null pointer
 bool pointer(PyObject* o, void** out)
 {
-    if (is_none(o)) { *out = nullptr; return true; }
-    const at::Tensor* t = tensor(o);
-    if (!t) return false;
-    *out = t->data_ptr();
-    return true;
+    *out = nullptr;
+    if (is_none(o)) return true;
+    if (THPVariable_Check(o)) {
+        *out = THPVariable_Unpack(o).data_ptr();
+        return true;
+    }
+    PyObject* address = PyObject_CallMethod(o, "data_ptr", nullptr);
+    if (!address) return false;
+    *out = PyLong_AsVoidPtr(address);
+    Py_DECREF(address);
+    return *out || !PyErr_Occurred();
 }
+// the packed weights: their address, and the device they live on, where the outputs go
+struct Weights {
+    void* ptr = nullptr;
+    c10::optional<at::Device> on;
+
+    bool arg(PyObject* o)
+    {
+        if (THPVariable_Check(o)) {
+            const at::Tensor& t = THPVariable_Unpack(o);
+            ptr = t.data_ptr();
+            on = t.device();
+            return true;
+        }
+        PyObject* d = PyObject_GetAttrString(o, "device");
+        if (!d) return false;
+        const bool is_device = THPDevice_Check(d);
+        if (is_device) on = ((THPDevice*)d)->device;
+        else PyErr_Format(PyExc_TypeError, "expected a tensor, got %s", Py_TYPE(o)->tp_name);
+        Py_DECREF(d);
+        return is_device && pointer(o, &ptr);
+    }
+    at::Device device() const { return *on; }
+};
 // the same for an argument that has to be a contiguous device tensor of this type and shape
 bool checked(PyObject* o, at::ScalarType type, at::IntArrayRef shape, void** out)
 {
@@ -398,19 +430,18 @@ PyObject* gemm(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyObject* kw)
     PyObject* a[13];
     int d[5], a_layout, w_layout;   // p, q, M, N, K
     if (!sig_gemm.parse(args, nargs, kw, a) || !to_ints(a, 5, d) || !to_int(a[6], &a_layout) || !to_int(a[8], &w_layout)) return nullptr;
-    const at::Tensor* w = tensor(a[7]);
+    Weights w;
     const int want = a[11] ? PyObject_IsTrue(a[11]) : 0;
-    if (!w || want < 0) return nullptr;
+    if (want < 0 || !w.arg(a[7])) return nullptr;
     Buffer y, acc;
     Workspace ws;
     void* ap;
     if (!pointer(a[5], &ap) || !y.arg(a[9], true) || !acc.arg(a[10], want) || !ws.arg(a[12], abq_gemm_workspace_bytes(d[0], d[1], d[2], d[3], d[4]))) return nullptr;
-    const void* wp = w->data_ptr();
     if (!call("abq_gemm", [&] {
-            uint16_t* yp = y.half(d[2], d[3], w->device());
-            int32_t* cp = acc.i32(d[2], d[3], w->device());
-            void* wsp = ws.make(w->device());
-            return abq_gemm(d[0], d[1], d[2], d[3], d[4], ap, a_layout, wp, w_layout, yp, cp, wsp, ws.bytes, stream());
+            uint16_t* yp = y.half(d[2], d[3], w.device());
+            int32_t* cp = acc.i32(d[2], d[3], w.device());
+            void* wsp = ws.make(w.device());
+            return abq_gemm(d[0], d[1], d[2], d[3], d[4], ap, a_layout, w.ptr, w_layout, yp, cp, wsp, ws.bytes, stream());
         }))
         return nullptr;
     return pack({result(a[9], y), result(a[10], acc)});
@@ -424,21 +455,20 @@ PyObject* gemm_act_codes(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyO
     PyObject* a[14];
     int d[5], w_layout;
     if (!sig_act_codes.parse(args, nargs, kw, a) || !to_ints(a, 5, d) || !to_int(a[9], &w_layout)) return nullptr;
-    const at::Tensor* w = tensor(a[8]);
+    Weights w;
     const int want = a[12] ? PyObject_IsTrue(a[12]) : 0;
-    if (!w || want < 0) return nullptr;
+    if (want < 0 || !w.arg(a[8])) return nullptr;
     Buffer y, acc;
     Workspace ws;
     void *ap, *sp, *zp;
     if (!pointer(a[5], &ap) || !pointer(a[6], &sp) || !pointer(a[7], &zp) || !y.arg(a[10], true) || !acc.arg(a[11], want) ||
         !ws.arg(a[13], abq_gemm_act_codes_workspace_bytes(d[0], d[1], d[2], d[3], d[4], w_layout)))
         return nullptr;
-    const void* wp = w->data_ptr();
     if (!call("abq_gemm_act_codes", [&] {
-            uint16_t* yp = y.half(d[2], d[3], w->device());
-            int32_t* cp = acc.i32(d[2], d[3], w->device());
-            void* wsp = ws.make(w->device());
-            return abq_gemm_act_codes(d[0], d[1], d[2], d[3], d[4], (const uint8_t*)ap, (const float*)sp, (const int32_t*)zp, wp, w_layout, yp, cp, wsp,
+            uint16_t* yp = y.half(d[2], d[3], w.device());
+            int32_t* cp = acc.i32(d[2], d[3], w.device());
+            void* wsp = ws.make(w.device());
+            return abq_gemm_act_codes(d[0], d[1], d[2], d[3], d[4], (const uint8_t*)ap, (const float*)sp, (const int32_t*)zp, w.ptr, w_layout, yp, cp, wsp,
                                       ws.bytes, stream());
         }))
         return nullptr;
@@ -453,9 +483,9 @@ PyObject* gemm_act_codes_requant(PyObject*, PyObject* const* args, Py_ssize_t na
     PyObject* a[15];
     int d[5], w_layout, q_out;
     if (!sig_requant.parse(args, nargs, kw, a) || !to_ints(a, 5, d) || !to_int(a[9], &w_layout) || !to_int(a[10], &q_out)) return nullptr;
-    const at::Tensor* w = tensor(a[8]);
+    Weights w;
     const int want = a[13] ? PyObject_IsTrue(a[13]) : 1;
-    if (!w || want < 0) return nullptr;
+    if (want < 0 || !w.arg(a[8])) return nullptr;
     void *ap, *sp, *zp, *osp, *ozp;
     if (!checked(a[11], at::kFloat, {d[2]}, &osp) || !checked(a[12], at::kInt, {d[2]}, &ozp)) return nullptr;
     Buffer codes, y;
@@ -463,12 +493,11 @@ PyObject* gemm_act_codes_requant(PyObject*, PyObject* const* args, Py_ssize_t na
     if (!pointer(a[5], &ap) || !pointer(a[6], &sp) || !pointer(a[7], &zp) || !codes.arg(nullptr, true) || !y.arg(nullptr, want) ||
         !ws.arg(a[14], abq_gemm_act_codes_workspace_bytes(d[0], d[1], d[2], d[3], d[4], w_layout)))
         return nullptr;
-    const void* wp = w->data_ptr();
     if (!call("abq_gemm_act_codes_requant", [&] {
-            void* kp = codes.make({d[2], d[3]}, at::kByte, w->device());
-            uint16_t* yp = y.half(d[2], d[3], w->device());
-            void* wsp = ws.make(w->device());
-            return abq_gemm_act_codes_requant(d[0], d[1], d[2], d[3], d[4], (const uint8_t*)ap, (const float*)sp, (const int32_t*)zp, wp, w_layout, q_out,
+            void* kp = codes.make({d[2], d[3]}, at::kByte, w.device());
+            uint16_t* yp = y.half(d[2], d[3], w.device());
+            void* wsp = ws.make(w.device());
+            return abq_gemm_act_codes_requant(d[0], d[1], d[2], d[3], d[4], (const uint8_t*)ap, (const float*)sp, (const int32_t*)zp, w.ptr, w_layout, q_out,
                                               (const float*)osp, (const int32_t*)ozp, (uint8_t*)kp, yp, wsp, ws.bytes, stream());
         }))
         return nullptr;
@@ -502,17 +531,16 @@ PyObject* f4_gemm(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyObject* 
     PyObject* a[10];
     int d[5];
     if (!sig_f4_gemm.parse(args, nargs, kw, a) || !to_ints(a, 5, d)) return nullptr;
-    const at::Tensor* w = tensor(a[6]);
+    Weights w;
     const int want = a[9] ? PyObject_IsTrue(a[9]) : 0;
-    if (!w || want < 0) return nullptr;
+    if (want < 0 || !w.arg(a[6])) return nullptr;
     Buffer y, acc;
     void* ap;
     if (!pointer(a[5], &ap) || !y.arg(a[7], true) || !acc.arg(a[8], want)) return nullptr;
-    const void* wp = w->data_ptr();
     if (!call("abq_f4_gemm", [&] {
-            uint16_t* yp = y.half(d[2], d[3], w->device());
-            int32_t* cp = acc.i32(d[2], d[3], w->device());
-            return abq_f4_gemm(d[0], d[1], d[2], d[3], d[4], ap, wp, yp, cp, stream());
+            uint16_t* yp = y.half(d[2], d[3], w.device());
+            int32_t* cp = acc.i32(d[2], d[3], w.device());
+            return abq_f4_gemm(d[0], d[1], d[2], d[3], d[4], ap, w.ptr, yp, cp, stream());
         }))
         return nullptr;
     return pack({result(a[7], y), result(a[8], acc)});
@@ -528,7 +556,9 @@ PyObject* gemm_grouped(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyObj
     if (!sig_grouped.parse(args, nargs, kw, a) || !to_ints(a, 3, d) || !to_int(a[4], &a_layout) || !to_int(a[5], &w_layout)) return nullptr;
     PyObject* arr = a[3];   // the ctypes array of make_problems, or what make_problems takes
     Py_INCREF(arr);
-    if (!PyObject_CheckBuffer(arr)) {
+    const int is_array = PyObject_IsInstance(arr, g_array);
+    if (is_array < 0) { Py_DECREF(arr); return nullptr; }
+    if (!is_array) {
         PyObject* made = PyObject_CallOneArg(g_make_problems, arr);
         Py_DECREF(arr);
         if (!(arr = made)) return nullptr;
@@ -555,17 +585,17 @@ PyObject* gemm_grouped(PyObject*, PyObject* const* args, Py_ssize_t nargs, PyObj
     END_HANDLE_TH_ERRORS
 }
 
-// binding.py hands over its exception class and make_problems once
+// binding.py hands over its exception class, make_problems and ctypes.Array once
 PyObject* init(PyObject*, PyObject* const* args, Py_ssize_t nargs)
 {
-    if (nargs != 2) {
-        PyErr_SetString(PyExc_TypeError, "init(error, make_problems)");
+    if (nargs != 3) {
+        PyErr_SetString(PyExc_TypeError, "init(error, make_problems, array)");
         return nullptr;
     }
-    Py_INCREF(args[0]);
-    Py_INCREF(args[1]);
+    for (int i = 0; i < 3; ++i) Py_INCREF(args[i]);
     g_error = args[0];
     g_make_problems = args[1];
+    g_array = args[2];
     Py_RETURN_NONE;
 }
 
@@ -595,7 +625,7 @@ PyMethodDef methods[] = {
                "abq_f4_gemm(p, q, M, N, K, packed_act, packed_w, y=None, acc=None, want_acc=False)\n--\n\n-> (y float16 [M,N], acc int32 [M,N] or None)."),
     ABQ_METHOD("abq_gemm_grouped", gemm_grouped,
                "abq_gemm_grouped(p, q, M, problems, a_layout, w_layout, workspace=None)\n--\n\nOne call for a list of independent problems that share p, q, M (see make_problems); outputs are written to\nthe y / acc tensors of each problem."),
-    {"init", (PyCFunction)(void (*)(void))init, METH_FASTCALL, "init(error, make_problems)"},
+    {"init", (PyCFunction)(void (*)(void))init, METH_FASTCALL, "init(error, make_problems, array)"},
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module_def = {PyModuleDef_HEAD_INIT, "abq_native", "The online entry points of libabq with torch tensors in and out.", -1, methods, nullptr, nullptr, nullptr, nullptr};

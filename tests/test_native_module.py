@@ -95,3 +95,29 @@ def test_integers_of_other_types():
     for other in (1.0, "1", None):
         with pytest.raises(TypeError):
             B.abq_gemm(4, 8, other, 64, 0, host(16), FIELDS, host(16), FIELDS)
+
+
+def test_operands_that_are_no_tensors():
+    """A storage, or any object with a data_ptr() (packed weights: and a device), is an operand; an object without is none, and neither
+    is a buffer that make_problems did not make."""
+    class Own:
+        device = torch.device("cpu")
+
+        def data_ptr(self):
+            return 4096
+
+    f, storage = FIELDS, host(16).untyped_storage()
+    for operand in (storage, Own()):
+        for call in (lambda: B.abq_gemm(4, 8, 1, 64, 0, operand, f, operand, f), lambda: B.abq_f4_gemm(2, 2, 1, 64, 0, operand, operand, operand, operand),
+                     lambda: B.abq_gemm_act_codes(4, 8, 1, 64, 0, operand, operand, operand, operand, f, operand, operand),
+                     lambda: B.abq_gemm_act_codes_static(4, 8, 1, 64, 0, operand, operand, operand, operand, f, operand, operand)):
+            with pytest.raises(RuntimeError):                   # (refused no earlier than a tensor)
+                call()
+    for other in (7, "text", [host(16)]):
+        with pytest.raises((AttributeError, TypeError)):
+            B.abq_gemm(4, 8, 1, 64, 0, other, f, host(16), f)
+        with pytest.raises((AttributeError, TypeError)):
+            B.abq_gemm(4, 8, 1, 64, 0, host(16), f, other, f)
+    for other in (bytes(72), bytearray(72), memoryview(bytes(144))):
+        with pytest.raises(TypeError):
+            B.abq_gemm_grouped(4, 8, 1, other, f, f)
