@@ -250,14 +250,33 @@ _NATIVE = ("abq_quant_pack_act", "abq_pack_act_codes", "abq_f4_pack_codes", "abq
            "abq_gemm_grouped", "abq_f4_gemm")
 
 
-def __getattr__(name):
-    """Loads abq_native at the first use of one of its functions, and puts all of them into this module."""
-    if name not in _NATIVE:
-        raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
+def _bind():
+    """Loads abq_native and puts its functions into this module."""
     load()
     if not os.path.exists(NATIVE_PATH):
         raise RuntimeError(f"{NATIVE_PATH} is missing: build it with `python -m paper_2408_08554_amd.build` (there is no fallback path)")
     from . import abq_native
     abq_native.init(AbqError, make_problems, _c.Array)
     globals().update({n: getattr(abq_native, n) for n in _NATIVE})
-    return globals()[name]
+
+
+def __getattr__(name):
+    """The online calls, bound at the first use of one of them.  Where nothing is built they are there all the same, and raise when called."""
+    if name not in _NATIVE:
+        raise AttributeError(f"module {__name__!r} has no attribute {name!r}")
+    if os.path.exists(LIB_PATH) and os.path.exists(NATIVE_PATH):
+        _bind()
+        return globals()[name]
+
+    def unbuilt(*args, **kwargs):
+        _bind()
+        return globals()[name](*args, **kwargs)
+    unbuilt.__name__ = unbuilt.__qualname__ = name
+    return unbuilt
+
+
+def __dir__():
+    return sorted({*globals(), *_NATIVE})
+
+
+__all__ = [n for n in globals() if not n.startswith("_")] + list(_NATIVE)

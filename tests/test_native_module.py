@@ -121,3 +121,26 @@ def test_operands_that_are_no_tensors():
     for other in (bytes(72), bytearray(72), memoryview(bytes(144))):
         with pytest.raises(TypeError):
             B.abq_gemm_grouped(4, 8, 1, other, f, f)
+
+
+def test_names_of_the_online_calls(monkeypatch):
+    """They show in dir() and come with `import *`, as the functions of the module itself do; without a build they are there and raise
+    when called."""
+    space = {}
+    exec("from paper_2408_08554_amd.binding import *", space)
+    for name in B._NATIVE:
+        assert name in dir(B) and callable(space[name]) and space[name] is getattr(B, name)
+    assert {"load", "make_problems", "ABQ_LAYOUT_FIELDS", "AbqError"} <= set(space) and not hasattr(B, "abq_no_such_call")
+    for name in B._NATIVE:
+        monkeypatch.delattr(B, name)
+    for missing in ("LIB_PATH", "NATIVE_PATH"):
+        with monkeypatch.context() as m:
+            m.setattr(B, missing, "/nonexistent.so")
+            m.setattr(B, "_lib", None)
+            assert all(hasattr(B, name) for name in B._NATIVE)
+            call = B.abq_gemm
+            with pytest.raises(RuntimeError, match="is missing"):
+                call(4, 8, 1, 64, 0, None, FIELDS, host(16), FIELDS)
+    with pytest.raises(RuntimeError) as e:                      # (bound at the call once there is a build)
+        call(4, 8, 1, 64, 0, None, FIELDS, host(16), FIELDS, host(1))
+    assert "is missing" not in str(e.value)
