@@ -375,9 +375,10 @@ def test_grouped_launch_equals_single_calls_bitwise(abq):
 
 @pytest.mark.parametrize("fused", [False, True], ids=["packed", "fused"])
 @pytest.mark.parametrize("kind", ["short_k", "many_rows", "planes", "ragged_k", "long_k16"])
-def test_grouped_falls_back_to_single_calls(abq, kind, fused):
-    """Groups that one launch cannot serve run problem by problem with the same results."""
-    say("grouped fallback", kind, fused)
+def test_grouped_launches_other_than_the_streaming_one(abq, kind, fused):
+    """Groups that the streaming launch does not fit run as direct launches (few rows of short, ragged or long K) or problem by problem
+    (many rows, bit-planes), with the same results.  Which of the two is tested with the ragged rows."""
+    say("grouped, no streaming launch", kind, fused)
     p, q, M, shapes, wl, al = 4, 8, 2, [(64, 4096), (40, 512)], FIELDS, FIELDS
     if kind == "many_rows":
         M, shapes = 40, [(64, 2048), (130, 2560)]

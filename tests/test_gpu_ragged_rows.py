@@ -234,3 +234,34 @@ def test_halves_that_are_no_numbers(abq, M, K):
     x[0, 3], x[1, K - 1], x[2, 1], x[2, 2] = np.inf, -np.inf, np.inf, -np.inf
     a, b = ([t.cpu().numpy() for t in abq.abq_unpack_act(q, M, K, layout, abq.abq_quant_pack_act(q, to_dev(torch, x), layout), FIELDS)] for layout in (FIELDS, 3))
     assert all(np.array_equal(s, t) for s, t in zip(a, b)) and np.isinf(a[1][:3]).all() and not a[0][:3].any()
+
+
+@pytest.mark.parametrize("M", [3, 260])
+@pytest.mark.parametrize("K", [1023, 2049, 4091, 4104, 6149, 8199, 12289, 16384, 32761, 32768, 32776])
+def test_producers_of_any_length(abq, M, K):
+    """RMSNorm with and without the residual (its sum over the residual itself) and SiLU * up over the row kernels' workgroup choices, few
+    rows and many, on a vector and off it, and one row past the longest of them."""
+    q, rng = 8, np.random.default_rng(6000 + K)
+    distinct = min(M, 5)                              # (the oracle takes its time: the other rows repeat these)
+    rows = np.arange(M) % distinct
+    x, res, up = (synth.act_fp16(6000 + 3 * K + i, distinct, K) for i in range(3))
+    gamma = (1.0 + 0.2 * rng.standard_normal(K)).astype(np.float16)
+    x[1], res[1] = 0, 0
+    print("producers", M, K, flush=True)
+    dev = lambda a: to_dev(torch, a[rows])
+    bits = lambda t: t.cpu().numpy().view(np.uint16)
+
+    def check(got, produced):
+        codes, scale, zero, out = got
+        c, s, z = oracle.quant_act(produced, q)
+        assert np.array_equal(bits(out), produced.view(np.uint16)[rows]) and np.array_equal(codes.cpu().numpy(), c[rows])
+        assert np.array_equal(scale.cpu().numpy(), s[rows]) and np.array_equal(zero.cpu().numpy(), z[rows])
+
+    g = to_dev(torch, gamma)
+    check(abq.abq_rmsnorm_quant_act(q, dev(x), g, 1e-5, want_y=True), oracle.rmsnorm_half(x, gamma, 1e-5))
+    h = oracle.add_half(x, res)
+    r = dev(res)
+    *got, h_out, y = abq.abq_add_rmsnorm_quant_act(q, dev(x), r, g, 1e-5, want_y=True, sum_out=r)
+    assert h_out.data_ptr() == r.data_ptr() and np.array_equal(bits(r), h.view(np.uint16)[rows])
+    check((*got, y), oracle.rmsnorm_half(h, gamma, 1e-5))
+    check(abq.abq_silu_mul_quant_act(q, dev(x), dev(up), want_h=True), oracle.silu_mul_half(x, up))

@@ -144,3 +144,51 @@ def test_names_of_the_online_calls(monkeypatch):
     with pytest.raises(RuntimeError) as e:                      # (bound at the call once there is a build)
         call(4, 8, 1, 64, 0, None, FIELDS, host(16), FIELDS, host(1))
     assert "is missing" not in str(e.value)
+
+
+def test_keywords_and_missing_arguments():
+    t, f = host(16), FIELDS
+    full = dict(p=4, q=8, M=1, N=64, K=0, packed_act=t, a_layout=f, packed_w=t, w_layout=f, y=host(1))
+    with pytest.raises(RuntimeError):                             # (all there: refused by what comes after the arguments)
+        B.abq_gemm(**full)
+    with pytest.raises(RuntimeError):
+        B.abq_gemm(4, 8, 1, 64, 0, t, f, w_layout=f, packed_w=t, workspace=t, want_acc=True, acc=None, y=host(1))
+    for name in list(full)[:9]:
+        with pytest.raises(TypeError, match="missing required argument: '%s'" % name):
+            B.abq_gemm(**{k: v for k, v in full.items() if k != name})
+    with pytest.raises(TypeError, match="multiple values for argument 'q'"):
+        B.abq_gemm(4, 8, q=8)
+    with pytest.raises(TypeError, match="unexpected keyword argument 'z'"):
+        B.abq_gemm(**full, z=1)
+    with pytest.raises(TypeError, match="at most 13 arguments"):
+        B.abq_gemm(*([4] * 14))
+
+
+def test_checked_tensors_have_to_be_on_the_device():
+    row = host(1, 16)
+    for call in (lambda: B.abq_quant_pack_act(8, row.half()), lambda: B.abq_pack_act_codes(8, row, host(1, dtype=torch.float32), host(1, dtype=torch.int32)),
+                 lambda: B.abq_f4_pack_codes(2, row, host(1, dtype=torch.float32), host(1, dtype=torch.int32)),
+                 lambda: B.abq_gemm_act_codes_requant(4, 8, 1, 64, 0, row, row, row, row, FIELDS, 8, host(1, dtype=torch.float32), host(1, dtype=torch.int32))):
+        with pytest.raises(AssertionError, match="contiguous device tensor"):
+            call()
+    with pytest.raises(ValueError, match="two dimensions"):
+        B.abq_quant_pack_act(8, host(16))
+
+
+@pytest.mark.gpu
+def test_checked_tensors_have_their_type_and_shape(abq):
+    """Refused before anything is launched; the same call with the right tensors goes through."""
+    dev = lambda *shape, dtype=torch.uint8: torch.zeros(shape, dtype=dtype, device="cuda")
+    codes, scale, zero = dev(2, 64), dev(2, dtype=torch.float32), dev(2, dtype=torch.int32)
+    for bad in ((codes.int(), scale, zero), (codes, scale.double(), zero), (codes, scale, zero.long()), (codes, dev(3, dtype=torch.float32), zero),
+                (codes, scale, zero.view(2, 1)), (dev(64, 2).T, scale, zero), (codes.cpu(), scale, zero)):
+        with pytest.raises(AssertionError, match="contiguous device tensor"):
+            abq.abq_pack_act_codes(8, *bad)
+    with pytest.raises(B.AbqError) as e:                          # the library's own refusals come with their status
+        abq.abq_pack_act_codes(9, codes, scale, zero)
+    assert e.value.status == B.ABQ_ERR_BITS
+    with pytest.raises(B.AbqError) as e:
+        abq.abq_pack_act_codes(8, codes, scale, zero, out=dev(16))
+    assert e.value.status == B.ABQ_ERR_SIZE
+    given = dev(B.abq_packed_act_bytes(8, 2, 64, FIELDS))
+    assert abq.abq_pack_act_codes(8, a_zero=zero, a_codes=codes, a_scale=scale, layout=FIELDS, out=given) is given
