@@ -228,10 +228,11 @@ __global__ __launch_bounds__(256, (WD == 4 ? 2 : (NTW <= 2 ? (MT == 4 ? 3 : 2) :
     const int8_t* a_tile = prm.a_codes + (size_t)m0 * prm.Kp;   // uniform
     auto a_prefetch = [&](int step, uint8_t* buf) {
         const int8_t* base = a_tile + (size_t)step * kStepK;     // uniform
-        // Scalar base + 32-bit lane offset; left alone, the step is folded into a second set of 64-bit lane offsets, 8 to 16
-        // registers: p = 7 on 64 x 128 tiles spilled inside the K loop (512 x 11008 x 4096 40.2 us, now 38.4), and p = 1 on 64 x 256
-        // fits three workgroups per CU now (2048 x 13824 x 5120 107.5, now 101.3).  One tile per wave has the registers (1 % slower so).
-        if constexpr (NTW >= 2) asm("" : "+s"(base));
+        // Scalar base + 32-bit lane offset; left alone, the step is folded into a second set of 64-bit lane offsets, 8 to 16 registers.
+        // Only where those are short: p = 7 on 64 x 128 tiles spilled inside the K loop (512 x 11008 x 4096 40.2 us, now 38.4), p = 1
+        // on 64 x 256 fits three workgroups per CU so (2048 x 13824 x 5120 107.5, now 101.3).  Elsewhere it gains nothing, and loses
+        // 0.5-1 % with one tile per wave and at p = 8.
+        if constexpr (NTW >= 2 && (P == 7 || P == 1)) asm("" : "+s"(base));
 #pragma unroll
         for (int u = 0; u < MT; ++u)
             __builtin_amdgcn_global_load_lds((const void*)(base + a_goff[u]),
@@ -470,7 +471,9 @@ __device__ __forceinline__ void step_g128(const u4v (*w)[phase_regs(P)], const u
     }
 }
 
-// The same step for p <= 6, where w' - z + 64 is a byte of 0..127 for every code and zero-point: the zero-point goes into the
+// The same step for p <= 6, where w' - z + 64 is a byte of 0..127 for every code and every zero-point that the packer's contract
+// allows (0..2^p-1; one outside would carry into its neighbour.  Clamping z here and adding the rest behind the K loop was right for
+// every signed byte, and cost one tile per wave 3-9 %: M = 32 4096^2 p = 5 14.9 -> 16.5 us).  The zero-point goes into the
 // operand (one add per dword of four bytes, no carries between them), and the 64 comes off again through the accumulators' start
 // value -64 sum_k a', an MFMA's result that serves all columns.  What remains per element and group is one multiply-add for the
 // token's zero-point, one conversion, one fused multiply-add, and with two tiles per wave these run under the next unit's MFMAs
