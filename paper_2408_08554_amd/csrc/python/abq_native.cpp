@@ -205,11 +205,16 @@ struct Workspace : Buffer {
         wanted = is_none(given) && need;
         bytes = need;
         if (is_none(given)) return true;
-        const at::Tensor* t = tensor(given);
-        if (!t) return false;
-        ptr = t->data_ptr();
-        bytes = (size_t)t->numel();
-        return true;
+        if (THPVariable_Check(given)) {
+            bytes = (size_t)THPVariable_Unpack(given).numel();
+        } else {
+            PyObject* n = PyObject_CallMethod(given, "numel", nullptr);
+            if (!n) return false;
+            bytes = PyLong_AsSize_t(n);
+            Py_DECREF(n);
+            if (bytes == (size_t)-1 && PyErr_Occurred()) return false;
+        }
+        return pointer(given, &ptr);
     }
     void* make(at::Device device) { return Buffer::make({(int64_t)bytes}, at::kByte, device); }
 };

@@ -106,6 +106,9 @@ def test_operands_that_are_no_tensors():
         def data_ptr(self):
             return 4096
 
+        def numel(self):
+            return 1 << 20
+
     f, storage = FIELDS, host(16).untyped_storage()
     for operand in (storage, Own()):
         for call in (lambda: B.abq_gemm(4, 8, 1, 64, 0, operand, f, operand, f), lambda: B.abq_f4_gemm(2, 2, 1, 64, 0, operand, operand, operand, operand),
@@ -113,6 +116,10 @@ def test_operands_that_are_no_tensors():
                      lambda: B.abq_gemm_act_codes_static(4, 8, 1, 64, 0, operand, operand, operand, operand, f, operand, operand)):
             with pytest.raises(RuntimeError):                   # (refused no earlier than a tensor)
                 call()
+    with pytest.raises(RuntimeError):                           # (a workspace says its size too)
+        B.abq_gemm(4, 8, 1, 64, 0, Own(), f, Own(), f, Own(), workspace=Own())
+    with pytest.raises(AttributeError, match="numel"):
+        B.abq_gemm(4, 8, 1, 64, 0, Own(), f, Own(), f, Own(), workspace=storage)
     for other in (7, "text", [host(16)]):
         with pytest.raises((AttributeError, TypeError)):
             B.abq_gemm(4, 8, 1, 64, 0, other, f, host(16), f)
