@@ -535,9 +535,13 @@ static int gemm_impl(int p, int q, int M, int N, int K, const void* packed_act, 
     GemmArgs g{p, q, M, N, K, (const uint8_t*)packed_act, nullptr, nullptr, nullptr, (const uint8_t*)packed_w, y_fp16, acc_i32,
                workspace, workspace_bytes, rq};
     hipStream_t s = (hipStream_t)stream;
-    if (W.g128)   // per-group weight parameters: the streaming kernel up to 16 rows of A, the tiled per-group kernel above
+    int shape;
+    if (W.g128) {   // per-group weight parameters: the streaming kernel up to 16 rows of A, the K-split or the tiled per-group kernel above
+        if (M > kSkinnyMaxM && ksplit_plan(g, A, W, &shape)) return hip_status(launch_gemm_ksplit(g, A, W, shape, s));
         return hip_status(M <= kSkinnyMaxM ? launch_decode(g, A, W, s) : launch_gemm_tiled(g, A, W, s));
+    }
     if (!choose_fields(can_fields, can_planes, force, p, q, M, N)) return hip_status(launch_gemm_bitserial(g, A, W, s));
+    if (M > kSkinnyMaxM && ksplit_plan(g, A, W, &shape)) return hip_status(launch_gemm_ksplit(g, A, W, shape, s));
     if (streaming_shape(M, N)) return hip_status(launch_decode(g, A, W, s));
     return hip_status(launch_gemm_tiled(g, A, W, s));
 }
@@ -625,6 +629,14 @@ static int gemm_act_codes_impl(int p, int q, int M, int N, int K, const uint8_t*
     if (!no_workspace) {
         if (!workspace) return ABQ_ERR_NULL;
         if (workspace_bytes < act_bytes + abq_gemm_workspace_bytes(p, q, M, N, K)) return ABQ_ERR_SIZE;
+    }
+    // The K-split kernel reads unpacked codes too (the workspace that the query names stays unused).
+    if (M > kSkinnyMaxM && W.has_fields && (W.g128 || choose_fields(true, W.has_planes, force, p, q, M, N))) {
+        ActLayout A;
+        if (!make_act_layout(q, M, K, ABQ_LAYOUT_FIELDS, &A)) return ABQ_ERR_LAYOUT;
+        const GemmArgs g{p, q, M, N, K, nullptr, a_codes, a_scale, a_zero, (const uint8_t*)packed_w, y_fp16, acc_i32, nullptr, 0, rq};
+        int shape;
+        if (ksplit_plan(g, A, W, &shape)) return hip_status(launch_gemm_ksplit(g, A, W, shape, s));
     }
     if (no_workspace || fused_act_ragged(W, force, p, q, M, N, K)) {
         ActLayout A;

@@ -153,6 +153,9 @@ bool direct_plan_g128(int p, int nsuper, DirectPlan* out);   // per-group blobs,
 bool gemm_direct_g128_fits(int p, int M, const GemmArgs& g, const ActLayout& A, const WeightLayout& W);
 hipError_t launch_gemm_direct_grouped(int p, int q, int M, int count, const GemmArgs* probs, const ActLayout* A, const WeightLayout* W,
                                       hipStream_t s);
+// The K-split prefill kernel (more than 16 rows of A over few output tiles): index of the workgroup shape.
+bool ksplit_plan(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, int* shape);   // false: another kernel takes the problem
+hipError_t launch_gemm_ksplit(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, int shape, hipStream_t s);
 hipError_t launch_gemm_tiled(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, hipStream_t s);
 hipError_t launch_gemm_bitserial(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, hipStream_t s);
 

@@ -1,0 +1,88 @@
+// Host side of the K-split prefill kernel: the choice of shape and the launch.
+#include "abq_ksplit_kernels.h"
+
+namespace abq {
+
+struct KsShapeInfo { int rt, ct; };
+static const KsShapeInfo kShapes[4] = {{2, 1}, {2, 2}, {4, 2}, {4, 4}};   // (as in ks_launch_p)
+
+// Shape: the smallest workgroup tile of which no compute unit gets more than one.  A workgroup's time goes with the operand bytes it
+// pulls (about 30 bytes a clock per compute unit), and a second round of workgroups costs what the first did.  Against the other
+// kernels (tiled, streaming; 957 sizes of M = 17..2048, N = 256..13824, K = 512..13824, all widths, packed and unpacked rows, per-channel
+// and per-group weights, timed in replays) the choice below is 1.41 times as fast on average, 2.4 % from the best of all kernels and
+// shapes at each size, and at most 7 % behind the others.  Where the lines lie (this kernel / the others, us):
+//   64 x 64, per-channel: the tiled kernel has overtaken while K is short (packed rows K < 1600 1.11 times, K = 3072..6144 0.92; unpacked
+//     rows, at most 64 of them, which the streaming kernel may take without a pack launch, up to K = 4608: 12880 ch x 3296,
+//     M = 38: 14.9 / 13.8);
+//   per-group, packed rows: the tiled per-group kernel wins below K = 1024 on 64 x 32 (1008: 7.9 / 6.1) and below 6144 on 64 x 64
+//     (1136: 11.3 / 8.6); with unpacked rows the pack launch decides (1.06 times and more at every K);
+//   up to 48 rows, per-channel, K >= 3072: the streaming kernel splits K as well, over tiles of 16 rows (1536 ch x 10400, M = 25: 11.2 /
+//     9.3; 512 ch x 5712, M = 44: 8.2 / 7.5); with unpacked rows of a K that is no multiple of 16 it needs a pack launch and loses.
+static int shape_by_rule(const GemmArgs& g, const WeightLayout& W)
+{
+    int shape = 0;
+    for (;; ++shape) {
+        if (shape == 4) return -1;
+        if ((long)((g.M + 16 * kShapes[shape].rt - 1) / (16 * kShapes[shape].rt)) * ((W.NT + kShapes[shape].ct - 1) / kShapes[shape].ct) <= (long)num_cus()) break;
+    }
+    const bool raw = g.a_raw != nullptr;
+    if (W.g128) return !raw && ((shape == 3 && g.K < 6144) || (shape == 2 && g.K < 1024)) ? -1 : shape;
+    if (shape == 3 && g.K < (raw && g.M <= 64 ? 4608 : 3072)) return -1;
+    if (shape <= 1 && g.M <= 48 && g.K >= 3072 && (shape == 0 || g.p >= 5) && !(raw && g.K % 16 != 0)) return -1;
+    return shape;
+}
+
+// False: another kernel takes the problem.
+bool ksplit_plan(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, int* shape)
+{
+    if (!W.has_fields || g.M <= 16) return false;
+    // (unpacked rows: any length of at least one 16-byte load; per-group weights, of whole ones)
+    if (g.a_raw ? g.K < 16 || (W.g128 && g.K % 16 != 0) : !A.has_fields) return false;
+    if (W.g128 && (g.acc || g.rq.codes)) return false;
+    PlanOverride ov;   // an entry for one of the other kernels is followed
+    lookup_plan(g.p, g.q, g.M, g.N, g.K, &ov);
+    if (ov.skinny_waves || ov.skinny_kgroups || ov.tiled_mt || ov.tiled_ntw || ov.tiled_wd || ov.tiled_band) return false;
+    const int env = tuning_env("ABQ_KS");   // tuning builds: -1 off, 1..4 a shape
+    *shape = env < 0 ? -1 : (env >= 1 && env <= 4 ? env - 1 : shape_by_rule(g, W));
+    return *shape >= 0;
+}
+
+hipError_t launch_gemm_ksplit(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, int shape, hipStream_t s)
+{
+    const KsShapeInfo& sh = kShapes[shape];
+    KsplitParams prm;
+    for (int i = 0; i < 3; ++i) prm.fields[i] = (const u4v*)(g.w_blob + W.off_fields[i]);
+    const bool raw = g.a_raw != nullptr;
+    prm.a = raw ? g.a_raw : g.act_blob + A.off_codes;
+    prm.aparams = raw ? nullptr : (const RowParams*)(g.act_blob + A.off_params);
+    prm.a_scale = g.a_scale;
+    prm.a_zero = g.a_zero;
+    prm.wparams = (const RowParams*)(g.w_blob + W.off_params);
+    prm.gparams = W.g128 ? (const u4v*)(g.w_blob + W.off_gparams) : nullptr;
+    prm.y = g.y; prm.acc = g.acc; prm.rq = g.rq;
+    prm.M = g.M; prm.N = g.N; prm.K = g.K;
+    prm.lda = raw ? g.K : A.Kp;
+    prm.nsuper = A.Kp / kSuperK;
+    prm.ntiles = W.NT;
+    prm.oa = g.q == 8 ? 128 : 0;
+    prm.ow = g.p == 8 ? 128 : 0;
+    prm.a_mask = ((1u << g.q) - 1u) * 0x01010101u;
+    prm.tiles_m = (g.M + 16 * sh.rt - 1) / (16 * sh.rt);
+    prm.tiles_n = (W.NT + sh.ct - 1) / sh.ct;
+    // bands of equal height, as in the tiled kernel
+    const int cap = (g.p <= 4 ? 512 : 1024) / (16 * sh.rt);
+    const int bands = (prm.tiles_m + cap - 1) / cap;
+    prm.band_m = (prm.tiles_m + bands - 1) / bands;
+    switch (g.p) {
+        case 1: return ksplit_launch_p1(prm, shape, raw, W.g128, s);
+        case 2: return ksplit_launch_p2(prm, shape, raw, W.g128, s);
+        case 3: return ksplit_launch_p3(prm, shape, raw, W.g128, s);
+        case 4: return ksplit_launch_p4(prm, shape, raw, W.g128, s);
+        case 5: return ksplit_launch_p5(prm, shape, raw, W.g128, s);
+        case 6: return ksplit_launch_p6(prm, shape, raw, W.g128, s);
+        case 7: return ksplit_launch_p7(prm, shape, raw, W.g128, s);
+        default: return ksplit_launch_p8(prm, shape, raw, W.g128, s);
+    }
+}
+
+}  // namespace abq

@@ -1,0 +1,92 @@
+"""The K-split prefill kernel (more than 16 rows over few output tiles): every workgroup shape at the edges of its tiles and of K,
+from packed and from unpacked rows, bit for bit against the tiled and streaming kernels (which a plan-table entry brings back)
+and against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2408_08554_amd import synth
+from helpers import check_against_oracle, check_g128, check_sampled, to_dev
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+FIELDS, G128 = 2, 4
+# rows, channels: 32 x 16, 32 x 32, 64 x 32 and 64 x 64 tiles on 256 compute units, whole and ragged in both directions
+SHAPES = {"32x16": [(17, 40), (33, 1003), (96, 64)], "32x32": [(50, 2100), (64, 4096)], "64x32": [(70, 4001), (257, 1600)], "64x64": [(129, 4100), (300, 3001)]}
+
+
+def other_kernel(abq, c, call):
+    """The same call while a plan-table entry asks for one of the other kernels."""
+    abq.abq_plan_set(c.p, c.q, c.M, c.N, c.K, tiled_mt=4, skinny_waves=4)
+    try:
+        return call()
+    finally:
+        abq.abq_plan_set(c.p, c.q, c.M, c.N, c.K)
+
+
+# K: one load, off a 16-byte boundary, one phase of 256 past and short of whole super-chunks, waves with one, two and three phases
+@pytest.mark.parametrize("K", [16, 255, 700, 2053, 3072, 4620])
+@pytest.mark.parametrize("shape", list(SHAPES))
+@pytest.mark.parametrize("p,q", [(1, 8), (2, 3), (3, 8), (4, 8), (5, 4), (6, 6), (7, 8), (8, 8), (8, 7)])
+def test_ksplit_equals_the_other_kernels(abq, p, q, shape, K):
+    if shape == "64x64" and K < 3072:
+        pytest.skip("64 x 64 tiles are taken from K = 3072")
+    for i, (M, N) in enumerate(SHAPES[shape]):
+        c = synth.make_case(p, q, M, N, K, seed=7000 + 10 * p + i, name=f"ksplit W{p}A{q} {M}x{N}x{K}")
+        print(c.name, flush=True)
+        a, sa, za = to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero)
+        pw = abq.abq_pack_weights(p, to_dev(torch, c.W), to_dev(torch, c.w_scale), to_dev(torch, c.w_zero))
+        pa = abq.abq_pack_act_codes(q, a, sa, za)
+        calls = [lambda acc: abq.abq_gemm_act_codes(p, q, M, N, K, a, sa, za, pw, FIELDS, want_acc=acc),
+                 lambda acc: abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, FIELDS, want_acc=acc)]
+        y0, acc0 = other_kernel(abq, c, lambda: calls[1](True))
+        for call in calls:
+            y, acc = call(True)
+            y2, _ = call(False)
+            assert torch.equal(acc, acc0) and torch.equal(y.view(torch.int16), y0.view(torch.int16)) and torch.equal(y2.view(torch.int16), y0.view(torch.int16))
+        check = check_against_oracle if M * N * K < 2e8 else check_sampled
+        check(c, y0.cpu().numpy(), acc0.cpu().numpy())
+
+
+@pytest.mark.parametrize("K", [16, 130, 1000, 2064, 6160])
+@pytest.mark.parametrize("shape", list(SHAPES))
+@pytest.mark.parametrize("p,q", [(1, 8), (3, 4), (4, 8), (6, 8), (7, 8), (8, 5)])
+def test_ksplit_per_group_weights(abq, p, q, shape, K):
+    M, N = SHAPES[shape][-1]
+    c = synth.make_case(p, q, M, N, K, seed=7100 + p, name=f"ksplit g128 W{p}A{q} {M}x{N}x{K}")
+    print(c.name, flush=True)
+    sh, zg = synth.group_quant_params(c)
+    if M * N * K > 1e9 and p not in (4, 8):
+        pytest.skip("the large sizes run for two widths")
+    top = (1 << p) - 1
+    zg[:, 0::2], c.W[0::3], c.A[0::4], c.a_zero[1::3] = top, 0, (1 << q) - 1, 0   # ends of the ranges against each other
+    c.a_scale[:] = np.float32(2e-4 * 1000 / max(K, 1000))
+    a, sa, za = to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero)
+    pw = abq.abq_pack_weights_g128(p, to_dev(torch, c.W), to_dev(torch, sh.view(np.float16)), to_dev(torch, zg))
+    pa = abq.abq_pack_act_codes(q, a, sa, za)
+    calls = [lambda: abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, G128)[0], lambda: abq.abq_gemm_act_codes(p, q, M, N, K, a, sa, za, pw, G128)[0]]
+    ys = [call().cpu().numpy() for call in calls] + [other_kernel(abq, c, calls[0]).cpu().numpy()]
+    for y in ys if M * N * K < 5e8 else ys[:1]:
+        check_g128(c, sh, zg, y)
+    for y in ys[1:]:   # sums of the same integers in another order
+        d, ref = (y - ys[0].astype(np.float64)), ys[0].astype(np.float64)
+        assert np.linalg.norm(d) <= 5e-4 * np.linalg.norm(ref)
+
+
+@pytest.mark.parametrize("p,q,M,N,K", [(4, 8, 40, 130, 1000), (8, 6, 100, 2051, 528)])
+def test_ksplit_codes_past_q_bits_and_requant(abq, p, q, M, N, K):
+    """Codes with bits above q set are masked as the packers mask them; the requantizing epilogue and the static call."""
+    c = synth.make_case(p, q, M, N, K, seed=7200, name=f"ksplit W{p}A{q} {M}x{N}x{K}")
+    print(c.name, flush=True)
+    a, sa, za = to_dev(torch, c.A | (0xFF & ~((1 << q) - 1))), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero)
+    pw = abq.abq_pack_weights(p, to_dev(torch, c.W), to_dev(torch, c.w_scale), to_dev(torch, c.w_zero))
+    so, zo = torch.rand(M, device="cuda") + 0.5, torch.randint(0, 256, (M,), dtype=torch.int32, device="cuda")
+    static = torch.empty((M, N), dtype=torch.float16, device="cuda")
+    abq.abq_gemm_act_codes_static(p, q, M, N, K, a, sa, za, pw, FIELDS, static)
+    run = lambda: abq.abq_gemm_act_codes_requant(p, q, M, N, K, a, sa, za, pw, FIELDS, 8, so, zo)
+    codes, y = run()[:2]
+    codes0, y0 = other_kernel(abq, c, run)[:2]
+    assert torch.equal(codes, codes0) and torch.equal(y.view(torch.int16), y0.view(torch.int16)) and torch.equal(static.view(torch.int16), y0.view(torch.int16))
+    check_against_oracle(c, y.cpu().numpy(), None)
