@@ -55,6 +55,7 @@ struct DirectParams {
     int first_tile[kDirectMaxGroup + 1];    // where each problem's tiles start in the grid
     int M, oa, ow;
     uint32_t a_mask;                        // (2^q - 1) in every byte (unpacked codes are masked to q bits)
+    int lane_order;                         // 1: the variant that loads the rows of A in lane order (direct_lane_order; eight operand rows and up)
     DirectProblem d[kDirectMaxGroup];
 };
 
@@ -251,7 +252,7 @@ __device__ __forceinline__ void direct_pick(const v4i* accI, int G, int32_t* v)
 // token's, both less the stored offsets; padded k hold a' = 0 and w' = z), then one conversion and one fma with the
 // group's scale; the lanes of a wave add their groups by lane exchange, and the 16 threads of the epilogue add the
 // waves in a fixed order.
-template <int P, int MR, int R, bool RAW, bool GROUPED, bool GQ = false>
+template <int P, int MR, int R, bool RAW, bool LO, bool GROUPED, bool GQ = false>
 __global__ __launch_bounds__(1024) void direct_kernel(DirectParams gp)
 {
     static_assert(!GQ || direct_has_gq(P, MR, R), "per-group parameters: one row of A and an accumulator per slice");
@@ -291,13 +292,18 @@ __global__ __launch_bounds__(1024) void direct_kernel(DirectParams gp)
         pw0 = pr.wparams[min(tile * kTileN + (t0 & 15), pr.N - 1)];
     }
 
-    // ---- the A operand quads: lane (r, G) holds row r % MR of A over 16 k of slice q*SL + r/MR of the wave's run
+    // ---- the A operand quads: lane (r, G) holds row r % MR of A over 16 k of slice q*SL + r/MR of the wave's run.  A load in that
+    // order has neighbouring lanes in different rows, and keeps the address path busy for several times as long as one in lane order
+    // (LO: 64 SL bytes of each row, lane l the 16-byte piece l % (4 SL) of row l / (4 SL)).  Where many such loads meet on a compute
+    // unit (direct_lane_order) they are made in lane order, and the lanes exchanged below, while the weights are on their way
+    // (kernel times: W2A8 M=8 11008->4096 6.9 -> 6.45 us, packed rows 6.2 -> 5.8, W4A8 M=8 block 24.2 -> 22.8, W4A8 M=16 3001->1000 7.0 -> 5.3).
+    static_assert(!LO || (MR >= 8 && !GQ), "few rows are few loads");
     v4i aq[NQ];
-    const int m_l = r % MR, i_l = r / MR;                            // (i_l >= SL: an operand row that stays zero)
+    const int m_l = LO ? lane / (4 * SL) : r % MR, i_l = LO ? lane / 4 % SL : r / MR, g_l = LO ? lane & 3 : G;   // (i_l >= SL: an operand row that stays zero)
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         const int sl = i_l < SL ? q * SL + i_l : 8 * R;
-        const int k = (sc0 * 8 + sl) * 64 + G * 16;
+        const int k = (sc0 * 8 + sl) * 64 + g_l * 16;
         v4i v{0, 0, 0, 0};
         if constexpr (RAW) {   // (masked and offset further down, behind the last load of this prologue: nothing waits in between)
             // (rows of codes may start anywhere: global memory takes 16-byte loads at any address.  The last K % 16 codes of a
@@ -338,7 +344,7 @@ __global__ __launch_bounds__(1024) void direct_kernel(DirectParams gp)
 #pragma unroll
         for (int q = 0; q < NQ; ++q) {
             const int sl = i_l < SL ? q * SL + i_l : 8 * R;
-            const bool live = m_l < M && sl < 8 * nsc && (sc0 * 8 + sl) * 64 + G * 16 < pr.K;
+            const bool live = m_l < M && sl < 8 * nsc && (sc0 * 8 + sl) * 64 + g_l * 16 < pr.K;
             const v4i c = aq[q];
             aq[q] = live ? v4i{(int)(((uint32_t)c.x & gp.a_mask) ^ flip), (int)(((uint32_t)c.y & gp.a_mask) ^ flip),
                                (int)(((uint32_t)c.z & gp.a_mask) ^ flip), (int)(((uint32_t)c.w & gp.a_mask) ^ flip)}
@@ -348,10 +354,21 @@ __global__ __launch_bounds__(1024) void direct_kernel(DirectParams gp)
 #pragma unroll
             for (int q = 0; q < NQ; ++q) {
                 const int sl = i_l < SL ? q * SL + i_l : 8 * R;
-                const int left = pr.K - ((sc0 * 8 + sl) * 64 + G * 16);
+                const int left = pr.K - ((sc0 * 8 + sl) * 64 + g_l * 16);
                 if (m_l < M && sl < 8 * nsc && left > 0 && left < 16) aq[q] = row_tail16(aq[q], left);
             }
         }
+    }
+
+    if constexpr (LO) {   // to the operand's order
+        const int from = 4 * ((r % MR) * (4 * SL) + 4 * (r / MR) + G);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const int v = __builtin_amdgcn_ds_bpermute(from, aq[q][d]);
+                aq[q][d] = MR * SL == 16 || r / MR < SL ? v : 0;
+            }
     }
 
     if constexpr (GQ) {
@@ -503,15 +520,22 @@ static hipError_t direct_launch_one(const DirectParams& gp, unsigned grid, int w
 {
     if (gp.d[0].gparams) {   // per-group weight parameters (every problem of a launch is of the same kind)
         if constexpr (direct_has_gq(P, MR, R)) {
-            if (gp.count > 1) direct_kernel<P, MR, R, RAW, true, true><<<grid, waves * 64, direct_lds_bytes(waves, MR, true), s>>>(gp);
-            else direct_kernel<P, MR, R, RAW, false, true><<<grid, waves * 64, direct_lds_bytes(waves, MR, true), s>>>(gp);
+            if (gp.count > 1) direct_kernel<P, MR, R, RAW, false, true, true><<<grid, waves * 64, direct_lds_bytes(waves, MR, true), s>>>(gp);
+            else direct_kernel<P, MR, R, RAW, false, false, true><<<grid, waves * 64, direct_lds_bytes(waves, MR, true), s>>>(gp);
             return hipGetLastError();
         } else {
             return hipErrorInvalidValue;
         }
     }
-    if (gp.count > 1) direct_kernel<P, MR, R, RAW, true><<<grid, waves * 64, direct_lds_bytes(waves, MR, false), s>>>(gp);
-    else direct_kernel<P, MR, R, RAW, false><<<grid, waves * 64, direct_lds_bytes(waves, MR, false), s>>>(gp);
+    if constexpr (MR >= 8) {
+        if (gp.lane_order) {
+            if (gp.count > 1) direct_kernel<P, MR, R, RAW, true, true><<<grid, waves * 64, direct_lds_bytes(waves, MR, false), s>>>(gp);
+            else direct_kernel<P, MR, R, RAW, true, false><<<grid, waves * 64, direct_lds_bytes(waves, MR, false), s>>>(gp);
+            return hipGetLastError();
+        }
+    }
+    if (gp.count > 1) direct_kernel<P, MR, R, RAW, false, true><<<grid, waves * 64, direct_lds_bytes(waves, MR, false), s>>>(gp);
+    else direct_kernel<P, MR, R, RAW, false, false><<<grid, waves * 64, direct_lds_bytes(waves, MR, false), s>>>(gp);
     return hipGetLastError();
 }
 

@@ -265,3 +265,13 @@ def test_producers_of_any_length(abq, M, K):
     assert h_out.data_ptr() == r.data_ptr() and np.array_equal(bits(r), h.view(np.uint16)[rows])
     check((*got, y), oracle.rmsnorm_half(h, gamma, 1e-5))
     check(abq.abq_silu_mul_quant_act(q, dev(x), dev(up), want_h=True), oracle.silu_mul_half(x, up))
+
+
+@pytest.mark.parametrize("M", [5, 8, 9, 16])
+@pytest.mark.parametrize("p,q,N,K", [(4, 8, 70, 10320), (8, 7, 90, 5872), (2, 8, 4100, 4096), (6, 8, 33, 9808), (3, 5, 40, 7001), (5, 8, 300, 6144), (7, 8, 4111, 3100)])
+def test_decode_rows_in_lane_order(abq, p, q, M, N, K):
+    """Eight and sixteen operand rows on enough K and tiles that the direct kernel loads the rows of A in lane order."""
+    c = synth.make_case(p, q, M, N, K, seed=5900 + M + p, name=f"W{p}A{q} {M}x{N}x{K}")
+    print(c.name, flush=True)
+    for y, acc in (gpu_gemm_fused(torch, abq, c, FIELDS), gpu_gemm(torch, abq, c, FIELDS, FIELDS)):
+        (check_against_oracle if M * N * K < 2e8 else check_sampled)(c, y, acc)
