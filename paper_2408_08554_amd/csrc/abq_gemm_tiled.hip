@@ -715,18 +715,17 @@ static hipError_t launch_g128_p(const TiledParams& prm, int ntw, dim3 grid, hipS
 template <int P, int NTW, int MT>
 static hipError_t launch_shape(const TiledParams& prm, dim3 grid, int cus, int plan_wd, hipStream_t s)
 {
-    // The deep rings exist for the small tile shapes (for two tiles of W per wave only up to p = 6: beyond, the
-    // registers run out) and run two workgroups per CU instead of three.  Measured: with at most one workgroup
-    // per CU (M = 64..128 on a 4096-wide layer) they are 20 % faster, with more workgroups (M = 128 on an
-    // 11008-wide layer and up) the traffic through L2, not the latency of a step, is the bound and they lose.
-    // With long K (13824) and p = 8 the plan search found them ahead up to 2.5 workgroups per CU (M = 512, 5120 channels:
-    // 75 vs 84 us); narrower weights lose or tie there (between one and two workgroups per CU, K = 11008..13824: W1A8
-    // 38 vs 33 us, W2A8 35 vs 28, W4A8 and W6A8 within 1 %), because the deep rings hold two workgroups per CU, not three.
-    // Override: the plan table (plan_wd).
+    // The deep rings exist for the small tile shapes (for two tiles of W per wave only up to p = 6: beyond, the registers run out) and run
+    // two workgroups per CU instead of three.  They are 20-30 % ahead with at most one workgroup per CU and long K (W8A8 M=256 4096 ch,
+    // K=11008 39.0 -> 28.4 us; p = 8 from K = 2048: M=316 1840 ch, K=2768 10.9 -> 10.4), at p = 8 and K >= 8192 also where two per CU just fill the
+    // chip (M=512 4096 ch 42.5 -> 41), and behind otherwise (W4A8 M=256 4096^2 9.5 us, 11.0 on them; W8A8 M=411 5120 ch, K=13824 65 / 68).  Override: the plan
+    // table (plan_wd).
     constexpr bool has_deep = MT == 4 && (NTW == 1 || (NTW == 2 && P <= 6));
     const int forced = plan_wd > 0 ? plan_wd : tuning_env("ABQ_TILED_WD");
     if constexpr (has_deep) {
-        if (forced == 4 || (forced != 2 && ((long)grid.x <= (long)cus || (P == 8 && (long)grid.x <= 3L * cus && prm.K >= 8192)))) {
+        const long wg = grid.x;
+        const bool once = wg <= (long)cus && prm.K >= (P == 8 ? 2048 : 8192), twice = P == 8 && wg <= 2L * cus && 10 * wg >= 19L * cus && prm.K >= 8192;
+        if (forced == 4 || (forced != 2 && (once || twice))) {
             tiled_kernel<P, NTW, MT, 4><<<grid, 256, 0, s>>>(prm);
             return hipGetLastError();
         }
@@ -788,30 +787,28 @@ hipError_t launch_gemm_tiled(const GemmArgs& g, const ActLayout& A, const Weight
             default: return launch_g128_p<8>(prm, ntw_g, grid_g, s);
         }
     }
-    // Tile shape (rows of A x rows of W per workgroup), measured on LLaMA-7B/13B prefill shapes: 128x128
-    // while it yields at least 1.5 workgroups per CU (two or three share a CU), else 64x128, else 64x64.
-    // Narrow weights (p <= 4) with M >= 1024 do better with 64 rows of A against 256 (or 128) rows of W: the
-    // launch-plan search on M = 1024..8192 found 64x256 3-19 % ahead of 128x128 at p = 2, 4 where it still
-    // yields three workgroups per CU, and 64x128 ahead of both where it does not (N = 5120: 124 vs 144 us);
-    // at M = 512 and at p = 8 128x128 stays ahead.
+    // Tile shape (rows of A x rows of W per workgroup).  From timings of 1430 sizes of M = 65..2048, N = 512..13824, K = 512..13824 at all
+    // widths (64 x 64, 64 x 128, 64 x 256, 128 x 64, 128 x 128, both ring depths); the choice below is 1.3 % from the best of them at each
+    // size (the rule before: 2.9 %).  Workgroups are counted per compute unit, of 128 x 128 tiles unless said:
+    //   p <= 2: 64 x 64 up to 1.5 of 64 x 128, then 64 x 128, 64 x 256 above 2.5 (W1A8 M=693 11008 ch 45.5 us on 128 x 128, 30.2) and where it
+    //     fills the chip exactly once;
+    //   p >= 3, up to 1.5: 64 x 128, or 64 x 64 while those are fewer than 1.5 (also for K >= 5120 at p = 4..6, where 64 x 128 on deep rings
+    //     had been taken: W5A8 M=512 4096 ch, K=11008 42.3 -> 32.7).  p = 8 takes 128 x 128 from 0.8 to 1.25 if K >= 2560: it halves the
+    //     weight bytes and nearly every unit has one (M=1024 5120 ch 39.1 -> 36.5); p = 7 takes 128 x 64 from 0.75 to 1 (31.2 -> 27.9);
+    //   above 1.5: 128 x 128, at p = 4 64 x 256.  From 2 to 2.5 their second round (two a unit) is nearly empty and 64 x 128 wins
+    //     (W8A8 M=1575 5008 ch 62.5 -> 52, W6A8 M=1024 9584 ch 144 -> 133), as it does at p = 4 above 2 while K is short (W4A8 1.08 times).
     int cus = 256, dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
     auto wgs = [&](int mt_, int ntw_) { return (long)((g.M + mt_ * 16 - 1) / (mt_ * 16)) * ((g.N + 64 * ntw_ - 1) / (64 * ntw_)); };
-    int mt = 8, ntw = 2;
-    // (p = 8: 128 x 128 also with 0.8..1 workgroups per CU, where it halves the weight bytes through L2 and every CU still
-    // has one: M = 256 on 13824 channels 40 -> 37 us, M = 1024 on 4096 channels 71 -> 67; with 1.25 per CU it loses 8 %.  64 x 256 also where it fills the chip exactly once
-    // at two workgroups per CU, 1.5..2 per CU: M = 2048 on 4096 channels, W4A8 K = 11008 95 -> 83 us.)
-    const bool mt8 = 2 * wgs(8, 2) >= 3L * cus || (g.p == 8 && 5 * wgs(8, 2) >= 4L * cus && wgs(8, 2) <= (long)cus);
-    if (g.M <= 64 || !mt8) { mt = 4; ntw = 2; }
-    else if (g.p <= 4 && g.M >= 1024) { mt = 4; ntw = (wgs(4, 4) >= 3L * cus || (wgs(4, 4) <= 2L * cus && 2 * wgs(4, 4) > 3L * cus)) ? 4 : 2; }
-    // K >= 5120, p = 4..6 and between 0.5 and 1.25 workgroups of 64 x 128 per CU: that tile on the deep rings is
-    // 4-11 % ahead of 64 x 64 (plan search, K = 5120, 11008, 13824: M = 128 on 13824 channels, M = 256 on 5120, M = 512 on
-    // 4096 and 5120; at K = 4096, M = 128 on 11008 channels, it is 3 % behind); with
-    // fewer workgroups 64 x 64 on the deep rings wins by a wide margin (M = 256 on 4096 channels: 24 vs 33 us), with two
-    // per CU the shallow rings do (M = 1024 on 4096 channels: 60 vs 66 us), and narrower weights prefer those anyway.
-    int rule_wd = 0;
-    if (mt == 4 && ntw == 2 && g.p >= 4 && g.p <= 6 && g.K >= 5120 && 2 * wgs(4, 2) > (long)cus && 4 * wgs(4, 2) <= 5L * cus) rule_wd = 4;
-    if (mt == 4 && ntw == 2 && rule_wd == 0 && 2 * wgs(4, 2) < 3L * cus) ntw = 1;
+    const long w82 = wgs(8, 2), w42 = wgs(4, 2), w44 = wgs(4, 4);
+    int mt = 4, ntw = 2 * w42 < 3L * cus ? 1 : 2;
+    if (g.p <= 2) {
+        if (ntw == 2 && g.M > 64 && (2 * w82 > 5L * cus || (w44 <= 2L * cus && 2 * w44 > 3L * cus))) ntw = 4;
+    } else if (g.M > 64) {
+        if (g.p == 8 && g.K >= 2560 && 5 * w82 >= 4L * cus && 4 * w82 <= 5L * cus) { mt = 8; ntw = 2; }
+        else if (g.p == 7 && 4 * w82 > 3L * cus && w82 <= (long)cus) { mt = 8; ntw = 1; }
+        else if (2 * w82 >= 3L * cus && !(w82 > 2L * cus && (2 * w82 <= 5L * cus || (g.p == 4 && g.K < 2560)))) { mt = g.p == 4 ? 4 : 8; ntw = g.p == 4 ? 4 : 2; }
+    }
     {
         const int forced_mt = tuning_env("ABQ_TILED_MT"), forced_ntw = tuning_env("ABQ_TILED_NTW");
         if (forced_mt == 4 || forced_mt == 8) mt = forced_mt;
@@ -821,7 +818,6 @@ hipError_t launch_gemm_tiled(const GemmArgs& g, const ActLayout& A, const Weight
     lookup_plan(g.p, g.q, g.M, g.N, g.K, &ov);
     if (ov.tiled_mt > 0) mt = ov.tiled_mt;
     if (ov.tiled_ntw > 0) ntw = ov.tiled_ntw;
-    const int wd_arg = ov.tiled_wd > 0 ? ov.tiled_wd : ((mt == 4 && ntw == 2) ? rule_wd : 0);
     prm.tiles_m = (g.M + mt * 16 - 1) / (mt * 16);
     prm.tiles_n = (g.N + 64 * ntw - 1) / (64 * ntw);
     // Bands of equal height.  The workgroups resident on one XCD (about 64) form a band_m x (64 / band_m)
@@ -836,14 +832,14 @@ hipError_t launch_gemm_tiled(const GemmArgs& g, const ActLayout& A, const Weight
     }
     dim3 grid((unsigned)(prm.tiles_m * prm.tiles_n));
     switch (g.p) {
-        case 1: return launch_p<1>(prm, ntw, mt, grid, cus, wd_arg, s);
-        case 2: return launch_p<2>(prm, ntw, mt, grid, cus, wd_arg, s);
-        case 3: return launch_p<3>(prm, ntw, mt, grid, cus, wd_arg, s);
-        case 4: return launch_p<4>(prm, ntw, mt, grid, cus, wd_arg, s);
-        case 5: return launch_p<5>(prm, ntw, mt, grid, cus, wd_arg, s);
-        case 6: return launch_p<6>(prm, ntw, mt, grid, cus, wd_arg, s);
-        case 7: return launch_p<7>(prm, ntw, mt, grid, cus, wd_arg, s);
-        default: return launch_p<8>(prm, ntw, mt, grid, cus, wd_arg, s);
+        case 1: return launch_p<1>(prm, ntw, mt, grid, cus, ov.tiled_wd, s);
+        case 2: return launch_p<2>(prm, ntw, mt, grid, cus, ov.tiled_wd, s);
+        case 3: return launch_p<3>(prm, ntw, mt, grid, cus, ov.tiled_wd, s);
+        case 4: return launch_p<4>(prm, ntw, mt, grid, cus, ov.tiled_wd, s);
+        case 5: return launch_p<5>(prm, ntw, mt, grid, cus, ov.tiled_wd, s);
+        case 6: return launch_p<6>(prm, ntw, mt, grid, cus, ov.tiled_wd, s);
+        case 7: return launch_p<7>(prm, ntw, mt, grid, cus, ov.tiled_wd, s);
+        default: return launch_p<8>(prm, ntw, mt, grid, cus, ov.tiled_wd, s);
     }
 }
 

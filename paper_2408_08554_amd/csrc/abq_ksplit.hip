@@ -13,7 +13,7 @@ static const KsShapeInfo kShapes[4] = {{2, 1}, {2, 2}, {4, 2}, {4, 4}};   // (as
 // shapes at each size, and at most 7 % behind the others.  Where the lines lie (this kernel / the others, us):
 //   64 x 64, per-channel: the tiled kernel has overtaken while K is short (packed rows K < 1600 1.11 times, K = 3072..6144 0.92; unpacked
 //     rows, at most 64 of them, which the streaming kernel may take without a pack launch, up to K = 4608: 12880 ch x 3296,
-//     M = 38: 14.9 / 13.8);
+//     M = 38: 14.9 / 13.8, as does p = 8: 2672 ch x 3088, M = 199: 16.1 / 14.6);
 //   per-group, packed rows: the tiled per-group kernel wins below K = 1024 on 64 x 32 (1008: 7.9 / 6.1) and below 6144 on 64 x 64
 //     (1136: 11.3 / 8.6); with unpacked rows the pack launch decides (1.06 times and more at every K);
 //   up to 48 rows, per-channel, K >= 3072: the streaming kernel splits K as well, over tiles of 16 rows (1536 ch x 10400, M = 25: 11.2 /
@@ -27,7 +27,7 @@ static int shape_by_rule(const GemmArgs& g, const WeightLayout& W)
     }
     const bool raw = g.a_raw != nullptr;
     if (W.g128) return !raw && ((shape == 3 && g.K < 6144) || (shape == 2 && g.K < 1024)) ? -1 : shape;
-    if (shape == 3 && g.K < (raw && g.M <= 64 ? 4608 : 3072)) return -1;
+    if (shape == 3 && g.K < (raw && (g.M <= 64 || g.p == 8) ? 4608 : 3072)) return -1;
     if (shape <= 1 && g.M <= 48 && g.K >= 3072 && (shape == 0 || g.p >= 5) && !(raw && g.K % 16 != 0)) return -1;
     return shape;
 }
