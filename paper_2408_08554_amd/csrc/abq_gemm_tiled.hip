@@ -471,22 +471,22 @@ __device__ __forceinline__ void step_g128(const u4v (*w)[phase_regs(P)], const u
     }
 }
 
-// The same step for p <= 6, where w' - z + 64 is a byte of 0..127 for every code and every zero-point that the packer's contract
-// allows (0..2^p-1; one outside would carry into its neighbour.  Clamping z here and adding the rest behind the K loop was right for
-// every signed byte, and cost one tile per wave 3-9 %: M = 32 4096^2 p = 5 14.9 -> 16.5 us).  The zero-point goes into the
-// operand (one add per dword of four bytes, no carries between them), and the 64 comes off again through the accumulators' start
-// value -64 sum_k a', an MFMA's result that serves all columns.  What remains per element and group is one multiply-add for the
+// The same step for p <= 6, where 128 + w' - z is a byte of 65..191 for every code and every zero-point that the packer's contract
+// allows (0..2^p-1), so that one add per dword of four bytes puts the zero-point into the operand with no carry between them, and a
+// flip of the top bits makes it the signed byte w' - z.  (Left at w' - z + 64, the operand needs no flip, and the accumulators a start
+// value -64 sum_k a' from eight more MFMAs to sixteen of the product: W4A8 M=1024 5120->13824 160 -> 141 us without them, M=700 4096^2 p = 5
+// 36.7 -> 28.8, with two vector instructions more between MFMAs.)  What remains per element and group is one multiply-add for the
 // token's zero-point, one conversion, one fused multiply-add, and with two tiles per wave these run under the next unit's MFMAs
 // (left alone, the scheduler puts all MFMAs of a unit first and the matrix pipe then idles through the flush).  The sums are the
-// same integers in the same order.  p = 7, 8 have no room for z in the byte.  With its quantizer, W4A8 M=1024 5120->13824 167 us
-// -> 153 by the centred operand -> 140 by the overlap; M=1024 11008->4096 p = 1..6 100-108 -> 81-96, M=32 4096^2 16-20 -> 13-14.
+// same integers in the same order.  p = 7, 8 have no room for z in the byte.  Against the uncentred step: W4A8 M=1024 5120->13824 with its
+// quantizer 167 us -> 125; M=1024 11008->4096 p = 1..6 100-108 -> 75-90.
 template <int P, int NTW, int MT, int PH>
 __device__ __forceinline__ void step_g128_centred(const u4v (*w)[phase_regs(P)], const u4v* gq, const uint8_t* a_buf, int r, int G,
                                                   const v4i* nzc, v4f (*facc)[NTW])
 {
-    const int one4 = 0x01010101, m64 = (int)0xC0C0C0C0u;
-    const v4i ones{one4, one4, one4, one4}, minus64{m64, m64, m64, m64}, zero4{0, 0, 0, 0}, wbase{-128 * 64, -128 * 64, -128 * 64, -128 * 64};
-    v4i a0[MT], a1[MT], start[MT], b[2][2], c[2][MT], wsum[2];
+    const int one4 = 0x01010101;
+    const v4i ones{one4, one4, one4, one4}, zero4{0, 0, 0, 0};
+    v4i a0[MT], a1[MT], b[2][2], c[2][MT], wsum[2];
     auto read_group = [&](auto JC) {
         constexpr int SL = 2 * decltype(JC)::value;
         read_a_operands<MT>(a_buf, r, G, SL, a0);
@@ -496,26 +496,20 @@ __device__ __forceinline__ void step_g128_centred(const u4v (*w)[phase_regs(P)],
     auto expand = [&](auto UC) {
         constexpr int U = decltype(UC)::value, J = U / NTW, nt = U % NTW, SL = 4 * PH + 2 * J, gj = 2 * PH + J, s = U & 1;
         const int z = ((int)(gq[nt].z << (24 - 8 * gj))) >> 24;
-        const uint32_t off = __builtin_amdgcn_perm(0u, (uint32_t)(64 - z), 0u);   // its low byte in all four
+        const uint32_t off = __builtin_amdgcn_perm(0u, (uint32_t)(128 - z), 0u);   // its low byte in all four
         b[s][0] = merged_operand<P, SL>(w[nt]);
         b[s][1] = merged_operand<P, SL + 1>(w[nt]);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            b[s][0][i] = (int)((uint32_t)b[s][0][i] + off);
-            b[s][1][i] = (int)((uint32_t)b[s][1][i] + off);
+            b[s][0][i] = (int)(((uint32_t)b[s][0][i] + off) ^ 0x80808080u);
+            b[s][1][i] = (int)(((uint32_t)b[s][1][i] + off) ^ 0x80808080u);
         }
     };
     auto multiply = [&](auto UC) {
         constexpr int U = decltype(UC)::value, s = U & 1;
-        if constexpr (U % NTW == 0) {
+        wsum[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones, b[s][0], zero4, 0, 0, 0);
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) start[mt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[mt], minus64, zero4, 0, 0, 0);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) start[mt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[mt], minus64, start[mt], 0, 0, 0);
-        }
-        wsum[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones, b[s][0], wbase, 0, 0, 0);
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) c[s][mt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[mt], b[s][0], start[mt], 0, 0, 0);
+        for (int mt = 0; mt < MT; ++mt) c[s][mt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a0[mt], b[s][0], zero4, 0, 0, 0);
         wsum[s] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ones, b[s][1], wsum[s], 0, 0, 0);   // (every row: the column's sum of w' - z)
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) c[s][mt] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a1[mt], b[s][1], c[s][mt], 0, 0, 0);
@@ -537,14 +531,14 @@ __device__ __forceinline__ void step_g128_centred(const u4v (*w)[phase_regs(P)],
     // (The next operands are expanded one unit ahead, or the MFMAs would wait for them in a row of their own.)
     auto overlap = [&](auto UC) {                      // products of unit U, flush of U - 1, operands of U + 1
         constexpr int U = decltype(UC)::value;
-        constexpr int mfmas = (U % NTW == 0 ? 2 * MT : 0) + 2 * MT + 2;
+        constexpr int mfmas = 2 * MT + 2;
         multiply(UC);
         flush(std::integral_constant<int, U - 1>{});
         if constexpr (U + 1 < 2 * NTW) expand(std::integral_constant<int, U + 1>{});
 #pragma unroll
         for (int i = 0; i < mfmas; ++i) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x002, U % NTW == 0 ? 4 : 7, 0);
+            __builtin_amdgcn_sched_group_barrier(0x002, 9, 0);
         }
         __builtin_amdgcn_sched_barrier(0);
     };
