@@ -78,13 +78,14 @@ hipError_t launch_gemm_direct(const GemmArgs& g, const ActLayout& A, const Weigh
 {
     DirectParams gp;
     gp.count = 1;
-    for (int i = 0; i <= kDirectMaxGroup; ++i) gp.first_tile[i] = i == 0 ? 0 : W.NT;
+    gp.first_tile[0] = 0;
+    gp.first_tile[1] = W.NT;
     gp.M = g.M;
     gp.oa = g.q == 8 ? 128 : 0;
     gp.ow = g.p == 8 ? 128 : 0;
     gp.a_mask = ((1u << g.q) - 1u) * 0x01010101u;
     gp.lane_order = direct_lane_order(g.p, g.M, pl, W.NT, g);
-    for (int i = 0; i < kDirectMaxGroup; ++i) fill_problem(gp.d[i], g, A, W, pl.R);   // unused slots repeat a valid descriptor
+    fill_problem(gp.d[0], g, A, W, pl.R);
     return launch_p(g.p, gp, pl.MR, pl.R, g.a_raw != nullptr, (unsigned)W.NT, pl.S, s);
 }
 

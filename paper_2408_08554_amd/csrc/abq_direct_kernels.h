@@ -27,6 +27,8 @@
 
 #include <hip/hip_fp16.h>
 
+#include <type_traits>
+
 namespace abq {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
@@ -50,14 +52,18 @@ struct DirectProblem {
     const u4v* gparams;        // per-group weight parameters (g128 blobs; null otherwise): [tiles][nsuper][16 channels] records
 };
 
-struct DirectParams {
+// MAX problems a launch (one for single calls: a launch copies its arguments, 1.2 KB of them for eight problems).
+template <int MAX>
+struct DirectParamsOf {
     int count;                              // problems in this launch
-    int first_tile[kDirectMaxGroup + 1];    // where each problem's tiles start in the grid
+    int first_tile[MAX + 1];                // where each problem's tiles start in the grid
     int M, oa, ow;
     uint32_t a_mask;                        // (2^q - 1) in every byte (unpacked codes are masked to q bits)
     int lane_order;                         // 1: the variant that loads the rows of A in lane order (direct_lane_order; eight operand rows and up)
-    DirectProblem d[kDirectMaxGroup];
+    DirectProblem d[MAX];
 };
+typedef DirectParamsOf<kDirectMaxGroup> DirectParams;
+typedef DirectParamsOf<1> DirectSingle;
 
 typedef int v4i_byte __attribute__((ext_vector_type(4), aligned(1)));
 
@@ -253,7 +259,7 @@ __device__ __forceinline__ void direct_pick(const v4i* accI, int G, int32_t* v)
 // group's scale; the lanes of a wave add their groups by lane exchange, and the 16 threads of the epilogue add the
 // waves in a fixed order.
 template <int P, int MR, int R, bool RAW, bool LO, bool GROUPED, bool GQ = false>
-__global__ __launch_bounds__(1024) void direct_kernel(DirectParams gp)
+__global__ __launch_bounds__(1024) void direct_kernel(typename std::conditional<GROUPED, DirectParams, DirectSingle>::type gp)
 {
     static_assert(!GQ || direct_has_gq(P, MR, R), "per-group parameters: one row of A and an accumulator per slice");
     using SH = DirectShape<P, MR, R>;
@@ -515,28 +521,30 @@ inline size_t direct_lds_bytes(int S, int MR, bool gq)
     return (size_t)S * MR * 16 * C * 4 + (size_t)S * MR * C * 4;
 }
 
+template <int P, int MR, int R, bool RAW, bool LO, bool GQ>
+static hipError_t direct_launch_kind(const DirectParams& gp, unsigned grid, int waves, hipStream_t s)
+{
+    const size_t lds = direct_lds_bytes(waves, MR, GQ);
+    if (gp.count > 1) {
+        direct_kernel<P, MR, R, RAW, LO, true, GQ><<<grid, waves * 64, lds, s>>>(gp);
+    } else {
+        const DirectSingle one{1, {gp.first_tile[0], gp.first_tile[1]}, gp.M, gp.oa, gp.ow, gp.a_mask, gp.lane_order, {gp.d[0]}};
+        direct_kernel<P, MR, R, RAW, LO, false, GQ><<<grid, waves * 64, lds, s>>>(one);
+    }
+    return hipGetLastError();
+}
+
 template <int P, int MR, int R, bool RAW>
 static hipError_t direct_launch_one(const DirectParams& gp, unsigned grid, int waves, hipStream_t s)
 {
     if (gp.d[0].gparams) {   // per-group weight parameters (every problem of a launch is of the same kind)
-        if constexpr (direct_has_gq(P, MR, R)) {
-            if (gp.count > 1) direct_kernel<P, MR, R, RAW, false, true, true><<<grid, waves * 64, direct_lds_bytes(waves, MR, true), s>>>(gp);
-            else direct_kernel<P, MR, R, RAW, false, false, true><<<grid, waves * 64, direct_lds_bytes(waves, MR, true), s>>>(gp);
-            return hipGetLastError();
-        } else {
-            return hipErrorInvalidValue;
-        }
+        if constexpr (direct_has_gq(P, MR, R)) return direct_launch_kind<P, MR, R, RAW, false, true>(gp, grid, waves, s);
+        else return hipErrorInvalidValue;
     }
     if constexpr (MR >= 8) {
-        if (gp.lane_order) {
-            if (gp.count > 1) direct_kernel<P, MR, R, RAW, true, true><<<grid, waves * 64, direct_lds_bytes(waves, MR, false), s>>>(gp);
-            else direct_kernel<P, MR, R, RAW, true, false><<<grid, waves * 64, direct_lds_bytes(waves, MR, false), s>>>(gp);
-            return hipGetLastError();
-        }
+        if (gp.lane_order) return direct_launch_kind<P, MR, R, RAW, true, false>(gp, grid, waves, s);
     }
-    if (gp.count > 1) direct_kernel<P, MR, R, RAW, false, true><<<grid, waves * 64, direct_lds_bytes(waves, MR, false), s>>>(gp);
-    else direct_kernel<P, MR, R, RAW, false, false><<<grid, waves * 64, direct_lds_bytes(waves, MR, false), s>>>(gp);
-    return hipGetLastError();
+    return direct_launch_kind<P, MR, R, RAW, false, false>(gp, grid, waves, s);
 }
 
 template <int P, int MR, int R>
