@@ -224,8 +224,9 @@ int abq_gemm(int p, int q, int M, int N, int K,
  *             tiles) on field-packed weights with K a multiple of 16 — the codes are offset to
  *             signed bytes and their row sums taken while the kernel stages them.  For every
  *             other problem the packed activations are written to the workspace and the two
- *             steps run back to back on the stream (few rows of another K run as one kernel all
- *             the same where that is faster; the workspace is still required, and unused).
+ *             steps run back to back on the stream (few rows of another K, and more than 16 rows
+ *             over few output tiles, run as one kernel all the same where that is faster; the
+ *             workspace is still required, and unused).
  * Errors as abq_gemm (ABQ_ERR_NULL / ABQ_ERR_SIZE when a needed workspace is missing / too small). */
 size_t abq_gemm_act_codes_workspace_bytes(int p, int q, int M, int N, int K, int w_layout);
 int abq_gemm_act_codes(int p, int q, int M, int N, int K,

@@ -1,8 +1,6 @@
 // Host side of the K-split prefill kernel: the choice of shape and the launch.
 #include "abq_ksplit_kernels.h"
 
-#include <limits.h>
-
 namespace abq {
 
 struct KsShapeInfo { int rt, ct; };
@@ -16,9 +14,10 @@ static const KsShapeInfo kShapes[4] = {{2, 1}, {2, 2}, {4, 2}, {4, 4}};   // (as
 //   64 x 64, per-channel: the tiled kernel has overtaken while K is short (packed rows K < 1600 1.11 times, K = 3072..6144 0.92; unpacked
 //     rows, at most 64 of them, which the streaming kernel may take without a pack launch, up to K = 4608: 12880 ch x 3296,
 //     M = 38: 14.9 / 13.8, as does p = 8: 2672 ch x 3088, M = 199: 16.1 / 14.6);
-//   per-group, packed rows: the tiled per-group kernel wins below K = 1024 on 64 x 32 (1008: 7.9 / 6.1), and on 64 x 64 at p <= 6 (0.75 to
-//     0.94 times) and below K = 2048 at p = 7, 8 (above 1.2 times); with unpacked rows, which it needs a pack launch for, below
-//     K = 1024 at p <= 6 (0.9; above 1.07 to 1.15; p = 7, 8 1.3 and more);
+//   per-group: one answer for packed and unpacked rows, because the order of the binary32 sums goes with the kernel and a call on codes
+//     returns the bits of packing and multiplying.  On 64 x 64 the tiled per-group kernel wins at p <= 6 (packed rows 0.75 to 0.94 times;
+//     unpacked, behind a pack launch, 1.07 to 1.15) and below K = 2048 at p = 7, 8 (above 1.2 and more); on 64 x 32 it is even below
+//     K = 1024 for packed rows (0.94 to 1.08; unpacked 1.5);
 //   up to 48 rows, per-channel, K >= 3072: the streaming kernel splits K as well, over tiles of 16 rows (1536 ch x 10400, M = 25: 11.2 /
 //     9.3; 512 ch x 5712, M = 44: 8.2 / 7.5); with unpacked rows of a K that is no multiple of 16 it needs a pack launch and loses.
 static int shape_by_rule(const GemmArgs& g, const WeightLayout& W)
@@ -29,10 +28,7 @@ static int shape_by_rule(const GemmArgs& g, const WeightLayout& W)
         if ((long)((g.M + 16 * kShapes[shape].rt - 1) / (16 * kShapes[shape].rt)) * ((W.NT + kShapes[shape].ct - 1) / kShapes[shape].ct) <= (long)num_cus()) break;
     }
     const bool raw = g.a_raw != nullptr;
-    if (W.g128) {
-        if (shape == 3) return g.K < (raw ? (g.p <= 6 ? 1024 : 0) : (g.p <= 6 ? INT_MAX : 2048)) ? -1 : shape;
-        return !raw && shape == 2 && g.K < 1024 ? -1 : shape;
-    }
+    if (W.g128) return shape == 3 && (g.p <= 6 || g.K < 2048) ? -1 : shape;
     if (shape == 3 && g.K < (raw && (g.M <= 64 || g.p == 8) ? 4608 : 3072)) return -1;
     if (shape <= 1 && g.M <= 48 && g.K >= 3072 && (shape == 0 || g.p >= 5) && !(raw && g.K % 16 != 0)) return -1;
     return shape;

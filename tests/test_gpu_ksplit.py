@@ -68,11 +68,11 @@ def test_ksplit_per_group_weights(abq, p, q, shape, K):
     pa = abq.abq_pack_act_codes(q, a, sa, za)
     calls = [lambda: abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, G128)[0], lambda: abq.abq_gemm_act_codes(p, q, M, N, K, a, sa, za, pw, G128)[0]]
     ys = [call().cpu().numpy() for call in calls] + [other_kernel(abq, c, calls[0]).cpu().numpy()]
+    assert np.array_equal(ys[0].view(np.uint16), ys[1].view(np.uint16))   # packed and unpacked rows: one order of sums
     for y in ys if M * N * K < 5e8 else ys[:1]:
         check_g128(c, sh, zg, y)
-    for y in ys[1:]:   # sums of the same integers in another order
-        d, ref = (y - ys[0].astype(np.float64)), ys[0].astype(np.float64)
-        assert np.linalg.norm(d) <= 5e-4 * np.linalg.norm(ref)
+    ref = ys[0].astype(np.float64)   # the same integers summed in another order: an output may round to the neighbouring binary16, at most 2^-10 of it
+    assert np.linalg.norm(ys[2] - ref) <= 2.0 ** -10 * np.linalg.norm(ref)
 
 
 @pytest.mark.parametrize("p,q,M,N,K", [(4, 8, 40, 130, 1000), (8, 6, 100, 2051, 528)])
