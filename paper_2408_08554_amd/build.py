@@ -42,8 +42,9 @@ def _compile(src: str, newest_header: float = 0.0) -> str:
 
 # Kernels that may not use scratch memory; the build fails if one does.  f4_gemm_kernel loads registers with hand-written load
 # instructions and waits for them by hand: the compiler does not know that such a register fills later, so it must not spill it
-# in between.  tiled_kernel's K loop counts on its loads staying in flight: a reload from scratch inside it waits for all of them.
-NO_SCRATCH = {"abq_f4.hip": "f4_gemm_kernel", "abq_gemm_tiled.hip": "tiled_kernel"}
+# in between.  The K loops of tiled_kernel and ksplit_kernel count on their loads staying in flight: a reload from scratch inside one waits
+# for all of them.
+NO_SCRATCH = {"abq_f4.hip": "f4_gemm_kernel", "abq_gemm_tiled.hip": "tiled_kernel", **{f"abq_ksplit_p{p}.hip": "ksplit_kernel" for p in range(1, 9)}}
 # (64 x 256 tiles at p = 7, three plane groups of four tiles per wave: two registers over the 256 of two workgroups per CU)
 SCRATCH_ALLOWED = ("tiled_kernelILi7ELi4ELi4ELi2E",)
 

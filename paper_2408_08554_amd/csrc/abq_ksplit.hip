@@ -45,7 +45,7 @@ bool ksplit_plan(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, i
     lookup_plan(g.p, g.q, g.M, g.N, g.K, &ov);
     if (ov.skinny_waves || ov.skinny_kgroups || ov.tiled_mt || ov.tiled_ntw || ov.tiled_wd || ov.tiled_band) return false;
     const int env = tuning_env("ABQ_KS");   // tuning builds: -1 off, 1..4 a shape
-    *shape = env < 0 ? -1 : (env >= 1 && env <= 4 ? env - 1 : shape_by_rule(g, W));
+    *shape = env < 0 ? -1 : (env >= 1 && env <= 4 && (!W.g128 || ks_has_gq(g.p, kShapes[env - 1].rt * kShapes[env - 1].ct)) ? env - 1 : shape_by_rule(g, W));
     return *shape >= 0;
 }
 

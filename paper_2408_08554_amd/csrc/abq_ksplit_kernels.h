@@ -5,10 +5,10 @@
 // prompts, narrow layers).  There the time is load latency, not arithmetic: a kernel whose waves share operands through LDS
 // advances one load latency and one barrier per step of K, and few workgroups keep few bytes in flight.  Here the waves of a
 // workgroup split K instead of the tile: every wave multiplies the whole workgroup tile (16 RT rows of A x 16 CT rows of W)
-// over its own phases of 256 k (wave, wave + S, ...), both operands straight from global memory into the MFMA's registers, one
-// phase (or half of one) ahead.  No operand passes through LDS and there is no barrier before the partial tiles meet in LDS at
-// the end, so the waves never wait for each other; the operand bytes a compute unit pulls are the same (each wave its own k).
-// The price is RT x CT accumulator tiles in every wave.
+// over its own phases of 256 k (wave, wave + S, ...), both operands loaded into its own registers one phase (or half of one) ahead.
+// Weights are multiplied from there; rows of A pass through a block of LDS that only their wave uses, to change lanes.  There is no
+// barrier before the partial tiles meet in LDS at the end, so the waves never wait for each other; the operand bytes a compute unit
+// pulls are the same (each wave its own k).  The price is RT x CT accumulator tiles in every wave.
 // RAW: rows of A are unpacked codes (one byte each): masked to q bits and made signed in registers, their sums taken on the way,
 // so a call needs no pack launch.  GQ: per-group weight parameters (groups of 128 along K); the groups of a wave's phases are
 // flushed into binary32 partial tiles.
@@ -39,6 +39,7 @@ struct KsplitParams {
     int oa, ow;
     uint32_t a_mask;             // (2^q - 1) in every byte
     int tiles_m, tiles_n, band_m;
+    int phase_q, phase_r;        // phases of a wave: phase_q, one more in the first phase_r waves
 };
 
 // Registers of one phase (256 k) of one 16-row tile of W: a b-bit group takes max(b/2, 1) of its 1 KiB chunks (a 1-bit chunk spans
@@ -80,6 +81,9 @@ __device__ __forceinline__ v4i ks_operand(const u4v* w)
     return r;
 }
 
+// Per-group weights on 64 x 64 tiles exist for p = 7, 8 only: below, the tiled per-group kernel is ahead of them (see shape_by_rule).
+__host__ __device__ constexpr bool ks_has_gq(int p, int tiles) { return p >= 7 || tiles < 16; }
+
 // Workgroup shapes: index -> rows / 16, channels / 16, waves, halves of a phase that the rows of A are fetched in, waves per SIMD
 // that the registers are held to.
 template <int RT_, int CT_, int S_, int AH_, int OCC_>
@@ -110,7 +114,6 @@ __global__ __launch_bounds__(64 * SH::S, SH::OCC) void ksplit_kernel(KsplitParam
     const int band_rows = min(prm.band_m, prm.tiles_m - band * prm.band_m);
     const int m_blk = band * prm.band_m + in_band % band_rows, n_blk = in_band / band_rows;
     const int m0 = m_blk * kBM, n0 = n_blk * kBN, tile0 = n_blk * CT;
-    const int nphase = prm.nsuper * 2;
 
     // the epilogue's parameters are requested first (their wait leaves the operand loads in flight), every load unconditional
     v4i pa{0, 0, 0, 0}, pw{0, 0, 0, 0};
@@ -136,13 +139,17 @@ __global__ __launch_bounds__(64 * SH::S, SH::OCC) void ksplit_kernel(KsplitParam
 
     // Loads of phase j: all unconditional.  Rows past M and tiles past the last re-read valid ones (never stored); unpacked rows are
     // clamped to their last 16 bytes and put right before use.
-    typedef typename std::conditional<RAW, v4i_byte, v4i>::type a_vec;   // (unpacked rows of any length start on any byte)
+    typedef __attribute__((address_space(1))) uint8_t a_byte;
+    typedef __attribute__((address_space(1))) typename std::conditional<RAW, v4i_byte, v4i>::type a_vec;   // (unpacked rows of any length start on any byte)
     auto load_a = [&](int j, int h, v4i (*a)[RT]) {
 #pragma unroll
         for (int s = 0; s < NSL; s += 2) {
             const int k = 256 * j + 64 * (h * NSL + s);
             const unsigned kk = RAW ? (unsigned)min(k + 16 * (lane & 7), prm.K - 16) : 0u;
-            const uint8_t* const base = RAW ? a_tile : a_tile + k;
+            const a_byte* base = (const a_byte*)(RAW ? a_tile : a_tile + k);
+            // Scalar base + 32-bit lane offset where registers are short (left alone, the step goes into 64-bit lane addresses, 16
+            // registers more, and 64 x 32 tiles at p = 7 are 2-5 % slower or go to scratch)
+            if constexpr (!RAW && P == 7 && !GQ) asm("" : "+s"(base));
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
@@ -325,9 +332,18 @@ __global__ __launch_bounds__(64 * SH::S, SH::OCC) void ksplit_kernel(KsplitParam
 
     v4i a0[NSL][RT], a1[NSL][RT];
     u4v w0[CT][PR], w1[CT][PR], g0[CT], g1[CT];
-    int j = wave;
-    load_w(j, w0, g0);
-    load_a(j, 0, a0);
+    int j = wave, n = prm.phase_q + (wave < prm.phase_r ? 1 : 0);
+    constexpr bool kSwapA = AH == 1;   // (with halves the buffers of A are back in place after a phase)
+    // An even number of phases starts in the other buffers, so that every wave ends in the same ones (64-row tiles; see below)
+    constexpr bool kOneEnd = RT == 4 && (!GQ || CT == 2 || (P == 7 && !RAW));
+    const bool even = kOneEnd && (n & 1) == 0;
+    if (even) {
+        load_w(j, w1, g1);
+        load_a(j, 0, kSwapA ? a1 : a0);
+    } else {
+        load_w(j, w0, g0);
+        load_a(j, 0, a0);
+    }
     if (tid < kBM) *reinterpret_cast<v4i*>(&par_a[tid]) = pa;
     if (!GQ && tid < kBN) *reinterpret_cast<v4i*>(&par_w[tid]) = pw;
     if constexpr (GQ) {
@@ -337,8 +353,8 @@ __global__ __launch_bounds__(64 * SH::S, SH::OCC) void ksplit_kernel(KsplitParam
 #pragma unroll
             for (int reg = 0; reg < 4; ++reg) nzc[rt][reg] = prm.oa - par_a[16 * rt + 4 * G + reg].zero;
     }
-    // One phase with the next one's loads under it, and the wave's last phase.  The loop leaves one or two phases to straight-line code
-    // of their own, so that no load is issued for a phase that does not exist and every wait counts exactly the loads behind it.
+    // One phase with the next one's loads under it, and the wave's last phase, which stands outside the loop, so that no load is issued
+    // for a phase that does not exist and every wait counts exactly the loads behind it.
     auto phase = [&](u4v (*w)[PR], u4v* gq, u4v (*wn)[PR], u4v* gqn, v4i (*a)[RT], v4i (*an)[RT]) {
         const int jn = j + waves;
         if constexpr (AH == 1) {
@@ -362,18 +378,29 @@ __global__ __launch_bounds__(64 * SH::S, SH::OCC) void ksplit_kernel(KsplitParam
         compute(H0{}, j, a, w, gq);
         if constexpr (AH == 2) compute(H1{}, j, an, w, gq);
     };
-    constexpr bool kSwapA = AH == 1;   // (with halves the buffers of A are back in place after a phase)
-    int n = (nphase - wave + waves - 1) / waves;
-    for (; n > 2; n -= 2) {
-        phase(w0, g0, w1, g1, a0, a1);
-        phase(w1, g1, w0, g0, kSwapA ? a1 : a0, kSwapA ? a0 : a1);
-    }
-    if (n == 2) {
-        phase(w0, g0, w1, g1, a0, a1);
-        last_phase(w1, g1, kSwapA ? a1 : a0, kSwapA ? a0 : a1);
-    } else {
-        asm volatile("; one phase" ::: "memory");
+    if constexpr (kOneEnd) {
+        // One last phase for both parities.  With one for each, as below, the buffers of one end stay alive across the other, and
+        // 64-row tiles went to scratch (M=256 1920 ch, K=2048, packed rows: per-group p = 3, 5, 7, 8 8.4, 10.0, 14.8, 8.7 us, now
+        // 6.9, 7.0, 7.9, 7.5; per-channel p = 7 8.2, now 6.6).  32-row tiles have the registers, and a short K is 2-4 % faster without a
+        // choice of buffers ahead of its first loads; so have the other per-group 64 x 64 tiles (M=512 2000 ch, K=8192 34.5 / 35.6).
+        if (even) phase(w1, g1, w0, g0, kSwapA ? a1 : a0, kSwapA ? a0 : a1);
+        for (; n > 2; n -= 2) {
+            phase(w0, g0, w1, g1, a0, a1);
+            phase(w1, g1, w0, g0, kSwapA ? a1 : a0, kSwapA ? a0 : a1);
+        }
         last_phase(w0, g0, a0, a1);
+    } else {
+        for (; n > 2; n -= 2) {
+            phase(w0, g0, w1, g1, a0, a1);
+            phase(w1, g1, w0, g0, kSwapA ? a1 : a0, kSwapA ? a0 : a1);
+        }
+        if (n == 2) {
+            phase(w0, g0, w1, g1, a0, a1);
+            last_phase(w1, g1, kSwapA ? a1 : a0, kSwapA ? a0 : a1);
+        } else {
+            asm volatile("; one phase" ::: "memory");
+            last_phase(w0, g0, a0, a1);
+        }
     }
 
     // the waves' partial tiles meet in LDS
@@ -445,17 +472,21 @@ typedef KsShape<4, 2, 8, 2, 2> Ks42;
 typedef KsShape<4, 4, 4, 2, 1> Ks44;
 
 template <int P, class SH, bool RAW, bool GQ>
-static hipError_t ks_launch_one(const KsplitParams& prm, hipStream_t s)
+static hipError_t ks_launch_one(KsplitParams prm, hipStream_t s)
 {
-    const int nphase = 2 * prm.nsuper;
-    const int waves = nphase < SH::S ? nphase : SH::S;
+    const int nphase = 2 * prm.nsuper, waves = nphase < SH::S ? nphase : SH::S;
+    prm.phase_q = nphase / waves;
+    prm.phase_r = nphase % waves;
     ksplit_kernel<P, SH, RAW, GQ><<<dim3((unsigned)(prm.tiles_m * prm.tiles_n)), 64 * waves, 0, s>>>(prm);
     return hipGetLastError();
 }
 template <int P, class SH>
 static hipError_t ks_launch_shape(const KsplitParams& prm, bool raw, bool gq, hipStream_t s)
 {
-    if (gq) return raw ? ks_launch_one<P, SH, true, true>(prm, s) : ks_launch_one<P, SH, false, true>(prm, s);
+    if (gq) {
+        if constexpr (ks_has_gq(P, SH::RT * SH::CT)) return raw ? ks_launch_one<P, SH, true, true>(prm, s) : ks_launch_one<P, SH, false, true>(prm, s);
+        else return hipErrorInvalidValue;
+    }
     return raw ? ks_launch_one<P, SH, true, false>(prm, s) : ks_launch_one<P, SH, false, false>(prm, s);
 }
 template <int P>

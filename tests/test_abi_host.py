@@ -459,3 +459,41 @@ def test_build_refuses_scratch_memory_in_kernels_with_hand_written_loads(tmp_pat
     bld._check_no_scratch(src, tiled((2, 0)) + tiled((4, 12)), "tiled_kernel")
     with pytest.raises(RuntimeError, match="scratch"):
         bld._check_no_scratch(src, tiled((2, 16)), "tiled_kernel")
+
+
+def _device_kernels(path):
+    """(name, scratch bytes per lane) of every gfx950 kernel in a library built here, from its code objects' metadata."""
+    import struct
+    import subprocess
+    import tempfile
+    blob, magic, out, at = open(path, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__", [], 0
+    with tempfile.TemporaryDirectory() as tmp:
+        names = []
+        while (at := blob.find(magic, at)) >= 0:
+            pos = at + 32
+            for _ in range(struct.unpack_from("<Q", blob, at + 24)[0]):   # entries: offset, size, length of the target's name, name
+                off, size, length = struct.unpack_from("<QQQ", blob, pos)
+                if b"gfx950" in blob[pos + 24:pos + 24 + length] and size:
+                    names.append(os.path.join(tmp, f"{len(names)}.elf"))
+                    with open(names[-1], "wb") as f:
+                        f.write(blob[at + off:at + off + size])
+                pos += 24 + length
+            at += len(magic)
+        notes = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", *names], check=True, capture_output=True, text=True).stdout
+    for block in notes.split("  - .agpr_count:")[1:]:
+        out.append((re.search(r"\.name: +(\S+)", block).group(1), int(re.search(r"\.private_segment_fixed_size: (\d+)", block).group(1))))
+    return out
+
+
+@pytest.fixture(scope="module")
+def device_kernels():
+    return _device_kernels(B.LIB_PATH)
+
+
+@pytest.mark.parametrize("kernel", ["ksplit_kernel"])
+def test_built_kernels_with_loads_in_flight_use_no_scratch(device_kernels, kernel):
+    """These kernels request operands a phase ahead and wait by count: a reload from scratch in between waits for all of them."""
+    from paper_2408_08554_amd import build as bld
+    mine = [(n, b) for n, b in device_kernels if kernel in n]
+    assert len(mine) >= 16 and [k for k in mine if k[1]] == []
+    assert kernel in bld.NO_SCRATCH.values()
