@@ -63,13 +63,12 @@ static hipError_t launch_p(int p, const DirectParams& gp, int MR, int R, bool ra
 // the compute unit some 50 clocks more: it pays from about forty full loads per compute unit, and always for rows off dword
 // boundaries.  Operand order / lane order, 260 sizes of M = 5..16, unpacked rows (packed): up to 16 loads 0.98 (1.00), 32: 0.98 (1.01),
 // 48: 1.01 (1.05), 64: 1.03 (1.06), 96: 1.06 (1.11), 192: 1.07 (1.18); off dword boundaries 1.02 to 1.2.
-static int direct_lane_order(int p, int M, const DirectPlan& pl, int tiles, const GemmArgs& g)
+static int direct_lane_order(int M, const DirectPlan& pl, int tiles, const GemmArgs& g)
 {
     if (pl.MR < 8) return 0;
     const int env = tuning_env("ABQ_LO");   // tuning builds: 1 operand order, 2 lane order
     if (env) return env - 1;
-    int slices = 16 / pl.MR;
-    if (p >= 5 && slices > 4) slices = 4;
+    const int slices = 16 / pl.MR;   // of 64 k that one load covers
     const long loads = (long)((8 * pl.R + slices - 1) / slices) * pl.S * ((tiles + num_cus() - 1) / num_cus());
     return loads * M > 40L * pl.MR || (g.a_raw && g.K % 4 != 0) ? 1 : 0;
 }
@@ -84,7 +83,7 @@ hipError_t launch_gemm_direct(const GemmArgs& g, const ActLayout& A, const Weigh
     gp.oa = g.q == 8 ? 128 : 0;
     gp.ow = g.p == 8 ? 128 : 0;
     gp.a_mask = ((1u << g.q) - 1u) * 0x01010101u;
-    gp.lane_order = direct_lane_order(g.p, g.M, pl, W.NT, g);
+    gp.lane_order = direct_lane_order(g.M, pl, W.NT, g);
     fill_problem(gp.d[0], g, A, W, pl.R);
     return launch_p(g.p, gp, pl.MR, pl.R, g.a_raw != nullptr, (unsigned)W.NT, pl.S, s);
 }
@@ -151,7 +150,7 @@ hipError_t launch_gemm_direct_grouped(int p, int q, int M, int count, const Gemm
         gp.count = n;
         for (int i = n; i < kDirectMaxGroup; ++i) { gp.d[i] = gp.d[0]; gp.first_tile[i] = tiles; }   // unused slots start at the end of the grid
         gp.first_tile[kDirectMaxGroup] = tiles;
-        gp.lane_order = direct_lane_order(p, M, pl, tiles, probs[lead]);
+        gp.lane_order = direct_lane_order(M, pl, tiles, probs[lead]);
         const hipError_t e = launch_p(p, gp, pl.MR, pl.R, probs[lead].a_raw != nullptr, (unsigned)tiles, pl.S, s);
         if (e != hipSuccess) return e;
         if (n == kDirectMaxGroup) --lead;   // more problems of this plan may be left: look again from the same place

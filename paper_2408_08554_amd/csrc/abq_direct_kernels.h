@@ -305,7 +305,7 @@ __global__ __launch_bounds__(1024) void direct_kernel(typename std::conditional<
     // (kernel times: W2A8 M=8 11008->4096 6.9 -> 6.45 us, packed rows 6.2 -> 5.8, W4A8 M=8 block 24.2 -> 22.8, W4A8 M=16 3001->1000 7.0 -> 5.3).
     static_assert(!LO || (MR >= 8 && !GQ), "few rows are few loads");
     v4i aq[NQ];
-    const int m_l = LO ? lane / (4 * SL) : r % MR, i_l = LO ? lane / 4 % SL : r / MR, g_l = LO ? lane & 3 : G;   // (i_l >= SL: an operand row that stays zero)
+    int m_l = LO ? lane / (4 * SL) : r % MR, i_l = LO ? lane / 4 % SL : r / MR, g_l = LO ? lane & 3 : G;   // (i_l >= SL: an operand row that stays zero)
 #pragma unroll
     for (int q = 0; q < NQ; ++q) {
         const int sl = i_l < SL ? q * SL + i_l : 8 * R;
@@ -343,6 +343,19 @@ __global__ __launch_bounds__(1024) void direct_kernel(typename std::conditional<
             for (int i = 0; i < b; ++i) w[rr][SH::load_base(gi) + i] = __builtin_nontemporal_load(base + i * 64);
         }
     }
+    // LO: to the operand's order.  Behind the masks below, which is sooner done; 8-bit weights on two super-chunks have no registers
+    // for both there (on scratch M=8 4096 ch, K=11008 took 12.0 us, operand order 11.1, this 10.65) and exchange the rows as they were loaded.
+    constexpr bool kExchangeFirst = LO && P == 8 && R == 2;
+    auto exchange = [&] {
+        static_assert(!LO || MR * SL == 16, "every lane's piece is in some operand row");
+        const int from = 4 * ((r % MR) * (4 * SL) + 4 * (r / MR) + G);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int d = 0; d < 4; ++d) aq[q][d] = __builtin_amdgcn_ds_bpermute(from, aq[q][d]);
+        m_l = r % MR; i_l = r / MR; g_l = G;
+    };
+    if constexpr (kExchangeFirst) exchange();
     if constexpr (RAW) {
         // unpacked codes -> operand bytes: bits above q dropped (as the packers drop them), less oa; positions that were
         // not loaded (rows past M, k past K) become -oa here and are cleared again
@@ -366,16 +379,7 @@ __global__ __launch_bounds__(1024) void direct_kernel(typename std::conditional<
         }
     }
 
-    if constexpr (LO) {   // to the operand's order
-        const int from = 4 * ((r % MR) * (4 * SL) + 4 * (r / MR) + G);
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-#pragma unroll
-            for (int d = 0; d < 4; ++d) {
-                const int v = __builtin_amdgcn_ds_bpermute(from, aq[q][d]);
-                aq[q][d] = MR * SL == 16 || r / MR < SL ? v : 0;
-            }
-    }
+    if constexpr (LO && !kExchangeFirst) exchange();
 
     if constexpr (GQ) {
         // R = 1: operand rows 8..15 (no slice lives there) become rows of ones

@@ -99,3 +99,13 @@ def check_g128(c, sh, zg, y):
     assert np.all(err <= tol), f"{c.name}: g128 output off by {np.max(err / tol):.3g} x bound"
     assert np.all(err <= y_tolerance(yref) + (c.K // 128 + 13) * 2.0 ** -24 * mag), f"{c.name}: outside the stated fp16 tolerance"
     return yref
+
+
+def kernel_names(torch, fn):
+    """Names of the kernels that a call launches, in order."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        fn()
+        torch.cuda.synchronize()
+    return [e.name for e in prof.events() if "abq::" in e.name]

@@ -490,9 +490,9 @@ def device_kernels():
     return _device_kernels(B.LIB_PATH)
 
 
-@pytest.mark.parametrize("kernel", ["ksplit_kernel"])
+@pytest.mark.parametrize("kernel", ["ksplit_kernel", "direct_kernel"])
 def test_built_kernels_with_loads_in_flight_use_no_scratch(device_kernels, kernel):
-    """These kernels request operands a phase ahead and wait by count: a reload from scratch in between waits for all of them."""
+    """These kernels request operands ahead and wait by count: a reload from scratch in between waits for all of them."""
     from paper_2408_08554_amd import build as bld
     mine = [(n, b) for n, b in device_kernels if kernel in n]
     assert len(mine) >= 16 and [k for k in mine if k[1]] == []

@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 from paper_2408_08554_amd import synth
-from helpers import check_against_oracle, check_g128, check_sampled, gpu_gemm, gpu_gemm_fused, to_dev
+from helpers import check_against_oracle, check_g128, check_sampled, gpu_gemm, gpu_gemm_fused, kernel_names, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -142,13 +142,7 @@ def test_kernel_of_ragged_rows(abq, p, M, N, K, one_kernel):
 
 
 def _kernels(fn):
-    """Names of the kernels that a call launches."""
-    from torch.profiler import ProfilerActivity, profile
-    torch.cuda.synchronize()
-    with profile(activities=[ProfilerActivity.CUDA]) as prof:
-        fn()
-        torch.cuda.synchronize()
-    return [e.name for e in prof.events() if "abq::" in e.name]
+    return kernel_names(torch, fn)
 
 
 @pytest.mark.parametrize("K", [4090, 4096])
@@ -275,3 +269,17 @@ def test_decode_rows_in_lane_order(abq, p, q, M, N, K):
     print(c.name, flush=True)
     for y, acc in (gpu_gemm_fused(torch, abq, c, FIELDS), gpu_gemm(torch, abq, c, FIELDS, FIELDS)):
         (check_against_oracle if M * N * K < 2e8 else check_sampled)(c, y, acc)
+
+
+@pytest.mark.parametrize("M,K", [(5, 9225), (5, 12288), (8, 8712), (8, 8720)])
+def test_lane_order_with_two_super_chunks_of_8_bit_weights(abq, M, K):
+    """The variant with the fewest registers to spare, which exchanges the lanes ahead of the masks: rows of whole vectors, of dwords and
+    off dwords, with codes past q bits that the masks have to drop."""
+    p, q, N = 8, 7, 70
+    c = synth.make_case(p, q, M, N, K, seed=5950 + M, name=f"W{p}A{q} {M}x{N}x{K}")
+    print(c.name, flush=True)
+    pw = abq.abq_pack_weights(p, to_dev(torch, c.W), to_dev(torch, c.w_scale), to_dev(torch, c.w_zero))
+    a, out = (to_dev(torch, c.A | 0x80), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero)), []
+    names = _kernels(lambda: out.extend(abq.abq_gemm_act_codes(p, q, M, N, K, *a, pw, FIELDS, want_acc=True)))
+    assert len(names) == 1 and "direct_kernel<8, 8, 2, true, true" in names[0], names
+    check_against_oracle(c, out[0].cpu().numpy(), out[1].cpu().numpy())
