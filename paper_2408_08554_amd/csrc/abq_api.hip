@@ -356,7 +356,7 @@ static const int kSkinnyMaxM = 16;   // one MFMA tile of activation rows: the st
 // Streaming kernel or tiled kernel (both on field-packed operands).  Few output tiles and M <= 64:
 // the tiled kernel would occupy a fraction of the chip with long K loops; the streaming kernel
 // splits K over waves instead (one pass over W per 16 rows of A).
-static bool streaming_shape(int M, int N)
+bool streaming_shape(int M, int N)
 {
     if (M <= kSkinnyMaxM) return true;
     const int env_m = tuning_env("ABQ_STREAM_MAX_M"), env_wgs = tuning_env("ABQ_STREAM_MAX_WGS");

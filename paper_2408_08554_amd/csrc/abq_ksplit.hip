@@ -19,7 +19,8 @@ static const KsShapeInfo kShapes[4] = {{2, 1}, {2, 2}, {4, 2}, {4, 4}};   // (as
 //     unpacked, behind a pack launch, 1.07 to 1.15) and below K = 2048 at p = 7, 8 (above 1.2 and more); on 64 x 32 it is even below
 //     K = 1024 for packed rows (0.94 to 1.08; unpacked 1.5);
 //   up to 48 rows, per-channel, K >= 3072: the streaming kernel splits K as well, over tiles of 16 rows (1536 ch x 10400, M = 25: 11.2 /
-//     9.3; 512 ch x 5712, M = 44: 8.2 / 7.5); with unpacked rows of a K that is no multiple of 16 it needs a pack launch and loses.
+//     9.3; 512 ch x 5712, M = 44: 8.2 / 7.5).  With unpacked rows of a K that is no multiple of 16 it needs a pack launch and loses, and
+//     above 8128 channels the prefill kernel would run in its place (8192 ch x 8192, M = 32: W5A8 12.9 / 21.4, W8A8 15.6 / 21.1).
 static int shape_by_rule(const GemmArgs& g, const WeightLayout& W)
 {
     int shape = 0;
@@ -30,7 +31,7 @@ static int shape_by_rule(const GemmArgs& g, const WeightLayout& W)
     const bool raw = g.a_raw != nullptr;
     if (W.g128) return shape == 3 && (g.p <= 6 || g.K < 2048) ? -1 : shape;
     if (shape == 3 && g.K < (raw && (g.M <= 64 || g.p == 8) ? 4608 : 3072)) return -1;
-    if (shape <= 1 && g.M <= 48 && g.K >= 3072 && (shape == 0 || g.p >= 5) && !(raw && g.K % 16 != 0)) return -1;
+    if (shape <= 1 && g.M <= 48 && g.K >= 3072 && (shape == 0 || g.p >= 5) && !(raw && g.K % 16 != 0) && streaming_shape(g.M, g.N)) return -1;
     return shape;
 }
 

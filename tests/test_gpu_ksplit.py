@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 from paper_2408_08554_amd import synth
-from helpers import check_against_oracle, check_g128, check_sampled, to_dev
+from helpers import check_against_oracle, check_g128, check_sampled, kernel_names, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -90,3 +90,20 @@ def test_ksplit_codes_past_q_bits_and_requant(abq, p, q, M, N, K):
     codes0, y0 = other_kernel(abq, c, run)[:2]
     assert torch.equal(codes, codes0) and torch.equal(y.view(torch.int16), y0.view(torch.int16)) and torch.equal(static.view(torch.int16), y0.view(torch.int16))
     check_against_oracle(c, y.cpu().numpy(), None)
+
+
+@pytest.mark.parametrize("raw", [False, True], ids=["packed", "codes"])
+@pytest.mark.parametrize("N,kernel", [(8128, "skinny_kernel"), (8129, "ksplit_kernel"), (8192, "ksplit_kernel")])
+def test_streaming_kernel_is_left_the_rows_that_it_takes(abq, N, kernel, raw):
+    """32 x 32 tiles of wide weights and long K are left to the streaming kernel; where it does not run (above 8128 channels) the prefill
+    kernel would take them at up to twice the time."""
+    p, q, M, K = 6, 8, 32, 3072
+    c = synth.make_case(p, q, M, N, K, seed=7300, name=f"ksplit or streaming W{p}A{q} {M}x{N}x{K}")
+    print(c.name, raw, flush=True)
+    a, sa, za = to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero)
+    pw = abq.abq_pack_weights(p, to_dev(torch, c.W), to_dev(torch, c.w_scale), to_dev(torch, c.w_zero))
+    pa, out = abq.abq_pack_act_codes(q, a, sa, za), []
+    names = kernel_names(torch, lambda: out.extend(abq.abq_gemm_act_codes(p, q, M, N, K, a, sa, za, pw, FIELDS, want_acc=True) if raw
+                                                   else abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, FIELDS, want_acc=True)))
+    assert len(names) == 1 and kernel in names[0], names
+    check_sampled(c, out[0].cpu().numpy(), out[1].cpu().numpy())
