@@ -149,6 +149,20 @@ static int check_bits_shape(int bits, int R, int K)
     return ABQ_OK;
 }
 
+static const int kSkinnyMaxM = 16;   // one MFMA tile of activation rows: the streaming kernel; above it the tiled kernel
+
+// Streaming kernel or tiled kernel (both on field-packed operands).  Few output tiles and M <= 64:
+// the tiled kernel would occupy a fraction of the chip with long K loops; the streaming kernel
+// splits K over waves instead (one pass over W per 16 rows of A).
+bool streaming_shape(int M, int N)
+{
+    if (M <= kSkinnyMaxM) return true;
+    const int env_m = tuning_env("ABQ_STREAM_MAX_M"), env_wgs = tuning_env("ABQ_STREAM_MAX_WGS");
+    const int max_m = env_m > 0 ? env_m : 64, max_wgs = env_wgs > 0 ? env_wgs : 128;
+    const long tiled_wgs = (long)((M + 63) / 64) * ((N + 63) / 64);
+    return M <= max_m && tiled_wgs < max_wgs;
+}
+
 }  // namespace abq
 
 using namespace abq;
@@ -349,20 +363,6 @@ static bool choose_fields(bool can_fields, bool can_planes, int force, int p, in
     if (force == ABQ_USE_PLANES) return false;
     if (force == ABQ_USE_FIELDS) return true;
     return can_fields;
-}
-
-static const int kSkinnyMaxM = 16;   // one MFMA tile of activation rows: the streaming kernel; above it the tiled kernel
-
-// Streaming kernel or tiled kernel (both on field-packed operands).  Few output tiles and M <= 64:
-// the tiled kernel would occupy a fraction of the chip with long K loops; the streaming kernel
-// splits K over waves instead (one pass over W per 16 rows of A).
-bool streaming_shape(int M, int N)
-{
-    if (M <= kSkinnyMaxM) return true;
-    const int env_m = tuning_env("ABQ_STREAM_MAX_M"), env_wgs = tuning_env("ABQ_STREAM_MAX_WGS");
-    const int max_m = env_m > 0 ? env_m : 64, max_wgs = env_wgs > 0 ? env_wgs : 128;
-    const long tiled_wgs = (long)((M + 63) / 64) * ((N + 63) / 64);
-    return M <= max_m && tiled_wgs < max_wgs;
 }
 
 // The two decode kernels (both on field-packed operands, M <= 16).  The direct kernel (A operand loaded straight into
