@@ -6,14 +6,27 @@ namespace abq {
 struct KsShapeInfo { int rt, ct; };
 static const KsShapeInfo kShapes[4] = {{2, 1}, {2, 2}, {4, 2}, {4, 4}};   // (as in ks_launch_p)
 
+// Unpacked rows on 64 x 64 tiles: the rows of A up to which they are packed first.  Masks, row sums and pieces of rows off 128-byte lines cost
+// every tile a share of its own time, the pack launch some 2 us and the bytes of A once, and the more rows, the fewer tiles read each.
+// This kernel alone / the pack launch and this kernel on packed rows, 1370 sizes of K >= 3072:
+//   rows              17..64  65..128  ..192  ..256  ..384  ..512  ..1000
+//   whole lines, p < 7  1.03    1.05    1.03   1.01   0.97   0.93   0.89;   p = 7, 8  0.98  0.97  0.99  0.95  0.96  0.90  0.85
+//   dwords, p < 7       1.10    1.08    1.06   1.04   1.01   0.97   0.92;   p = 7, 8  1.05  1.05  1.04  1.02  0.99  0.96  0.92
+//   others, p < 7       1.20    1.17    1.15   1.10   1.05   1.00   0.96;   p = 7, 8  1.13  1.10  1.08  1.10  0.94  -     0.95
+static int packed_up_to(int p, int K)
+{
+    if (K % 128 == 0) return p >= 7 ? 0 : 256;
+    return (K % 4 == 0 ? 384 : 512) - (p >= 7 ? 128 : 0);
+}
+
 // Shape: the smallest workgroup tile of which no compute unit gets more than one.  A workgroup's time goes with the operand bytes it
 // pulls (about 30 bytes a clock per compute unit), and a second round of workgroups costs what the first did.  Against the other
 // kernels (tiled, streaming; 957 sizes of M = 17..2048, N = 256..13824, K = 512..13824, all widths, packed and unpacked rows, per-channel
 // and per-group weights, timed in replays) the choice below is 1.41 times as fast on average, 2.4 % from the best of all kernels and
 // shapes at each size, and at most 7 % behind the others.  Where the lines lie (this kernel / the others, us):
-//   64 x 64, per-channel: the tiled kernel has overtaken while K is short (packed rows K < 1600 1.11 times, K = 3072..6144 0.92; unpacked
-//     rows, at most 64 of them, which the streaming kernel may take without a pack launch, up to K = 4608: 12880 ch x 3296,
-//     M = 38: 14.9 / 13.8, as does p = 8: 2672 ch x 3088, M = 199: 16.1 / 14.6);
+//   64 x 64, per-channel: the tiled kernel has overtaken while K is short (packed rows K < 1600 1.11 times, K = 3072..6144 0.92), up to
+//     64 rows of p = 8 until K = 4608 (12880 ch x 3296, M = 38, with the pack launch in front of both: 16.9 / 15.9);
+//   64 x 64, unpacked rows: see packed_up_to;
 //   per-group: one answer for packed and unpacked rows, because the order of the binary32 sums goes with the kernel and a call on codes
 //     returns the bits of packing and multiplying.  On 64 x 64 the tiled per-group kernel wins at p <= 6 (packed rows 0.75 to 0.94 times;
 //     unpacked, behind a pack launch, 1.07 to 1.15) and below K = 2048 at p = 7, 8 (above 1.2 and more); on 64 x 32 it is even below
@@ -30,7 +43,8 @@ static int shape_by_rule(const GemmArgs& g, const WeightLayout& W)
     }
     const bool raw = g.a_raw != nullptr;
     if (W.g128) return shape == 3 && (g.p <= 6 || g.K < 2048) ? -1 : shape;
-    if (shape == 3 && g.K < (raw && (g.M <= 64 || g.p == 8) ? 4608 : 3072)) return -1;
+    if (shape == 3 && g.K < (g.p == 8 && g.M <= 64 ? 4608 : 3072)) return -1;
+    if (shape == 3 && raw && g.M <= packed_up_to(g.p, g.K)) return -1;   // (packed first, and asked again)
     if (shape <= 1 && g.M <= 48 && g.K >= 3072 && (shape == 0 || g.p >= 5) && !(raw && g.K % 16 != 0) && streaming_shape(g.M, g.N)) return -1;
     return shape;
 }

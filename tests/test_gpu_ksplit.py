@@ -107,3 +107,25 @@ def test_streaming_kernel_is_left_the_rows_that_it_takes(abq, N, kernel, raw):
                                                    else abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, FIELDS, want_acc=True)))
     assert len(names) == 1 and kernel in names[0], names
     check_sampled(c, out[0].cpu().numpy(), out[1].cpu().numpy())
+
+
+KS44 = "ksplit_kernel<%d, abq::KsShape<4, 4"
+
+
+@pytest.mark.parametrize("p,M,N,K,kernels", [(4, 57, 11008, 5120, ["act_code", KS44 % 4]), (2, 38, 12880, 3296, ["act_code", KS44 % 2]),
+                                             (8, 38, 12880, 3296, ["act_code", "tiled_kernel"]), (8, 57, 11008, 4620, ["act_code", KS44 % 8]),
+                                             (8, 199, 2672, 3072, [KS44 % 8]), (3, 199, 4000, 3076, ["act_code", KS44 % 3]),
+                                             (3, 400, 2000, 3076, [KS44 % 3]), (3, 400, 2000, 3075, ["act_code", KS44 % 3]), (3, 520, 1600, 3075, [KS44 % 3])])
+def test_codes_on_64x64_tiles(abq, p, M, N, K, kernels):
+    """Where codes go as they are and where they are packed first, and that the result is the same bits."""
+    q = 8 if p < 8 else 7
+    c = synth.make_case(p, q, M, N, K, seed=7400 + p, name=f"codes on 64 x 64 W{p}A{q} {M}x{N}x{K}")
+    print(c.name, flush=True)
+    a, sa, za = to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero)
+    pw = abq.abq_pack_weights(p, to_dev(torch, c.W), to_dev(torch, c.w_scale), to_dev(torch, c.w_zero))
+    pa, out = abq.abq_pack_act_codes(q, a, sa, za), []
+    names = kernel_names(torch, lambda: out.extend(abq.abq_gemm_act_codes(p, q, M, N, K, a, sa, za, pw, FIELDS, want_acc=True)))
+    assert len(names) == len(kernels) and all(k in n for k, n in zip(kernels, names)), names
+    y0, acc0 = other_kernel(abq, c, lambda: abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, FIELDS, want_acc=True))
+    assert torch.equal(out[1], acc0) and torch.equal(out[0].view(torch.int16), y0.view(torch.int16))
+    check_sampled(c, y0.cpu().numpy(), acc0.cpu().numpy())
