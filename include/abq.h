@@ -295,9 +295,11 @@ int abq_f4_gemm(int p, int q, int M, int N, int K, const void* packed_act, const
  * set of kernel configurations found by timing them).  The library chooses every launch plan from closed-form
  * rules; this table lets a tuner (paper_2408_08554_amd/tune.py times the candidates on the device) replace the
  * rule for exact problem sizes.  A field left 0 keeps the rule for that knob; a plan that does not fit the
- * problem (say, more waves than K has 512-blocks) is ignored and the rule applies.  Results never depend on
- * the plan (per-group weight scales: to their stated bound).  Process-wide, thread-safe; entries hold no
- * device state.
+ * problem (say, more waves than K has 512-blocks) is ignored and the rule applies.  Above 16 rows the rule may
+ * choose a kernel without knobs; a plan takes a problem from it by a K split of the decode kernel where that
+ * kernel is the other choice (M <= 64, few output tiles), else by tiled_mt or tiled_ntw, and never on per-group
+ * blobs.  Results never depend on the plan (per-group weight scales: to their stated bound).  Process-wide,
+ * thread-safe; entries hold no device state.
  *   skinny_waves    waves per workgroup of the decode kernel = K split of a tile: 1, 2, 4..8
  *   skinny_kgroups  K groups of the decode kernel: 1..4
  *   tiled_mt        rows of A per workgroup tile of the prefill kernel / 16: 4 or 8

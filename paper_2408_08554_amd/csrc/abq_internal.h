@@ -130,6 +130,7 @@ struct GemmArgs {
     Requant rq = Requant{nullptr, nullptr, nullptr, 0};
 };
 bool streaming_shape(int M, int N);   // whether the streaming kernel, not the prefill kernel, is the other choice beside the K-split kernel
+bool skinny_entry_fits(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, const PlanOverride& ov);   // whether a table entry names a K split that the problem has
 hipError_t launch_gemm_skinny(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, hipStream_t s);
 bool gemm_grouped_fits(int M, int count, const GemmArgs* probs, const ActLayout* A, const WeightLayout* W, int* waves,
                        size_t* lds_bytes);

@@ -56,9 +56,10 @@ bool ksplit_plan(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, i
     // (unpacked rows: any length of at least one 16-byte load; per-group weights, of whole ones)
     if (g.a_raw ? g.K < 16 || (W.g128 && g.K % 16 != 0) : !A.has_fields) return false;
     if (W.g128 && (g.acc || g.rq.codes)) return false;
-    PlanOverride ov;   // an entry for one of the other kernels is followed
-    lookup_plan(g.p, g.q, g.M, g.N, g.K, &ov);
-    if (ov.skinny_waves || ov.skinny_kgroups || ov.tiled_mt || ov.tiled_ntw || ov.tiled_wd || ov.tiled_band) return false;
+    // A plan-table entry is followed where it asks for a shape of the kernel that runs instead (per-channel only: the key does not tell
+    // the kinds of blobs apart, and the per-group kernels above 16 rows have no knobs).
+    PlanOverride ov;
+    if (!W.g128 && lookup_plan(g.p, g.q, g.M, g.N, g.K, &ov) && (streaming_shape(g.M, g.N) ? skinny_entry_fits(g, A, W, ov) : ov.tiled_mt > 0 || ov.tiled_ntw > 0)) return false;
     const int env = tuning_env("ABQ_KS");   // tuning builds: -1 off, 1..4 a shape
     *shape = env < 0 ? -1 : (env >= 1 && env <= 4 && (!W.g128 || ks_has_gq(g.p, kShapes[env - 1].rt * kShapes[env - 1].ct)) ? env - 1 : shape_by_rule(g, W));
     return *shape >= 0;

@@ -200,6 +200,14 @@ static void fill_operands(SkinnyParams& prm, const GemmArgs& g, const ActLayout&
     prm.ntiles = W.NT;
 }
 
+bool skinny_entry_fits(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, const PlanOverride& ov)
+{
+    SkinnyPlan pl;
+    return (ov.skinny_waves > 0 || ov.skinny_kgroups > 0) &&
+           pick_plan(g.M, A.Kp, W.NT, num_cus(), 0, W.g128, ov.skinny_waves, ov.skinny_kgroups, &pl) &&
+           (ov.skinny_waves == 0 || pl.waves == ov.skinny_waves) && (ov.skinny_kgroups == 0 || pl.kgroups == ov.skinny_kgroups);
+}
+
 hipError_t launch_gemm_skinny(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, hipStream_t s)
 {
     SkinnyParams prm;
