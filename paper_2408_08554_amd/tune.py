@@ -8,7 +8,8 @@ and reports them fastest first.  `--save` merges the winner into a JSON file whe
 by more than `--min-gain`; `load_plans(path)` installs such a file into the running process.
 
 Timing: a HIP-graph replay over rotating weight blobs (>= 1 GiB in total).  The timed
-call is abq_gemm_act_codes where that is one kernel, abq_gemm on packed activations elsewhere.
+call is abq_gemm_act_codes, with the pack launch in front where the plan's kernel needs one: above 16 rows
+the rule may choose a kernel that reads codes as they are, which a plan then gives up.
 """
 import argparse
 import itertools
@@ -31,7 +32,8 @@ def candidates(p, q, M, N, K):
         for r in (1, 2, 4):
             if -(-nsuper // r) <= 16:
                 out.append({"direct_r": r})
-    if M <= 64:     # the streaming decode kernel (M <= 16 always; up to 64 when there are few output tiles)
+    streams = M <= 16 or (M <= 64 and -(-N // 64) < 128)   # the streaming decode kernel (above 16 rows: few output tiles)
+    if streams:
         direct_off = {"direct_r": -1} if M <= 16 else {}
         if direct_off:
             out.append(dict(direct_off))
@@ -42,7 +44,7 @@ def candidates(p, q, M, N, K):
         if M > 8 and K >= 8192:
             for w, g in itertools.product((4, 6, 8), (2, 3, 4)):
                 out.append({"skinny_waves": w, "skinny_kgroups": g, **direct_off})
-    if M > 16:      # prefill kernel
+    else:           # prefill kernel
         bands = sorted({b for b in (2, 4, 8, 16) if b <= max(2, -(-M // 64))})
         for mt, ntw in itertools.product((4, 8), (1, 2, 4)):
             for wd in ((2, 4) if mt == 4 and ntw <= 2 else (2,)):
@@ -73,18 +75,14 @@ class Problem:
         self.blobs = [self.pool[i * stride:i * stride + nb] for i in range(R)]
         for b in self.blobs:
             b.copy_(blob0)
-        self.pa = abq.abq_pack_act_codes(q, self.A, self.a_s, self.az, self.layout)
-        self.fused = abq.abq_gemm_act_codes_workspace_bytes(p, q, M, N, K, self.layout) == 0
+        self.workspace = torch.empty(max(16, abq.abq_gemm_act_codes_workspace_bytes(p, q, M, N, K, self.layout)), dtype=torch.uint8, device="cuda")
         self.y = torch.empty((M, N), dtype=torch.float16, device="cuda")
         self.acc = torch.empty((M, N), dtype=torch.int32, device="cuda")
 
     def call(self, i, acc=None):
         p, q, M, N, K = self.shape
         blob = self.blobs[i % len(self.blobs)]
-        if self.fused:
-            abq.abq_gemm_act_codes(p, q, M, N, K, self.A, self.a_s, self.az, blob, self.layout, y=self.y, acc=acc)
-        else:
-            abq.abq_gemm(p, q, M, N, K, self.pa, self.layout, blob, self.layout, y=self.y, acc=acc)
+        abq.abq_gemm_act_codes(p, q, M, N, K, self.A, self.a_s, self.az, blob, self.layout, y=self.y, acc=acc, workspace=self.workspace)
 
     def result(self):
         """(y bits, acc) of one call under the plan currently set."""

@@ -359,6 +359,10 @@ def test_tuner_candidate_plans_are_valid_plan_table_entries():
             B.abq_plan_set(*shape, **plan) if plan else B.abq_plan_set(*shape)
             assert {k: v for k, v in B.abq_plan_get(*shape).items() if v} == plan
     B.abq_plan_clear()
+    # above 16 rows the knobs of the one kernel that would run: few output tiles up to 64 rows the streaming kernel, else the prefill kernel
+    for N, M, knob in [(8128, 64, "skinny_"), (8129, 64, "tiled_"), (100, 65, "tiled_"), (100, 17, "skinny_")]:
+        plans = tune.candidates(4, 8, M, N, 4096)[1:]
+        assert plans and all(k.startswith(knob) for plan in plans for k in plan)
 
 
 def test_shipped_plan_table_is_well_formed():

@@ -7,7 +7,7 @@ import pytest
 
 import oracle
 from paper_2408_08554_amd import synth
-from helpers import check_against_oracle, check_g128, check_sampled, gpu_gemm, gpu_gemm_fused, to_dev
+from helpers import check_against_oracle, check_g128, check_sampled, gpu_gemm, gpu_gemm_fused, kernel_names, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -741,6 +741,19 @@ def test_tuner_search_reports_the_rule_and_restores_the_table(abq):
     assert rows == sorted(rows, key=lambda r: r[0])
     assert abq.abq_plan_get(4, 8, 1, 512, 2048)["skinny_waves"] == 2
     abq.abq_plan_clear()
+
+
+def test_tuner_times_the_call_on_codes(abq):
+    """What a plan costs a program that has codes: with the pack launch that a prefill tile brings back, without it under the rule."""
+    from paper_2408_08554_amd import tune
+    shape = (4, 8, 128, 600, 2048)
+    problem = tune.Problem(*shape, rotate_bytes=1 << 22, launches=4)
+    try:
+        assert [("ksplit" in n) for n in kernel_names(torch, lambda: problem.call(0))] == [True]
+        abq.abq_plan_set(*shape, tiled_mt=4, tiled_ntw=1)
+        assert [("tiled_kernel" in n) for n in kernel_names(torch, lambda: problem.call(0))] == [False, True]
+    finally:
+        abq.abq_plan_clear()
 
 
 # ---- per-group weight scales and zero-points, groups of 128 along K (Appendix C) -------------------------
