@@ -1,5 +1,7 @@
 """Shared pieces of the GPU parity tests: run one synthetic case through the C ABI and compare
 with the CPU oracle (int32 accumulator bit-exact, fp16 output within the stated tolerance)."""
+import ctypes
+
 import numpy as np
 
 import oracle
@@ -101,11 +103,47 @@ def check_g128(c, sh, zg, y):
     return yref
 
 
-def kernel_names(torch, fn):
-    """Names of the kernels that a call launches, in order."""
-    from torch.profiler import ProfilerActivity, profile
+def kernel_names(torch, call):
+    """Names of the library's kernels that a call launches, in order: the kernel nodes of the call as captured, never replayed."""
+    hip, cxx = ctypes.CDLL("libamdhip64.so"), ctypes.CDLL("libstdc++.so.6")
+    hip.hipKernelNameRefByPtr.restype = ctypes.c_char_p
+    cxx.__cxa_demangle.restype = ctypes.c_char_p
+    dim3 = ctypes.c_uint32 * 3
+
+    class NodeParams(ctypes.Structure):   # hipKernelNodeParams
+        _fields_ = [("block", dim3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p), ("grid", dim3), ("args", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+
     torch.cuda.synchronize()
-    with profile(activities=[ProfilerActivity.CUDA]) as prof:
-        fn()
-        torch.cuda.synchronize()
-    return [e.name for e in prof.events() if "abq::" in e.name]
+    graph, stream = torch.cuda.CUDAGraph(keep_graph=True), torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        graph.capture_begin()
+        try:
+            keep = call()
+        finally:
+            graph.capture_end()
+    raw, count, names = ctypes.c_void_p(graph.raw_cuda_graph()), ctypes.c_size_t(0), []
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(count)) == 0
+    nodes = (ctypes.c_void_p * count.value)()
+    assert hip.hipGraphGetNodes(raw, nodes, ctypes.byref(count)) == 0
+    for node in nodes:
+        kind, params = ctypes.c_int(-1), NodeParams()
+        assert hip.hipGraphNodeGetType(ctypes.c_void_p(node), ctypes.byref(kind)) == 0
+        if kind.value == 0:   # a kernel
+            assert hip.hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(params)) == 0
+            name = hip.hipKernelNameRefByPtr(ctypes.c_void_p(params.func), None)
+            names.append((cxx.__cxa_demangle(name, None, None, None) or name).decode())
+    del keep
+    return [n for n in names if "abq::" in n]
+
+
+def run_named(torch, call):
+    """What the call returns, and the kernels that it launches."""
+    return call(), kernel_names(torch, call)
+
+
+def gpu_gemm_named(torch, abq, c, want_acc=True):
+    """gpu_gemm on field-packed operands, and the kernels of the matmul alone."""
+    pw = abq.abq_pack_weights(c.p, to_dev(torch, c.W), to_dev(torch, c.w_scale), to_dev(torch, c.w_zero))
+    pa = abq.abq_pack_act_codes(c.q, to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero), abq.ABQ_LAYOUT_FIELDS)
+    (y, acc), names = run_named(torch, lambda: abq.abq_gemm(c.p, c.q, c.M, c.N, c.K, pa, abq.ABQ_LAYOUT_FIELDS, pw, abq.ABQ_LAYOUT_FIELDS, want_acc=want_acc))
+    return y.cpu().numpy(), (acc.cpu().numpy() if acc is not None else None), names

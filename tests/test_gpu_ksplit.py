@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 from paper_2408_08554_amd import synth
-from helpers import check_against_oracle, check_g128, check_sampled, kernel_names, to_dev
+from helpers import check_against_oracle, check_g128, check_sampled, run_named, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -29,12 +29,6 @@ def other_kernel(abq, c, call):
         abq.abq_plan_set(c.p, c.q, c.M, c.N, c.K)
 
 
-def run_named(call):
-    """What the call returns, and the kernels that it launched."""
-    out = []
-    return out, kernel_names(torch, lambda: out.extend(call()))
-
-
 # K: one load, off a 16-byte boundary, one phase of 256 past and short of whole super-chunks, waves with one to five phases
 @pytest.mark.parametrize("K", [16, 255, 700, 2053, 3072, 3077, 4096, 4620])
 @pytest.mark.parametrize("shape", list(SHAPES))
@@ -53,10 +47,10 @@ def test_ksplit_equals_the_other_kernels(abq, p, q, shape, K):
         pa = abq.abq_pack_act_codes(q, a, sa, za)
         calls = [lambda acc: abq.abq_gemm_act_codes(p, q, M, N, K, a, sa, za, pw, FIELDS, want_acc=acc),
                  lambda acc: abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, FIELDS, want_acc=acc)]
-        (y0, acc0), names = run_named(lambda: other_kernel(abq, c, lambda: calls[1](True)))
+        (y0, acc0), names = run_named(torch, lambda: other_kernel(abq, c, lambda: calls[1](True)))
         assert len(names) == 1 and ("tiled_kernel" in names[0] or "skinny_kernel" in names[0]), names
         for call in calls:
-            (y, acc), names = run_named(lambda: call(True))
+            (y, acc), names = run_named(torch, lambda: call(True))
             y2, _ = call(False)
             assert f"ksplit_kernel<{p}, abq::{KERNEL[shape]}" in names[-1] and (len(names) == 1 or call is calls[0]), names
             unpacked += call is calls[0] and len(names) == 1
@@ -86,7 +80,7 @@ def test_ksplit_per_group_weights(abq, p, q, shape, K):
     calls = [lambda: abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, G128)[:1], lambda: abq.abq_gemm_act_codes(p, q, M, N, K, a, sa, za, pw, G128)[:1]]
     ys = []
     for call in calls:
-        out, names = run_named(call)
+        out, names = run_named(torch, call)
         assert f"ksplit_kernel<{p}, abq::{KERNEL[shape]}" in names[-1] and len(names) == 1 + (call is calls[1] and K % 16 != 0), names
         ys.append(out[0].cpu().numpy())
     assert np.array_equal(ys[0].view(np.uint16), ys[1].view(np.uint16))   # packed and unpacked rows: one order of sums
@@ -94,7 +88,7 @@ def test_ksplit_per_group_weights(abq, p, q, shape, K):
     M2 = max(M, 64 * (256 // ((N + 63) // 64) + 1))
     rows = torch.arange(M2, device="cuda") % M
     pa2 = abq.abq_pack_act_codes(q, a[rows].contiguous(), sa[rows].contiguous(), za[rows].contiguous())
-    out, names = run_named(lambda: abq.abq_gemm(p, q, M2, N, K, pa2, FIELDS, pw, G128)[:1])
+    out, names = run_named(torch, lambda: abq.abq_gemm(p, q, M2, N, K, pa2, FIELDS, pw, G128)[:1])
     assert len(names) == 1 and "tiled_g128_kernel" in names[0], names
     ys.append(out[0][:M].cpu().numpy())
     for y in ys[1:] if M * N * K < 5e8 else ys[1:2]:
@@ -130,9 +124,9 @@ def test_streaming_kernel_is_left_the_rows_that_it_takes(abq, N, kernel, raw):
     print(c.name, raw, flush=True)
     a, sa, za = to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero)
     pw = abq.abq_pack_weights(p, to_dev(torch, c.W), to_dev(torch, c.w_scale), to_dev(torch, c.w_zero))
-    pa, out = abq.abq_pack_act_codes(q, a, sa, za), []
-    names = kernel_names(torch, lambda: out.extend(abq.abq_gemm_act_codes(p, q, M, N, K, a, sa, za, pw, FIELDS, want_acc=True) if raw
-                                                   else abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, FIELDS, want_acc=True)))
+    pa = abq.abq_pack_act_codes(q, a, sa, za)
+    out, names = run_named(torch, lambda: abq.abq_gemm_act_codes(p, q, M, N, K, a, sa, za, pw, FIELDS, want_acc=True) if raw
+                           else abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, FIELDS, want_acc=True))
     assert len(names) == 1 and kernel in names[0], names
     check_sampled(c, out[0].cpu().numpy(), out[1].cpu().numpy())
 
@@ -151,8 +145,8 @@ def test_codes_on_64x64_tiles(abq, p, M, N, K, kernels):
     print(c.name, flush=True)
     a, sa, za = to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero)
     pw = abq.abq_pack_weights(p, to_dev(torch, c.W), to_dev(torch, c.w_scale), to_dev(torch, c.w_zero))
-    pa, out = abq.abq_pack_act_codes(q, a, sa, za), []
-    names = kernel_names(torch, lambda: out.extend(abq.abq_gemm_act_codes(p, q, M, N, K, a, sa, za, pw, FIELDS, want_acc=True)))
+    pa = abq.abq_pack_act_codes(q, a, sa, za)
+    out, names = run_named(torch, lambda: abq.abq_gemm_act_codes(p, q, M, N, K, a, sa, za, pw, FIELDS, want_acc=True))
     assert len(names) == len(kernels) and all(k in n for k, n in zip(kernels, names)), names
     y0, acc0 = other_kernel(abq, c, lambda: abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, FIELDS, want_acc=True))
     assert torch.equal(out[1], acc0) and torch.equal(out[0].view(torch.int16), y0.view(torch.int16))
@@ -184,9 +178,8 @@ def test_plan_entries_that_do_not_apply_leave_the_rules_kernel(abq, M, plan, ker
     try:
         abq.abq_plan_set(p, q, M, N, K, **plan)
         for call, y in zip(calls, y0):
-            out = []
-            names = kernel_names(torch, lambda: out.append(call()))
+            out, names = run_named(torch, call)
             assert kernel in names[-1] and len(names) == 1 + (kernel == "tiled_kernel" and call is calls[1]), (plan, names)
-            assert torch.equal(out[0].view(torch.int16), y.view(torch.int16))
+            assert torch.equal(out.view(torch.int16), y.view(torch.int16))
     finally:
         abq.abq_plan_set(p, q, M, N, K)

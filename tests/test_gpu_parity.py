@@ -7,7 +7,7 @@ import pytest
 
 import oracle
 from paper_2408_08554_amd import synth
-from helpers import check_against_oracle, check_g128, check_sampled, gpu_gemm, gpu_gemm_fused, kernel_names, to_dev
+from helpers import check_against_oracle, check_g128, check_sampled, gpu_gemm, gpu_gemm_fused, gpu_gemm_named, kernel_names, run_named, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -94,11 +94,12 @@ def test_shapes(abq, layout, M, N, K, p, q):
     check_against_oracle(c, y, acc)
 
 
-TILED_SHAPES = [(65, 40, 700), (128, 128, 512), (200, 150, 1100), (129, 257, 64), (300, 16, 2048), (257, 130, 1536),
+# (most of them are few enough tiles for the K-split kernel now)
+PREFILL_SHAPES = [(65, 40, 700), (128, 128, 512), (200, 150, 1100), (129, 257, 64), (300, 16, 2048), (257, 130, 1536),
                 (128, 4096, 4096), (96, 300, 5632), (512, 11008, 1024), (70, 129, 3584)]
 
 
-@pytest.mark.parametrize("M,N,K", TILED_SHAPES)
+@pytest.mark.parametrize("M,N,K", PREFILL_SHAPES)
 @pytest.mark.parametrize("p,q", [(1, 1), (2, 8), (3, 3), (4, 8), (5, 5), (6, 6), (7, 7), (8, 8), (8, 2)])
 def test_prefill_shapes(abq, M, N, K, p, q):
     say("prefill shape", M, N, K, p, q)
@@ -110,20 +111,44 @@ def test_prefill_shapes(abq, M, N, K, p, q):
         check_sampled(c, y, acc)
 
 
-@pytest.mark.parametrize("p,q,M,N,K", [(4, 4, 2050, 6000, 200),     # 64x256 workgroup tiles by the rule, ragged on every side
-                                       (2, 8, 1030, 5500, 300),     # 64x128 tiles by the rule
-                                       (3, 8, 1024, 13824, 128),    # K of half a super-chunk
-                                       (8, 8, 520, 5100, 8200)])    # p = 8, long K: deep rings past one workgroup per CU
-def test_prefill_large_ragged_rule_paths(abq, p, q, M, N, K):
+@pytest.mark.parametrize("p,q,M,N,K,tile", [(4, 4, 1030, 5500, 300, "4, 4, 2"),    # 64x256 workgroup tiles by the rule, ragged on every side
+                                            (4, 4, 2050, 6000, 200, "2, 4, 2"),    # 64x128: short K, a second round
+                                            (1, 8, 2050, 5500, 300, "4, 4, 2"),    # 64x256 at p <= 2
+                                            (2, 8, 1030, 5500, 300, "2, 4, 2"),    # 64x128 tiles by the rule
+                                            (3, 8, 1024, 13824, 128, "2, 8, 2"),   # K of half a super-chunk
+                                            (7, 8, 1000, 3900, 700, "1, 8, 2"),    # 128x64
+                                            (8, 8, 520, 5100, 8200, "1, 4, 2"),    # p = 8, long K
+                                            (8, 8, 500, 4050, 8200, "1, 4, 4"),    # deep rings, two workgroups per CU that just fill the chip
+                                            (8, 8, 316, 1840, 2768, "1, 4, 4")])   # deep rings, at most one
+def test_prefill_large_ragged_rule_paths(abq, p, q, M, N, K, tile):
     say("prefill rule path", p, q, M, N, K)
     c = synth.make_case(p, q, M, N, K, seed=synth.case_seed(7, p, q) + M + N + K, name=f"W{p}A{q} {M}x{N}x{K}")
-    y, acc = gpu_gemm(torch, abq, c, FIELDS, FIELDS)
+    y, acc, names = gpu_gemm_named(torch, abq, c)
+    assert len(names) == 1 and f"tiled_kernel<{p}, {tile}>" in names[0], names
     check_sampled(c, y, acc, count=8192)
     # the last row and column blocks in full (partial tiles at both edges)
     ms = np.arange(M - 70, M)
     ns = np.arange(N - 300, N)
     sub = synth.Case(p, q, len(ms), len(ns), K, c.W[ns], c.A[ms], c.w_scale[ns], c.w_zero[ns], c.a_scale[ms], c.a_zero[ms], c.seed, c.name)
     check_against_oracle(sub, y[np.ix_(ms, ns)], acc[np.ix_(ms, ns)])
+
+
+@pytest.mark.parametrize("mt,ntw,wd", [(4, 1, 2), (4, 1, 4), (4, 2, 2), (4, 2, 4), (4, 4, 2), (8, 1, 2), (8, 2, 2), (8, 4, 2)])
+@pytest.mark.parametrize("p,q", [(1, 8), (2, 3), (3, 8), (4, 4), (5, 8), (6, 6), (7, 8), (8, 8)])
+def test_prefill_tiles_by_plan_entry(abq, p, q, mt, ntw, wd):
+    """Every tile shape and ring depth, ragged on every side, on K of less and of more steps than the deep ring holds."""
+    if wd == 4 and ntw == 2 and p >= 7:
+        pytest.skip("no deep ring with two tiles of 7 or 8 bits per wave")
+    for M, N, K in [(65, 40, 200), (200, 330, 1100), (130, 70, 3590)]:
+        c = synth.make_case(p, q, M, N, K, seed=synth.case_seed(7, p, q) + M + mt + ntw + wd, name=f"W{p}A{q} {M}x{N}x{K} tile {mt} {ntw} {wd}")
+        say(c.name)
+        abq.abq_plan_set(p, q, M, N, K, tiled_mt=mt, tiled_ntw=ntw, tiled_wd=wd)
+        try:
+            y, acc, names = gpu_gemm_named(torch, abq, c)
+        finally:
+            abq.abq_plan_set(p, q, M, N, K)
+        assert len(names) == 1 and f"tiled_kernel<{p}, {ntw}, {mt}, {wd}>" in names[0], names
+        check_against_oracle(c, y, acc)
 
 
 def test_prefill_bitserial(abq):
@@ -172,17 +197,20 @@ def test_longest_k(abq):
 def test_prefill_long_k_sums_of_codes_beyond_24_bits(abq):
     """M > 16 with K * (2^q - 1) or K * (2^p - 1) at or above 2^23: the prefill kernel's epilogue must leave its 24-bit
     multiply-adds for 32-bit multiplies (the host decides), with and without the accumulator output."""
-    for p, q, M, N, K in [(2, 8, 40, 70, 40000), (8, 2, 33, 130, 36000), (1, 8, 70, 24, 131072)]:
+    for p, q, M, N, K in [(2, 8, 40, 70, 40000), (8, 2, 33, 130, 36000), (2, 8, 70, 66, 40000), (8, 2, 133, 130, 36000), (1, 8, 70, 24, 131072)]:
         assert K * ((1 << max(p, q)) - 1) >= 1 << 23
         c = synth.make_case(p, q, M, N, K, seed=31 + p + q)
         say(c.name)
-        y, acc = gpu_gemm(torch, abq, c, FIELDS, FIELDS)
-        check_against_oracle(c, y, acc)
-        pw = abq.abq_pack_weights(p, to_dev(torch, c.W), to_dev(torch, c.w_scale), to_dev(torch, c.w_zero), FIELDS)
-        pa = abq.abq_pack_act_codes(q, to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero), FIELDS)
-        y_only, _ = abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, FIELDS)
-        torch.cuda.synchronize()
-        assert np.array_equal(y_only.cpu().numpy().view(np.uint16), np.asarray(y).view(np.uint16))
+        for kernel in [""] + (["tiled_kernel"] if M > 64 else []):   # the rule (the streaming or K-split kernel), and the prefill kernel
+            if kernel:
+                abq.abq_plan_set(p, q, M, N, K, tiled_mt=4, tiled_ntw=1)
+            try:
+                for want_acc in (True, False):
+                    y, acc, names = gpu_gemm_named(torch, abq, c, want_acc)
+                    assert len(names) == 1 and kernel in names[0], names
+                    check_against_oracle(c, y, acc)
+            finally:
+                abq.abq_plan_set(p, q, M, N, K)
 
 
 # Long K with up to 16 rows of A: the streaming kernel stages A one K group at a time and keeps per-tile
@@ -773,6 +801,14 @@ def run_g128(abq, c, sh, zg, fused):
     return y.cpu().numpy()
 
 
+def run_g128_named(abq, c, sh, zg):
+    """run_g128 on packed rows, and the kernels of the matmul alone."""
+    pw = abq.abq_pack_weights_g128(c.p, to_dev(torch, c.W), to_dev(torch, sh.view(np.float16)), to_dev(torch, zg))
+    pa = abq.abq_pack_act_codes(c.q, to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero), FIELDS)
+    (y, _), names = run_named(torch, lambda: abq.abq_gemm(c.p, c.q, c.M, c.N, c.K, pa, FIELDS, pw, G128))
+    return y.cpu().numpy(), names
+
+
 @pytest.mark.parametrize("fused", [False, True], ids=["packed", "fused"])
 @pytest.mark.parametrize("p,q", list(itertools.product(range(1, 9), [1, 4, 8])))
 def test_g128_all_widths(abq, p, q, fused):
@@ -953,7 +989,7 @@ def test_config5_sweep_samples(abq, p, q, shape_idx, m_idx):
     check_sampled(c, y, acc)
 
 
-# ---- per-group weight parameters in the prefill shape (the tiled per-group kernel, M > 16) --------------------------
+# ---- per-group weight parameters in the prefill shape (M > 16: the tiled per-group kernel and the K-split kernel) --------------------------
 @pytest.mark.parametrize("fused", [False, True], ids=["packed", "fused"])
 @pytest.mark.parametrize("M,N,K", [(128, 300, 2048), (512, 1000, 4096), (2048, 256, 1024), (70, 130, 1000), (17, 64, 127),
                                    (200, 4100, 640)])
@@ -967,26 +1003,30 @@ def test_g128_prefill_shapes(abq, p, q, M, N, K, fused):
     check_g128(c, sh, zg, run_g128(abq, c, sh, zg, fused))
 
 
-def test_g128_prefill_exact_when_the_float_sum_is_exact(abq):
-    """Power-of-two scales and small codes: every product and partial sum is exact in binary32, so the tiled per-group
-    kernel must return the oracle's binary16 values bit for bit."""
-    M, N, K = 96, 80, 1024
+@pytest.mark.parametrize("N,kernel", [(80, "ksplit_kernel"), (4200, "tiled_g128_kernel<2, 1>")])
+def test_g128_prefill_exact_when_the_float_sum_is_exact(abq, N, kernel):
+    """Power-of-two scales and small codes: every product and partial sum is exact in binary32, so the per-group prefill
+    kernels must return the oracle's binary16 values bit for bit."""
+    M, K = 96, 1024
     c = synth.make_case(2, 4, M, N, K, seed=4242, name="g128 prefill exact")
     rng = np.random.Generator(np.random.PCG64(5))
     G = (K + 127) // 128
     sh = (2.0 ** rng.integers(-6, -2, size=(N, G))).astype(np.float16).view(np.uint16)
     zg = rng.integers(0, 4, size=(N, G)).astype(np.int32)
     c.a_scale = (2.0 ** rng.integers(-8, -4, size=M)).astype(np.float32)
-    y = run_g128(abq, c, sh, zg, False)
+    y, names = run_g128_named(abq, c, sh, zg)
+    assert len(names) == 1 and kernel in names[0], names
     _, y16ref = oracle.dequant_grouped(c.A, c.W, c.a_zero, c.a_scale, zg, sh, gs=128)
     assert np.array_equal(y.view(np.uint16), y16ref)
 
 
-@pytest.mark.parametrize("M,N", [(33, 100), (300, 9850)], ids=["one_tile_per_wave", "two_tiles_per_wave"])
-@pytest.mark.parametrize("p", [1, 3, 5, 6, 7])
-def test_g128_prefill_extremes(abq, p, M, N):
-    """Zero-points at both ends of their range against codes at both ends, for tokens and groups (the operand byte w' - z + 64
-    then takes its extremes), a last group of 20 values that also leaves two groups of the last step empty, and the two tile widths."""
+@pytest.mark.parametrize("M,N,kernel", [(33, 100, "ksplit_kernel<%d, "), (33, 8300, "tiled_g128_kernel<%d, 1>"), (300, 9850, "tiled_g128_kernel<%d, 2>")],
+                         ids=["k_split", "one_tile_per_wave", "two_tiles_per_wave"])
+@pytest.mark.parametrize("p", [1, 2, 3, 4, 5, 6, 7, 8])
+def test_g128_prefill_extremes(abq, p, M, N, kernel):
+    """Zero-points at both ends of their range against codes at both ends, for tokens and groups (up to p = 6 the operand byte
+    128 + w' - z then takes its extremes), a last group of 20 values that also leaves two groups of the last step empty, in the K-split
+    kernel and both tile widths of the tiled per-group kernel."""
     q, K = 8, 128 * 9 + 20
     c = synth.make_case(p, q, M, N, K, seed=9850 + p, name=f"g128 prefill ends W{p}A{q} {M}x{N}x{K}")
     say(c.name)
@@ -997,7 +1037,9 @@ def test_g128_prefill_extremes(abq, p, M, N):
     c.A[0::4], c.A[1::4] = 255, 0
     c.a_zero[0::2], c.a_zero[1::2] = 0, 255
     c.a_scale[:] = np.float32(2e-4)      # (outputs of saturated rows stay inside binary16)
-    check_g128(c, sh, zg, run_g128(abq, c, sh, zg, False))
+    y, names = run_g128_named(abq, c, sh, zg)
+    assert len(names) == 1 and kernel % p in names[0], names
+    check_g128(c, sh, zg, y)
 
 
 # ---- ReQuant fused into the matmul epilogue (the consumer side of Fig. 3b) --------------------------------------

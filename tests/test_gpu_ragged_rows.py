@@ -5,7 +5,7 @@ import pytest
 
 import oracle
 from paper_2408_08554_amd import synth
-from helpers import check_against_oracle, check_g128, check_sampled, gpu_gemm, gpu_gemm_fused, kernel_names, to_dev
+from helpers import check_against_oracle, check_g128, check_sampled, gpu_gemm, gpu_gemm_fused, run_named, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -142,7 +142,7 @@ def test_kernel_of_ragged_rows(abq, p, M, N, K, one_kernel):
 
 
 def _kernels(fn):
-    return kernel_names(torch, fn)
+    return run_named(torch, fn)[1]
 
 
 @pytest.mark.parametrize("K", [4090, 4096])
@@ -279,7 +279,7 @@ def test_lane_order_with_two_super_chunks_of_8_bit_weights(abq, M, K):
     c = synth.make_case(p, q, M, N, K, seed=5950 + M, name=f"W{p}A{q} {M}x{N}x{K}")
     print(c.name, flush=True)
     pw = abq.abq_pack_weights(p, to_dev(torch, c.W), to_dev(torch, c.w_scale), to_dev(torch, c.w_zero))
-    a, out = (to_dev(torch, c.A | 0x80), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero)), []
-    names = _kernels(lambda: out.extend(abq.abq_gemm_act_codes(p, q, M, N, K, *a, pw, FIELDS, want_acc=True)))
+    a = (to_dev(torch, c.A | 0x80), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero))
+    out, names = run_named(torch, lambda: abq.abq_gemm_act_codes(p, q, M, N, K, *a, pw, FIELDS, want_acc=True))
     assert len(names) == 1 and "direct_kernel<8, 8, 2, true, true" in names[0], names
     check_against_oracle(c, out[0].cpu().numpy(), out[1].cpu().numpy())
