@@ -710,16 +710,16 @@ template <int P, int NTW, int MT>
 static hipError_t launch_shape(const TiledParams& prm, dim3 grid, int cus, int plan_wd, hipStream_t s)
 {
     // The deep rings exist for the small tile shapes (for two tiles of W per wave only up to p = 6: beyond, the registers run out) and run
-    // two workgroups per CU instead of three.  They are 20-30 % ahead with at most one workgroup per CU and long K (W8A8 M=256 4096 ch,
-    // K=11008 39.0 -> 28.4 us; p = 8 from K = 2048: M=316 1840 ch, K=2768 10.9 -> 10.4), at p = 8 and K >= 8192 also where two per CU just fill the
-    // chip (M=512 4096 ch 42.5 -> 41), and behind otherwise (W4A8 M=256 4096^2 9.5 us, 11.0 on them; W8A8 M=411 5120 ch, K=13824 65 / 68).  Override: the plan
-    // table (plan_wd).
+    // two workgroups per CU instead of three.  By the rule they are left for 8-bit weights on 64 x 64 tiles: with at most one workgroup per
+    // CU from K = 2048 (M=316 1840 ch, K=2768 10.9 -> 10.4 us; the K-split kernel has the longer K), and at K >= 8192 where two per CU just fill
+    // the chip (M=512 4096 ch, K=11008 42.5 -> 41).  Elsewhere that the rule uses this kernel they lose (W8A8 M=411 5120 ch, K=13824 65 / 68).  Override: the
+    // plan table (plan_wd).
     constexpr bool has_deep = MT == 4 && (NTW == 1 || (NTW == 2 && P <= 6));
     const int forced = plan_wd > 0 ? plan_wd : tuning_env("ABQ_TILED_WD");
     if constexpr (has_deep) {
         const long wg = grid.x;
-        const bool once = wg <= (long)cus && prm.K >= (P == 8 ? 2048 : 8192), twice = P == 8 && wg <= 2L * cus && 10 * wg >= 19L * cus && prm.K >= 8192;
-        if (forced == 4 || (forced != 2 && (once || twice))) {
+        const bool once = wg <= (long)cus && prm.K >= 2048, twice = wg <= 2L * cus && 10 * wg >= 19L * cus && prm.K >= 8192;
+        if (forced == 4 || (P == 8 && forced != 2 && (once || twice))) {
             tiled_kernel<P, NTW, MT, 4><<<grid, 256, 0, s>>>(prm);
             return hipGetLastError();
         }
