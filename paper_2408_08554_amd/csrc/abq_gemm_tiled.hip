@@ -711,14 +711,16 @@ static hipError_t launch_shape(const TiledParams& prm, dim3 grid, int cus, int p
 {
     // The deep rings exist for the small tile shapes (for two tiles of W per wave only up to p = 6: beyond, the registers run out) and run
     // two workgroups per CU instead of three.  By the rule they are left for 8-bit weights on 64 x 64 tiles: with at most one workgroup per
-    // CU from K = 2048 (M=316 1840 ch, K=2768 10.9 -> 10.4 us; the K-split kernel has the longer K), and at K >= 8192 where two per CU just fill
-    // the chip (M=512 4096 ch, K=11008 42.5 -> 41).  Elsewhere that the rule uses this kernel they lose (W8A8 M=411 5120 ch, K=13824 65 / 68).  Override: the
-    // plan table (plan_wd).
+    // CU from K = 2048 (M=316 1840 ch, K=2768 10.3 -> 9.7 us; the K-split kernel has the longer K), and at K >= 8192 where two per CU just fill the
+    // chip and, 32 apart in their XCD's order, multiply the same rows of A (shallow / deep, 100 sizes: 2, 4, 8 row blocks 1.01, 1.03, 1.02, M=512
+    // 4096 ch, K=11008 46.1 / 44.5 us; 16 0.98; 3, 6, 7, 9, 10, 12 0.91 to 0.95).  Elsewhere that the rule uses this kernel they lose (W8A8 M=411 5120 ch,
+    // K=13824 65 / 68).  Override: the plan table (plan_wd).
     constexpr bool has_deep = MT == 4 && (NTW == 1 || (NTW == 2 && P <= 6));
     const int forced = plan_wd > 0 ? plan_wd : tuning_env("ABQ_TILED_WD");
     if constexpr (has_deep) {
         const long wg = grid.x;
-        const bool once = wg <= (long)cus && prm.K >= 2048, twice = wg <= 2L * cus && 10 * wg >= 19L * cus && prm.K >= 8192;
+        const bool once = wg <= (long)cus && prm.K >= 2048, same_rows = prm.tiles_m <= 8 && 8 % prm.tiles_m == 0;
+        const bool twice = wg <= 2L * cus && 10 * wg >= 19L * cus && prm.K >= 8192 && same_rows;
         if (forced == 4 || (P == 8 && forced != 2 && (once || twice))) {
             tiled_kernel<P, NTW, MT, 4><<<grid, 256, 0, s>>>(prm);
             return hipGetLastError();

@@ -118,7 +118,8 @@ def test_prefill_shapes(abq, M, N, K, p, q):
                                             (3, 8, 1024, 13824, 128, "2, 8, 2"),   # K of half a super-chunk
                                             (7, 8, 1000, 3900, 700, "1, 8, 2"),    # 128x64
                                             (8, 8, 520, 5100, 8200, "1, 4, 2"),    # p = 8, long K
-                                            (8, 8, 500, 4050, 8200, "1, 4, 4"),    # deep rings, two workgroups per CU that just fill the chip
+                                            (8, 8, 500, 4050, 8200, "1, 4, 4"),    # deep rings, two workgroups per CU that just fill the chip, eight row blocks
+                                            (8, 8, 440, 4600, 8200, "1, 4, 2"),    # as full, seven row blocks
                                             (8, 8, 316, 1840, 2768, "1, 4, 4")])   # deep rings, at most one
 def test_prefill_large_ragged_rule_paths(abq, p, q, M, N, K, tile):
     say("prefill rule path", p, q, M, N, K)
