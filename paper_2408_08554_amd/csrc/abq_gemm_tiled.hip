@@ -474,12 +474,12 @@ __device__ __forceinline__ void step_g128(const u4v (*w)[phase_regs(P)], const u
 // The same step for p <= 6, where 128 + w' - z is a byte of 65..191 for every code and every zero-point that the packer's contract
 // allows (0..2^p-1), so that one add per dword of four bytes puts the zero-point into the operand with no carry between them, and a
 // flip of the top bits makes it the signed byte w' - z.  (Left at w' - z + 64, the operand needs no flip, and the accumulators a start
-// value -64 sum_k a' from eight more MFMAs to sixteen of the product: W4A8 M=1024 5120->13824 160 -> 141 us without them, M=700 4096^2 p = 5
-// 36.7 -> 28.8, with two vector instructions more between MFMAs.)  What remains per element and group is one multiply-add for the
+// value -64 sum_k a' from eight more MFMAs to sixteen of the product: W4A8 M=1024 5120->13824 with its quantizer 135 us a pass, 125 without them,
+// M=700 4096^2 p = 5 36.7 -> 28.8, with two vector instructions more between MFMAs.)  What remains per element and group is one multiply-add for the
 // token's zero-point, one conversion, one fused multiply-add, and with two tiles per wave these run under the next unit's MFMAs
 // (left alone, the scheduler puts all MFMAs of a unit first and the matrix pipe then idles through the flush).  The sums are the
-// same integers in the same order.  p = 7, 8 have no room for z in the byte.  Against the uncentred step: W4A8 M=1024 5120->13824 with its
-// quantizer 167 us -> 125; M=1024 11008->4096 p = 1..6 100-108 -> 75-90.
+// same integers in the same order.  p = 7, 8 have no room for z in the byte.  Against the uncentred step: the same pass 167
+// -> 125 us; the kernel alone, M=1024 11008->4096 p = 1..6 100-108 -> 79, 80, 88, 83, 93, 93.
 template <int P, int NTW, int MT, int PH>
 __device__ __forceinline__ void step_g128_centred(const u4v (*w)[phase_regs(P)], const u4v* gq, const uint8_t* a_buf, int r, int G,
                                                   const v4i* nzc, v4f (*facc)[NTW])

@@ -23,7 +23,7 @@ static int packed_up_to(int p, int K)
 // pulls (about 30 bytes a clock per compute unit), and a second round of workgroups costs what the first did.  Against the other
 // kernels (tiled, streaming; 957 sizes of M = 17..2048, N = 256..13824, K = 512..13824, all widths, packed and unpacked rows, per-channel
 // and per-group weights, timed in replays) the choice below is 1.41 times as fast on average, 2.4 % from the best of all kernels and
-// shapes at each size, and at most 7 % behind the others.  Where the lines lie (this kernel / the others, us):
+// shapes at each size, and at most 7 % behind the others but for the per-group sizes named below.  Where the lines lie (this kernel / the others, us):
 //   64 x 64, per-channel: the tiled kernel has overtaken while K is short (packed rows K < 1600 1.11 times, K = 3072..6144 0.92), up to
 //     64 rows of p = 8 until K = 4608 (12880 ch x 3296, M = 38, with the pack launch in front of both: 16.9 / 15.9);
 //   64 x 64, unpacked rows: see packed_up_to;
