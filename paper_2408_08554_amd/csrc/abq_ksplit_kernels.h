@@ -195,39 +195,42 @@ __global__ __launch_bounds__(64 * SH::S, SH::OCC) void ksplit_kernel(KsplitParam
     auto stage_part = [&](auto TC, int klive, v4i (*a)[RT]) {
         constexpr bool TAIL = decltype(TC)::value;
 #pragma unroll
-        for (int s = 0; s < NSL; s += 2)
+        for (int s = 0; s < NSL; s += 2) {
+            // TAIL: the loads began `sh` bytes early, and `live` bytes of a lane's vectors lie inside their rows.  Masks once for all rows: a wave
+            // that ends in a tail is the last of its workgroup, and the compiler merges masks written per vector only by chance (per vector / once,
+            // unpacked rows, 70 sizes: 32 x 16 tiles 0.957, 32 x 32 0.980, 64 x 32 0.926 times; W3A5 77x1003x4091 7.67 -> 7.53 us a pass).
+            const int live = klive - 64 * s - 16 * (lane & 7), sh = max(16 - live, 0);
+            uint32_t keep[4], fl[4];
+#pragma unroll
+            for (int d = 0; d < 4; ++d) {
+                const uint32_t inside = TAIL ? (uint32_t)((1ull << (8 * min(max(live - 4 * d, 0), 4))) - 1) : ~0u;
+                keep[d] = prm.a_mask & inside;
+                fl[d] = flip & inside;
+            }
 #pragma unroll
             for (int rt = 0; rt < RT; ++rt)
 #pragma unroll
                 for (int i = 0; i < 2; ++i) {
                     v4i v = a[s + i][rt];
                     if constexpr (RAW) {
-                        uint32_t fl[4] = {flip, flip, flip, flip};
-                        if constexpr (TAIL) {   // the load began `sh` bytes early; `live` bytes of the vector lie inside the row
-                            const int live = klive - 64 * s - 16 * (lane & 7), sh = 16 - live;
+                        if constexpr (TAIL) {
                             if (sh > 0) {
                                 if (sh & 8) v = v4i{v.z, v.w, 0, 0};
                                 if (sh & 4) v = v4i{v.y, v.z, v.w, 0};
                                 const uint32_t bits = 8 * (sh & 3);
                                 v = v4i{(int)__builtin_amdgcn_alignbit((uint32_t)v.y, (uint32_t)v.x, bits), (int)__builtin_amdgcn_alignbit((uint32_t)v.z, (uint32_t)v.y, bits),
                                         (int)__builtin_amdgcn_alignbit((uint32_t)v.w, (uint32_t)v.z, bits), (int)((uint32_t)v.w >> bits)};
-#pragma unroll
-                                for (int d = 0; d < 4; ++d) {
-                                    const int n = min(max(live - 4 * d, 0), 4);
-                                    const uint32_t keep = (uint32_t)((1ull << (8 * n)) - 1);
-                                    v[d] &= (int)keep;
-                                    fl[d] &= keep;
-                                }
                             }
                         }
 #pragma unroll
                         for (int d = 0; d < 4; ++d) {
-                            v[d] = (int)(((uint32_t)v[d] & prm.a_mask) ^ fl[d]);
+                            v[d] = (int)(((uint32_t)v[d] & keep[d]) ^ fl[d]);
                             if constexpr (!GQ) code_sum[rt][i] = __builtin_amdgcn_sdot4(v[d], 0x01010101, code_sum[rt][i], false);
                         }
                     }
                     *reinterpret_cast<v4i*>(a_lds + 1024 * RT * s + 2048 * rt + (w_pos ^ (128 * i))) = v;
                 }
+        }
     };
     auto stage_a = [&](int j, int h, v4i (*a)[RT]) {
         const int klive = prm.K - (256 * j + 64 * h * NSL);
