@@ -337,8 +337,8 @@ __global__ __launch_bounds__(64 * SH::S, SH::OCC) void ksplit_kernel(KsplitParam
     u4v w0[CT][PR], w1[CT][PR], g0[CT], g1[CT];
     int j = wave, n = prm.phase_q + (wave < prm.phase_r ? 1 : 0);
     constexpr bool kSwapA = AH == 1;   // (with halves the buffers of A are back in place after a phase)
-    // An even number of phases starts in the other buffers, so that every wave ends in the same ones (64-row tiles; see below)
-    constexpr bool kOneEnd = RT == 4 && (!GQ || CT == 2 || (P == 7 && !RAW));
+    // An even number of phases starts in the other buffers, so that every wave ends in the same ones (64-row tiles short of registers; see below)
+    constexpr bool kOneEnd = RT == 4 && (CT == 2 ? GQ || RAW || P == 7 : !GQ || (P == 7 && !RAW));
     const bool even = kOneEnd && (n & 1) == 0;
     if (even) {
         load_w(j, w1, g1);
@@ -385,7 +385,9 @@ __global__ __launch_bounds__(64 * SH::S, SH::OCC) void ksplit_kernel(KsplitParam
         // One last phase for both parities.  With one for each, as below, the buffers of one end stay alive across the other, and
         // 64-row tiles went to scratch (M=256 1920 ch, K=2048, packed rows: per-group p = 3, 5, 7, 8 8.4, 10.0, 14.8, 8.7 us, now
         // 6.9, 7.0, 7.9, 7.5; per-channel p = 7 8.2, now 6.6).  32-row tiles have the registers, and a short K is 2-4 % faster without a
-        // choice of buffers ahead of its first loads; so have the other per-group 64 x 64 tiles (M=512 2000 ch, K=8192 34.5 / 35.6).
+        // choice of buffers ahead of its first loads; so have the other per-group 64 x 64 tiles (M=512 2000 ch, K=8192 34.5 / 35.6), and 64 x 32
+        // tiles of packed rows but for p = 7: there one end is 1 % faster where every wave has an odd count, and 1-2 % slower, up to 3, elsewhere
+        // (125 sizes).
         if (even) phase(w1, g1, w0, g0, kSwapA ? a1 : a0, kSwapA ? a0 : a1);
         for (; n > 2; n -= 2) {
             phase(w0, g0, w1, g1, a0, a1);
