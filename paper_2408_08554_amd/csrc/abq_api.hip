@@ -543,6 +543,7 @@ static int gemm_impl(int p, int q, int M, int N, int K, const void* packed_act, 
     if (!choose_fields(can_fields, can_planes, force, p, q, M, N)) return hip_status(launch_gemm_bitserial(g, A, W, s));
     if (M > kSkinnyMaxM && ksplit_plan(g, A, W, &shape)) return hip_status(launch_gemm_ksplit(g, A, W, shape, s));
     if (streaming_shape(M, N)) return hip_status(launch_decode(g, A, W, s));
+    if (block_plan(g, W, &shape)) return hip_status(launch_gemm_block(g, A, W, shape, s));
     return hip_status(launch_gemm_tiled(g, A, W, s));
 }
 

@@ -743,6 +743,33 @@ static hipError_t launch_p(const TiledParams& prm, int ntw, int mt, dim3 grid, i
     return launch_shape<P, 4, 8>(prm, grid, cus, plan_wd, s);
 }
 
+// Tile shape (16 mt rows of A x 64 ntw rows of W per workgroup).  From timings of 1430 sizes of M = 65..2048, N = 512..13824, K = 512..13824 at all
+// widths (64 x 64, 64 x 128, 64 x 256, 128 x 64, 128 x 128, both ring depths); the choice below is 1.3 % from the best of them at each
+// size (the rule before: 2.9 %).  Workgroups are counted per compute unit, of 128 x 128 tiles unless said:
+//   p <= 2: 64 x 64 up to 1.5 of 64 x 128, then 64 x 128, 64 x 256 above 2.5 (W1A8 M=693 11008 ch 45.5 us on 128 x 128, 30.2) and where it
+//     fills the chip exactly once;
+//   p >= 3, up to 1.5: 64 x 128, or 64 x 64 while those are fewer than 1.5 (also for K >= 5120 at p = 4..6, where 64 x 128 on deep rings
+//     had been taken: W5A8 M=512 4096 ch, K=11008 42.3 -> 32.7).  p = 8 takes 128 x 128 from 0.8 to 1.25 if K >= 2560: it halves the
+//     weight bytes and nearly every unit has one (M=1024 5120 ch 39.1 -> 36.5); p = 7 takes 128 x 64 from 0.75 to 1 (31.2 -> 27.9);
+//   above 1.5: 128 x 128, at p = 4 64 x 256.  From 2 to 2.5 their second round (two a unit) is nearly empty and 64 x 128 wins
+//     (W8A8 M=1575 5008 ch 62.5 -> 52, W6A8 M=1024 9584 ch 144 -> 133), as it does at p = 4 above 2 while K is short (W4A8 1.08 times).
+void tiled_shape_by_rule(int p, int M, int N, int K, int* mt_out, int* ntw_out)
+{
+    const long cus = num_cus();
+    auto wgs = [&](int mt_, int ntw_) { return (long)((M + mt_ * 16 - 1) / (mt_ * 16)) * ((N + 64 * ntw_ - 1) / (64 * ntw_)); };
+    const long w82 = wgs(8, 2), w42 = wgs(4, 2), w44 = wgs(4, 4);
+    int mt = 4, ntw = 2 * w42 < 3L * cus ? 1 : 2;
+    if (p <= 2) {
+        if (ntw == 2 && M > 64 && (2 * w82 > 5L * cus || (w44 <= 2L * cus && 2 * w44 > 3L * cus))) ntw = 4;
+    } else if (M > 64) {
+        if (p == 8 && K >= 2560 && 5 * w82 >= 4L * cus && 4 * w82 <= 5L * cus) { mt = 8; ntw = 2; }
+        else if (p == 7 && 4 * w82 > 3L * cus && w82 <= (long)cus) { mt = 8; ntw = 1; }
+        else if (2 * w82 >= 3L * cus && !(w82 > 2L * cus && (2 * w82 <= 5L * cus || (p == 4 && K < 2560)))) { mt = p == 4 ? 4 : 8; ntw = p == 4 ? 4 : 2; }
+    }
+    *mt_out = mt;
+    *ntw_out = ntw;
+}
+
 hipError_t launch_gemm_tiled(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, hipStream_t s)
 {
     TiledParams prm;
@@ -783,28 +810,9 @@ hipError_t launch_gemm_tiled(const GemmArgs& g, const ActLayout& A, const Weight
             default: return launch_g128_p<8>(prm, ntw_g, grid_g, s);
         }
     }
-    // Tile shape (rows of A x rows of W per workgroup).  From timings of 1430 sizes of M = 65..2048, N = 512..13824, K = 512..13824 at all
-    // widths (64 x 64, 64 x 128, 64 x 256, 128 x 64, 128 x 128, both ring depths); the choice below is 1.3 % from the best of them at each
-    // size (the rule before: 2.9 %).  Workgroups are counted per compute unit, of 128 x 128 tiles unless said:
-    //   p <= 2: 64 x 64 up to 1.5 of 64 x 128, then 64 x 128, 64 x 256 above 2.5 (W1A8 M=693 11008 ch 45.5 us on 128 x 128, 30.2) and where it
-    //     fills the chip exactly once;
-    //   p >= 3, up to 1.5: 64 x 128, or 64 x 64 while those are fewer than 1.5 (also for K >= 5120 at p = 4..6, where 64 x 128 on deep rings
-    //     had been taken: W5A8 M=512 4096 ch, K=11008 42.3 -> 32.7).  p = 8 takes 128 x 128 from 0.8 to 1.25 if K >= 2560: it halves the
-    //     weight bytes and nearly every unit has one (M=1024 5120 ch 39.1 -> 36.5); p = 7 takes 128 x 64 from 0.75 to 1 (31.2 -> 27.9);
-    //   above 1.5: 128 x 128, at p = 4 64 x 256.  From 2 to 2.5 their second round (two a unit) is nearly empty and 64 x 128 wins
-    //     (W8A8 M=1575 5008 ch 62.5 -> 52, W6A8 M=1024 9584 ch 144 -> 133), as it does at p = 4 above 2 while K is short (W4A8 1.08 times).
-    int cus = 256, dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) cus = 256;
-    auto wgs = [&](int mt_, int ntw_) { return (long)((g.M + mt_ * 16 - 1) / (mt_ * 16)) * ((g.N + 64 * ntw_ - 1) / (64 * ntw_)); };
-    const long w82 = wgs(8, 2), w42 = wgs(4, 2), w44 = wgs(4, 4);
-    int mt = 4, ntw = 2 * w42 < 3L * cus ? 1 : 2;
-    if (g.p <= 2) {
-        if (ntw == 2 && g.M > 64 && (2 * w82 > 5L * cus || (w44 <= 2L * cus && 2 * w44 > 3L * cus))) ntw = 4;
-    } else if (g.M > 64) {
-        if (g.p == 8 && g.K >= 2560 && 5 * w82 >= 4L * cus && 4 * w82 <= 5L * cus) { mt = 8; ntw = 2; }
-        else if (g.p == 7 && 4 * w82 > 3L * cus && w82 <= (long)cus) { mt = 8; ntw = 1; }
-        else if (2 * w82 >= 3L * cus && !(w82 > 2L * cus && (2 * w82 <= 5L * cus || (g.p == 4 && g.K < 2560)))) { mt = g.p == 4 ? 4 : 8; ntw = g.p == 4 ? 4 : 2; }
-    }
+    int mt, ntw;
+    tiled_shape_by_rule(g.p, g.M, g.N, g.K, &mt, &ntw);
+    const int cus = num_cus();
     {
         const int forced_mt = tuning_env("ABQ_TILED_MT"), forced_ntw = tuning_env("ABQ_TILED_NTW");
         if (forced_mt == 4 || forced_mt == 8) mt = forced_mt;

@@ -158,6 +158,10 @@ hipError_t launch_gemm_direct_grouped(int p, int q, int M, int count, const Gemm
 // The K-split prefill kernel (more than 16 rows of A over few output tiles): index of the workgroup shape.
 bool ksplit_plan(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, int* shape);   // false: another kernel takes the problem
 hipError_t launch_gemm_ksplit(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, int shape, hipStream_t s);
+// The block kernel (prompts whose output has many tiles): index of the workgroup shape.
+bool block_plan(const GemmArgs& g, const WeightLayout& W, int* shape);   // packed rows; false: the tiled kernel takes the problem
+hipError_t launch_gemm_block(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, int shape, hipStream_t s);
+void tiled_shape_by_rule(int p, int M, int N, int K, int* mt, int* ntw);   // 16-row tiles of A per workgroup, 16-row tiles of W per wave
 hipError_t launch_gemm_tiled(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, hipStream_t s);
 hipError_t launch_gemm_bitserial(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, hipStream_t s);
 

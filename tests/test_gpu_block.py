@@ -1,0 +1,63 @@
+"""The block kernel (prompts over many output tiles): every workgroup shape, ragged in all three directions, bit for bit against the tiled
+kernel (which writes the int32 accumulator, so a call that asks for it takes that kernel) and against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2408_08554_amd import synth
+from helpers import check_sampled, run_named, to_dev
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+FIELDS = 2
+WAVES = {"256": "2, 4, 8, ", "192": "2, 4, 4, 3,", "128": "2, 4, 4, 2,", "128x2": "2, 2, 4, 4,", "64x2": "1, 4, 4, 2,"}
+# shape by the rule, width, rows, channels, K: fewer steps than the ring has places, parts of a super-chunk, several of them
+CASES = [("256", 1, 1025, 11694, 100), ("256", 2, 1230, 9781, 100), ("256", 3, 1223, 9940, 1100), ("256", 4, 1157, 10048, 520),
+         ("256", 5, 900, 12816, 101), ("256", 6, 960, 12385, 530), ("256", 7, 654, 12064, 1040), ("256", 8, 846, 9375, 1027),
+         ("192", 1, 330, 11040, 101), ("192", 3, 1470, 3992, 103), ("192", 4, 257, 13216, 528), ("192", 6, 261, 13168, 521), ("192", 7, 386, 12224, 108),
+         ("192", 8, 261, 13176, 520), ("128", 2, 130, 11344, 2567), ("128", 4, 134, 10912, 1061), ("128", 5, 133, 11232, 1560), ("128", 7, 133, 12304, 1029),
+         ("128", 8, 130, 11038, 520), ("128x2", 1, 396, 13981, 107), ("128x2", 3, 465, 12432, 100), ("128x2", 4, 129, 11073, 106),
+         ("128x2", 5, 328, 10910, 101), ("128x2", 6, 258, 13288, 104), ("128x2", 7, 389, 12832, 103), ("128x2", 8, 197, 8288, 101),
+         ("64x2", 1, 71, 8462, 1106), ("64x2", 2, 70, 8464, 104), ("64x2", 3, 259, 9904, 101), ("64x2", 4, 264, 11080, 100), ("64x2", 5, 194, 12208, 103),
+         ("64x2", 6, 201, 12192, 101), ("64x2", 7, 133, 12456, 101), ("64x2", 8, 65, 8304, 563),
+         ("64x2", 4, 1000, 1100, 33000)]   # (sums past 2^23: the 32-bit epilogue)
+
+
+def problem(abq, shape, p, q, M, N, K):
+    c = synth.make_case(p, q, M, N, K, seed=7300 + 10 * p + q, name=f"block {shape} W{p}A{q} {M}x{N}x{K}")
+    print(c.name, flush=True)
+    c.W[::5], c.A[::7] = (1 << p) - 1, (1 << q) - 1   # the largest codes, whole rows of them, against each other
+    pw = abq.abq_pack_weights(p, to_dev(torch, c.W), to_dev(torch, c.w_scale), to_dev(torch, c.w_zero))
+    return c, pw, abq.abq_pack_act_codes(q, to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero))
+
+
+@pytest.mark.parametrize("q", [8, 4])
+@pytest.mark.parametrize("shape,p,M,N,K", CASES)
+def test_block_equals_the_tiled_kernel(abq, shape, p, q, M, N, K):
+    c, pw, pa = problem(abq, shape, p, q, M, N, K)
+    (y0, acc0), names = run_named(torch, lambda: abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, FIELDS, want_acc=True))
+    assert len(names) == 1 and f"tiled_kernel<{p}, " in names[0], names
+    (y, _), names = run_named(torch, lambda: abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, FIELDS))
+    assert len(names) == 1 and f"block_kernel<{p}, {WAVES[shape]}" in names[0], names
+    assert torch.equal(y.view(torch.int16), y0.view(torch.int16))
+    check_sampled(c, y.cpu().numpy(), acc0.cpu().numpy())
+
+
+@pytest.mark.parametrize("shape,p,M,N,K", [c for c in CASES if c[1] in (4, 7, 8) and c[4] < 2000])
+def test_block_writes_the_next_layers_codes(abq, shape, p, M, N, K):
+    """Output codes with and without the binary16 output: those of the values that it stores."""
+    q, qo = 8, 6
+    c, pw, pa = problem(abq, shape, p, q, M, N, K)
+    y0, _ = abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, FIELDS)
+    a, sa, za = to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero)
+    rng = np.random.default_rng(5)
+    so, zo = rng.uniform(0.5, 4.0, M).astype(np.float32), rng.integers(0, 1 << qo, M).astype(np.int32)
+    dso, dzo = to_dev(torch, so), to_dev(torch, zo)
+    call = lambda **kw: abq.abq_gemm_act_codes_requant(p, q, M, N, K, a, sa, za, pw, FIELDS, qo, dso, dzo, **kw)
+    (codes, y), names = run_named(torch, call)
+    assert f"block_kernel<{p}, {WAVES[shape]}" in names[-1], names
+    assert torch.equal(y.view(torch.int16), y0.view(torch.int16))
+    assert np.array_equal(codes.cpu().numpy(), oracle.requant(y0.cpu().numpy(), qo, so, zo))
+    assert torch.equal(call(want_y=False)[0], codes)
