@@ -49,7 +49,7 @@ def _compile(src: str, newest_header: float = 0.0) -> str:
 # in between.  The K loops of tiled_kernel, ksplit_kernel and block_kernel count on their loads staying in flight: a reload from scratch inside one waits
 # for all of them.  direct_kernel has all loads of a wave in flight at once, and spills them ahead of the weights it waits for.
 NO_SCRATCH = {"abq_f4.hip": "f4_gemm_kernel", "abq_gemm_tiled.hip": "tiled_kernel", **{f"abq_ksplit_p{p}.hip": "ksplit_kernel" for p in range(1, 9)},
-              **{f"abq_block_p{p}.hip": "block_kernel" for p in range(1, 9)},
+              **{f"abq_block_p{p}.hip": "block_" for p in range(1, 9)},
               **{f"abq_direct_p{p}.hip": "direct_kernel" for p in (12, 34, 56, 78)}}
 # (64 x 256 tiles at p = 7, three plane groups of four tiles per wave: two registers over the 256 of two workgroups per CU)
 SCRATCH_ALLOWED = ("tiled_kernelILi7ELi4ELi4ELi2E",)

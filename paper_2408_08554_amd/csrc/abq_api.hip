@@ -536,9 +536,10 @@ static int gemm_impl(int p, int q, int M, int N, int K, const void* packed_act, 
                workspace, workspace_bytes, rq};
     hipStream_t s = (hipStream_t)stream;
     int shape;
-    if (W.g128) {   // per-group weight parameters: the streaming kernel up to 16 rows of A, the K-split or the tiled per-group kernel above
+    if (W.g128) {   // per-group weight parameters: the streaming kernel up to 16 rows of A, the K-split, block or tiled per-group kernel above
         if (M > kSkinnyMaxM && ksplit_plan(g, A, W, &shape)) return hip_status(launch_gemm_ksplit(g, A, W, shape, s));
-        return hip_status(M <= kSkinnyMaxM ? launch_decode(g, A, W, s) : launch_gemm_tiled(g, A, W, s));
+        if (M <= kSkinnyMaxM) return hip_status(launch_decode(g, A, W, s));
+        return hip_status(block_g128_plan(g, &shape) ? launch_gemm_block_g128(g, A, W, shape, s) : launch_gemm_tiled(g, A, W, s));
     }
     if (!choose_fields(can_fields, can_planes, force, p, q, M, N)) return hip_status(launch_gemm_bitserial(g, A, W, s));
     if (M > kSkinnyMaxM && ksplit_plan(g, A, W, &shape)) return hip_status(launch_gemm_ksplit(g, A, W, shape, s));

@@ -1,5 +1,5 @@
-// Host side of the block kernel: the choice of shape and the launch.
-#include "abq_block_kernels.h"
+// Host side of the block kernels: the choice of shape and the launch.
+#include "abq_block_g128_kernels.h"
 
 namespace abq {
 
@@ -89,6 +89,63 @@ hipError_t launch_gemm_block(const GemmArgs& g, const ActLayout& A, const Weight
         case 6: return block_launch_p6(prm, shape, s);
         case 7: return block_launch_p7(prm, shape, s);
         default: return block_launch_p8(prm, shape, s);
+    }
+}
+
+// ---- per-group weights
+static const BkShapeInfo kG128Shapes[2] = {{256, 128, 1}, {128, 128, 2}};   // (as in block_g128_launch)
+
+// Costs as above, from 1500 sizes of M = 48..2048 that the K-split kernel leaves; the tiled per-group kernel's by its tiles (64 x 64, 64 x 128).
+static const struct { Cost block[2], tiled[2]; } kG128Costs[2] = {
+    {{{0, 7.012f, {1.282f, 0, 0}}, {3.391f, 2.608f, {0.741f, 1.423f, 0}}},         // p = 1, 2, 4 (64 x 64: three workgroups a unit)
+     {{0, 4.617f, {0, 0.466f, 0.705f}}, {3.42f, 2.239f, {0.417f, 0.89f, 0}}}},
+    {{{0.394f, 6.649f, {1.388f, 0, 0}}, {3.63f, 2.345f, {0.816f, 1.542f, 0}}},     // p = 3, 5, 6
+     {{3.511f, 0.924f, {0.233f, 0.548f, 0}}, {3.28f, 2.088f, {0.471f, 1.026f, 0}}}},
+};
+
+// The cheaper shape where it is 6 % below the tiled per-group kernel, on more than twelve groups of K (up to there the rounds' own
+// cost decides, and this kernel takes 1.10 times the other's time on average).  It takes a fifth of those sizes, at 0.88 times the time (W4A8 M=1024
+// 5120->13824 157 / 130 us), and none at 1.03 times or more but one in a thousand.  7- and 8-bit weights have no room for z in the byte.
+bool block_g128_plan(const GemmArgs& g, int* shape)
+{
+    if (g.p > 6 || g.K <= 1536) return false;
+    const int env = tuning_env("ABQ_BLOCK");   // tuning builds: -1 off, 1 or 2 a shape
+    if (env) { *shape = env - 1; return env > 0 && env <= 2; }
+    const bool merged = g.p == 3 || g.p >= 5;
+    const auto& w = kG128Costs[merged ? 1 : 0];
+    double c[2];
+    for (int i = 0; i < 2; ++i) c[i] = cost_of(w.block[i], g.M, g.N, g.K, kG128Shapes[i].bm, kG128Shapes[i].bn, kG128Shapes[i].occ);
+    *shape = c[1] < c[0] ? 1 : 0;
+    const int ntw = tiled_g128_ntw(g.M, g.N);
+    return cost_of(w.tiled[ntw - 1], g.M, g.N, g.K, 64, 64 * ntw, ntw == 1 && !merged ? 3 : 2) * 0.94 >= c[*shape];
+}
+
+hipError_t launch_gemm_block_g128(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, int shape, hipStream_t s)
+{
+    const int bm = kG128Shapes[shape].bm, bn = kG128Shapes[shape].bn;
+    BlockG128Params prm;
+    for (int i = 0; i < 3; ++i) prm.fields[i] = g.w_blob + W.off_fields[i];
+    prm.gparams = g.w_blob + W.off_gparams;
+    prm.a = g.act_blob + A.off_codes;
+    prm.aparams = (const RowParams*)(g.act_blob + A.off_params);
+    prm.y = g.y;
+    prm.M = g.M; prm.N = g.N;
+    prm.lda = A.Kp;
+    prm.nsuper = A.Kp / kSuperK;
+    prm.ntiles = W.NT;
+    prm.oa = g.q == 8 ? 128 : 0;
+    prm.tiles_m = (g.M + bm - 1) / bm;
+    prm.tiles_n = (g.N + bn - 1) / bn;
+    const int cap = 1024 / bm, bands = (prm.tiles_m + cap - 1) / cap;
+    prm.band_m = (prm.tiles_m + bands - 1) / bands;
+    switch (g.p) {
+        case 1: return block_g128_launch_p1(prm, shape, s);
+        case 2: return block_g128_launch_p2(prm, shape, s);
+        case 3: return block_g128_launch_p3(prm, shape, s);
+        case 4: return block_g128_launch_p4(prm, shape, s);
+        case 5: return block_g128_launch_p5(prm, shape, s);
+        case 6: return block_g128_launch_p6(prm, shape, s);
+        default: return hipErrorInvalidValue;
     }
 }
 

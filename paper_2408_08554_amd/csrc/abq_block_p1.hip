@@ -1,6 +1,7 @@
-// Block kernel: the variants of 1-bit weights.
-#include "abq_block_kernels.h"
+// Block kernels: the variants of 1-bit weights.
+#include "abq_block_g128_kernels.h"
 
 namespace abq {
 ABQ_BLOCK_LAUNCH(1) { return block_launch<1>(prm, shape, s); }
+ABQ_BLOCK_G128_LAUNCH(1) { return block_g128_launch<1>(prm, shape, s); }
 }  // namespace abq

@@ -770,6 +770,11 @@ void tiled_shape_by_rule(int p, int M, int N, int K, int* mt_out, int* ntw_out)
     *ntw_out = ntw;
 }
 
+int tiled_g128_ntw(int M, int N)
+{
+    return 2L * ((M + 63) / 64) * ((N + 127) / 128) >= 3L * num_cus() ? 2 : 1;
+}
+
 hipError_t launch_gemm_tiled(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, hipStream_t s)
 {
     TiledParams prm;
@@ -789,10 +794,7 @@ hipError_t launch_gemm_tiled(const GemmArgs& g, const ActLayout& A, const Weight
     prm.narrow_sums = ((long)g.K * ((1 << g.p) - 1) < (1L << 23) && (long)g.K * ((1 << g.q) - 1) < (1L << 23)) ? 1 : 0;
     if (W.g128) {
         // per-group weight parameters: 64 rows of A against 128 (or, for few workgroups, 64) rows of W per workgroup
-        int cus_g = 256, dev_g = 0;
-        if (hipGetDevice(&dev_g) != hipSuccess || hipDeviceGetAttribute(&cus_g, hipDeviceAttributeMultiprocessorCount, dev_g) != hipSuccess || cus_g <= 0) cus_g = 256;
-        const long wg2 = (long)((g.M + 63) / 64) * ((g.N + 127) / 128);
-        const int ntw_g = 2 * wg2 >= 3L * cus_g ? 2 : 1;
+        const int ntw_g = tiled_g128_ntw(g.M, g.N);
         prm.tiles_m = (g.M + 63) / 64;
         prm.tiles_n = (g.N + 64 * ntw_g - 1) / (64 * ntw_g);
         const int cap = (g.p <= 4 ? 512 : 1024) / 64;

@@ -161,7 +161,10 @@ hipError_t launch_gemm_ksplit(const GemmArgs& g, const ActLayout& A, const Weigh
 // The block kernel (prompts whose output has many tiles): index of the workgroup shape.
 bool block_plan(const GemmArgs& g, const WeightLayout& W, int* shape);   // packed rows; false: the tiled kernel takes the problem
 hipError_t launch_gemm_block(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, int shape, hipStream_t s);
+bool block_g128_plan(const GemmArgs& g, int* shape);   // per-group weights, packed rows; false: the tiled per-group kernel takes the problem
+hipError_t launch_gemm_block_g128(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, int shape, hipStream_t s);
 void tiled_shape_by_rule(int p, int M, int N, int K, int* mt, int* ntw);   // 16-row tiles of A per workgroup, 16-row tiles of W per wave
+int tiled_g128_ntw(int M, int N);   // per-group weights: 16-row tiles of W per wave
 hipError_t launch_gemm_tiled(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, hipStream_t s);
 hipError_t launch_gemm_bitserial(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, hipStream_t s);
 

@@ -5,13 +5,13 @@ import pytest
 
 import oracle
 from paper_2408_08554_amd import synth
-from helpers import check_sampled, run_named, to_dev
+from helpers import check_g128, check_sampled, run_named, to_dev
 
 pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-FIELDS = 2
+FIELDS, G128 = 2, 4
 WAVES = {"256": "2, 4, 8, ", "192": "2, 4, 4, 3,", "128": "2, 4, 4, 2,", "128x2": "2, 2, 4, 4,", "64x2": "1, 4, 4, 2,"}
 # shape by the rule, width, rows, channels, K: fewer steps than the ring has places, parts of a super-chunk, several of them
 CASES = [("256", 1, 1025, 11694, 100), ("256", 2, 1230, 9781, 100), ("256", 3, 1223, 9940, 1100), ("256", 4, 1157, 10048, 520),
@@ -61,3 +61,40 @@ def test_block_writes_the_next_layers_codes(abq, shape, p, M, N, K):
     assert torch.equal(y.view(torch.int16), y0.view(torch.int16))
     assert np.array_equal(codes.cpu().numpy(), oracle.requant(y0.cpu().numpy(), qo, so, zo))
     assert torch.equal(call(want_y=False)[0], codes)
+
+
+# both shapes by the rule, widths of one and of two plane groups, a last group that is short and groups past K, ragged rows and channels
+@pytest.mark.parametrize("waves,p,M,N,K", [("2, 4, 8,", 1, 577, 10147, 1539), ("2, 4, 8,", 2, 454, 12312, 1547), ("2, 4, 8,", 3, 322, 11195, 1544),
+                                           ("2, 4, 8,", 4, 580, 9735, 1561), ("2, 4, 8,", 5, 391, 9408, 1541), ("2, 4, 8,", 6, 331, 11022, 1665),
+                                           ("1, 4, 8,", 1, 195, 12184, 1652), ("1, 4, 8,", 2, 196, 12712, 1579), ("1, 4, 8,", 3, 193, 12280, 1546),
+                                           ("1, 4, 8,", 4, 194, 12499, 1597), ("1, 4, 8,", 5, 202, 12293, 2049), ("1, 4, 8,", 6, 193, 12752, 1556)])
+@pytest.mark.parametrize("q", [8, 5])
+def test_block_per_group_weights(abq, waves, p, q, M, N, K):
+    """Zero-points and codes at both ends of their ranges against each other.  The groups are summed in the tiled per-group kernel's order, so
+    every row has the bits that it has in a call of 64 rows, which that kernel takes; some rows against the oracle."""
+    c = synth.make_case(p, q, M, N, K, seed=7500 + 10 * p + q, name=f"block g128 W{p}A{q} {M}x{N}x{K}")
+    print(c.name, flush=True)
+    sh, zg = synth.group_quant_params(c)
+    top, atop = (1 << p) - 1, (1 << q) - 1
+    zg[:, 0::3], zg[:, 1::3] = 0, top
+    c.W[0::3], c.W[1::3] = top, 0
+    c.A[0::4], c.A[1::4] = atop, 0
+    c.a_zero[0::2], c.a_zero[1::2] = 0, atop
+    c.a_scale[:] = np.float32(1e-4)
+    pw = abq.abq_pack_weights_g128(p, to_dev(torch, c.W), to_dev(torch, sh.view(np.float16)), to_dev(torch, zg))
+    A, sa, za = to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero)
+    pa = abq.abq_pack_act_codes(q, A, sa, za)
+    (y, _), names = run_named(torch, lambda: abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, G128))
+    assert len(names) == 1 and f"block_g128_kernel<{p}, {waves}" in names[0], names
+    for m in range(0, M, 64):
+        rows = min(64, M - m)
+        if rows < 33:
+            m, rows = M - 64, 64
+        part = abq.abq_pack_act_codes(q, A[m:m + rows].clone(), sa[m:m + rows].clone(), za[m:m + rows].clone())
+        call = lambda: abq.abq_gemm(p, q, rows, N, K, part, FIELDS, pw, G128)
+        (ref, _), names = run_named(torch, call) if m == 0 else (call(), ["tiled_g128_kernel"])
+        assert "tiled_g128_kernel" in names[0], names
+        assert torch.equal(y[m:m + rows].view(torch.int16), ref.view(torch.int16))
+    ms = np.r_[0:8, M - 8:M]
+    sub = synth.Case(p, q, len(ms), N, K, c.W, c.A[ms], c.w_scale, c.w_zero, c.a_scale[ms], c.a_zero[ms], c.seed, c.name)
+    check_g128(sub, sh, zg, y.cpu().numpy()[ms])
