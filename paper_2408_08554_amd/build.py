@@ -34,7 +34,7 @@ def _compile(src: str, newest_header: float = 0.0) -> str:
     if newest_header and os.path.exists(obj) and os.path.getmtime(obj) >= max(newest_header, os.path.getmtime(src)):
         return obj   # --incremental: neither the source nor any header is newer than the object
     extra = ["-Rpass-analysis=kernel-resource-usage"] if os.path.basename(src) in NO_SCRATCH else []
-    if os.path.basename(src).startswith("abq_block_p"):
+    if os.path.basename(src).startswith(("abq_block_p", "abq_f4")):
         # accumulators in ordinary registers also where one workgroup of four waves has a unit to itself; left alone, the compiler
         # puts them into the other register file and copies them to and fro inside the K loop
         extra += ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
@@ -44,10 +44,8 @@ def _compile(src: str, newest_header: float = 0.0) -> str:
     return obj
 
 
-# Kernels that may not use scratch memory; the build fails if one does.  f4_gemm_kernel loads registers with hand-written load
-# instructions and waits for them by hand: the compiler does not know that such a register fills later, so it must not spill it
-# in between.  The K loops of tiled_kernel, ksplit_kernel and block_kernel count on their loads staying in flight: a reload from scratch inside one waits
-# for all of them.  direct_kernel has all loads of a wave in flight at once, and spills them ahead of the weights it waits for.
+# Kernels that may not use scratch memory; the build fails if one does.  Their K loops count on loads staying in flight: a reload from
+# scratch inside one waits for all of them.  direct_kernel has all loads of a wave in flight at once, and spills them ahead of the weights it waits for.
 NO_SCRATCH = {"abq_f4.hip": "f4_gemm_kernel", "abq_gemm_tiled.hip": "tiled_kernel", **{f"abq_ksplit_p{p}.hip": "ksplit_kernel" for p in range(1, 9)},
               **{f"abq_block_p{p}.hip": "block_" for p in range(1, 9)},
               **{f"abq_direct_p{p}.hip": "direct_kernel" for p in (12, 34, 56, 78)}}

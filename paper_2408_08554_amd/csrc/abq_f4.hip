@@ -13,15 +13,11 @@
 // L % 16, k = 128 block + 32 (L / 16) .. + 31 as 32 nibbles, which is the MFMA operand of that block as it stands.
 // Rows past the end and k past K hold code 0.
 //
-// Kernel: workgroup tile 256 rows of A x 128 channels of W, four waves of 64 x 128 each (32 accumulator tiles; 64 x 128
-// with waves of 16 x 128 for problems of few tiles), K in
-// steps of 128: the step's 16 + 8 operand blocks go global -> LDS with direct 128-bit loads (a block is one wave
-// instruction and lands in LDS as the operand layout: conflict-free 128-bit reads), one barrier per step; three workgroups
-// share a compute unit with two operand buffers each, or two with three buffers each (launch_f4_gemm says when), and
-// hide each other's waits.
-#include "abq_internal.h"
+// Kernel: both operands through an LDS ring, workgroup tiles of 32 x 64 to 256 x 256 (see f4_gemm_kernel).
+#include "abq_rows.h"
 #include "../../include/abq.h"
 
+#include <type_traits>
 
 namespace abq {
 
@@ -30,7 +26,6 @@ typedef int v8i_f4 __attribute__((ext_vector_type(8)));
 typedef float v4f_f4 __attribute__((ext_vector_type(4)));
 
 constexpr int kF4BlockK = 128;                 // k per operand block
-constexpr int kF4TileN = 128;                  // channels of W per workgroup tile (the rows of A: F4Shape)
 
 static inline int f4_row_tiles(int rows) { return (rows + 15) / 16; }
 static inline int f4_k_blocks(int K) { return (K + kF4BlockK - 1) / kF4BlockK; }
@@ -158,244 +153,206 @@ struct F4Params {
     int M, N, K, kblocks;
     int a_tiles, w_tiles;      // 16-row tiles of the two operands
     int tiles_m, tiles_n;      // workgroup tiles
+    int band_m;                // row tiles per band of the tile order
 };
 
-// RT: 16-row tiles of A per wave (4: workgroup tile 256 x 128, the shape for large M; 1: 64 x 128, for problems that would
-// otherwise leave compute units idle).
-template <int RT> struct F4Shape {
-    static constexpr int kTileM = 64 * RT;
-    static constexpr int kWBufBytes = 8 * 1024;                         // the eight W blocks of a step
-    static constexpr int kPassRows = RT >= 2 ? 32 : 16;                 // rows a wave stages per pass of the epilogue
-    static constexpr int kStageBytes = 4 * kPassRows * 272;
-    static constexpr int kParamOffset = (kStageBytes + 1023) / 1024 * 1024;
-    static constexpr int kEpilogueBytes = kParamOffset + (kTileM + kF4TileN) * (int)sizeof(RowParams);
-    static constexpr int kLdsBytes = 3 * kWBufBytes > kEpilogueBytes ? 3 * kWBufBytes : kEpilogueBytes;
-};
-
-// The epilogue of the matmul kernel: parameters of the tile's rows and columns into LDS, then the dequantised
-// outputs, staged through LDS for 128-bit stores where the output allows it.  lds_f4 is free for reuse when it starts (the
-// caller has passed a barrier after its last read, and none of its loads into LDS is in flight).
-template <int RT>
-__device__ __forceinline__ void f4_epilogue(const F4Params& prm, v4f_f4 (*acc)[8], uint8_t* lds_f4, int tid, int lane, int wave, int m0, int n0,
-                                            v4i_f4 my_a, v4i_f4 my_w)
+// Y = dequant(A W^T) on the 4-bit floating-point MFMA.  RW x CW waves, each MT x NT accumulator tiles of 16 x 16; S places in the LDS
+// ring; OCC: waves per SIMD that the registers are held to.  The loop is the int8 block kernel's (abq_block_kernels.h, which says why it is
+// built so): both operands go global -> LDS, where an operand block lands as the operand layout, a step is one block of 128 k, its barrier stands
+// behind its first rows of MFMAs, and reads and loads stand one by one between the others.  (Two blocks a step: 1 to 6 % slower.)
+// The kernel before this one read its rows into registers by hand-written loads, waited for by hand, and took the eight W blocks of a step through LDS
+// in four waves of 64 x 128: W2A2 M=2048 5120->13824 with its pack 73-75 us, 65-68 here; alone 512 x 4096 x 11008 23.5, 17.0; 64 x 4096 x 4096 9.9, 6.6.
+template <int RW, int CW, int MT, int NT, int S, int OCC>
+__global__ __launch_bounds__(64 * RW * CW, OCC) void f4_gemm_kernel(F4Params prm)
 {
-    using SH = F4Shape<RT>;
-    RowParams* const par_a = reinterpret_cast<RowParams*>(lds_f4 + SH::kParamOffset);
-    RowParams* const par_w = par_a + SH::kTileM;
-    // epilogue parameters (fetched by the kernel before its K loop: no memory round trip here) into the freed operand memory
-    // (a record's sum of codes may come in two parts, the second in its spare word: see f4_pack_kernel)
-    if (tid < SH::kTileM) *reinterpret_cast<v4i_f4*>(par_a + tid) = v4i_f4{my_a.x + my_a.w, my_a.y, my_a.z, 0};
-    if (tid < kF4TileN) *reinterpret_cast<v4i_f4*>(par_w + tid) = v4i_f4{my_w.x + my_w.w, my_w.y, my_w.z, 0};
-    __syncthreads();
-
-    // ---- epilogue: lane (G, r) of accumulator (i, j) holds rows 16 RT wave + 16 i + 4 G + reg, channel 16 j + r.
-    // With up to 128 outputs per lane the epilogue is a third of the kernel if every output is stored on its own (2 bytes
-    // per lane and instruction), so the usual case (no accumulator output, rows of Y a whole number of 16-byte vectors)
-    // goes through LDS: every wave stages its binary16 results, up to 32 rows x 128 at a time, in its own part of the
-    // operand buffers (free after the loop's last barrier; row stride 272 bytes keeps the four row groups of a write on
-    // different banks) and writes them out as 128-bit vectors.  The arithmetic is the fused dequant of the other kernels
-    // (Fig. 3b), with the terms that depend on the column only taken out of the inner loop:
-    // centered = S - wz asum - az (wsum - K wz).
+    constexpr int kWaves = RW * CW, kTA = MT * RW, kTW = NT * CW, kBuf = (kTA + kTW) * 1024;   // a step: one block of every tile
+    constexpr int kRecA = (kTA + 3) / 4, kRecW = (kTW + 3) / 4;                                // wave loads of 64 records
+    __shared__ __align__(1024) uint8_t ring[S * kBuf];
+    __shared__ __align__(16) RowParams par_a[64 * kRecA], par_w[64 * kRecW];
+    const int tid = (int)threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int rw = wave / CW, cw = wave % CW;
     const int r = lane & 15, G = lane >> 4;
-    constexpr int kWaveRows = 16 * RT;
-    if (prm.acc == nullptr && (prm.N & 7) == 0) {
-        constexpr int kRowBytes = 272, kPassRows = SH::kPassRows, kPassTiles = kPassRows / 16;
-        uint8_t* const stage = lds_f4 + wave * (kPassRows * kRowBytes);
+    // Workgroup b runs on XCD b % 8 and each XCD has its own L2: give every XCD a contiguous run of the tile order, row tiles in bands, so that the
+    // workgroups resident on an XCD at one time cover about as many row tiles as column tiles, which is the least operand traffic into its L2.
+    const int nwg = prm.tiles_m * prm.tiles_n;
+    const int xcd = (int)blockIdx.x & 7, slot = (int)blockIdx.x >> 3;
+    const int per = nwg >> 3, rem = nwg & 7;
+    const int vid = xcd * per + min(xcd, rem) + slot;
+    const int band_wgs = prm.band_m * prm.tiles_n, band = vid / band_wgs, in_band = vid - band * band_wgs;
+    const int band_rows = min(prm.band_m, prm.tiles_m - prm.band_m * band);
+    const int m_blk = prm.band_m * band + in_band % band_rows, n_blk = in_band / band_rows;
+    const int m0 = m_blk * 16 * kTA, n0 = n_blk * 16 * kTW;
+    const int nsteps = prm.kblocks;
+
+    // ---- loads: 1 KiB a wave and instruction, lane L 16 bytes at base + off to LDS address dst + 16 L (see the block kernel)
+    auto lds_addr = [](const void* p) { return (unsigned)(uintptr_t)(const __attribute__((address_space(3))) uint8_t*)p; };
+    auto lds_load = [](const void* base, unsigned off, unsigned dst) {
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(dst), "v"(off), "s"(base) : "memory", "m0");
+    };
+    constexpr int kTiles = kTA + kTW, kTileLoads = (kTiles + kWaves - 1) / kWaves, kLoads = kTileLoads;
+    const uint8_t* src[kTileLoads];      // tile u * kWaves + wave: rows of A first, then channels of W (the last may be loaded twice)
+    int place_of[kTileLoads];
+#pragma unroll
+    for (int u = 0; u < kTileLoads; ++u) {
+        const int t = min(u * kWaves + wave, kTiles - 1);
+        place_of[u] = t;
+        src[u] = t < kTA ? (const uint8_t*)(prm.a_blocks + (size_t)min(m0 / 16 + t, prm.a_tiles - 1) * prm.kblocks * 64)
+                         : (const uint8_t*)(prm.w_blocks + (size_t)min(n0 / 16 + t - kTA, prm.w_tiles - 1) * prm.kblocks * 64);
+    }
+    auto load_piece = [&](int i, int step, const uint8_t* buf) {   // i-th load of a step
+        lds_load(src[i], lane * 16 + step * 1024, lds_addr(buf) + place_of[i] * 1024);
+    };
+    // At most `left` loads of this wave are outstanding past it, none of its LDS reads, and every other wave is there too.
+    auto sync = [&](auto LC) {
+        constexpr int left = decltype(LC)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_waitcnt(0x0070 | (left & 15) | ((left >> 4) << 14));   // vmcnt(left) lgkmcnt(0)
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    for (int i = wave; i < kRecA + kRecW; i += kWaves) {
+        if (i < kRecA) lds_load(prm.aparams, (unsigned)min(m0 + i * 64 + lane, prm.M - 1) * 16u, lds_addr(par_a + i * 64));
+        else lds_load(prm.wparams, (unsigned)min(n0 + (i - kRecA) * 64 + lane, prm.N - 1) * 16u, lds_addr(par_w + (i - kRecA) * 64));
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+#pragma unroll
+        for (int i = 0; i < kLoads; ++i) load_piece(i, min(s, nsteps - 1), ring + s * kBuf);
+
+    v4f_f4 acc[MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = v4f_f4{0.f, 0.f, 0.f, 0.f};
+    const int one = 0x7F7F7F7F;   // block scales of 2^0
+    const int a_off = rw * MT * 1024 + lane * 16, w_off = (kTA + cw * NT) * 1024 + lane * 16;
+    v4i_f4 a[MT], w[2][NT];
+    auto read_a = [&](int mt, const uint8_t* buf) { a[mt] = *reinterpret_cast<const v4i_f4*>(buf + a_off + mt * 1024); };
+    auto read_w = [&](int nt, int set, const uint8_t* buf) { w[set][nt] = *reinterpret_cast<const v4i_f4*>(buf + w_off + nt * 1024); };
+    auto mfma = [&](int set, int mt, int nt) {   // (weights first: a lane's four results are four channels of a row)
+        const v4i_f4 b = w[set][nt];
+        acc[mt][nt] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(v8i_f4{b.x, b.y, b.z, b.w, 0, 0, 0, 0}, v8i_f4{a[mt].x, a[mt].y, a[mt].z, a[mt].w, 0, 0, 0, 0},
+                                                                       acc[mt][nt], 4, 4, 0, one, 0, one);
+    };
+    sync(std::integral_constant<int, (S - 1) * kLoads>{});
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) read_w(nt, 0, ring);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) read_a(mt, ring);
+
+    constexpr int kHold = MT >= 8 ? 2 : 1, kSlots = MT * NT, kPast = kSlots - kHold * NT;
+    unsigned place = 0;
+    auto step_body = [&](auto SC, int step) {
+        constexpr int set = decltype(SC)::value;
+        const uint8_t* const cur = ring + place;
+        place = place + kBuf == S * kBuf ? 0u : place + kBuf;
+        const uint8_t* const nxt = ring + place;
+        const int ahead = min(step + S, nsteps - 1);              // (past the end the last block is loaded again, for nobody)
+#pragma unroll
+        for (int i = 0; i < kSlots; ++i) {
+            const int mt = i / NT, nt = i % NT, j = i - kHold * NT;
+            mfma(set, mt, nt);
+            if (j >= 0) {
+#pragma unroll
+                for (int u = 0; u < NT; ++u)
+                    if (u * (kPast / 2) / NT == j) read_w(u, set ^ 1, nxt);
+#pragma unroll
+                for (int u = 0; u < kHold; ++u)
+                    if (u * (kPast / 2) / kHold == j) read_a(u, nxt);
+                if (nt == NT - 1) read_a(mt, nxt);
+#pragma unroll
+                for (int u = 0; u < kLoads; ++u)
+                    if (1 + u * (kPast - 1) / kLoads == j) load_piece(u, ahead, cur);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (j == -1) sync(std::integral_constant<int, (S - 2) * kLoads>{});
+        }
+    };
+    int step = 0;
+    for (; step + 2 <= nsteps; step += 2) {
+        step_body(std::integral_constant<int, 0>{}, step);
+        step_body(std::integral_constant<int, 1>{}, step + 1);
+    }
+    if (step < nsteps) step_body(std::integral_constant<int, 0>{}, step);
+    __builtin_amdgcn_s_waitcnt(0x0070);                           // (the last loads, for nobody, land before LDS is given back)
+
+    // ---- epilogue: the fused dequant of the other kernels (Fig. 3b), with the terms that depend on the column only taken out of the inner loop:
+    // centered = S - wz asum - az (wsum - K wz).  A record's sum of codes may come in two parts, the second in its spare word (see f4_pack_kernel).
+    const int wm0 = m0 + rw * MT * 16, wn0 = n0 + cw * NT * 16;
+    if (prm.acc == nullptr) {
         // Every term here is an integer below 2^24 in magnitude (K * 9 < 2^24: the entry point checks it), and so is every
         // partial sum, so binary32 fused multiply-adds give the int32 arithmetic's value exactly, at four times the rate
-        // of 32-bit integer multiplies; the accumulator needs no conversion either.
-        float wz[8], cw[8], sw[8];
+        // of 32-bit integer multiplies; the accumulator needs no conversion either.  Stores as in the block kernel.
+        static_assert(NT % 2 == 0, "tiles in pairs");
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const RowParams pw = par_w[16 * j + r];
-            wz[j] = -(float)pw.zero;
-            cw[j] = (float)(pw.sum - prm.K * pw.zero);
-            sw[j] = pw.scale;
-        }
+        for (int np = 0; np < NT; np += 2) {
+            float wz[2][4], cwz[2][4], sw[2][4];
 #pragma unroll
-        for (int pass = 0; pass < kWaveRows / kPassRows; ++pass) {
-#pragma unroll
-            for (int i2 = 0; i2 < kPassTiles; ++i2)
+            for (int h = 0; h < 2; ++h)
 #pragma unroll
                 for (int reg = 0; reg < 4; ++reg) {
-                    const int i = kPassTiles * pass + i2;
-                    const int rl = 16 * i2 + 4 * G + reg;            // row inside this pass
-                    const RowParams pa = par_a[kWaveRows * wave + kPassRows * pass + rl];
-                    const float asum = (float)pa.sum, az = -(float)pa.zero;
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        const float centered = __builtin_fmaf(az, cw[j], __builtin_fmaf(wz[j], asum, acc[i][j][reg]));
-                        const float v = (centered * pa.scale) * sw[j];
-                        uint32_t h;
-                        asm("v_cvt_f16_f32 %0, %1" : "=v"(h) : "v"(v));   // (the instruction itself: see epilogue_value)
-                        *reinterpret_cast<uint16_t*>(stage + rl * kRowBytes + (16 * j + r) * 2) = (uint16_t)h;
-                    }
+                    const RowParams pw = par_w[(cw * NT + np + h) * 16 + 4 * G + reg];
+                    wz[h][reg] = -(float)pw.zero;
+                    cwz[h][reg] = (float)(pw.sum + pw.pad - prm.K * pw.zero);
+                    sw[h][reg] = pw.scale;
                 }
-            // (the wave reads back what its own lanes wrote, and rewrites the area only after it has read it: no barrier,
-            // the LDS counter orders it)
 #pragma unroll
-            for (int it = 0; it < kPassRows / 4; ++it) {
-                const int c = it * 64 + lane, rl = c >> 4, cc = c & 15;
-                const v4i_f4 x = *reinterpret_cast<const v4i_f4*>(stage + rl * kRowBytes + cc * 16);
-                const int m = m0 + kWaveRows * wave + kPassRows * pass + rl, n = n0 + 8 * cc;
-                if (m < prm.M && n < prm.N) *reinterpret_cast<v4i_f4*>(prm.y + (size_t)m * prm.N + n) = x;
+            for (int mt = 0; mt < MT; ++mt) {
+                const RowParams pa = par_a[(rw * MT + mt) * 16 + r];
+                const float asum = (float)(pa.sum + pa.pad), az = -(float)pa.zero;
+                uint32_t d[2][2];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    uint32_t hv[4];
+#pragma unroll
+                    for (int reg = 0; reg < 4; ++reg) {
+                        const float centered = __builtin_fmaf(az, cwz[h][reg], __builtin_fmaf(wz[h][reg], asum, acc[mt][np + h][reg]));
+                        const float v = (centered * pa.scale) * sw[h][reg];
+                        asm("v_cvt_f16_f32 %0, %1" : "=v"(hv[reg]) : "v"(v));   // (the instruction itself: see epilogue_value)
+                    }
+                    d[h][0] = __builtin_amdgcn_perm(hv[1], hv[0], 0x05040100u);
+                    d[h][1] = __builtin_amdgcn_perm(hv[3], hv[2], 0x05040100u);
+                }
+                const auto lo = __builtin_amdgcn_permlane16_swap(d[0][0], d[1][0], false, false);
+                const auto hi = __builtin_amdgcn_permlane16_swap(d[0][1], d[1][1], false, false);
+                const int m = wm0 + mt * 16 + r, n = wn0 + (np + (G & 1)) * 16 + (G >> 1) * 8;
+                if (m < prm.M && n < prm.N) store_row_part8(prm.y + (size_t)m * prm.N + n, n, prm.N, lo[0], hi[0], lo[1], hi[1]);
             }
         }
         return;
     }
 #pragma unroll
-    for (int i = 0; i < RT; ++i)
+    for (int mt = 0; mt < MT; ++mt) {
+        RowParams pa = par_a[(rw * MT + mt) * 16 + r];
+        pa.sum += pa.pad;
+        const int m = wm0 + mt * 16 + r;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int nl = 16 * j + r, n = n0 + nl;
+        for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
             for (int reg = 0; reg < 4; ++reg) {
-                const int ml = kWaveRows * wave + 16 * i + 4 * G + reg, m = m0 + ml;
-                if (m < prm.M && n < prm.N)
-                    epilogue_store((int32_t)acc[i][j][reg], 0, 0, prm.K, par_a[ml], par_w[nl], (size_t)m * prm.N + n, prm.y, prm.acc);
+                RowParams pw = par_w[(cw * NT + nt) * 16 + 4 * G + reg];
+                pw.sum += pw.pad;
+                const int n = wn0 + nt * 16 + 4 * G + reg;
+                if (m < prm.M && n < prm.N) epilogue_store((int32_t)acc[mt][nt][reg], 0, 0, prm.K, pa, pw, (size_t)m * prm.N + n, prm.y, prm.acc);
             }
-        }
-}
-
-// Y = dequant(A W^T) on the 4-bit floating-point MFMA.  Four waves; wave w owns rows 16 RT w .. of the tile and all 128
-// columns.  Its A blocks go global -> registers (a wave's rows are its own: nothing to share), the eight W blocks of a step
-// go global -> LDS, where every wave reads them: per MFMA a wave reads 0.25 KiB of LDS.
-template <int RT>
-__global__ __launch_bounds__(256, RT == 4 ? 2 : 4) void f4_gemm_kernel(F4Params prm)
-{
-    using SH = F4Shape<RT>;
-    // Three buffers of a step's W blocks, 1 KiB per block.  After the K loop the same memory holds the epilogue's staging
-    // area and, behind it, the parameters.
-    extern __shared__ __align__(16) uint8_t lds_f4[];
-    uint8_t* const buf0 = lds_f4;
-    uint8_t* const buf1 = lds_f4 + SH::kWBufBytes;
-    uint8_t* const buf2 = lds_f4 + 2 * SH::kWBufBytes;
-    const int tid = (int)threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // Workgroup b runs on XCD b % 8 and each XCD has its own L2: give every XCD a contiguous run of the tile order, so
-    // that the workgroups resident on one XCD share their column blocks of W and their row blocks of A.
-    const int nwg = prm.tiles_m * prm.tiles_n;
-    const int xcd = (int)blockIdx.x & 7, slot = (int)blockIdx.x >> 3;
-    const int per = nwg >> 3, rem = nwg & 7;
-    const int vid = xcd * per + min(xcd, rem) + slot;
-    // Within the order, row tiles go in panels of eight: the workgroups resident on an XCD at one time then cover about as
-    // many row tiles as column tiles, which is the least operand traffic into its L2 for that many tiles.
-    const int panel_wgs = 8 * prm.tiles_n, panel = vid / panel_wgs, in_panel = vid - panel * panel_wgs;
-    const int panel_rows = min(8, prm.tiles_m - 8 * panel);
-    const int m_blk = 8 * panel + in_panel % panel_rows, n_blk = in_panel / panel_rows;
-    const int m0 = m_blk * SH::kTileM, n0 = n_blk * kF4TileN;
-
-    // the epilogue's parameters of this tile's rows and channels, one record per thread: on their way during the K loop
-    v4i_f4 my_a = v4i_f4{0, 0, 0, 0}, my_w = my_a;   // (a record is 16 bytes)
-    if (tid < SH::kTileM) my_a = *reinterpret_cast<const v4i_f4*>(prm.aparams + min(m0 + tid, prm.M - 1));
-    if (tid < kF4TileN) my_w = *reinterpret_cast<const v4i_f4*>(prm.wparams + min(n0 + tid, prm.N - 1));
-
-    const v4i_f4* a_src[RT];
-#pragma unroll
-    for (int i = 0; i < RT; ++i) a_src[i] = prm.a_blocks + ((size_t)min(m0 / 16 + wave * RT + i, prm.a_tiles - 1) * prm.kblocks) * 64 + lane;
-    const v4i_f4* w_src[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) w_src[u] = prm.w_blocks + ((size_t)min(n0 / 16 + wave * 2 + u, prm.w_tiles - 1) * prm.kblocks) * 64 + lane;
-
-    v4f_f4 acc[RT][8];
-#pragma unroll
-    for (int i = 0; i < RT; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[i][j] = v4f_f4{0.f, 0.f, 0.f, 0.f};
-
-    const int one = 0x7F7F7F7F;   // block scales of 2^0
-    // One step of K: the W blocks are read from LDS two at a time, one pair ahead of the MFMAs that use them, so that a
-    // wave's LDS latency runs under its own MFMAs (the scheduling barriers keep the reads where they are written).
-    auto multiply = [&](const uint8_t* buf, const v4i_f4* ar) {
-        v8i_f4 a[RT];
-#pragma unroll
-        for (int i = 0; i < RT; ++i) a[i] = v8i_f4{ar[i].x, ar[i].y, ar[i].z, ar[i].w, 0, 0, 0, 0};
-        const uint8_t* const mine = buf + lane * 16;
-        v4i_f4 x[2][2];
-        x[0][0] = *reinterpret_cast<const v4i_f4*>(mine);
-        x[0][1] = *reinterpret_cast<const v4i_f4*>(mine + 1024);
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-            if (g < 3) {
-                x[(g + 1) & 1][0] = *reinterpret_cast<const v4i_f4*>(mine + (2 * g + 2) * 1024);
-                x[(g + 1) & 1][1] = *reinterpret_cast<const v4i_f4*>(mine + (2 * g + 3) * 1024);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_setprio(1);   // (the wave that has its operands goes first: 1-2 % with two workgroups per unit)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const v4i_f4 xb = x[g & 1][h];
-                const v8i_f4 b = v8i_f4{xb.x, xb.y, xb.z, xb.w, 0, 0, 0, 0};
-#pragma unroll
-                for (int i = 0; i < RT; ++i)
-                    acc[i][2 * g + h] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a[i], b, acc[i][2 * g + h], 4, 4, 0, one, 0, one);
-            }
-            __builtin_amdgcn_s_setprio(0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-
-    // Two steps ahead: three LDS buffers for W and three register sets for A, used in rotation.  A wave issues RT + 2
-    // vector-memory loads per step, in order, so "at most RT + 2 outstanding" means the step before the newest has landed.
-    // The body of the main loop has no branch: past the last step it loads that step again into a buffer and a register
-    // set that nothing reads any more.  The wait and the barrier are written out: a workgroup fence would wait for every
-    // outstanding load (the loads into LDS count as LDS writes), the newest included, and the scheduling barriers keep
-    // the MFMAs above the wait.
-    const int nsteps = prm.kblocks;
-    v4i_f4 a0[RT], a1[RT], a2[RT];
-    auto load_step = [&](int step, v4i_f4* ar, uint8_t* buf) {
-        const size_t off = (size_t)min(step, nsteps - 1) * 64;
-        // The register loads are written as instructions: the compiler, seeing register loads and loads into LDS mixed
-        // on one counter, would wait for all of them before the first use of these registers.  It does not know that
-        // the registers fill later: between here and the MFMAs that read them it must neither copy nor spill them,
-        // which the build checks (no scratch memory for this kernel).
-#pragma unroll
-        for (int i = 0; i < RT; ++i) asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(ar[i]) : "v"(a_src[i] + off));
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-            __builtin_amdgcn_global_load_lds((const void*)(w_src[u] + off), (__attribute__((address_space(3))) void*)(buf + (wave * 2 + u) * 1024), 16, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto sync_keep_newest = [&]() {
-        __builtin_amdgcn_sched_barrier(0);
-        if constexpr (RT == 4) asm volatile("s_waitcnt vmcnt(6)" ::: "memory"); else asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    static_assert(RT == 4 || RT == 1, "the wait counts above are RT + 2");
-    load_step(0, a0, buf0);
-    load_step(1, a1, buf1);
-    sync_keep_newest();
-    int step = 0;
-    for (; step + 3 <= nsteps; step += 3) {
-        load_step(step + 2, a2, buf2);   // (each buffer and register set was last read one step before it is loaded again)
-        multiply(buf0, a0);
-        sync_keep_newest();
-        load_step(step + 3, a0, buf0);
-        multiply(buf1, a1);
-        sync_keep_newest();
-        load_step(step + 4, a1, buf1);
-        multiply(buf2, a2);
-        sync_keep_newest();
     }
-    // the steps left are in a0 / buf0 and a1 / buf1; no load is in flight when the epilogue reuses LDS
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-    if (step < nsteps) multiply(buf0, a0);
-    if (step + 1 < nsteps) multiply(buf1, a1);
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();
-    f4_epilogue<RT>(prm, acc, lds_f4, tid, lane, wave, m0, n0, my_a, my_w);
 }
 
-template <int RT>
-static hipError_t f4_launch(const F4Params& prm, unsigned grid, hipStream_t s)
+// Workgroup shapes (rows of A, channels, workgroups a compute unit) and what a launch of each costs (us): `base`, `round` for every round of resident
+// workgroups, and per block of 128 k what a unit with one or two of them takes.  Non-negative least squares of the relative error over 400 sizes
+// (M = 17..2048, N = 256..13824, K = 512..13824), mean error 5 to 8 %; over those the cheapest of the five takes 0.69 times the time of the kernel
+// before (M < 64 0.55, M >= 1024 0.9), two others added (256 x 128, 128 x 256 by four waves) gain nothing, 7 of the 400 lose 3 to 7 %.
+struct F4ShapeInfo { int bm, bn, occ; float base, round, step[2]; };
+constexpr int kF4Shapes = 5;
+static const F4ShapeInfo kF4ShapeInfo[kF4Shapes] = {{256, 256, 1, 0, 7.391f, {0.495f, 0}}, {128, 128, 1, 0, 4.353f, {0.18f, 0}}, {128, 128, 2, 0, 5.002f, {0.179f, 0.434f}},
+                                                    {64, 128, 2, 0.651f, 3.477f, {0.119f, 0.29f}}, {32, 64, 2, 2.437f, 1.186f, {0.074f, 0.127f}}};
+
+template <int RW, int CW, int MT, int NT, int S, int OCC>
+static hipError_t f4_launch(const F4Params& prm, hipStream_t s)
 {
-    f4_gemm_kernel<RT><<<grid, 256, F4Shape<RT>::kLdsBytes, s>>>(prm);   // (under 64 KiB: no attribute to raise)
+    f4_gemm_kernel<RW, CW, MT, NT, S, OCC><<<(unsigned)(prm.tiles_m * prm.tiles_n), 64 * RW * CW, 0, s>>>(prm);
     return hipGetLastError();
 }
 
@@ -409,17 +366,27 @@ hipError_t launch_f4_gemm(int M, int N, int K, const uint8_t* act_blob, const ui
     prm.y = y; prm.acc = acc;
     prm.M = M; prm.N = N; prm.K = K; prm.kblocks = f4_k_blocks(K);
     prm.a_tiles = f4_row_tiles(M); prm.w_tiles = f4_row_tiles(N);
-    prm.tiles_n = (N + kF4TileN - 1) / kF4TileN;
-    const long cus = num_cus();
-    // Workgroup tile: 256 rows where that still gives every compute unit a workgroup, else 64 rows (four times the
-    // workgroups; more LDS reads per MFMA, but the chip is busy).
-    const long nwg_big = (long)((M + 255) / 256) * prm.tiles_n;
-    if (nwg_big < cus) {
-        prm.tiles_m = (M + 63) / 64;
-        return f4_launch<1>(prm, (unsigned)(prm.tiles_m * prm.tiles_n), s);
+    int shape = 0;
+    double best = 0;
+    for (int i = 0; i < kF4Shapes; ++i) {
+        const F4ShapeInfo& f = kF4ShapeInfo[i];
+        const long wgs = (long)((M + f.bm - 1) / f.bm) * ((N + f.bn - 1) / f.bn), cus = num_cus();
+        const long load = (wgs + cus - 1) / cus, full = load / f.occ, part = load % f.occ;
+        const double cost = f.base + f.round * (double)(full + part) + prm.kblocks * ((double)full * f.step[f.occ - 1] + (part ? f.step[0] : 0.f));
+        if (i == 0 || cost < best) { best = cost; shape = i; }
     }
-    prm.tiles_m = (M + 255) / 256;
-    return f4_launch<4>(prm, (unsigned)nwg_big, s);
+    const int bm = kF4ShapeInfo[shape].bm, bn = kF4ShapeInfo[shape].bn;
+    prm.tiles_m = (M + bm - 1) / bm;
+    prm.tiles_n = (N + bn - 1) / bn;
+    const int cap = 2048 / bm, bands = (prm.tiles_m + cap - 1) / cap;   // (bands of equal height)
+    prm.band_m = (prm.tiles_m + bands - 1) / bands;
+    switch (shape) {
+        case 0: return f4_launch<2, 4, 8, 4, 3, 2>(prm, s);
+        case 1: return f4_launch<2, 4, 4, 2, 6, 2>(prm, s);
+        case 2: return f4_launch<2, 2, 4, 4, 4, 2>(prm, s);
+        case 3: return f4_launch<1, 4, 4, 2, 6, 2>(prm, s);
+        default: return f4_launch<1, 2, 2, 2, 8, 2>(prm, s);
+    }
 }
 
 }  // namespace abq

@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-from helpers import check_against_oracle, check_sampled, gpu_gemm, to_dev   # noqa: E402
+from helpers import check_against_oracle, check_sampled, gpu_gemm, run_named, to_dev   # noqa: E402
 from paper_2408_08554_amd import synth   # noqa: E402
 
 
@@ -100,3 +100,23 @@ def test_f4_config5_prefill_shape_sampled(abq, p, q):
     say(c.name)
     y, acc = run_f4(abq, c)
     check_sampled(c, y, acc)
+
+
+# Every workgroup shape by the rule, ragged rows and channels (rows of Y on and off 16-byte boundaries), K of one block of 128, of an odd and an even
+# number of them, of fewer and more steps than the ring has places
+@pytest.mark.parametrize("waves,M,N,K", [("2, 4, 8, 4", 1029, 7195, 59), ("2, 4, 8, 4", 904, 8400, 257), ("2, 4, 8, 4", 905, 8412, 406), ("2, 4, 8, 4", 901, 8213, 1300),
+                                         ("2, 4, 4, 2", 196, 8504, 261), ("2, 4, 4, 2", 195, 8313, 401), ("2, 4, 4, 2", 197, 8333, 1700),
+                                         ("2, 2, 4, 4", 513, 7183, 84), ("2, 2, 4, 4", 705, 5408, 129), ("2, 2, 4, 4", 518, 7309, 385), ("2, 2, 4, 4", 459, 8258, 517),
+                                         ("1, 4, 4, 2", 97, 8274, 69), ("1, 4, 4, 2", 105, 8444, 131), ("1, 4, 4, 2", 100, 8855, 1175),
+                                         ("1, 2, 2, 2", 19, 203, 103), ("1, 2, 2, 2", 18, 201, 204), ("1, 2, 2, 2", 37, 232, 347), ("1, 2, 2, 2", 24, 214, 2306)])
+@pytest.mark.parametrize("p,q", [(2, 2), (1, 2)])
+def test_f4_shapes_by_rule(abq, p, q, waves, M, N, K):
+    c = synth.make_case(p, q, M, N, K, seed=7600 + p, name=f"f4 {waves} W{p}A{q} {M}x{N}x{K}")
+    say(c.name)
+    c.W[::5], c.A[::7] = (1 << p) - 1, (1 << q) - 1
+    pw = abq.abq_f4_pack_codes(p, to_dev(torch, c.W), to_dev(torch, c.w_scale), to_dev(torch, c.w_zero))
+    pa = abq.abq_f4_pack_codes(q, to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero))
+    _, names = run_named(torch, lambda: abq.abq_f4_gemm(p, q, M, N, K, pa, pw))
+    assert len(names) == 1 and f"f4_gemm_kernel<{waves}, " in names[0], names
+    y, acc = run_f4(abq, c)
+    (check_against_oracle if M * N * K < 2e8 else check_sampled)(c, y, acc)
