@@ -10,22 +10,22 @@ static int shape_bn(int p, int shape) { return shape == 0 && p == 7 ? 192 : kSha
 
 // What a launch costs (us): `base`, `round` for every round of resident workgroups (first loads, epilogue, and the gap to the next workgroup),
 // and per step of 128 k what a unit with 1, 2 or 3 of the shape's workgroups takes.  Non-negative least squares of the relative error over
-// 2400 sizes that the K-split kernel leaves (M = 48..2048, N = 256..13824, K = 512..13824), mean error 7 to 13 %.
+// 1830 sizes that the K-split kernel leaves (M = 49..2048, N = 256..13824, K = 512..13824), mean error 4 to 9 %, tiled 9 to 14 %.
 struct Cost { float base, round, step[3]; };
 struct WidthCosts { Cost block[kBlockShapes], tiled[3]; };   // tiled: 64 x 64, 64 x 128, 64 x 256
 static const WidthCosts kCosts[6] = {
-    {{{0, 9.436f, {1.027f, 0, 0}}, {0.125f, 6.141f, {0.471f, 0, 0}}, {1.062f, 4.048f, {0.349f, 0, 0}}, {2.211f, 3.673f, {0.353f, 0.7f, 0}}, {2.843f, 1.716f, {0.226f, 0.374f, 0}}},   // p = 1, 2
-     {{4.838f, 0, {0.139f, 0.269f, 0.4f}}, {4.947f, 1.356f, {0.065f, 0.452f, 0.614f}}, {8.31f, 2.498f, {0.339f, 0.701f, 0}}}},
-    {{{0, 10.526f, {1.165f, 0, 0}}, {0.719f, 6.203f, {0.62f, 0, 0}}, {1.303f, 4.349f, {0.438f, 0, 0}}, {2.376f, 3.92f, {0.457f, 0.878f, 0}}, {3.074f, 1.855f, {0.286f, 0.465f, 0}}},   // p = 3
-     {{5.21f, 0, {0.131f, 0.31f, 0.464f}}, {3.924f, 2.746f, {0.324f, 0.551f, 0.798f}}, {}}},
-    {{{0, 9.576f, {1.01f, 0, 0}}, {0, 6.327f, {0.455f, 0, 0}}, {0.661f, 4.709f, {0.346f, 0, 0}}, {0.766f, 3.528f, {0.467f, 0.762f, 0}}, {1.904f, 2.828f, {0.21f, 0.418f, 0}}},   // p = 4
-     {{4.788f, 0, {0.15f, 0.281f, 0.468f}}, {2.312f, 4.769f, {0, 0.44f, 0.662f}}, {}}},
-    {{{0, 9.587f, {1.182f, 0, 0}}, {0, 6.626f, {0.636f, 0, 0}}, {0.552f, 4.801f, {0.462f, 0, 0}}, {2.267f, 2.933f, {0.516f, 0.977f, 0}}, {1.979f, 2.725f, {0.293f, 0.533f, 0}}},   // p = 5, 6
-     {{4.728f, 0, {0.187f, 0.305f, 0.569f}}, {4.94f, 1.929f, {0.377f, 0.588f, 0.853f}}, {}}},
-    {{{0, 9.063f, {1.151f, 0, 0}}, {0, 7.177f, {0.86f, 0, 0}}, {0.709f, 5.01f, {0.614f, 0, 0}}, {0.842f, 5.436f, {0.634f, 1.187f, 0}}, {2.537f, 2.546f, {0.389f, 0.686f, 0}}},   // p = 7
-     {{4.918f, 0, {0.235f, 0.424f, 0.702f}}, {0.179f, 6.379f, {0.148f, 0.793f, 1.114f}}, {}}},
-    {{{0, 9.726f, {1.011f, 0, 0}}, {0, 6.513f, {0.535f, 0, 0}}, {0, 5.063f, {0.368f, 0, 0}}, {0, 4.122f, {0.537f, 0.888f, 0}}, {1.416f, 3.033f, {0.27f, 0.559f, 0}}},   // p = 8
-     {{4.527f, 0, {0.21f, 0.335f, 0.602f}}, {3.166f, 3.019f, {0.15f, 0.554f, 0.939f}}, {}}},
+    {{{0, 9.144f, {0.985f, 0, 0}}, {0.391f, 5.682f, {0.469f, 0, 0}}, {1.124f, 3.7f, {0.344f, 0, 0}}, {1.943f, 3.554f, {0.343f, 0.679f, 0}}, {2.85f, 1.66f, {0.214f, 0.351f, 0}}},   // p = 1, 2
+     {{4.87f, 0, {0.137f, 0.26f, 0.399f}}, {4.166f, 2.417f, {0, 0.409f, 0.59f}}, {5.59f, 2.758f, {0.336f, 0.758f, 0}}}},
+    {{{0, 9.718f, {1.153f, 0, 0}}, {0.81f, 5.817f, {0.627f, 0, 0}}, {1.535f, 3.576f, {0.447f, 0, 0}}, {2.717f, 3.159f, {0.466f, 0.857f, 0}}, {3.741f, 1.113f, {0.271f, 0.475f, 0}}},   // p = 3
+     {{0, 5.241f, {0.149f, 0.29f, 0.478f}}, {9.106f, 0.731f, {0, 0.492f, 0.649f}}, {}}},
+    {{{0, 9.251f, {0.979f, 0, 0}}, {0, 6.093f, {0.453f, 0, 0}}, {1.017f, 4.042f, {0.347f, 0, 0}}, {0.065f, 3.967f, {0.452f, 0.766f, 0}}, {2.17f, 2.39f, {0.204f, 0.406f, 0}}},   // p = 4
+     {{4.871f, 0, {0.147f, 0.277f, 0.444f}}, {2.393f, 3.984f, {0.459f, 0.467f, 0.652f}}, {}}},
+    {{{0, 9.543f, {1.129f, 0, 0}}, {0.492f, 5.959f, {0.635f, 0, 0}}, {1.149f, 4.056f, {0.455f, 0, 0}}, {2.163f, 2.877f, {0.505f, 0.931f, 0}}, {2.248f, 2.435f, {0.286f, 0.504f, 0}}},   // p = 5, 6
+     {{5.057f, 0, {0.158f, 0.31f, 0.526f}}, {6.833f, 0.752f, {0.341f, 0.574f, 0.853f}}, {}}},
+    {{{0, 8.586f, {1.139f, 0, 0}}, {0.668f, 6.019f, {0.875f, 0, 0}}, {1.225f, 4.196f, {0.613f, 0, 0}}, {3.875f, 2.112f, {0.63f, 1.185f, 0}}, {3.137f, 1.839f, {0.384f, 0.675f, 0}}},   // p = 7
+     {{4.901f, 0, {0.228f, 0.427f, 0.646f}}, {0.597f, 6.999f, {0, 0.621f, 1.126f}}, {}}},
+    {{{0, 9.307f, {0.99f, 0, 0}}, {0, 6.138f, {0.541f, 0, 0}}, {0.046f, 4.672f, {0.366f, 0, 0}}, {0, 3.718f, {0.548f, 0.852f, 0}}, {1.545f, 2.573f, {0.283f, 0.555f, 0}}},   // p = 8
+     {{4.162f, 0, {0.234f, 0.349f, 0.628f}}, {4.02f, 2.662f, {0, 0.594f, 0.86f}}, {}}},
 };
 
 static double cost_of(const Cost& c, int M, int N, int K, int bm, int bn, int occ)
@@ -36,9 +36,10 @@ static double cost_of(const Cost& c, int M, int N, int K, int bm, int bn, int oc
     return c.base + c.round * (double)(full + (part > 0)) + steps * ((double)full * c.step[occ - 1] + (part ? c.step[part - 1] : 0.f));
 }
 
-// The cheapest shape by the costs above, unless the tiled kernel's is 6 % below it (its 64 x 64 tiles, three workgroups a unit, where K is
-// short or the output leaves the larger tiles' last round nearly empty).  Over those sizes the choice is 1.6 % from the best of all
-// of them and takes 0.92 times the tiled kernel's time (M = 256..2048 0.91), 3 % of the sizes lose 3 % or more.
+// The cheapest shape by the costs above, unless the tiled kernel's is 7 % below it, 10 % for widths of more than one plane group, whose tiled
+// costs scatter more (its 64 x 64 tiles, three workgroups a unit, where K is short or the output leaves the larger tiles' last round
+// nearly empty; W6A6 M=128 4096->11008 with its quantizer 17.1 us there, 18.2 here).  Over those sizes the choice takes 0.86 times the
+// tiled kernel's time for p = 1, 2, 4, 8 and 0.93 times for the others; 2.0 and 0.7 % of the sizes lose 3 to 12 %.
 // A plan-table entry with a knob of the tiled kernel asks for that; so does a call for the int32 accumulator, which only that kernel writes.
 bool block_plan(const GemmArgs& g, const WeightLayout& W, int* shape)
 {
@@ -56,7 +57,8 @@ bool block_plan(const GemmArgs& g, const WeightLayout& W, int* shape)
     int mt, ntw;
     tiled_shape_by_rule(g.p, g.M, g.N, g.K, &mt, &ntw);
     if (mt == 8 || (g.p >= 3 && ntw == 4)) return true;   // (one of its large tiles: those lose at every such size)
-    return cost_of(w.tiled[ntw / 2], g.M, g.N, g.K, 16 * mt, 64 * ntw, ntw == 4 ? 2 : 3) * 0.94 >= best;
+    const double lead = group_count(g.p) > 1 ? 0.90 : 0.93;
+    return cost_of(w.tiled[ntw / 2], g.M, g.N, g.K, 16 * mt, 64 * ntw, ntw == 4 ? 2 : 3) * lead >= best;
 }
 
 hipError_t launch_gemm_block(const GemmArgs& g, const ActLayout& A, const WeightLayout& W, int shape, hipStream_t s)
@@ -95,17 +97,17 @@ hipError_t launch_gemm_block(const GemmArgs& g, const ActLayout& A, const Weight
 // ---- per-group weights
 static const BkShapeInfo kG128Shapes[2] = {{256, 128, 1}, {128, 128, 2}};   // (as in block_g128_launch)
 
-// Costs as above, from 1500 sizes of M = 48..2048 that the K-split kernel leaves; the tiled per-group kernel's by its tiles (64 x 64, 64 x 128).
+// Costs as above, from 1700 sizes of M = 48..2048, K > 1536 that the K-split kernel leaves; the tiled per-group kernel's by its tiles (64 x 64, 64 x 128).
 static const struct { Cost block[2], tiled[2]; } kG128Costs[2] = {
-    {{{0, 7.012f, {1.282f, 0, 0}}, {3.391f, 2.608f, {0.741f, 1.423f, 0}}},         // p = 1, 2, 4 (64 x 64: three workgroups a unit)
-     {{0, 4.617f, {0, 0.466f, 0.705f}}, {3.42f, 2.239f, {0.417f, 0.89f, 0}}}},
-    {{{0.394f, 6.649f, {1.388f, 0, 0}}, {3.63f, 2.345f, {0.816f, 1.542f, 0}}},     // p = 3, 5, 6
-     {{3.511f, 0.924f, {0.233f, 0.548f, 0}}, {3.28f, 2.088f, {0.471f, 1.026f, 0}}}},
+    {{{0, 5.923f, {1.266f, 0, 0}}, {4.608f, 0.765f, {0.742f, 1.34f, 0}}},          // p = 1, 2, 4 (64 x 64: three workgroups a unit)
+     {{0, 4.456f, {0, 0.465f, 0.694f}}, {4.193f, 1.724f, {0.436f, 0.865f, 0}}}},
+    {{{0, 6.13f, {1.378f, 0, 0}}, {4.757f, 0.762f, {0.812f, 1.453f, 0}}},          // p = 3, 5, 6
+     {{4.612f, 0.038f, {0.249f, 0.533f, 0}}, {5.148f, 1.313f, {0.476f, 0.989f, 0}}}},
 };
 
-// The cheaper shape where it is 6 % below the tiled per-group kernel, on more than twelve groups of K (up to there the rounds' own
-// cost decides, and this kernel takes 1.10 times the other's time on average).  It takes a fifth of those sizes, at 0.88 times the time (W4A8 M=1024
-// 5120->13824 157 / 130 us), and none at 1.03 times or more but one in a thousand.  7- and 8-bit weights have no room for z in the byte.
+// The cheaper shape unless the tiled per-group kernel is 6 % below it, on more than twelve groups of K (up to there the rounds' own
+// cost decides, and the better shape takes 1.10 times the other kernel's time on average).  It takes a third of those sizes, at 0.86 times the time (W4A8
+// M=1024 5120->13824 157 / 130 us); 0.5 % of the sizes lose 3 to 6 %.  7- and 8-bit weights have no room for z in the byte.
 bool block_g128_plan(const GemmArgs& g, int* shape)
 {
     if (g.p > 6 || g.K <= 1536) return false;

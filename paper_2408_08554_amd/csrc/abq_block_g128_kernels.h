@@ -266,7 +266,6 @@ __global__ __launch_bounds__(64 * RW * CW, OCC) void block_g128_kernel(BlockG128
     // ---- epilogue: Y = half(a_scale * sum over groups); lanes exchange as in block_kernel
     static_assert(NT == 2, "tiles in pairs");
     const int n = n0 + (cw * NT + (G & 1)) * 16 + (G >> 1) * 8;
-    const bool vec_ok = (prm.N & 7) == 0;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
         const int row = (rw * MT + mt) * 16 + r, m = m0 + row;
@@ -285,16 +284,7 @@ __global__ __launch_bounds__(64 * RW * CW, OCC) void block_g128_kernel(BlockG128
         }
         const auto lo = __builtin_amdgcn_permlane16_swap(d[0][0], d[1][0], false, false);
         const auto hi = __builtin_amdgcn_permlane16_swap(d[0][1], d[1][1], false, false);
-        if (m < prm.M && n < prm.N) {
-            uint16_t* dst = prm.y + (size_t)m * prm.N + n;
-            const uint32_t w4[4] = {lo[0], hi[0], lo[1], hi[1]};
-            if (vec_ok) *reinterpret_cast<uint4*>(dst) = uint4{w4[0], w4[1], w4[2], w4[3]};
-            else {
-#pragma unroll
-                for (int e = 0; e < 8; ++e)
-                    if (n + e < prm.N) dst[e] = (uint16_t)(w4[e >> 1] >> (16 * (e & 1)));
-            }
-        }
+        if (m < prm.M && n < prm.N) store_row_part8(prm.y + (size_t)m * prm.N + n, n, prm.N, lo[0], hi[0], lo[1], hi[1]);
     }
 }
 

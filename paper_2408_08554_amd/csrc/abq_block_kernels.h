@@ -16,7 +16,7 @@
 // Before / now (tiled kernel / this one, rows packed, replays): W4A4 M=2048 5120->13824 135 / 111 us, W8A8 147 / 119, M=1024 70 / 51 and
 // 79 / 60, W8A8 M=512 4096->11008 32.5 / 26.5, 11008->4096 42 / 29.
 #pragma once
-#include "abq_internal.h"
+#include "abq_rows.h"
 
 #include <type_traits>
 
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(64 * RW * CW, OCC) void block_kernel(BlockParams pr
     }
     __syncthreads();
     const int wm0 = m0 + rw * MT * 16, wn0 = n0 + cw * NT * 16;
-    const bool vec_ok = (prm.N & 7) == 0;                        // rows of Y 16-byte aligned
+    const bool vec_ok = (prm.N & 3) == 0;                        // (of an odd tile: rows of Y 8-byte aligned)
     auto dequant = [&](auto narrow, auto plain) {
 #pragma unroll
         for (int np = 0; np < NT; np += 2) {
@@ -361,13 +361,12 @@ __global__ __launch_bounds__(64 * RW * CW, OCC) void block_kernel(BlockParams pr
                 }
                 if (prm.y && m < prm.M && n < prm.N) {
                     uint16_t* dst = prm.y + (size_t)m * prm.N + n;
-                    if (vec_ok) {
-                        if (two == 2) *reinterpret_cast<uint4*>(dst) = uint4{w4[0], w4[1], w4[2], w4[3]};
-                        else *reinterpret_cast<uint2*>(dst) = uint2{w4[0], w4[1]};
-                    } else {
+                    if (two == 2) store_row_part8(dst, n, prm.N, w4[0], w4[1], w4[2], w4[3]);
+                    else if (vec_ok) *reinterpret_cast<uint2*>(dst) = uint2{w4[0], w4[1]};
+                    else {
 #pragma unroll
-                        for (int e = 0; e < 8; ++e)
-                            if (e < 4 * two && n + e < prm.N) dst[e] = (uint16_t)(w4[e >> 1] >> (16 * (e & 1)));
+                        for (int e = 0; e < 4; ++e)
+                            if (n + e < prm.N) dst[e] = (uint16_t)(w4[e >> 1] >> (16 * (e & 1)));
                     }
                 }
             }
