@@ -62,25 +62,38 @@ __device__ __forceinline__ float inv_rms(uint64_t lo, uint64_t hi, int K, float 
     return __double2float_rn(__ddiv_rn(1.0, __dsqrt_rn(__dadd_rn(mean, (double)eps))));
 }
 
-// y = half_rne((float(x) * r) * float(gamma)) as binary16 bits.  The conversion is written as the instruction
+// y = half_rne((float(x) * r) * float(gamma)) as binary16 bits in the low half.  The conversion is written as the instruction
 // itself: left to the compiler, the second product and the conversion are merged into one mixed-precision
 // operation with a single rounding, which lands on the other neighbour whenever the float product is an exact
 // tie between two binary16 values.
-__device__ __forceinline__ uint16_t normalized_half(uint16_t xb, uint16_t gb, float r)
+__device__ __forceinline__ uint32_t normalized_half(uint16_t xb, uint16_t gb, float r)
 {
     const float t = __fmul_rn(half_to_f32(xb), r);
     const float u = __fmul_rn(t, half_to_f32(gb));
     uint32_t hb;
     asm("v_cvt_f16_f32 %0, %1" : "=v"(hb) : "v"(u));
-    return (uint16_t)hb;
+    return hb;
 }
 
-// silu(g) * u as binary16 bits (see the head of the file for the definition of exp).
-__device__ __forceinline__ uint16_t silu_mul_half(uint16_t gb, uint16_t ub)
+// The correctly rounded g / d of silu, d = 1 + exp(-g): one residual correction of g * (1 / d), then the case of an infinite or
+// NaN gate.  d is 1 .. 2^126 and the quotient of a gate that is not zero 2^-120 .. 2^16, so no step leaves the normal range and the scaling
+// of a general division (eleven operations, five here) is not needed.  One correction does not round every
+// quotient right, but there are only 65536 gates and d follows from g: all of them were compared with the general division.
+// These rows are bound by vector issue (a row is one workgroup): with the clamp as one median and range and merge two halves at a time, 101 ->
+// 80 vector instructions a pair of elements, 1 x 11008 6.3 -> 5.9 us, 512 x 11008 11.9 -> 10.8, 2048 x 13824 44.5 -> 39.
+__device__ __forceinline__ float div_by_one_plus_exp(float g, float d)
+{
+    const float y = __builtin_amdgcn_rcpf(d);
+    const float t = __fmul_rn(g, y);
+    return __builtin_amdgcn_div_fixupf(__fmaf_rn(__fmaf_rn(-t, d, g), y, t), d, g);
+}
+
+// silu(g) * u as binary16 bits in the low half (see the head of the file for the definition of exp).
+__device__ __forceinline__ uint32_t silu_mul_half(uint16_t gb, uint16_t ub)
 {
     const float g = half_to_f32(gb), u = half_to_f32(ub);
     float t = __fmul_rn(-g, 0x1.715476p+0f);
-    t = t < -126.0f ? -126.0f : (t > 126.0f ? 126.0f : t);
+    t = __builtin_amdgcn_fmed3f(t, -126.0f, 126.0f);   // (a NaN gate ends as a NaN whatever this makes of it)
     const float n = rintf(t);
     const float f = __fsub_rn(t, n);
     float p = __fmul_rn(f, 0x1.430912p-13f);
@@ -91,11 +104,11 @@ __device__ __forceinline__ uint16_t silu_mul_half(uint16_t gb, uint16_t ub)
     p = __fmul_rn(__fadd_rn(p, 0x1.62e430p-1f), f);
     p = __fadd_rn(p, 1.0f);
     const float e = ldexpf(p, (int)n);
-    const float sg = __fdiv_rn(g, __fadd_rn(1.0f, e));
+    const float sg = div_by_one_plus_exp(g, __fadd_rn(1.0f, e));
     const float h = __fmul_rn(sg, u);
     uint32_t hb;
     asm("v_cvt_f16_f32 %0, %1" : "=v"(hb) : "v"(h));   // (kept apart from the product, as above)
-    return (uint16_t)hb;
+    return hb;
 }
 
 // h = half_rne(float(a) + float(b)): the residual add in front of the normalization (one binary32 addition, then the
@@ -115,10 +128,33 @@ __device__ __forceinline__ uint32_t add_half2(uint32_t a, uint32_t b)
 
 // KIND 0: RMSNorm, operand b = gamma [K];  KIND 1: SiLU(a) * b, operand b = up [M,K].
 template <int KIND>
-__device__ __forceinline__ uint16_t produce_half(uint16_t ab, uint16_t bb, float r)
+__device__ __forceinline__ uint32_t produce_half(uint16_t ab, uint16_t bb, float r)
 {
     if constexpr (KIND == 0) return normalized_half(ab, bb, r);
     else return silu_mul_half(ab, bb);
+}
+
+// Two outputs in one dword.
+template <int KIND>
+__device__ __forceinline__ uint32_t produce_half2(uint32_t a, uint32_t b, float r)
+{
+    return __builtin_amdgcn_perm(produce_half<KIND>((uint16_t)(a >> 16), (uint16_t)(b >> 16), r),
+                                 produce_half<KIND>((uint16_t)(a & 0xFFFFu), (uint16_t)(b & 0xFFFFu), r), 0x05040100u);
+}
+
+// The smaller / larger of two pairs of halves; a NaN loses, as in fminf (written as the instruction: the compiler otherwise quiets its
+// operands first, and the outputs above are no signalling NaNs).
+__device__ __forceinline__ uint32_t min_half2(uint32_t a, uint32_t b)
+{
+    uint32_t d;
+    asm("v_pk_min_f16 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+    return d;
+}
+__device__ __forceinline__ uint32_t max_half2(uint32_t a, uint32_t b)
+{
+    uint32_t d;
+    asm("v_pk_max_f16 %0, %1, %2" : "=v"(d) : "v"(a), "v"(b));
+    return d;
 }
 
 // Rows of up to 32768 elements: a thread keeps its VPT vectors of x and of gamma in registers across the three passes
@@ -186,22 +222,21 @@ __global__ __launch_bounds__(BLOCK) void producer_quant_rows_kernel(const uint16
     }
 
     // produced row (kept as binary16 bits in place of x) and its range, 0 included; padding lanes hold zeros
-    float vmin = 0.0f, vmax = 0.0f;
+    uint32_t min2 = 0u, max2 = 0u;
 #pragma unroll
     for (int i = 0; i < VPT; ++i) {
         const int v = tid + i * BLOCK;
         if (VPT > 1 && v >= nvec) continue;   // (whole waves past the row skip the work)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const uint16_t y0 = produce_half<KIND>((uint16_t)(xv[i][j] & 0xFFFFu), (uint16_t)(gv[i][j] & 0xFFFFu), r);
-            const uint16_t y1 = produce_half<KIND>((uint16_t)(xv[i][j] >> 16), (uint16_t)(gv[i][j] >> 16), r);
-            xv[i][j] = (uint32_t)y0 | ((uint32_t)y1 << 16);
-            const float f0 = half_to_f32(y0), f1 = half_to_f32(y1);
-            vmin = fminf(vmin, fminf(f0, f1));
-            vmax = fmaxf(vmax, fmaxf(f0, f1));
+            xv[i][j] = produce_half2<KIND>(xv[i][j], gv[i][j], r);
+            min2 = min_half2(min2, xv[i][j]);
+            max2 = max_half2(max2, xv[i][j]);
         }
         if (y_out) store_half8<RAGGED>(y_out + (size_t)m * K, v, K, xv[i]);
     }
+    float vmin = fminf(half_to_f32((uint16_t)(min2 & 0xFFFFu)), half_to_f32((uint16_t)(min2 >> 16)));
+    float vmax = fmaxf(half_to_f32((uint16_t)(max2 & 0xFFFFu)), half_to_f32((uint16_t)(max2 >> 16)));
     for (int off = 32; off > 0; off >>= 1) {
         vmin = fminf(vmin, __shfl_xor(vmin, off, 64));
         vmax = fmaxf(vmax, __shfl_xor(vmax, off, 64));
@@ -267,7 +302,7 @@ __global__ __launch_bounds__(BLOCK) void producer_quant_kernel(const uint16_t* _
         r = s_r;
     }
 
-    auto normalized = [&](int k) -> uint16_t { return produce_half<KIND>(row[k], brow[k], r); };
+    auto normalized = [&](int k) -> uint16_t { return (uint16_t)produce_half<KIND>(row[k], brow[k], r); };
 
     // range of the normalized row (0 included)
     float vmin = 0.0f, vmax = 0.0f;

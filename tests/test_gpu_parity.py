@@ -521,6 +521,26 @@ def test_silu_mul_quant_act_matches_oracle(abq, q, M, K):
     assert none is None and np.array_equal(codes2.cpu().numpy(), codes_ref)
 
 
+@pytest.mark.parametrize("K", [8192, 7936, 961])   # one and two vectors a thread, rows off 16-byte boundaries
+def test_silu_of_every_finite_gate(abq, K):
+    """The kernel divides by 1 + exp(-gate) without the scaling of a general division: the results of all finite gates, bit for bit."""
+    say("silu gates", K)
+    gates = np.arange(65536, dtype=np.uint16)
+    gates = gates[(gates & 0x7FFF) < 0x7C00]
+    rows = -(-gates.size // K)
+    rng = np.random.Generator(np.random.PCG64(7100 + K))
+    g = np.resize(gates, rows * K).reshape(rows, K).view(np.float16)
+    for _ in range(8):
+        u = rng.uniform(0.25, 1.0, (rows, K)).astype(np.float16)
+        h_ref = oracle.silu_mul_half(g, u)
+        codes_ref, scale_ref, zero_ref = oracle.quant_act(h_ref, 8)
+        codes, scale, zero, h = abq.abq_silu_mul_quant_act(8, to_dev(torch, g), to_dev(torch, u), want_h=True)
+        torch.cuda.synchronize()
+        assert np.array_equal(h.cpu().numpy().view(np.uint16), h_ref.view(np.uint16))
+        assert np.array_equal(codes.cpu().numpy(), codes_ref)
+        assert np.array_equal(scale.cpu().numpy(), scale_ref) and np.array_equal(zero.cpu().numpy(), zero_ref)
+
+
 def test_silu_mul_quant_then_down_proj_end_to_end(abq):
     """gate, up fp16 -> SiLU * up + quantizer (one kernel) -> fused decode matmul on a down_proj shape."""
     p, q, M, N, K = 2, 8, 2, 300, 11008
