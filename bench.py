@@ -41,11 +41,11 @@ PROFILE_OF = {
     "C5 W2A8 M=16 K=5120 N=13824": "shared_a_kernel_w2a8_gemv_m16_k5120_n13824.md",
     "C2 W4A8 GEMV 4096x4096 g128": "direct_kernel_w4a8_g128_gemv_m1_k4096_n4096.md",
     "C5 W4A8 M=1 K=5120 N=13824 g128": "direct_kernel_w4a8_g128_gemv_m1_k5120_n13824.md",
-    "C4 W6A6 GEMM M=512 4096->11008": "tiled_kernel_w6a6_gemm_m512_k4096_n11008.md",
+    "C4 W6A6 GEMM M=512 4096->11008": "block_kernel_w6a6_gemm_m512_k4096_n11008.md",
     "C4 W6A6 GEMM M=128 4096->11008": "tiled_kernel_w6a6_gemm_m128_k4096_n11008.md",
-    "C5 W4A4 M=2048 K=5120 N=13824": "tiled_kernel_w4a4_gemm_m2048_k5120_n13824.md",
-    "C5 W2A8 M=2048 K=5120 N=13824": "tiled_kernel_w2a8_gemm_m2048_k5120_n13824.md",
-    "C5 W4A4 M=2048 K=5120 N=13824 g128": "tiled_g128_kernel_w4a4_gemm_m2048_k5120_n13824.md",
+    "C5 W4A4 M=2048 K=5120 N=13824": "block_kernel_w4a4_gemm_m2048_k5120_n13824.md",
+    "C5 W2A8 M=2048 K=5120 N=13824": "block_kernel_w2a8_gemm_m2048_k5120_n13824.md",
+    "C5 W4A4 M=2048 K=5120 N=13824 g128": "block_g128_kernel_w4a4_gemm_m2048_k5120_n13824.md",
     "C5 W2A2 M=2048 K=5120 N=13824 f4": "f4_gemm_kernel_w2a2_gemm_m2048_k5120_n13824.md",
     ("block", 4, 8, 1): "direct_kernel_grouped_w4a8_m1_llama7b_block.md",
     ("block", 8, 8, 1): "grouped_kernel_w8a8_m1_llama7b_block.md",
@@ -727,7 +727,7 @@ def main():
         out["cpu_baseline"] = cpu_baseline(c, args.cpu_seconds, (g_scale_half, g_zero) if args.g128 else None)
     if args.other_paths and not args.g128 and args.workload == "c2" and args.grouped_steps > 0:
         # the other kernels of the path, each as a short run of this script in a child process (own parity check):
-        # the same decode step on per-group (g128) weight parameters, and a prefill matmul on the tiled kernel
+        # the same decode step on per-group (g128) weight parameters, and prefill matmuls on the tiled, block and F4 kernels
         short = ["--steps", "20", "--warmup", "5"]
         out["other_paths"] = {
             "decode_w2a8_m1_c3": child_summary(["--workload", "c3m1", *short]),
