@@ -105,7 +105,7 @@ static const struct { Cost block[2], tiled[2]; } kG128Costs[2] = {
      {{4.612f, 0.038f, {0.249f, 0.533f, 0}}, {5.148f, 1.313f, {0.476f, 0.989f, 0}}}},
 };
 
-// The cheaper shape unless the tiled per-group kernel is 6 % below it, on more than twelve groups of K (up to there the rounds' own
+// The cheaper shape where its cost is 6 % below the tiled per-group kernel's, on more than twelve groups of K (up to there the rounds' own
 // cost decides, and the better shape takes 1.10 times the other kernel's time on average).  It takes a third of those sizes, at 0.86 times the time (W4A8
 // M=1024 5120->13824 157 / 130 us); 0.5 % of the sizes lose 3 to 6 %.  7- and 8-bit weights have no room for z in the byte.
 bool block_g128_plan(const GemmArgs& g, int* shape)
