@@ -296,6 +296,10 @@ __global__ __launch_bounds__(64 * RW * CW, OCC) void block_kernel(BlockParams pr
     // ---- epilogue.  Lane (G, r) holds channels 4 G .. 4 G + 3 of row r of every tile; two neighbouring tiles exchange quarters of
     // a wave, after which a lane has eight adjacent channels: one 16-byte store.  (The outputs leave faster than the vector ALU makes
     // them, 4 us a 256 x 256 tile; staged through LDS they take the same time.)
+    // Output codes are made from the same eight values and leave as one 8-byte store, with a row's parameters loaded once: nothing runs beside a
+    // workgroup's epilogue here.  (With 32-bit multiplies, parameters loaded and a byte stored per element, calls with codes took 1.02 to 1.06 times the
+    // tiled kernel's time, up to 1.39, over 100 sizes that the rule takes; now 0.70 with the values and 0.73 without, pack launch
+    // included: W8A8 M=512 4096->11008 55.8 us tiled, 53.5 so, 40.5 now.)
     __builtin_amdgcn_s_waitcnt(0x0070);                          // (the last loads, for nobody, land before LDS is given back)
     for (int i = tid; i < kBN; i += 64 * kWaves) {               // a channel's record becomes what the epilogue needs of it
         const RowParams pw = par_w[i];
@@ -309,7 +313,17 @@ __global__ __launch_bounds__(64 * RW * CW, OCC) void block_kernel(BlockParams pr
     __syncthreads();
     const int wm0 = m0 + rw * MT * 16, wn0 = n0 + cw * NT * 16;
     const bool vec_ok = (prm.N & 3) == 0;                        // (of an odd tile: rows of Y 8-byte aligned)
-    auto dequant = [&](auto narrow, auto plain) {
+    auto dequant = [&](auto narrow, auto coded) {                // coded: the next layer's codes as well as (or instead of) the values
+        float rq_scale[MT];
+        int rq_zero[MT];
+        if constexpr (decltype(coded)::value) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) {
+                const int m = min(wm0 + mt * 16 + r, prm.M - 1);
+                rq_scale[mt] = prm.rq.scale[m];
+                rq_zero[mt] = prm.rq.zero[m];
+            }
+        }
 #pragma unroll
         for (int np = 0; np < NT; np += 2) {
             const int two = np + 1 < NT ? 2 : 1;                 // (an odd tile is left on its own: 8-byte stores)
@@ -340,13 +354,6 @@ __global__ __launch_bounds__(64 * RW * CW, OCC) void block_kernel(BlockParams pr
                             centered = (int32_t)((uint32_t)s + (uint32_t)c.wz * (uint32_t)pa.sum + (uint32_t)naz * (uint32_t)c.cw);
                         const float v = ((float)centered * pa.scale) * c.scale;
                         asm("v_cvt_f16_f32 %0, %1" : "=v"(hv[reg]) : "v"(v));   // (the instruction itself: see epilogue_value)
-                        if constexpr (!decltype(plain)::value) {
-                            const int n = wn0 + (np + h) * 16 + 4 * G + reg;
-                            if (m < prm.M && n < prm.N) {
-                                if (prm.rq.codes)
-                                    prm.rq.codes[(size_t)m * prm.N + n] = requant_code((uint16_t)hv[reg], prm.rq.scale[m], prm.rq.zero[m], prm.rq.qmax);
-                            }
-                        }
                     }
                     d[h][0] = __builtin_amdgcn_perm(hv[1], hv[0], 0x05040100u);   // the low halves of both
                     d[h][1] = __builtin_amdgcn_perm(hv[3], hv[2], 0x05040100u);
@@ -359,7 +366,21 @@ __global__ __launch_bounds__(64 * RW * CW, OCC) void block_kernel(BlockParams pr
                     n = wn0 + (np + (G & 1)) * 16 + (G >> 1) * 8;
                     w4[0] = lo[0]; w4[1] = hi[0]; w4[2] = lo[1]; w4[3] = hi[1];
                 }
-                if (prm.y && m < prm.M && n < prm.N) {
+                if (m >= prm.M || n >= prm.N) continue;
+                if constexpr (decltype(coded)::value) {
+                    uint32_t c8[2] = {0u, 0u};
+#pragma unroll
+                    for (int e = 0; e < 8; ++e)
+                        if (e < 4 * two) c8[e >> 2] |= (uint32_t)requant_code((uint16_t)(w4[e >> 1] >> (16 * (e & 1))), rq_scale[mt], rq_zero[mt], prm.rq.qmax) << (8 * (e & 3));
+                    uint8_t* dst = prm.rq.codes + (size_t)m * prm.N + n;
+                    if (two == 2 && n + 8 <= prm.N) *reinterpret_cast<u32x2_byte*>(dst) = u32x2_byte{c8[0], c8[1]};
+                    else {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (e < 4 * two && n + e < prm.N) dst[e] = (uint8_t)(c8[e >> 2] >> (8 * (e & 3)));
+                    }
+                }
+                if (!decltype(coded)::value || prm.y) {
                     uint16_t* dst = prm.y + (size_t)m * prm.N + n;
                     if (two == 2) store_row_part8(dst, n, prm.N, w4[0], w4[1], w4[2], w4[3]);
                     else if (vec_ok) *reinterpret_cast<uint2*>(dst) = uint2{w4[0], w4[1]};
@@ -372,8 +393,13 @@ __global__ __launch_bounds__(64 * RW * CW, OCC) void block_kernel(BlockParams pr
             }
         }
     };
-    if (prm.narrow_sums && prm.rq.codes == nullptr) dequant(std::true_type{}, std::true_type{});   // (the same for every thread)
-    else dequant(std::false_type{}, std::false_type{});
+    if (prm.rq.codes == nullptr) {                               // (the same for every thread, as is narrow_sums)
+        if (prm.narrow_sums) dequant(std::true_type{}, std::false_type{});
+        else dequant(std::false_type{}, std::false_type{});
+    } else {
+        if (prm.narrow_sums) dequant(std::true_type{}, std::true_type{});
+        else dequant(std::false_type{}, std::true_type{});
+    }
 }
 
 template <int P, int RW, int CW, int MT, int NT, int S, int OCC>

@@ -63,6 +63,27 @@ def test_block_writes_the_next_layers_codes(abq, shape, p, M, N, K):
     assert torch.equal(call(want_y=False)[0], codes)
 
 
+@pytest.mark.parametrize("shape,p,M,N,K", [c for c in CASES if not (c[1] in (4, 7, 8) and c[4] < 2000)])
+def test_block_codes_of_the_other_widths(abq, shape, p, M, N, K):
+    """The same for every other width and for sums past 2^23, with parameters that clamp codes at both ends."""
+    q, qo = 5 if p % 2 else 8, 8 if p % 2 else 3
+    c, pw, _ = problem(abq, shape, p, q, M, N, K)
+    a, sa, za = to_dev(torch, c.A), to_dev(torch, c.a_scale), to_dev(torch, c.a_zero)
+    y0, _ = abq.abq_gemm_act_codes(p, q, M, N, K, a, sa, za, pw, FIELDS)
+    rng = np.random.default_rng(6)
+    spread = np.maximum(np.abs(y0.float().cpu().numpy()).max(axis=1), 1e-3)
+    so = (spread / (1 << qo) * rng.choice([0.5, 2.0, 4.0], M)).astype(np.float32)
+    zo = rng.integers(-3, (1 << qo) + 3, M).astype(np.int32)
+    dso, dzo = to_dev(torch, so), to_dev(torch, zo)
+    call = lambda **kw: abq.abq_gemm_act_codes_requant(p, q, M, N, K, a, sa, za, pw, FIELDS, qo, dso, dzo, **kw)
+    codes, y = call()
+    (only, _), names = run_named(torch, lambda: call(want_y=False))
+    assert f"block_kernel<{p}, {WAVES[shape]}" in names[-1], names
+    assert torch.equal(y.view(torch.int16), y0.view(torch.int16))
+    assert np.array_equal(codes.cpu().numpy(), oracle.requant(y0.cpu().numpy(), qo, so, zo))
+    assert torch.equal(only, codes)
+
+
 # both shapes by the rule, widths of one and of two plane groups, a last group that is short and groups past K, ragged rows and channels
 @pytest.mark.parametrize("waves,p,M,N,K", [("2, 4, 8,", 1, 577, 10147, 1539), ("2, 4, 8,", 2, 454, 12312, 1547), ("2, 4, 8,", 3, 322, 11195, 1544),
                                            ("2, 4, 8,", 4, 580, 9735, 1561), ("2, 4, 8,", 5, 391, 9408, 1541), ("2, 4, 8,", 6, 331, 11022, 1665),
