@@ -501,3 +501,16 @@ def test_built_kernels_with_loads_in_flight_use_no_scratch(device_kernels, kerne
     mine = [(n, b) for n, b in device_kernels if kernel in n]
     assert len(mine) >= 16 and [k for k in mine if k[1]] == []
     assert kernel in bld.NO_SCRATCH.values()
+
+
+def test_every_block_kernel_has_a_test_size(device_kernels):
+    """The sizes of tests/test_gpu_block.py name each variant of the block kernels that the library holds."""
+    import test_gpu_block as tb
+    built = lambda name: {tuple(int(v) for v in re.findall(r"Li(\d+)E", n)) for n, _ in device_kernels if re.match(r"_ZN3abq\d+" + name + "I", n)}
+    waves = lambda text: tuple(int(v) for v in re.findall(r"\d+", text))
+    named = {(p, *waves(tb.WAVES[shape])) for shape, p, *_ in tb.CASES}
+    covers = lambda variant: any(variant[:len(n)] == n for n in named)
+    variants = built("block_kernel")
+    assert len(variants) == 37 and [v for v in variants if not covers(v)] == []
+    groups = {(p, *waves(w)) for w, p, *_ in tb.G128_CASES}
+    assert {v[:4] for v in built("block_g128_kernel")} == groups and len(groups) == 12
