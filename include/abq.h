@@ -108,9 +108,9 @@ int abq_pack_weights(int p, int N, int K,
  * The order of that binary32 sum follows the launch plan (how K is split over waves), so the same problem
  * through different entry points agrees to this bound, not to the bit.
  * abq_gemm, abq_gemm_act_codes and abq_gemm_grouped take such a blob with w_layout =
- * ABQ_LAYOUT_FIELDS_G128.  Up to 16 rows of A run on the streaming (decode) kernel, more rows on a tiled kernel
- * that flushes its integer accumulators through the group's scale every 128 k.  They cannot return the raw integer
- * accumulator: acc_i32 must be NULL (ABQ_ERR_LAYOUT otherwise).  abq_pack_weights rejects this layout value
+ * ABQ_LAYOUT_FIELDS_G128.  Up to 16 rows of A run on the decode kernels, more rows on the prefill kernels (K-split,
+ * block, tiled); all flush their integer accumulators through the group's scale every 128 k.  They cannot return the
+ * raw integer accumulator: acc_i32 must be NULL (ABQ_ERR_LAYOUT otherwise).  abq_pack_weights rejects this layout value
  * (ABQ_ERR_LAYOUT). */
 int abq_pack_weights_g128(int p, int N, int K,
                           const uint8_t* w_codes, const uint16_t* w_scale_fp16, const int32_t* w_zero,
@@ -296,10 +296,12 @@ int abq_f4_gemm(int p, int q, int M, int N, int K, const void* packed_act, const
  * rules; this table lets a tuner (paper_2408_08554_amd/tune.py times the candidates on the device) replace the
  * rule for exact problem sizes.  A field left 0 keeps the rule for that knob; a plan that does not fit the
  * problem (say, more waves than K has 512-blocks) is ignored and the rule applies.  Above 16 rows the rule may
- * choose a kernel without knobs; a plan takes a problem from it by a K split of the decode kernel where that
- * kernel is the other choice (M <= 64, few output tiles), else by tiled_mt or tiled_ntw, and never on per-group
- * blobs.  Results never depend on the plan (per-group weight scales: to their stated bound).  Process-wide,
- * thread-safe; entries hold no device state.
+ * choose a kernel without knobs.  A plan takes a problem from the K-split kernel by a K split of the decode kernel
+ * where that kernel is the other choice (M <= 64, few output tiles), else by tiled_mt or tiled_ntw, and from the
+ * block kernel (many output tiles) by any of the four tiled_ knobs: a plan found for the tiled kernel keeps it, so a
+ * table older than the library is worth a new search.  Per-group blobs stay where the rule puts them.  Results never
+ * depend on the plan (per-group weight scales: to their stated bound).  Process-wide, thread-safe; entries hold no
+ * device state.
  *   skinny_waves    waves per workgroup of the decode kernel = K split of a tile: 1, 2, 4..8
  *   skinny_kgroups  K groups of the decode kernel: 1..4
  *   tiled_mt        rows of A per workgroup tile of the prefill kernel / 16: 4 or 8

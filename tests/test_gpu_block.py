@@ -87,6 +87,25 @@ def test_block_codes_of_the_other_widths(abq, shape, p, M, N, K):
     assert torch.equal(only, codes)
 
 
+@pytest.mark.parametrize("plan,kernel", [(dict(tiled_mt=4), "tiled_kernel"), (dict(tiled_ntw=2), "tiled_kernel"), (dict(tiled_wd=2), "tiled_kernel"),
+                                         (dict(tiled_band=2), "tiled_kernel"), (dict(skinny_waves=4), "block_kernel"), (dict(skinny_kgroups=2), "block_kernel"),
+                                         (dict(direct_r=1), "block_kernel")])
+def test_tiled_knobs_keep_the_tiled_kernel(abq, plan, kernel):
+    """As the header says: any knob of the tiled kernel takes a problem from the block kernel, the decode kernels' knobs do not."""
+    p, q, M, N, K = 4, 8, 264, 11080, 100
+    c, pw, pa = problem(abq, "64x2", p, q, M, N, K)
+    call = lambda: abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, FIELDS)[0]
+    y0, names = run_named(torch, call)
+    assert "block_kernel" in names[-1], names
+    abq.abq_plan_set(p, q, M, N, K, **plan)
+    try:
+        y, names = run_named(torch, call)
+    finally:
+        abq.abq_plan_set(p, q, M, N, K)
+    assert len(names) == 1 and kernel in names[0], names
+    assert torch.equal(y.view(torch.int16), y0.view(torch.int16))
+
+
 # both shapes by the rule, widths of one and of two plane groups, a last group that is short and groups past K, ragged rows and channels
 G128_CASES = [("2, 4, 8,", 1, 577, 10147, 1539), ("2, 4, 8,", 2, 454, 12312, 1547), ("2, 4, 8,", 3, 322, 11195, 1544),
               ("2, 4, 8,", 4, 580, 9735, 1561), ("2, 4, 8,", 5, 391, 9408, 1541), ("2, 4, 8,", 6, 331, 11022, 1665),
