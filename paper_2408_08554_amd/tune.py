@@ -3,7 +3,8 @@
 The paper's engine picks its kernel configuration per problem size by timing candidates (Appendix D,
 auto kernel search).  The library picks launch plans from closed-form rules; this tool times the
 candidate plans of one exact problem size through the plan table of the C ABI (abq_plan_set), checks
-that every candidate returns the default plan's result bit for bit (accumulator and fp16 output),
+that every candidate returns the default plan's result bit for bit (fp16 output of the timed call,
+and accumulator),
 and reports them fastest first.  `--save` merges the winner into a JSON file when it beats the rule
 by more than `--min-gain`; `load_plans(path)` installs such a file into the running process.
 
@@ -85,12 +86,17 @@ class Problem:
         abq.abq_gemm_act_codes(p, q, M, N, K, self.A, self.a_s, self.az, blob, self.layout, y=self.y, acc=acc, workspace=self.workspace)
 
     def result(self):
-        """(y bits, acc) of one call under the plan currently set."""
-        self.y.fill_(float("nan"))
-        self.acc.fill_(-1)
-        self.call(0, acc=self.acc)
-        torch.cuda.synchronize()
-        return self.y.view(torch.int16).clone(), self.acc.clone()
+        """(y bits of the call that is timed, y bits and acc of the call that also returns the accumulator) under the plan currently
+        set.  Two calls: the accumulator may come from another kernel than the one that the rule or the plan times."""
+        out = []
+        for acc in (None, self.acc):
+            self.y.fill_(float("nan"))
+            if acc is not None:
+                acc.fill_(-1)
+            self.call(0, acc=acc)
+            torch.cuda.synchronize()
+            out += [self.y.view(torch.int16).clone()] + ([] if acc is None else [acc.clone()])
+        return out
 
     def time(self):
         """Seconds per launch under the plan currently set."""
@@ -121,7 +127,7 @@ def search(p, q, M, N, K, launches=None, rotate_bytes=1 << 30, log=None, passes=
     before = abq.abq_plan_get(p, q, M, N, K)
     prob = Problem(p, q, M, N, K, rotate_bytes, launches)
     abq.abq_plan_set(p, q, M, N, K)          # the rule
-    y0, acc0 = prob.result()
+    rule = prob.result()
     plans = candidates(p, q, M, N, K)
     best = [float("inf")] * len(plans)
 
@@ -134,8 +140,7 @@ def search(p, q, M, N, K, launches=None, rotate_bytes=1 << 30, log=None, passes=
     try:
         for plan in plans:
             install(plan)
-            y, acc = prob.result()
-            if not (torch.equal(y, y0) and torch.equal(acc, acc0)):
+            if not (torch.equal(rule[0], rule[1]) and all(torch.equal(a, b) for a, b in zip(prob.result(), rule))):
                 raise AssertionError(f"plan {plan} changes the result of {p, q, M, N, K}")
         # Timings depend on what ran before: the clock needs about half a second of load to settle, and a
         # candidate that follows a slow, low-occupancy one reads a few percent high.  So: an untimed warm-up, then

@@ -106,6 +106,18 @@ def test_tiled_knobs_keep_the_tiled_kernel(abq, plan, kernel):
     assert torch.equal(y.view(torch.int16), y0.view(torch.int16))
 
 
+def test_tuner_checks_the_call_that_it_times(abq):
+    """Its timed call runs the block kernel by the rule; the accumulator comes from another kernel, so one call cannot stand for both."""
+    from paper_2408_08554_amd import tune
+    prob = tune.Problem(4, 8, 264, 11080, 100, rotate_bytes=1 << 22, launches=4)
+    assert "block_kernel" in run_named(torch, lambda: prob.call(0))[1][-1]
+    assert "tiled_kernel" in run_named(torch, lambda: prob.call(0, acc=prob.acc))[1][-1]
+    asked, call = [], prob.call
+    prob.call = lambda i, acc=None: (asked.append(acc is not None), call(i, acc=acc))
+    out = prob.result()
+    assert sorted(asked) == [False, True] and len(out) == 3 and torch.equal(out[0], out[1])
+
+
 # both shapes by the rule, widths of one and of two plane groups, a last group that is short and groups past K, ragged rows and channels
 G128_CASES = [("2, 4, 8,", 1, 577, 10147, 1539), ("2, 4, 8,", 2, 454, 12312, 1547), ("2, 4, 8,", 3, 322, 11195, 1544),
               ("2, 4, 8,", 4, 580, 9735, 1561), ("2, 4, 8,", 5, 391, 9408, 1541), ("2, 4, 8,", 6, 331, 11022, 1665),
