@@ -541,6 +541,42 @@ def test_silu_of_every_finite_gate(abq, K):
         assert np.array_equal(scale.cpu().numpy(), scale_ref) and np.array_equal(zero.cpu().numpy(), zero_ref)
 
 
+@pytest.mark.parametrize("part", range(8))
+def test_silu_quotients_to_the_last_bit(abq, part):
+    """The test above rounds each quotient to binary16 with some twenty factors, which hides most changes by one unit of binary32.  With
+    every mantissa as the factor a quotient that is one unit off shows wherever it can reach an output at all: some product lands on the other
+    side of a tie (a sixth of the gates in each direction; for the others all 1024 products round alike)."""
+    gates = np.arange(65536, dtype=np.uint16)
+    gates = gates[(gates & 0x7FFF) < 0x7C00].reshape(8, 7936)
+    ups = (0x3C00 + 128 * part + np.arange(128)).astype(np.uint16)
+    g = np.tile(gates, (128, 1)).view(np.float16)
+    u = np.ascontiguousarray(np.broadcast_to(np.repeat(ups, 8)[:, None], g.shape)).view(np.float16)
+    say("silu quotients", part, g.shape)
+    h = abq.abq_silu_mul_quant_act(8, to_dev(torch, g), to_dev(torch, u), want_h=True)[3]
+    torch.cuda.synchronize()
+    assert np.array_equal(h.cpu().numpy().view(np.uint16), oracle.silu_mul_half(g, u).view(np.uint16))
+
+
+@pytest.mark.parametrize("K", [64, 961, 7936])
+def test_silu_of_infinite_gates(abq, K):
+    """exp's argument is clamped, so an infinite gate keeps its infinity, times the factor's sign; an infinite factor of zero is a NaN, which moves
+    no range and gets the code of zero.  (NaN gates: test_halves_that_are_no_numbers.)"""
+    say("silu infinities", K)
+    rng = np.random.Generator(np.random.PCG64(7300 + K))
+    g, u = (rng.standard_normal((4, K)).astype(np.float16) for _ in range(2))
+    u[u == 0] = 1.0
+    g[0, K // 2], g[1, K - 1], g[2, 0], g[2, 1] = np.inf, -np.inf, np.inf, -np.inf
+    g[3, :2], u[3, :2] = np.float16(0), [np.inf, -np.inf]
+    with np.errstate(invalid="ignore"):
+        want = np.where(np.isinf(g), g * np.sign(u), oracle.silu_mul_half(np.where(np.isinf(g), np.float16(0), g), u)).astype(np.float16)
+    codes, scale, zero, h = (t.cpu().numpy() for t in abq.abq_silu_mul_quant_act(8, to_dev(torch, g), to_dev(torch, u), want_h=True))
+    assert np.isnan(h[3, :2]).all() and not np.isnan(h[:3]).any()
+    assert np.array_equal(h[:3].view(np.uint16), want[:3].view(np.uint16)) and np.array_equal(h[3, 2:], want[3, 2:])
+    assert np.isinf(scale[:3]).all() and not codes[:3].any()
+    ref = oracle.quant_act(np.where(np.isnan(h[3:]), np.float16(0), h[3:]), 8)
+    assert all(np.array_equal(a[3:], b) for a, b in zip((codes, scale, zero), ref))
+
+
 def test_silu_mul_quant_then_down_proj_end_to_end(abq):
     """gate, up fp16 -> SiLU * up + quantizer (one kernel) -> fused decode matmul on a down_proj shape."""
     p, q, M, N, K = 2, 8, 2, 300, 11008
