@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 from paper_2408_08554_amd import synth
-from helpers import check_g128, check_sampled, run_named, to_dev
+from helpers import check_against_oracle, check_g128, check_sampled, run_named, to_dev
 
 pytestmark = pytest.mark.gpu
 
@@ -85,6 +85,47 @@ def test_block_codes_of_the_other_widths(abq, shape, p, M, N, K):
     assert torch.equal(y.view(torch.int16), y0.view(torch.int16))
     assert np.array_equal(codes.cpu().numpy(), oracle.requant(y0.cpu().numpy(), qo, so, zo))
     assert torch.equal(only, codes)
+
+
+# what the rule leaves to the tiled kernel: width, rows, channels, K, and the tile (channels of W per wave / 16, rows of A / 16)
+DECLINED = [(1, 67, 4512, 113, "1, 4"), (1, 74, 4140, 2535, "1, 4"), (1, 387, 12760, 1048, "2, 4"), (2, 68, 4864, 103, "1, 4"), (2, 68, 4654, 1687, "1, 4"),
+            (2, 388, 12376, 514, "2, 4"), (2, 1191, 13376, 1552, "4, 4"), (3, 68, 4097, 536, "1, 4"), (3, 1269, 4808, 535, "2, 4"), (4, 65, 4528, 100, "1, 4"),
+            (4, 69, 4977, 2647, "1, 4"), (4, 776, 10280, 101, "2, 4"), (5, 68, 4273, 1359, "1, 4"), (5, 728, 10888, 100, "2, 4"), (6, 65, 4469, 533, "1, 4"),
+            (6, 587, 13240, 100, "2, 4"), (6, 1386, 13592, 1034, "2, 8"), (7, 73, 4759, 568, "1, 4"), (7, 1181, 4816, 528, "2, 4"), (7, 450, 12384, 1583, "2, 8"),
+            (8, 75, 4320, 104, "1, 4"), (8, 73, 4129, 1172, "1, 4")]
+
+
+@pytest.mark.parametrize("q", [8, 3])
+@pytest.mark.parametrize("p,M,N,K,tile", DECLINED)
+def test_tiled_kernel_by_the_rule_without_accumulator(abq, p, q, M, N, K, tile):
+    """Ordinary calls that the block kernel leaves alone run the tiled kernel's epilogue without accumulator; calls that ask for it, the other one."""
+    c, pw, pa = problem(abq, "declined", p, q, M, N, K)
+    call = lambda **kw: abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, FIELDS, **kw)
+    (y, none), names = run_named(torch, call)
+    assert none is None and len(names) == 1 and f"tiled_kernel<{p}, {tile}, " in names[0], names
+    y0, acc0 = call(want_acc=True)
+    assert torch.equal(y.view(torch.int16), y0.view(torch.int16))
+    check_sampled(c, y.cpu().numpy(), acc0.cpu().numpy())
+
+
+@pytest.mark.parametrize("mt,ntw,wd", [(4, 1, 2), (4, 1, 4), (4, 2, 2), (4, 2, 4), (4, 4, 2), (8, 1, 2), (8, 2, 2), (8, 4, 2)])
+@pytest.mark.parametrize("p,q", [(1, 8), (2, 3), (3, 8), (4, 4), (5, 8), (6, 6), (7, 8), (8, 8)])
+def test_tiled_shapes_by_plan_entry_without_accumulator(abq, p, q, mt, ntw, wd):
+    """Every tile and ring depth through the epilogue of an ordinary call, against the one that writes the accumulator as well."""
+    if wd == 4 and ntw == 2 and p >= 7:
+        pytest.skip("no deep ring with two tiles of 7 or 8 bits per wave")
+    for M, N, K in [(65, 40, 200), (200, 330, 1100), (130, 72, 3590)]:
+        c, pw, pa = problem(abq, f"tile {mt} {ntw} {wd}", p, q, M, N, K)
+        call = lambda **kw: abq.abq_gemm(p, q, M, N, K, pa, FIELDS, pw, FIELDS, **kw)
+        abq.abq_plan_set(p, q, M, N, K, tiled_mt=mt, tiled_ntw=ntw, tiled_wd=wd)
+        try:
+            (y, _), names = run_named(torch, call)
+            y0, acc0 = call(want_acc=True)
+        finally:
+            abq.abq_plan_set(p, q, M, N, K)
+        assert len(names) == 1 and f"tiled_kernel<{p}, {ntw}, {mt}, {wd}>" in names[0], names
+        assert torch.equal(y.view(torch.int16), y0.view(torch.int16))
+        check_against_oracle(c, y.cpu().numpy(), acc0.cpu().numpy())
 
 
 @pytest.mark.parametrize("plan,kernel", [(dict(tiled_mt=4), "tiled_kernel"), (dict(tiled_ntw=2), "tiled_kernel"), (dict(tiled_wd=2), "tiled_kernel"),
