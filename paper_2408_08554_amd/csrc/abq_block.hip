@@ -62,7 +62,7 @@ static double cost_of(const Cost& c, int M, int N, int K, int bm, int bn, int oc
 // output leaves the larger tiles' last round nearly empty; W6A6 M=128 4096->11008 with its quantizer 17.1 us there, 18.2 on 64 x 128 here).  Over those sizes
 // the choice takes 0.86 times the tiled kernel's time in cache and 0.85 times from memory, 0.84 for p = 1, 2, 4, 8 and 0.88 for the others; 0.3 % of the sizes lose
 // 3 to 8 % in cache, 1.5 % lose 3 to 19 % from memory.  (Costs that were the same for all N, with steps that cost nothing at some loads, from times in cache alone: 2.3 %
-// of the sizes slower than the tiled kernel by more than 3 %, 7.9 % from memory, W2A8 M=68 8960->8480 32 us against 27.)
+// of the sizes slower than the tiled kernel by more than 3 %, 7.9 % from memory, W2A8 M=68 8958->8480 32 us against 27.)
 // A plan-table entry with a knob of the tiled kernel asks for that; so does a call for the int32 accumulator, which only that kernel writes.
 bool block_plan(const GemmArgs& g, const WeightLayout& W, int* shape)
 {
@@ -130,7 +130,7 @@ static const struct { Cost block[2], tiled[2]; } kG128Costs[2] = {
 
 // The cheaper shape where its cost is 3 % below the tiled per-group kernel's, on more than twelve groups of K (up to there the rounds' own
 // cost decides, and the better shape takes 1.10 times the other kernel's time on average).  It takes a third of those sizes,
-// at 0.87 times the time (W4A8 M=1024 5120->13824 157 / 130 us); 0.1 % of the sizes lose 3 to 8 % in cache, 0.4 % from memory.
+// at 0.87 times the time (W4A4 M=2048 5120->13824 226 / 202 us in cache); 0.1 % of the sizes lose 3 to 8 % in cache, 0.4 % from memory.
 // 7- and 8-bit weights have no room for z in the byte.
 bool block_g128_plan(const GemmArgs& g, int* shape)
 {

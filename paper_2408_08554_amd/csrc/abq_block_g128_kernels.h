@@ -8,8 +8,9 @@
 //
 // What bounds it is the vector ALU: a multiply-add, a conversion and a fused multiply-add per element and group (48 clocks a tile of 16 x 16, against 32 of
 // its two MFMAs), and the operands' expansion.  Waves of 128 x 32 make that expansion serve eight tiles (the tiled kernel's 64 x 32: four), which leaves
-// 76 clocks of vector issue a tile, and a row's flush runs under the next row's MFMAs.  Measured: 3190 clocks a step of 2450 clocks of vector issue (77 %
-// busy), W4A8 M=1024 5120->13824 157 us on the tiled kernel, 130 here.  Three waves a SIMD (64 x 32 each) spill, two such are no faster.
+// 73 clocks of vector issue a tile, and a row's flush runs under the next row's MFMAs.  Measured at 256 x 128: 2950-3030 clocks a step, of them 2340 of vector
+// issue (586 instructions a SIMD, 78 %) and 1150 of MFMAs.  W4A8 M=1024 5120->13824 on the tiled kernel / 256 x 128 / 128 x 128, two a unit, replays in cache 122 / 115 /
+// 114 us, from memory 127 / 120 / 119; W4A4 M=2048 226 / 225 / 202 and 231 / 231 / 205.  Three waves a SIMD (64 x 32 each) spill, two such are no faster.
 #pragma once
 #include "abq_block_kernels.h"
 

@@ -8,11 +8,11 @@
 // MFMAs), rows of A as whole 128-byte lines, XOR-swizzled so that the operand reads have no bank conflicts.  (Unpacked rows, masked and
 // made signed in registers, take 1.3 to 2 times as long: every wave of a row of waves converts them again.  They are packed first.)
 //
-// What bounds it is the matrix pipe and, past that, power: at 256 x 256 tiles the K loop keeps the pipe 92 % busy (2200-2230 clocks a
-// step of 2048 clocks of MFMAs), while the chip holds 1.5 (W8A8) to 1.9 GHz (W4A4).  How it gets there: eight waves of 128 x 64
-// take the fewest LDS bytes per MFMA that 256 registers allow; the one barrier of a step stands inside its second slice, where
+// What bounds it is the matrix pipe and, past that, power: at 256 x 256 tiles the K loop keeps the pipe 90-93 % busy on operands in cache (2200-2280
+// clocks a step of 2048 clocks of MFMAs), 82-85 % with weights from memory, while the chip holds 1.65 (W8A8) to 2.1 GHz (W4A4).  How it gets there: eight waves
+// of 128 x 64 take the fewest LDS bytes per MFMA that 256 registers allow; the one barrier of a step stands inside its second slice, where
 // every operand of the MFMAs around it is in registers already; reads, loads and expansions stand one by one between MFMAs, because behind the
-// barrier all waves run in step, and what stands in a row of its own there is time of the matrix pipe (400 clocks a step).
+// barrier all waves run in step, and what stands in a row of its own there is time of the matrix pipe.
 // Before / now (tiled kernel / this one, rows packed, replays): W4A4 M=2048 5120->13824 135 / 111 us, W8A8 147 / 119, M=1024 70 / 51 and
 // 79 / 60, W8A8 M=512 4096->11008 32.5 / 26.5, 11008->4096 42 / 29.
 #pragma once

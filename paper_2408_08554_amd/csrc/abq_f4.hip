@@ -161,7 +161,9 @@ struct F4Params {
 // built so): both operands go global -> LDS, where an operand block lands as the operand layout, a step is one block of 128 k, its barrier stands
 // behind its first rows of MFMAs, and reads and loads stand one by one between the others.  (Two blocks a step: 1 to 6 % slower.)
 // The kernel before this one read its rows into registers by hand-written loads, waited for by hand, and took the eight W blocks of a step through LDS
-// in four waves of 64 x 128: W2A2 M=2048 5120->13824 with its pack 73-75 us, 65-68 here; alone 512 x 4096 x 11008 23.5, 17.0; 64 x 4096 x 4096 9.9, 6.6.
+// in four waves of 64 x 128.  The gain is at few and middling rows: 400 sizes of M = 1..2048 take 0.69 times its time in cache, 0.61 with weights from memory (17..63
+// rows 0.60 and 0.52, from 1024 on 0.83 and 0.80; 5 and 4 of them are 3 to 10 % slower).  W2A2 M=2048 5120->13824 traced 72.2 us, 65.6, but a pass
+// with its pack, 68-74 us by process, is hardly faster than it was (72-75).
 template <int RW, int CW, int MT, int NT, int S, int OCC>
 __global__ __launch_bounds__(64 * RW * CW, OCC) void f4_gemm_kernel(F4Params prm)
 {
@@ -342,8 +344,7 @@ __global__ __launch_bounds__(64 * RW * CW, OCC) void f4_gemm_kernel(F4Params prm
 
 // Workgroup shapes (rows of A, channels, workgroups a compute unit) and what a launch of each costs (us): `base`, `round` for every round of resident
 // workgroups, and per block of 128 k what a unit with one or two of them takes.  Non-negative least squares of the relative error over 400 sizes
-// (M = 17..2048, N = 256..13824, K = 512..13824), mean error 5 to 8 %; over those the cheapest of the five takes 0.69 times the time of the kernel
-// before (M < 64 0.55, M >= 1024 0.9), two others added (256 x 128, 128 x 256 by four waves) gain nothing, 7 of the 400 lose 3 to 7 %.
+// (M = 17..2048, N = 256..13824, K = 512..13824) in cache, mean error 5 to 8 %; two shapes more (256 x 128, 128 x 256 by four waves) gained nothing there.
 struct F4ShapeInfo { int bm, bn, occ; float base, round, step[2]; };
 constexpr int kF4Shapes = 5;
 static const F4ShapeInfo kF4ShapeInfo[kF4Shapes] = {{256, 256, 1, 0, 7.391f, {0.495f, 0}}, {128, 128, 1, 0, 4.353f, {0.18f, 0}}, {128, 128, 2, 0, 5.002f, {0.179f, 0.434f}},

@@ -24,7 +24,7 @@ def run_f4(abq, c):
     y = torch.full((c.M, c.N), float("nan"), dtype=torch.float16, device="cuda")
     acc = torch.full((c.M, c.N), -7, dtype=torch.int32, device="cuda")
     abq.abq_f4_gemm(c.p, c.q, c.M, c.N, c.K, pa, pw, y=y, acc=acc)
-    # without the accumulator output the kernel takes its staged epilogue (vector stores): the same bits
+    # without the accumulator output the kernel takes its binary32 epilogue (vector stores): the same bits
     y_only = torch.full((c.M, c.N), float("nan"), dtype=torch.float16, device="cuda")
     abq.abq_f4_gemm(c.p, c.q, c.M, c.N, c.K, pa, pw, y=y_only)
     torch.cuda.synchronize()
@@ -32,7 +32,7 @@ def run_f4(abq, c):
     return y.cpu().numpy(), acc.cpu().numpy()
 
 
-# one tile and less, ragged in every dimension, several workgroup tiles (256 x 128) with ragged tails, odd and even numbers
+# one tile and less, ragged in every dimension, several workgroup tiles (32 x 64) with ragged tails, odd and even numbers
 # of 128-k steps, K ending inside a step
 F4_SHAPES = [(1, 1, 1), (1, 16, 128), (5, 33, 200), (16, 16, 129), (17, 130, 1000), (256, 128, 1024), (300, 520, 1000),
              (513, 257, 384), (64, 1000, 2048), (700, 300, 4096 + 64), (260, 136, 256), (31, 8, 64)]
@@ -83,9 +83,8 @@ def test_f4_drops_bits_above_the_width(abq):
 
 
 def test_f4_large_tile_sampled(abq):
-    """256 workgroups of the 256-row tile (one per compute unit: the smallest grid that takes this tile), ragged K (eight
-    steps: two turns of the three-buffer ring and a tail of two): sampled outputs.  A second case with several panels of
-    row tiles and a partial last panel."""
+    """Two workgroups of 128 x 128 on every compute unit, K of eight steps (two turns of the ring), the last one short; then 256 x 256 tiles with
+    two bands of row tiles, the second of fewer: sampled outputs."""
     for M, N, K in [(1024, 8192, 1000), (2600, 3300, 640)]:
         c = synth.make_case(2, 2, M, N, K, seed=synth.case_seed(11, 2, 2, 55, 66), name=f"f4 W2A2 {M}x{N}x{K}")
         say(c.name)

@@ -122,6 +122,7 @@ def test_prefill_shapes(abq, M, N, K, p, q):
                                             (8, 8, 440, 4600, 8200, "1, 4, 2"),    # as full, seven row blocks
                                             (8, 8, 316, 1840, 2768, "1, 4, 4")])   # deep rings, at most one
 def test_prefill_large_ragged_rule_paths(abq, p, q, M, N, K, tile):
+    """The tiled kernel's own rule, as calls for the accumulator meet it (calls without: tests/test_gpu_block.py)."""
     say("prefill rule path", p, q, M, N, K)
     c = synth.make_case(p, q, M, N, K, seed=synth.case_seed(7, p, q) + M + N + K, name=f"W{p}A{q} {M}x{N}x{K}")
     y, acc, names = gpu_gemm_named(torch, abq, c)
